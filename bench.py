@@ -66,8 +66,8 @@ def mass_assign_algorithmic_bytes(n_part, nn, F, k_ref, d=2, c_m=4, with_vol=Fal
 # and the sources each one was taken from
 COUNTERS = {2: (os.path.join(ROOT, "profiles", "counters_k_cgr3_tg1024.md"),
                 ("k_cgr.hip", "cg_common.hpp", "p2m_internal.hpp")),
-            4: (os.path.join(ROOT, "profiles", "counters_k_cgrc3_tg1024.md"),
-                ("k_cgrc.hip", "cg_common.hpp", "p2m_internal.hpp"))}
+            4: (os.path.join(ROOT, "profiles", "counters_k_pcg3_tg1024.md"),
+                ("k_pcg.hip", "cg_common.hpp", "p2m_internal.hpp"))}
 
 
 def measured_traffic(solver, inner_rtol):
@@ -858,7 +858,7 @@ def main():
                               nodes=nn, particles=int(vals.shape[1]), fields=F, tol=args.tol),
                   plan=None if plan is None else dict(solver={1: "streaming (k_cg)", 2: "resident (k_cgr)",
                                                               3: "tile-streaming (k_cgb)",
-                                                              4: "resident, Chebyshev (k_cgrc)"}[plan.solver],
+                                                              4: "Chebyshev polynomial (k_pcg)"}[plan.solver],
                                                       groups=plan.groups, scatter_tile=plan.scatter_tile or 15,
                                                       inner_rtol=(plan.inner_rtol if plan.inner_rtol >= 0
                                                                   else opts.inner_rtol),
@@ -917,11 +917,11 @@ def main():
     if k_ref is not None:
         kk = max(k_ref)
         achieved = cg_algorithmic_bytes(kk, nn, F) / (cg_ms * 1e-3) / 1e9
-        solver = plan.solver if plan is not None else 2
+        solver = plan.solver if plan is not None else 4
         kernel = {1: f"k_cg<float,2,{F}> (grid-synchronised mass solve)",
                   2: f"k_cgr<{F}> (register-resident mass solve)",
                   3: f"k_cgb<{F}> (tile-streaming mass solve)",
-                  4: f"k_cgrc<{F}> (register-resident mass solve, Chebyshev preconditioner)"}[solver]
+                  4: f"k_pcg<float, 64x64, {F}> (mass solve, Chebyshev polynomial preconditioner)"}[solver]
         traffic = measured_traffic(solver, result["plan"]["inner_rtol"] if plan is not None
                                    else opts.inner_rtol)
         result["roofline"] = dict(bound="hbm", kernel=kernel,

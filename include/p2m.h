@@ -139,24 +139,24 @@ p2m_status p2m_create(void** ctx, int device);
 p2m_status p2m_destroy(void* ctx);
 
 /* Mass-solve kernels.  Every one solves the same system to the same tolerance;
- * their rounding differs, except that the resident and the tile-streaming kernels
- * give identical bits (the same per-tile arithmetic and reduction order).
- *   P2M_SOLVER_AUTO       the register-resident kernel where it applies (2D FP32,
- *                         F <= 3, at most one 128 x 32 node tile per workgroup that
- *                         fits the device at once), else the tile-streaming
- *                         kernel (2D FP32, F <= 3, any size), else the streaming
- *                         kernel; a tuned plan of the problem's shape class
- *                         (p2m_tune) overrides this choice
+ * their rounding differs, except that RESIDENT and TILES give identical bits (the
+ * same per-tile arithmetic and reduction order), and so do AUTO and RESIDENT_CHEB.
+ *   P2M_SOLVER_AUTO       RESIDENT_CHEB where it applies, else the streaming kernel;
+ *                         a tuned plan of the problem's shape class (p2m_tune)
+ *                         overrides this choice
  *   P2M_SOLVER_STREAMING  grid-synchronised streaming kernel (any problem)
- *   P2M_SOLVER_RESIDENT   register-resident kernel where it applies (as AUTO)
- *   P2M_SOLVER_TILES      tile-streaming kernel where it applies
+ *   P2M_SOLVER_RESIDENT   register-resident kernel with the diagonal preconditioner
+ *                         (2D FP32, F <= 3, at most one 128 x 32 node tile per
+ *                         workgroup that fits the device at once), else TILES
+ *   P2M_SOLVER_TILES      tile-streaming kernel (2D FP32, F <= 3)
  *   P2M_SOLVER_RESIDENT_CHEB
- *                         the register-resident kernel with a degree-2 Chebyshev
- *                         polynomial preconditioner, u = (c0 + c1 D^-1 M) D^-1 r,
- *                         instead of the diagonal one (D = diag M): the same system
- *                         and tolerance in fewer iterations, one grid barrier each;
- *                         where it does not apply, as AUTO.  The tuner tries it;
- *                         AUTO itself keeps the diagonal preconditioner. */
+ *                         tile kernel with a Chebyshev polynomial preconditioner,
+ *                         u = (c0 + c1 A + c2 A^2) r with A = D^-1/2 M D^-1/2, instead
+ *                         of the diagonal one (D = diag M): the same system and
+ *                         tolerance in a third of the iterations, one grid barrier
+ *                         each (2D, F <= 3; FP32 meshes of any size up to 2^27 nodes,
+ *                         resident or streamed; FP64 where every 32 x 32 node tile
+ *                         fits the device at once); where it does not apply, as AUTO */
 enum { P2M_SOLVER_AUTO = 0, P2M_SOLVER_STREAMING = 1, P2M_SOLVER_RESIDENT = 2, P2M_SOLVER_TILES = 3,
        P2M_SOLVER_RESIDENT_CHEB = 4 };
 
@@ -451,16 +451,17 @@ p2m_status p2m_ns_step(void* ctx, const p2m_problem* prob, int32_t assign, doubl
  * A batch is nprob independent 2D FP32 problems (each its own mesh size, box,
  * particles and volumes) with the same field count F, 1 <= F <= 3, nprob <= 128
  * and nprob * F <= 256.  Every instance is mass-assigned exactly as
- * p2m_mass_assign would do it alone with the register-resident solver
- * (P2M_OPT_SOLVER 0 or 2): the same binning, the same scatter sums and the same
- * solver arithmetic in the same order, so each instance's nodal values and
- * report equal the single-problem ones bit for bit, whatever the other
- * instances are.
+ * p2m_mass_assign would do it alone under the same P2M_OPT_SOLVER (AUTO and
+ * RESIDENT_CHEB: the polynomial-preconditioned solve; RESIDENT and TILES: the
+ * diagonally preconditioned one; STREAMING: as AUTO, equal to the single call under
+ * AUTO): the same binning, the same scatter sums and the same solver arithmetic in
+ * the same order, so each instance's nodal values and report equal the
+ * single-problem ones bit for bit, whatever the other instances are.
  *
  * The whole batch is one HIP graph: clears, binning, scatter of all instances
- * and one persistent solve kernel over the solver tiles of all instances (tiles
- * are shared out over at most one workgroup per compute unit; the kernel's
- * grid-wide barriers rely on all its workgroups being resident, which holds on a
+ * and one persistent solve kernel over the solver tiles of all instances (two where
+ * meshes above and below 512 x 512 nodes meet in a batch; tiles are shared out over
+ * at most two workgroups per compute unit; the kernel's grid-wide barriers rely on all its workgroups being resident, which holds on a
  * device not shared with other work, and its waits are bounded: a timed-out wait
  * ends the solve with P2M_FLAG_BREAKDOWN | P2M_FLAG_NOT_CONVERGED).
  *

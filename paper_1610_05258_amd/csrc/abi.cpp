@@ -309,9 +309,43 @@ p2m_status run_assemble(const Prepared& pp, const p2m_problem* prob, const void*
     return P2M_OK;
 }
 
-// Solve kernel: the choice's kernel where it applies; AUTO and RESIDENT take the
-// register-resident kernel where the mesh fits, else the tile-streaming one, else
-// the grid-synchronised streaming kernel (1D, FP64, F > 3).
+// Workspace of the polynomial-preconditioned solve inside a problem's layout: FP32
+// problems use the areas of the two tile solvers (adjacent), FP64 ones those of the
+// streaming solve.
+struct PolyArea {
+    size_t off, bytes;
+};
+PolyArea poly_area(const Layout& L, size_t tsize) {
+    return tsize == 4 ? PolyArea{L.resident, L.learned - L.resident} : PolyArea{L.r, L.resident - L.r};
+}
+
+// The polynomial-preconditioned solve of this problem, if it applies: 2D, F <= 3, and
+// in FP64 only where every tile is resident (the streamed state has no FP64 form).
+// False: another kernel has to take it.
+template <typename T>
+bool poly_solve_for(const Context* c, const Mesh& m, int F, const Layout& L, PolySolve<T>& ps) {
+    if (m.dim != 2 || F > kResidentMaxFields || m.nn > kPolyMaxNodes) return false;
+    ps.small = sizeof(T) == 8 || pcg_small(m);
+    PolyInst& I = ps.one;
+    I.m = m;
+    I.no = 0;
+    I.pt = 0;
+    I.npt = pcg_tiles(m, ps.small, &I.ptx);
+    pcg_interval(m, I.pc);
+    ps.F = F;
+    ps.ntiles = I.npt;
+    ps.nodes = (size_t)m.nn;
+    ps.grid = pcg_grid((int)sizeof(T), ps.small, false, F, I.npt, c->device);
+    if (ps.grid < 1 || (sizeof(T) == 8 && ps.grid < ps.ntiles)) return false;
+    return pcg_workspace_bytes((int)sizeof(T), ps.small, F, 1, ps.ntiles, ps.nodes, ps.grid) <=
+           poly_area(L, sizeof(T)).bytes;
+}
+
+// Solve kernel: the choice's kernel where it applies.  AUTO and RESIDENT_CHEB take the
+// polynomial-preconditioned solve (2D, F <= 3), RESIDENT the register-resident one
+// with the diagonal preconditioner, RESIDENT beyond it and TILES the tile-streaming
+// one, and everything else the grid-synchronised streaming kernel (1D, F > 3, large
+// FP64 meshes).
 template <typename T>
 p2m_status run_solve(const Context* c, const Prepared& pp, int F, T* b, const T* w, T* coef,
                      int start, const p2m_solve_opts& caller_opts, void* x, const Choice& ch) {
@@ -319,16 +353,22 @@ p2m_status run_solve(const Context* c, const Prepared& pp, int F, T* b, const T*
     if (ch.inner_rtol >= 0.0 && ch.inner_rtol < 1.0) opts.inner_rtol = ch.inner_rtol;
     const bool tiled = sizeof(T) == 4 && pp.m.dim == 2 && F <= kResidentMaxFields;
     const int kind = ch.solver;
-    if (tiled && kind == P2M_SOLVER_RESIDENT_CHEB && cgrc_supported(pp.m, F, c->device)) {
-        P2M_TRY(launch_cg_resident_cheb(pp.m, F, (float*)coef, (float*)b, (const float*)w,
-                                        (float*)x, start, pp.ws + pp.L.resident, opts, pp.rep,
-                                        pp.clear_rep, pp.solve_spin, pp.stream));
+    PolySolve<T> ps;
+    if ((kind == P2M_SOLVER_AUTO || kind == P2M_SOLVER_RESIDENT_CHEB) &&
+        poly_solve_for<T>(c, pp.m, F, pp.L, ps)) {
+        ps.one.out = x;
+        ps.one.rep = pp.rep;
+        ps.coef = coef;
+        ps.b = b;
+        ps.w = w;
+        ps.ws = pp.ws + poly_area(pp.L, sizeof(T)).off;
+        ps.clear_rep = pp.clear_rep ? pp.rep : nullptr;
+        ps.spin = pp.solve_spin;
+        P2M_TRY(launch_pcg<T>(ps, start, opts, pp.stream));
         pp.clear_rep = false;
         return P2M_OK;
     }
-    if (tiled && (kind == P2M_SOLVER_AUTO || kind == P2M_SOLVER_RESIDENT ||
-                  kind == P2M_SOLVER_RESIDENT_CHEB) &&
-        cgr_supported(pp.m, F, c->device)) {
+    if (tiled && kind == P2M_SOLVER_RESIDENT && cgr_supported(pp.m, F, c->device)) {
         P2M_TRY(launch_cg_resident(pp.m, F, (float*)coef, (float*)b, (const float*)w, (float*)x,
                                    start, pp.ws + pp.L.resident, opts, pp.rep, pp.clear_rep,
                                    pp.solve_spin, pp.stream));
@@ -400,6 +440,16 @@ struct BatchPlan {
     std::vector<BatchInst> inst;
     std::vector<int32_t> lmap, amap, rmap, omap;
     size_t inst_b = 0, lmap_b = 0, amap_b = 0, rmap_b = 0, omap_b = 0;   // upload sections
+    // the polynomial-preconditioned solve: the instances with small and with large
+    // tiles are two launches, each with its own tables
+    struct Poly {
+        std::vector<PolyInst> inst;
+        std::vector<int32_t> rmap, order;
+        int grid = 0;
+        size_t inst_o = 0, rmap_o = 0, order_o = 0;   // offsets in the uploaded head
+    } poly[2];
+    bool jacobi = false;                 // the diagonally preconditioned solve was asked for
+    size_t head = 0;                     // bytes uploaded to the head of the workspace
     size_t o_key = 0, o_counts = 0, o_cs = 0, o_perm = 0, o_scan = 0, o_b = 0, o_w = 0,
            o_coef = 0, o_solve = 0, total = 0;
 };
@@ -476,8 +526,8 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
     // g, g + grid, ...): instances with fewer particles per node first (they need
     // the most CG iterations, so their tiles should sit on distinct workgroups), then
     // instances with more tiles, then by index.  Ownership changes no arithmetic.
+    std::vector<int> ord(nprob);
     {
-        std::vector<int> ord(nprob);
         for (int k = 0; k < nprob; ++k) ord[k] = k;
         auto before = [&](int x, int y) {
             const BatchInst& X = P.inst[x];
@@ -498,6 +548,35 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
         for (int k : ord)
             for (int t = 0; t < P.inst[k].nrt; ++t) P.omap.push_back(P.inst[k].rt + t);
     }
+    P.jacobi = c->solver_mode == P2M_SOLVER_RESIDENT || c->solver_mode == P2M_SOLVER_TILES;
+    for (const BatchInst& I : P.inst) P.jacobi = P.jacobi || I.m.nn > kPolyMaxNodes;
+    for (int cls = 0; cls < 2; ++cls) {
+        BatchPlan::Poly& Q = P.poly[cls];
+        std::vector<int> at(nprob, -1);
+        for (int k = 0; k < nprob; ++k) {
+            const Mesh& m = P.inst[k].m;
+            if (pcg_small(m) != (cls == 0)) continue;
+            PolyInst I;
+            memset(&I, 0, sizeof(I));
+            I.m = m;
+            I.out = P.inst[k].out;
+            I.rep = P.inst[k].rep;
+            I.no = P.inst[k].no;
+            I.pt = (int32_t)Q.rmap.size();
+            I.npt = pcg_tiles(m, cls == 0, &I.ptx);
+            pcg_interval(m, I.pc);
+            at[k] = (int)Q.inst.size();
+            Q.rmap.insert(Q.rmap.end(), I.npt, at[k]);
+            Q.inst.push_back(I);
+        }
+        for (int k : ord)
+            if (at[k] >= 0)
+                for (int t = 0; t < Q.inst[at[k]].npt; ++t) Q.order.push_back(Q.inst[at[k]].pt + t);
+        if (!Q.rmap.empty()) {
+            Q.grid = pcg_grid(4, cls == 0, true, F, (int)Q.rmap.size(), c->device);
+            if (Q.grid < 1) return P2M_ERR_UNSUPPORTED;
+        }
+    }
     P.grid = cgb_grid(F, P.nrt, c->device);
     if (P.grid < 1) return P2M_ERR_UNSUPPORTED;
     size_t off = 0;
@@ -512,6 +591,18 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
     P.rmap_b = align_up(sizeof(int32_t) * P.nrt);
     P.omap_b = align_up(sizeof(int32_t) * P.nrt);
     take(P.inst_b + P.lmap_b + P.amap_b + P.rmap_b + P.omap_b);
+    size_t poly_b = 0;
+    for (int cls = 0; cls < 2; ++cls) {
+        BatchPlan::Poly& Q = P.poly[cls];
+        if (Q.rmap.empty()) continue;
+        Q.inst_o = take(sizeof(PolyInst) * Q.inst.size());
+        Q.rmap_o = take(sizeof(int32_t) * Q.rmap.size());
+        Q.order_o = take(sizeof(int32_t) * Q.order.size());
+        const size_t n = pcg_workspace_bytes(4, cls == 0, F, (int)Q.inst.size(), (int)Q.rmap.size(),
+                                             (size_t)nn, Q.grid);
+        if (n > poly_b) poly_b = n;
+    }
+    P.head = off;
     P.o_key = take(sizeof(int32_t) * 2 * (size_t)np);      // keys, then in-cell ranks
     P.o_counts = take(sizeof(int32_t) * (size_t)nn);
     P.o_scan = take(scan_workspace_bytes((int)nn));   // right after counts: one fill clears both
@@ -520,7 +611,8 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
     P.o_b = take(sizeof(float) * (size_t)F * nn);
     P.o_w = take(sizeof(float) * (size_t)nn);
     P.o_coef = take(sizeof(float) * (size_t)4 * nn);
-    P.o_solve = take(cgb_workspace_bytes(F, nprob, P.nrt, (size_t)nn));
+    const size_t cgb_b = cgb_workspace_bytes(F, nprob, P.nrt, (size_t)nn);
+    P.o_solve = take(cgb_b > poly_b ? cgb_b : poly_b);   // either solve, and both tile classes in turn
     P.total = off;
     return P2M_OK;
 }
@@ -558,6 +650,28 @@ hipError_t enqueue_batch(const BatchPlan& P, char* ws, p2m_report* reps, const p
     if ((e = launch_assemble_batch(P.F, inst, amap, P.nat, perm, cs, b, w, coef, stream)) !=
         hipSuccess)
         return e;
+    if (!P.jacobi) {
+        for (const BatchPlan::Poly& Q : P.poly) {
+            if (Q.rmap.empty()) continue;
+            PolySolve<float> ps;
+            ps.inst = (const PolyInst*)(ws + Q.inst_o);
+            ps.rmap = (const int32_t*)(ws + Q.rmap_o);
+            ps.order = (const int32_t*)(ws + Q.order_o);
+            ps.nprob = (int)Q.inst.size();
+            ps.F = P.F;
+            ps.ntiles = (int)Q.rmap.size();
+            ps.grid = Q.grid;
+            ps.small = &Q == &P.poly[0];
+            ps.nodes = (size_t)P.nn;
+            ps.coef = coef;
+            ps.b = b;
+            ps.w = w;
+            ps.ws = ws + P.o_solve;
+            ps.spin = solve_spin;
+            if ((e = launch_pcg<float>(ps, opts.start, opts, stream)) != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     BatchSolveBufs bb;
     bb.inst = inst;
     bb.nprob = P.nprob;
@@ -1645,10 +1759,11 @@ p2m_status p2m_mass_assign_batched(void* ctx, const p2m_problem* probs, int32_t 
     put(&reps, sizeof(reps));
     put(&c->scan_spin, sizeof(c->scan_spin));
     put(&c->solve_spin, sizeof(c->solve_spin));
+    put(&P.jacobi, sizeof(P.jacobi));
     if (!bc.exec || key != bc.key) {
         bc.release();
         // the instance table and tile maps go to the head of the workspace
-        bc.upload.assign(P.inst_b + P.lmap_b + P.amap_b + P.rmap_b + P.omap_b, 0);
+        bc.upload.assign(P.head, 0);
         unsigned char* u = bc.upload.data();
         memcpy(u, P.inst.data(), sizeof(BatchInst) * P.nprob);
         memcpy(u + P.inst_b, P.lmap.data(), sizeof(int32_t) * P.nlb);
@@ -1656,6 +1771,12 @@ p2m_status p2m_mass_assign_batched(void* ctx, const p2m_problem* probs, int32_t 
         memcpy(u + P.inst_b + P.lmap_b + P.amap_b, P.rmap.data(), sizeof(int32_t) * P.nrt);
         memcpy(u + P.inst_b + P.lmap_b + P.amap_b + P.rmap_b, P.omap.data(),
                sizeof(int32_t) * P.nrt);
+        for (const BatchPlan::Poly& Q : P.poly) {
+            if (Q.rmap.empty()) continue;
+            memcpy(u + Q.inst_o, Q.inst.data(), sizeof(PolyInst) * Q.inst.size());
+            memcpy(u + Q.rmap_o, Q.rmap.data(), sizeof(int32_t) * Q.rmap.size());
+            memcpy(u + Q.order_o, Q.order.data(), sizeof(int32_t) * Q.order.size());
+        }
         P2M_TRY(hipMemcpyAsync(ws, u, bc.upload.size(), hipMemcpyHostToDevice, strm));
         P2M_TRY(hipStreamSynchronize(strm));
         P2M_TRY(hipStreamBeginCapture(bc.capture, hipStreamCaptureModeThreadLocal));
@@ -1775,12 +1896,15 @@ p2m_status p2m_tune(void* ctx, const p2m_problem* prob, const void* values, int3
         }
     };
     const bool tiled = prob->dtype == P2M_F32 && pp.m.dim == 2 && nfields <= kResidentMaxFields;
+    PolySolve<float> p32;
+    PolySolve<double> p64;
+    const bool poly = prob->dtype == P2M_F32 ? poly_solve_for<float>(c, pp.m, nfields, pp.L, p32)
+                                             : poly_solve_for<double>(c, pp.m, nfields, pp.L, p64);
     const int tiles[2] = {0, 8};
     for (int ti = 0; ti < (pp.m.dim == 2 ? 2 : 1); ++ti) {
         const int tile = tiles[ti];
         if (tiled && cgr_supported(pp.m, nfields, c->device)) add(P2M_SOLVER_RESIDENT, 0, tile);
-        if (tiled && cgrc_supported(pp.m, nfields, c->device))
-            add(P2M_SOLVER_RESIDENT_CHEB, 0, tile);
+        if (poly) add(P2M_SOLVER_RESIDENT_CHEB, 0, tile);
         if (tiled) {
             const int cap = cgt_grid(pp.m, nfields, 0, c->device);
             if (cap > 0) add(P2M_SOLVER_TILES, cap, tile);

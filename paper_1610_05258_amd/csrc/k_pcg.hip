@@ -1,0 +1,1109 @@
+// Mass-matrix solve with a polynomial preconditioner, for 2D problems: the solve
+// that P2M_SOLVER_AUTO, P2M_SOLVER_RESIDENT_CHEB and the batches take.
+//
+// Mixed-precision iterative refinement as in every solve here (FP64 solution and
+// residual outside, conjugate gradients in T with FP64 dot products inside), with an
+// inner iteration built to need few grid barriers:
+//
+//  * the inner system is scaled symmetrically, A = D^-1/2 M D^-1/2 (unit diagonal,
+//    so three stencil planes instead of four and no division), and preconditioned
+//    by the polynomial p(A) = c0 + c1 A + c2 A^2 that makes 1 - l p(l) the scaled
+//    Chebyshev polynomial T3 on [lo, hi].  T3 is odd: beyond hi, 1 - l p(l) is
+//    negative, below lo it lies in (0, 1), so l p(l) > 0 for every l > 0 and the
+//    preconditioner is positive definite whatever the spectrum; [lo, hi] only
+//    decides how fast it is (pcg_interval);
+//  * Chronopoulos-Gear conjugate gradients: (r, u), (w, u) and (r, r) with u = p(A) r,
+//    w = A u are reduced together, so an iteration has one grid barrier, and needs a
+//    third of the iterations of the diagonal preconditioner (5-6 for 15 at 8
+//    particles per cell, 17 for 45 at 2);
+//  * the three stencil products of an iteration read r up to three nodes outside the
+//    tile.  A workgroup keeps its own copy of that ring's r and s (and, on the
+//    innermost ring, p, d and x), advanced by the same operations on the same values
+//    as their owners, so that per iteration only w crosses tiles: every tile publishes
+//    the w of its border strip (device-coherent stores) and reads its ring's after
+//    the barrier.
+//
+// A workgroup owns one tile for the whole solve and keeps its state in registers and
+// its stencil in LDS; with more tiles than workgroups it owns several and streams
+// their state from owner-only arrays.  The arithmetic and the order of every sum
+// depend on the tile only, never on how the tiles are dealt, so a problem gives the
+// same bits alone, in a batch, resident or streamed.
+//
+// Bound: the latency of one iteration (three LDS stencil products, a block sum, the
+// grid barrier), not traffic, while one tile per workgroup fits the chip; the traffic of
+// the streamed state beyond.  Solve kernel alone, before (diagonal preconditioner, or
+// the FP64 streaming solve) and now: 256 x 256 at 4 per cell, F = 1, 220 -> 80 us;
+// 1024 x 1024 at 8 per cell, F = 3, 346 -> 271 us; 2048 x 2048 3215 -> 1966 us; 512 x 512
+// FP64 at 8 per cell, F = 1, 1178 -> 105 us.
+#include <string.h>
+
+#include "cg_common.hpp"
+
+namespace p2m {
+
+namespace {
+
+constexpr int PH = 3;   // ring depth: one per stencil product of an iteration
+
+// Tile of TX x TY nodes on NT threads; a thread owns OWN consecutive rows of one
+// column (a column's stencil reads slide down the rows) and at most one ring slot.
+template <int TX_, int TY_, int NT_>
+struct PTile {
+    static constexpr int TX = TX_, TY = TY_, NT = NT_;
+    static constexpr int EX = TX + 2 * PH, EY = TY + 2 * PH, EN = EX * EY;
+    static constexpr int OWN = TX * TY / NT;
+    static constexpr int NRING = EN - TX * TY;
+    static constexpr int NRP = (NRING + 63) / 64 * 64;
+    static_assert(NT % TX == 0 && OWN * NT == TX * TY && NRING <= NT && EN % 4 == 0, "tile");
+};
+using TileS = PTile<32, 32, 512>;
+using TileL = PTile<64, 64, 1024>;
+
+template <typename T>
+struct PArgs {
+    PolyInst one;          // the problem of a single solve
+    const PolyInst* inst;  // the instances of a batch
+    const int32_t* rmap;   // batch: tile -> instance
+    const int32_t* order;  // batch: dealing order of the tiles
+    int nprob, ntiles;
+    T* coef;               // [4][nn] blocks at 4*no (orphan diagonals set to 1 here)
+    T* b;                  // [F][nn] blocks at F*no (orphan entries set to 0 here)
+    const T* w;            // [nn] blocks at no
+    double* x64;           // [F][nn] blocks at F*no, owner-only
+    T* pubR;               // [F][nn] blocks at F*no, published scaled residual of the strips
+    T* pubW[2];            // the same of w, by iteration parity
+    double* xring;         // [tile][F][NRP] ring copies of x, owner-only
+    // streamed state (workgroups that own several tiles), by tile
+    T* own;                // [tile][6][F][TX*TY]: p, d, s, r, w, u
+    T* ring;               // [tile][5][F][NRP]: p, d, s, r, u
+    T* sqd;                // [tile][TX*TY] square roots of the diagonal
+    T* cimg;               // [tile][3][EN] scaled stencil
+    RSync sy;              // part: [2][3F][ntiles]; tot: [2][nprob][3F]
+    int start;
+    p2m_solve_opts opts;
+};
+
+__device__ __forceinline__ float mul_t(float a, float b) { return __fmul_rn(a, b); }
+__device__ __forceinline__ double mul_t(double a, double b) { return __dmul_rn(a, b); }
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __fma_rn(a, b, c); }
+__device__ __forceinline__ double dot_t(double acc, float a, float b) { return dot_acc(acc, a, b); }
+__device__ __forceinline__ double dot_t(double acc, double a, double b) { return __fma_rn(a, b, acc); }
+
+// 1/sqrt and sqrt of a diagonal entry; 1 for an orphan row (identity) and for a
+// diagonal too small to invert (the row then decouples: its products with the
+// neighbours are below its rounding)
+__device__ __forceinline__ float rs_of(float d, bool orphan) {
+    return orphan || !(d >= 1.17549435e-38f) ? 1.0f : __fdiv_rn(1.0f, __fsqrt_rn(d));
+}
+__device__ __forceinline__ double rs_of(double d, bool orphan) {
+    return orphan || !(d >= 2.2250738585072014e-308) ? 1.0 : __ddiv_rn(1.0, __dsqrt_rn(d));
+}
+__device__ __forceinline__ float sq_of(float d, bool orphan) {
+    return orphan || !(d >= 1.17549435e-38f) ? 1.0f : __fsqrt_rn(d);
+}
+__device__ __forceinline__ double sq_of(double d, bool orphan) {
+    return orphan || !(d >= 2.2250738585072014e-308) ? 1.0 : __dsqrt_rn(d);
+}
+
+// Accesses at a 32-bit byte offset from a uniform base: one address register each
+// (meshes are at most kPolyMaxNodes)
+template <typename T>
+__device__ __forceinline__ T ldo(const T* p, uint32_t i) {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(p) + i * (uint32_t)sizeof(T));
+}
+template <typename T>
+__device__ __forceinline__ T* ato(T* p, uint32_t i) {
+    return reinterpret_cast<T*>(reinterpret_cast<char*>(p) + i * (uint32_t)sizeof(T));
+}
+
+// The value, opaque to the optimiser: addresses formed from it are formed where they are
+// used.  Hoisted out of the solve's loops they take more registers than its state does.
+__device__ __forceinline__ int fresh(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// FP64 stencil product with coefficients of type T
+template <typename T>
+__device__ __forceinline__ double stencil_x(const T (&c)[7], double x0, double xe, double xw,
+                                            double xn, double xs, double xne, double xsw) {
+    double acc = __dmul_rn((double)c[0], x0);
+    acc = __fma_rn((double)c[1], xe, acc);
+    acc = __fma_rn((double)c[2], xw, acc);
+    acc = __fma_rn((double)c[3], xn, acc);
+    acc = __fma_rn((double)c[4], xs, acc);
+    acc = __fma_rn((double)c[5], xne, acc);
+    acc = __fma_rn((double)c[6], xsw, acc);
+    return acc;
+}
+
+template <typename T, class TC, int F, bool BATCH, bool STREAM>
+__global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
+    constexpr int NT = TC::NT, OWN = TC::OWN, EX = TC::EX, EN = TC::EN, NRP = TC::NRP;
+    constexpr int NTN = TC::TX * TC::TY, NV = 3 * F, NW = NT / 64;
+    // two exchange buffers per field where they fit (one workgroup barrier per stencil
+    // product), else one (two barriers)
+    constexpr size_t kTwo = ((size_t)(3 + 2 * F) * EN + NTN) * sizeof(T) + (BATCH ? 23000 : 1500);
+    constexpr bool PP = kTwo <= (NT == 512 ? 80000u : 160000u);
+    constexpr int UB = (PP ? 2 : 1) * F * EN;
+    static_assert((size_t)UB * sizeof(T) >= (size_t)EN * sizeof(double), "the x plane fits");
+    constexpr int MAXP = BATCH ? kBatchMaxPairs : F, MAXK = BATCH ? kBatchMaxInstances : 1;
+
+    __shared__ __align__(16) T cf[3 * EN];    // scaled E, N, NE of the tile and its ring
+    __shared__ __align__(16) T ub[UB];        // exchange planes; x (FP64) in the residual phase
+    __shared__ T sqd[NTN];                    // square roots of the own nodes' diagonal, by thread
+    __shared__ double red[NW * NV];
+    __shared__ double vals[BATCH ? 3 * kBatchMaxPairs : NV];
+    __shared__ double s_bb[MAXP], s_gam[MAXP], s_alpha[MAXP], s_relres[MAXP], s_target[MAXP];
+    __shared__ T s_af[MAXP], s_bf[MAXP];
+    __shared__ int s_iters[MAXP], s_refines[MAXP];
+    __shared__ unsigned char s_done[MAXP], s_inner[MAXP], s_zero[MAXP];
+    __shared__ uint32_t s_flags[MAXK];
+    __shared__ int s_ok;
+
+    const int G = gridDim.x, g = blockIdx.x, tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int col = tid % TC::TX, row0 = (tid / TC::TX) * OWN;
+    const int o_q0 = (row0 + PH) * EX + col + PH;   // LDS index of the first own node
+    constexpr bool keep = !STREAM;            // one tile per workgroup: its state stays here
+
+    // ---- the current tile ----------------------------------------------------
+    int k = 0, tile = 0, i0 = 0, j0 = 0, nx = 0, ny = 0, nn = 0, no = 0, txa = 0, tya = 0;
+    int o_g0 = 0, o_rg = 0, o_rq = 0, rdep = 0;   // first own node; ring slot: node, LDS index, depth (0: none)
+    uint32_t am = 0, sm = 0;                  // own nodes inside the mesh; on the published strip
+    T c0 = 0, c1 = 0, c2 = 0;
+    T* out = nullptr;
+    auto inst_of = [&](int kk) -> const PolyInst& {
+        if constexpr (BATCH) return a.inst[kk];
+        else return a.one;
+    };
+    auto set_tile = [&](int i) {
+        tile = i;
+        if constexpr (BATCH) {
+            tile = __builtin_amdgcn_readfirstlane(a.order[i]);
+            k = __builtin_amdgcn_readfirstlane(a.rmap[tile]);
+        }
+        const PolyInst& I = inst_of(k);
+        const int lt = tile - I.pt;
+        i0 = (lt % I.ptx) * TC::TX;
+        j0 = (lt / I.ptx) * TC::TY;
+        nx = I.m.nx;
+        ny = I.m.ny;
+        nn = I.m.nn;
+        no = I.no;
+        out = (T*)I.out;
+        c0 = (T)I.pc[0];
+        c1 = (T)I.pc[1];
+        c2 = (T)I.pc[2];
+        txa = min(TC::TX, nx - i0);
+        tya = min(TC::TY, ny - j0);
+        o_g0 = (j0 + row0) * nx + i0 + col;
+        am = sm = 0;
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) {
+            const int r = row0 + o;
+            if (!(col < txa && r < tya)) continue;
+            am |= 1u << o;
+            if (col < PH || col >= txa - PH || r < PH || r >= tya - PH) sm |= 1u << o;
+        }
+        // ring slots: PH rows below, PH above (corners included), PH columns left, right
+        const int rw = txa + 2 * PH;
+        int h = tid, lc = 0, lr = 0;
+        const bool on = h < 2 * PH * rw + 2 * PH * tya;
+        if (h < 2 * PH * rw) {
+            const bool up = h >= PH * rw;
+            if (up) h -= PH * rw;
+            const int rr = h >= 2 * rw ? 2 : (h >= rw ? 1 : 0);
+            lr = up ? tya + rr : rr - PH;
+            lc = h - rr * rw - PH;
+        } else {
+            h -= 2 * PH * rw;
+            const bool right = h >= PH * tya;
+            if (right) h -= PH * tya;
+            lr = h / PH;
+            lc = h - lr * PH + (right ? txa : -PH);
+        }
+        const int dx = lc < 0 ? -lc : (lc >= txa ? lc - txa + 1 : 0);
+        const int dy = lr < 0 ? -lr : (lr >= tya ? lr - tya + 1 : 0);
+        rdep = on ? max(dx, dy) : 0;
+        int gc = (i0 + lc) % nx, gr = (j0 + lr) % ny;
+        if (gc < 0) gc += nx;
+        if (gr < 0) gr += ny;
+        o_rg = on ? gc + nx * gr : 0;
+        o_rq = on ? (lr + PH) * EX + lc + PH : 0;
+    };
+    auto inner_mask = [&]() {
+        uint32_t mk = 0;
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+            if (s_inner[k * F + f]) mk |= 1u << f;
+        return mk;
+    };
+
+    // ---- state of the current tile -------------------------------------------
+    T vp[F][OWN], vd[F][OWN], vs[F][OWN], vr[F][OWN], vw[F][OWN];
+    T np_[F], nd[F], ns[F], nr[F];            // ring copies of p, d, s, r
+    struct Vec { T v[OWN]; };
+    auto own_at = [&](int v, int f) {
+        return ato(a.own + (((size_t)tile * 6 + v) * F + f) * NTN, tid * OWN);
+    };
+    auto ring_at = [&](int v, int f) {
+        return ato(a.ring + (((size_t)tile * 5 + v) * F + f) * NRP, tid);
+    };
+    auto ld_own = [&](int v, int f, T (&x)[OWN]) {
+        const Vec t = *reinterpret_cast<const Vec*>(__builtin_assume_aligned(own_at(v, f), OWN * sizeof(T)));
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) x[o] = t.v[o];
+    };
+    auto st_own = [&](int v, int f, const T (&x)[OWN]) {
+        Vec t;
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) t.v[o] = x[o];
+        *reinterpret_cast<Vec*>(__builtin_assume_aligned(own_at(v, f), OWN * sizeof(T))) = t;
+    };
+    auto load_img = [&]() {
+        struct alignas(16) Q { unsigned u[4]; };
+        constexpr int n = 3 * EN * (int)sizeof(T) / 16;
+        const Q* src = reinterpret_cast<const Q*>(a.cimg + (size_t)tile * 3 * EN);
+        Q* dst = reinterpret_cast<Q*>(cf);
+        for (int i = tid; i < n; i += NT) dst[i] = src[i];
+    };
+    auto start_value = [&](int f, int kk) -> double {
+        if (a.start == P2M_START_ZERO) return 0.0;
+        const T wk = a.w[(size_t)no + kk];
+        if (!(wk > (T)0)) return 0.0;
+        const size_t o = (size_t)f * nn + kk;
+        return a.start == P2M_START_FLIP ? (double)a.b[(size_t)F * no + o] / (double)wk
+                                         : (double)out[o];
+    };
+
+    unsigned epoch = 0;   // reductions done
+    unsigned tep = 0;     // barrier passes done
+    // block sums of the n values a thread holds (its sums over its nodes of the current
+    // tile), in a fixed order, stored as the tile's partials of the next reduction
+    auto store_sums = [&](const double (&v)[NV], int n) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) {
+            if (j >= n) break;
+            const double r = row_sum16(v[j]);
+            const double s =
+                (readlane_d(r, 0) + readlane_d(r, 16)) + (readlane_d(r, 32) + readlane_d(r, 48));
+            if (lane == 0) red[wave * NV + j] = s;
+        }
+        __syncthreads();
+        if (tid < n) {
+            double s = 0.0;
+#pragma unroll
+            for (int wv = 0; wv < NW; ++wv) s += red[wv * NV + tid];
+            // value-major: the lanes that sum one value read consecutive words
+            st_c(&a.sy.part[((size_t)((epoch + 1) & 1) * NV + tid) * a.ntiles + tile], s);
+        }
+        if (!keep) __syncthreads();
+    };
+    // totals over an instance's tiles [t0, t0 + nt) of nv values: value jv by the 32
+    // lanes of one half wave, lane l over tiles l, l + 32, ..., then the two row sums
+    auto sum_tiles = [&](int t0, int nt, int nv, auto put) {
+        const double* part = a.sy.part + (size_t)(epoch & 1) * NV * a.ntiles;
+        const int l = lane & 31;
+        for (int jb = wave * 2; jb < nv; jb += NT / 32) {
+            const int jv = jb + (lane >> 5);
+            double acc = 0.0;
+            if (jv < nv) {
+                const double* p = part + (size_t)jv * a.ntiles + t0;
+                for (int b0 = l; b0 < nt; b0 += 256) {
+                    double v[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) v[u] = b0 + 32 * u < nt ? ld_c(p + b0 + 32 * u) : 0.0;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (b0 + 32 * u < nt) acc += v[u];
+                }
+            }
+            const double r = row_sum16(acc);
+            const double lo = readlane_d(r, 0) + readlane_d(r, 16);
+            const double hi = readlane_d(r, 32) + readlane_d(r, 48);
+            if (jv < nv && l == 0) put(jv, (lane & 32) ? hi : lo);
+        }
+    };
+    auto barrier = [&]() -> bool {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        ++tep;
+        if (tid == 0) {
+            if (tree_arrive(a.sy, tep, G)) tree_release(a.sy, tep);
+            s_ok = tree_wait(a.sy, tep) ? 1 : 0;
+        }
+        __syncthreads();
+        return s_ok != 0;
+    };
+    // One reduction: every tile's partials are stored, then each workgroup sums them
+    // itself (a single problem), or the workgroup assigned to an instance sums that
+    // instance's and publishes the totals (a batch).  vals[kk * nv + j] on return.
+    auto reduce = [&](int nv) -> bool {
+        ++epoch;
+        if (!barrier()) return false;
+        if constexpr (BATCH) {
+            double* tot = a.sy.tot + (size_t)(epoch & 1) * a.nprob * NV;
+            for (int kk = g; kk < a.nprob; kk += G) {
+                const PolyInst& I = a.inst[kk];
+                sum_tiles(I.pt, I.npt, nv, [&](int jv, double v) { st_c(&tot[(size_t)kk * NV + jv], v); });
+            }
+            if (!barrier()) return false;
+            for (int i = tid; i < a.nprob * nv; i += NT) {
+                const int kk = i / nv, jv = i - kk * nv;
+                vals[i] = ld_c(&tot[(size_t)kk * NV + jv]);
+            }
+        } else {
+            sum_tiles(0, a.ntiles, nv, [&](int jv, double v) { vals[jv] = v; });
+        }
+        __syncthreads();
+        return true;
+    };
+
+    for (int p = tid; p < a.nprob * F; p += NT) {
+        s_iters[p] = 0; s_refines[p] = 0; s_done[p] = 0; s_inner[p] = 0; s_zero[p] = 0;
+        s_relres[p] = 0.0; s_bb[p] = 0.0;
+    }
+    for (int kk = tid; kk < a.nprob; kk += NT) s_flags[kk] = 0u;
+
+    // ---- set-up: scaled stencil, orphan regularisation, start ------------------
+    for (int i = g; i < a.ntiles; i += G) {
+        set_tile(i);
+        const int g0 = o_g0, q0 = o_q0, rg = o_rg, rq = o_rq;
+        T* C = a.coef + (size_t)4 * no;
+        const T* w = a.w + no;
+        T dg[OWN], wg[OWN], e1[OWN], e2[OWN], e3[OWN], bg[F][OWN];
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) {
+            const int kk = (am & (1u << o)) ? g0 + o * nx : 0;
+            dg[o] = ldo(C, kk);
+            wg[o] = ldo(w, kk);
+            e1[o] = ldo(C + nn, kk);
+            e2[o] = ldo(C + (size_t)2 * nn, kk);
+            e3[o] = ldo(C + (size_t)3 * nn, kk);
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+                bg[f][o] = a.start == P2M_START_USER ? ldo(out + (size_t)f * nn, kk)
+                                                     : ldo(a.b + (size_t)F * no + (size_t)f * nn, kk);
+        }
+        const T rd = ldo(C, rg), rw = ldo(w, rg), r1 = ldo(C + nn, rg), r2 = ldo(C + (size_t)2 * nn, rg),
+                r3 = ldo(C + (size_t)3 * nn, rg);
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+            if (rdep == 1) a.xring[((size_t)tile * F + f) * NRP + tid] = start_value(f, rg);
+        // the inverse square roots of the diagonal, in ub
+        T rso[OWN];
+        const T rsr = rs_of(rd, !(rw > (T)0));
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) {
+            const bool orphan = !(wg[o] > (T)0);
+            rso[o] = rs_of(dg[o], orphan);
+            sqd[o * NT + tid] = sq_of(dg[o], orphan);
+            if (am & (1u << o)) ub[q0 + o * EX] = rso[o];
+        }
+        if (rdep) ub[rq] = rsr;
+        __syncthreads();
+        // a coupling whose far node lies outside the ring is never used
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) {
+            if (!(am & (1u << o))) continue;
+            const int q = q0 + o * EX;
+            cf[q] = mul_t(mul_t(e1[o], rso[o]), ub[q + 1]);
+            cf[EN + q] = mul_t(mul_t(e2[o], rso[o]), ub[q + EX]);
+            cf[2 * EN + q] = mul_t(mul_t(e3[o], rso[o]), ub[q + EX + 1]);
+        }
+        if (rdep) {
+            const int qc = rq % EX, qr = rq / EX;
+            const bool ex = qc + 1 < txa + 2 * PH, ey = qr + 1 < tya + 2 * PH;
+            cf[rq] = ex ? mul_t(mul_t(r1, rsr), ub[rq + 1]) : (T)0;
+            cf[EN + rq] = ey ? mul_t(mul_t(r2, rsr), ub[rq + EX]) : (T)0;
+            cf[2 * EN + rq] = ex && ey ? mul_t(mul_t(r3, rsr), ub[rq + EX + 1]) : (T)0;
+        }
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) {
+            if (!(am & (1u << o))) continue;
+            const int kk = g0 + o * nx;
+            const bool orphan = !(wg[o] > (T)0);
+            if (orphan) C[kk] = (T)1;
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                const size_t q = (size_t)F * no + (size_t)f * nn + kk;
+                double x0;
+                if (orphan) {
+                    a.b[q] = (T)0;
+                    x0 = 0.0;
+                } else if (a.start == P2M_START_FLIP) {
+                    x0 = (double)bg[f][o] / (double)wg[o];
+                } else if (a.start == P2M_START_ZERO) {
+                    x0 = 0.0;
+                } else {
+                    x0 = (double)bg[f][o];
+                }
+                a.x64[q] = x0;
+            }
+            p2m_report* rep = inst_of(k).rep;
+            if (orphan && rep) {
+                atomicAdd(&rep->n_orphan, 1);
+                atomicOr(&rep->flags, (uint32_t)P2M_FLAG_ORPHAN);
+            }
+        }
+        __syncthreads();
+        if (!keep) {
+            struct alignas(16) Q { unsigned u[4]; };
+            Q* dst = reinterpret_cast<Q*>(a.cimg + (size_t)tile * 3 * EN);
+            const Q* s4 = reinterpret_cast<const Q*>(cf);
+            for (int q = tid; q < 3 * EN * (int)sizeof(T) / 16; q += NT) dst[q] = s4[q];
+            Vec t;
+#pragma unroll
+            for (int o = 0; o < OWN; ++o) t.v[o] = sqd[o * NT + tid];
+            *reinterpret_cast<Vec*>(a.sqd + (size_t)tile * NTN + (size_t)tid * OWN) = t;
+            __syncthreads();
+        }
+    }
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+#pragma unroll
+        for (int o = 0; o < OWN; ++o) vp[f][o] = vd[f][o] = vs[f][o] = vr[f][o] = vw[f][o] = (T)0;
+        np_[f] = nd[f] = ns[f] = nr[f] = (T)0;
+    }
+    __syncthreads();
+
+    // A x at the own nodes (qo) and, with rn, at this thread's ring slot (qn), for the
+    // fields in im; the same operations in the same order at either, so a ring value
+    // equals its owner's bit for bit
+    auto apply = [&](const T* U, uint32_t im, bool rn, T (&qo)[F][OWN], T (&qn)[F]) {
+        // two rows at a time: a window slides down each column, and the coefficients of
+        // more rows at once would not fit beside the state
+        constexpr int R = 2;
+#pragma unroll
+        for (int h = 0; h < OWN; h += R) {
+            const int q0 = fresh(o_q0) + h * EX;
+            T cE[R], cW[R], cN[R + 1], cD[R], cS[R];
+#pragma unroll
+            for (int o = 0; o < R; ++o) {
+                const int q = q0 + o * EX;
+                cE[o] = cf[q];
+                cW[o] = cf[q - 1];
+                cN[o + 1] = cf[EN + q];
+                cD[o] = cf[2 * EN + q];
+                cS[o] = cf[2 * EN + q - EX - 1];
+            }
+            cN[0] = cf[EN + q0 - EX];
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                if (!(im & (1u << f))) continue;
+                const T* L = U + f * EN + q0;
+                T x[R + 2], e[R + 1], v[R + 1];
+#pragma unroll
+                for (int o = 0; o < R + 2; ++o) x[o] = L[(o - 1) * EX];
+#pragma unroll
+                for (int o = 0; o < R + 1; ++o) {
+                    e[o] = L[o * EX + 1];
+                    v[o] = L[(o - 1) * EX - 1];
+                }
+#pragma unroll
+                for (int o = 0; o < R; ++o) {
+                    T s = fma_t(cE[o], e[o], x[o + 1]);
+                    s = fma_t(cW[o], v[o + 1], s);
+                    s = fma_t(cN[o + 1], x[o + 2], s);
+                    s = fma_t(cN[o], x[o], s);
+                    s = fma_t(cD[o], e[o + 1], s);
+                    qo[f][h + o] = fma_t(cS[o], v[o], s);
+                }
+            }
+        }
+        if (rn) {
+            const int rq = fresh(o_rq);
+            const T rE = cf[rq], rW = cf[rq - 1], rN = cf[EN + rq], rS = cf[EN + rq - EX],
+                    rD = cf[2 * EN + rq], rM = cf[2 * EN + rq - EX - 1];
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                if (!(im & (1u << f))) continue;
+                const T* L = U + f * EN + rq;
+                T s = fma_t(rE, L[1], L[0]);
+                s = fma_t(rW, L[-1], s);
+                s = fma_t(rN, L[EX], s);
+                s = fma_t(rS, L[-EX], s);
+                s = fma_t(rD, L[EX + 1], s);
+                qn[f] = fma_t(rM, L[-EX - 1], s);
+            }
+        }
+    };
+    T* const bA = ub;
+    T* const bB = PP ? ub + F * EN : ub;
+    auto put = [&](T* U, uint32_t im, const T (&xo)[F][OWN], bool rn, const T (&xn)[F]) {
+        const int q0 = fresh(o_q0), rq = fresh(o_rq);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            if (!(im & (1u << f))) continue;
+#pragma unroll
+            for (int o = 0; o < OWN; ++o)
+                if (am & (1u << o)) U[f * EN + q0 + o * EX] = xo[f][o];
+            if (rn) U[f * EN + rq] = xn[f];
+        }
+    };
+
+    // the ring's published values
+    auto ring_pub = [&](T* src, uint32_t im, T (&x)[F]) {
+        const int rg = fresh(o_rg);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            x[f] = (T)0;
+            if (rdep && (im & (1u << f))) x[f] = ld_c(ato(src + (size_t)F * no + (size_t)f * nn, rg));
+        }
+    };
+    // p = u + beta p, d += alpha p, s = w + beta s, r -= alpha s, at the own nodes and the ring
+    auto update = [&](uint32_t im, const T (&uo)[F][OWN], const T (&un)[F], const T (&wn)[F]) {
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            if (!(im & (1u << f))) continue;
+            const T al = s_af[k * F + f], be = s_bf[k * F + f];
+#pragma unroll
+            for (int o = 0; o < OWN; ++o) {
+                vp[f][o] = fma_t(be, vp[f][o], uo[f][o]);
+                vd[f][o] = fma_t(al, vp[f][o], vd[f][o]);
+                vs[f][o] = fma_t(be, vs[f][o], vw[f][o]);
+                vr[f][o] = fma_t(-al, vs[f][o], vr[f][o]);
+            }
+            np_[f] = fma_t(be, np_[f], un[f]);
+            nd[f] = fma_t(al, np_[f], nd[f]);
+            ns[f] = fma_t(be, ns[f], wn[f]);
+            nr[f] = fma_t(-al, ns[f], nr[f]);
+        }
+    };
+
+    bool alive = true;
+    int ex = 0;   // pubW parity written next
+    for (int outer = 0; alive; ++outer) {
+        // ---- residual phase: x += D^-1/2 d (outer > 0), r = D^-1/2 (b - M x), FP64 ----
+        for (int i = g; i < a.ntiles; i += G) {
+            if (!keep) set_tile(i);
+            uint32_t todo = 0;
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+                if (!s_done[k * F + f]) todo |= 1u << f;
+            if (!todo) continue;
+            const T* C = a.coef + (size_t)4 * no;
+            const int g0 = fresh(o_g0), q0 = fresh(o_q0), rg = fresh(o_rg), rq = fresh(o_rq);
+            T c7[OWN][7];
+            double xo[F][OWN];
+            T bo[F][OWN];
+            const int dw = i0 + col == 0 ? nx - 1 : -1;
+#pragma unroll
+            for (int o = 0; o < OWN; ++o) {
+                const bool on = am & (1u << o);
+                const int kk = on ? g0 + o * nx : 0;
+                const int kw = on ? kk + dw : 0;
+                const int ds = j0 + row0 + o == 0 ? nn - nx : -nx;
+                const int ks = on ? kk + ds : 0, kd = on ? kw + ds : 0;
+                c7[o][0] = ldo(C, kk);
+                c7[o][1] = ldo(C + nn, kk);
+                c7[o][2] = ldo(C + nn, kw);
+                c7[o][3] = ldo(C + (size_t)2 * nn, kk);
+                c7[o][4] = ldo(C + (size_t)2 * nn, ks);
+                c7[o][5] = ldo(C + (size_t)3 * nn, kk);
+                c7[o][6] = ldo(C + (size_t)3 * nn, kd);
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    const size_t q = (size_t)F * no + (size_t)f * nn;
+                    xo[f][o] = ldo(a.x64 + q, kk);
+                    bo[f][o] = ldo(a.b + q, kk);
+                }
+            }
+            T rsr = (T)1;
+            double xn[F];
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+                xn[f] = rdep == 1 ? a.xring[((size_t)tile * F + f) * NRP + tid] : 0.0;
+            if (outer > 0 && rdep == 1) rsr = rs_of(C[rg], !(a.w[(size_t)no + rg] > (T)0));
+            if (!keep) {
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    if (outer > 0) {
+                        ld_own(1, f, vd[f]);
+                        if (rdep == 1) nd[f] = *ring_at(1, f);
+                    }
+                }
+            }
+            T rso[OWN];
+#pragma unroll
+            for (int o = 0; o < OWN; ++o) rso[o] = rs_of(c7[o][0], false);
+            if (outer > 0) {
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    if (!(todo & (1u << f))) continue;
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) {
+                        xo[f][o] += (double)mul_t(vd[f][o], rso[o]);
+                        if (!(am & (1u << o))) continue;
+                        const size_t q = (size_t)f * nn;
+                        *ato(a.x64 + (size_t)F * no + q, g0 + o * nx) = xo[f][o];
+                        *ato(out + q, g0 + o * nx) = (T)xo[f][o];
+                    }
+                    if (rdep == 1) {
+                        xn[f] += (double)mul_t(nd[f], rsr);
+                        a.xring[((size_t)tile * F + f) * NRP + tid] = xn[f];
+                    }
+                }
+            }
+            double pr[NV];
+#pragma unroll
+            for (int q = 0; q < NV; ++q) pr[q] = 0.0;
+            double* X = reinterpret_cast<double*>(ub);
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                if (!(todo & (1u << f))) {
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) vr[f][o] = (T)0;
+                    continue;
+                }
+#pragma unroll
+                for (int o = 0; o < OWN; ++o)
+                    if (am & (1u << o)) X[q0 + o * EX] = xo[f][o];
+                if (rdep == 1) X[rq] = xn[f];
+                __syncthreads();
+#pragma unroll
+                for (int o = 0; o < OWN; ++o) {
+                    const int q = q0 + o * EX;
+                    const double mx = stencil_x(c7[o], xo[f][o], X[q + 1], X[q - 1], X[q + EX],
+                                                X[q - EX], X[q + EX + 1], X[q - EX - 1]);
+                    const bool on = am & (1u << o);
+                    const double bk = on ? (double)bo[f][o] : 0.0;
+                    const double r64 = on ? bk - mx : 0.0;
+                    pr[f] = sq_acc(pr[f], r64);
+                    if (outer == 0) pr[F + f] = sq_acc(pr[F + f], bk);
+                    vr[f][o] = mul_t((T)r64, rso[o]);
+                    if (sm & (1u << o))
+                        st_c(ato(a.pubR + (size_t)F * no + (size_t)f * nn, g0 + o * nx), vr[f][o]);
+                }
+                if (!keep) st_own(3, f, vr[f]);
+                __syncthreads();
+            }
+            store_sums(pr, 2 * F);
+        }
+        alive = reduce(2 * F);
+        if (!alive) break;
+        int more = 0;
+        for (int p = tid; p < a.nprob * F; p += NT) {   // one thread per (instance, field)
+            const int kk = BATCH ? p / F : 0, f = p - kk * F;
+            if (s_done[p]) continue;
+            s_refines[p] += 1;
+            const double rr = vals[kk * 2 * F + f];
+            if (outer == 0) s_bb[p] = vals[kk * 2 * F + F + f];
+            const double bb = s_bb[p];
+            const double relres = bb == 0.0 ? 0.0 : sqrt(rr / bb);
+            s_relres[p] = relres;
+            if (bb == 0.0) {
+                s_zero[p] = 1;
+                s_done[p] = 1;
+            } else if (relres <= a.opts.tol || outer >= a.opts.max_refine ||
+                       s_iters[p] >= a.opts.maxit || !(relres == relres)) {
+                s_done[p] = 1;
+                if (!(relres <= a.opts.tol)) atomicOr(&s_flags[kk], (uint32_t)P2M_FLAG_NOT_CONVERGED);
+            } else {
+                // a goal within a tenth of the inner reduction is gone for at once:
+                // a residual phase costs more than the last iteration it would save
+                const double goal = 0.25 * a.opts.tol * a.opts.tol * bb;
+                const double rel = a.opts.inner_rtol * a.opts.inner_rtol * rr;
+                s_target[p] = goal >= 0.01 * rel ? goal : rel;
+                s_inner[p] = 1;
+                more = 1;
+            }
+        }
+        if (!__syncthreads_or(more)) break;
+
+        // ---- inner iterations; the first only forms u, w and their products ------
+        if (keep) {
+            const uint32_t im = inner_mask();
+            ring_pub(a.pubR, im, nr);
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                np_[f] = nd[f] = ns[f] = (T)0;
+#pragma unroll
+                for (int o = 0; o < OWN; ++o) vp[f][o] = vd[f][o] = vs[f][o] = (T)0;
+            }
+        }
+        for (int it = 0;; ++it) {
+            for (int i = g; i < a.ntiles; i += G) {
+                if (!keep) set_tile(i);
+                const uint32_t im = inner_mask();
+                if (!im) continue;
+                const int g0 = fresh(o_g0);
+                if (!keep) {
+                    load_img();
+                    const Vec t = *reinterpret_cast<const Vec*>(a.sqd + (size_t)tile * NTN +
+                                                                (size_t)tid * OWN);
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) sqd[o * NT + tid] = t.v[o];
+                }
+                if (STREAM) {
+                    T uo[F][OWN], un[F], wn[F];
+                    ring_pub(it == 0 ? a.pubR : a.pubW[ex ^ 1], im, wn);
+#pragma unroll
+                    for (int f = 0; f < F; ++f) {
+                        np_[f] = nd[f] = ns[f] = un[f] = (T)0;
+                        nr[f] = it == 0 ? wn[f] : (T)0;
+#pragma unroll
+                        for (int o = 0; o < OWN; ++o) vp[f][o] = vd[f][o] = vs[f][o] = (T)0;
+                        if (!(im & (1u << f))) continue;
+                        ld_own(3, f, vr[f]);
+                        if (it == 0) continue;
+                        ld_own(4, f, vw[f]);
+                        ld_own(5, f, uo[f]);
+                        if (rdep) nr[f] = *ring_at(3, f);
+                        if (rdep == 1) un[f] = *ring_at(4, f);
+                        if (it == 1) continue;   // p = d = s = 0 so far
+                        ld_own(0, f, vp[f]);
+                        ld_own(1, f, vd[f]);
+                        ld_own(2, f, vs[f]);
+                        if (rdep) ns[f] = *ring_at(2, f);
+                        if (rdep == 1) {
+                            np_[f] = *ring_at(0, f);
+                            nd[f] = *ring_at(1, f);
+                        }
+                    }
+                    if (it > 0) update(im, uo, un, wn);
+                }
+                // u = c0 r + A (c1 r + c2 A r), w = A u
+                T qo[F][OWN], qn[F];
+                put(bA, im, vr, rdep != 0, nr);
+                __syncthreads();
+                apply(bA, im, rdep == 1 || rdep == 2, qo, qn);
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    if (!(im & (1u << f))) continue;
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) qo[f][o] = fma_t(c2, qo[f][o], mul_t(c1, vr[f][o]));
+                    qn[f] = fma_t(c2, qn[f], mul_t(c1, nr[f]));
+                }
+                if (!PP) __syncthreads();
+                put(bB, im, qo, rdep == 1 || rdep == 2, qn);
+                __syncthreads();
+                apply(bB, im, rdep == 1, qo, qn);
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    if (!(im & (1u << f))) continue;
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) qo[f][o] = fma_t(c0, vr[f][o], qo[f][o]);
+                    qn[f] = fma_t(c0, nr[f], qn[f]);
+                }
+                if (!PP) __syncthreads();
+                put(bA, im, qo, rdep == 1, qn);
+                if (!keep) {
+#pragma unroll
+                    for (int f = 0; f < F; ++f) {
+                        if (!(im & (1u << f))) continue;
+                        st_own(5, f, qo[f]);
+                        if (rdep == 1) *ring_at(4, f) = qn[f];
+                        if (it > 0) {
+                            st_own(0, f, vp[f]);
+                            st_own(1, f, vd[f]);
+                            st_own(2, f, vs[f]);
+                            st_own(3, f, vr[f]);
+                            if (rdep) *ring_at(2, f) = ns[f];
+                            if (rdep == 1) {
+                                *ring_at(0, f) = np_[f];
+                                *ring_at(1, f) = nd[f];
+                            }
+                        }
+                        if (rdep) *ring_at(3, f) = nr[f];
+                    }
+                }
+                __syncthreads();
+                apply(bA, im, false, qo, qn);
+                const int q0 = fresh(o_q0);
+                double pd[NV];
+#pragma unroll
+                for (int q = 0; q < NV; ++q) pd[q] = 0.0;
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    if (!(im & (1u << f))) {
+#pragma unroll
+                        for (int o = 0; o < OWN; ++o) vw[f][o] = (T)0;
+                        continue;
+                    }
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) {
+                        const bool on = am & (1u << o);
+                        vw[f][o] = on ? qo[f][o] : (T)0;
+                        if (sm & (1u << o))
+                            st_c(ato(a.pubW[ex] + (size_t)F * no + (size_t)f * nn, g0 + o * nx), vw[f][o]);
+                        const T uk = on ? bA[f * EN + q0 + o * EX] : (T)0;
+                        const T rk = mul_t(vr[f][o], sqd[o * NT + tid]);
+                        pd[f] = dot_t(pd[f], vr[f][o], uk);
+                        pd[F + f] = dot_t(pd[F + f], vw[f][o], uk);
+                        pd[2 * F + f] = dot_t(pd[2 * F + f], rk, rk);
+                    }
+                    if (!keep) st_own(4, f, vw[f]);
+                }
+                store_sums(pd, NV);
+            }
+            ex ^= 1;
+            alive = reduce(NV);
+            if (!alive) break;
+            more = 0;
+            for (int p = tid; p < a.nprob * F; p += NT) {
+                const int kk = BATCH ? p / F : 0, f = p - kk * F;
+                if (!s_inner[p]) continue;
+                const double gam = vals[kk * NV + f], del = vals[kk * NV + F + f],
+                             rho = vals[kk * NV + 2 * F + f];
+                double den = del;
+                double beta = 0.0;
+                if (it > 0) {
+                    s_iters[p] += 1;
+                    if (!(rho > s_target[p]) || s_iters[p] >= a.opts.maxit) {
+                        s_inner[p] = 0;
+                        continue;
+                    }
+                    beta = gam / s_gam[p];
+                    den = del - beta * gam / s_alpha[p];
+                }
+                if (!(den > 0.0) || !(gam > 0.0)) {
+                    s_inner[p] = 0;
+                    atomicOr(&s_flags[kk], (uint32_t)P2M_FLAG_BREAKDOWN);
+                    if (it == 0) {
+                        s_done[p] = 1;
+                        atomicOr(&s_flags[kk], (uint32_t)P2M_FLAG_NOT_CONVERGED);
+                    }
+                    continue;
+                }
+                s_alpha[p] = gam / den;
+                s_gam[p] = gam;
+                s_af[p] = (T)s_alpha[p];
+                s_bf[p] = (T)beta;
+                more = 1;
+            }
+            if (!__syncthreads_or(more)) break;
+            if (keep) {
+                const uint32_t im = inner_mask();
+                const int q0 = fresh(o_q0), rq = fresh(o_rq);
+                T uo[F][OWN], un[F], wn[F];
+                ring_pub(a.pubW[ex ^ 1], im, wn);
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) uo[f][o] = bA[f * EN + q0 + o * EX];
+                    un[f] = rdep == 1 ? bA[f * EN + rq] : (T)0;
+                }
+                update(im, uo, un, wn);
+            }
+        }
+    }
+
+    if (!alive)
+        for (int kk = tid; kk < a.nprob; kk += NT)
+            s_flags[kk] |= P2M_FLAG_BREAKDOWN | P2M_FLAG_NOT_CONVERGED;
+    __syncthreads();
+    // result of the fields that no later residual phase stored (solved by the start,
+    // b == 0, an aborted solve): the FP64 solution rounded to T, 0 where b == 0
+    for (int i = g; i < a.ntiles; i += G) {
+        if (!keep) set_tile(i);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            const int p = k * F + f;
+            if (alive && s_refines[p] > 1) continue;
+#pragma unroll
+            for (int o = 0; o < OWN; ++o) {
+                if (!(am & (1u << o))) continue;
+                const size_t q = (size_t)f * nn + o_g0 + o * nx;
+                out[q] = s_zero[p] ? (T)0 : (T)a.x64[(size_t)F * no + q];
+            }
+        }
+    }
+    if (g == 0) {
+        for (int kk = tid; kk < a.nprob; kk += NT) {
+            p2m_report* rep = inst_of(kk).rep;
+            if (!rep) continue;
+            for (int f = 0; f < F; ++f) {
+                rep->iters[f] = s_iters[kk * F + f];
+                rep->refines[f] = s_refines[kk * F + f];
+                rep->rel_residual[f] = s_relres[kk * F + f];
+            }
+            if (s_flags[kk]) atomicOr(&rep->flags, s_flags[kk]);
+        }
+    }
+}
+
+// barrier counters to zero; with rep, that report too (one launch for both)
+__global__ void k_pcg_clear(unsigned* words, int n, p2m_report* rep) {
+    for (int t = threadIdx.x; t < n; t += blockDim.x) words[t] = 0u;
+    if (rep) {
+        const int t = threadIdx.x;
+        if (t < 8) {
+            rep->iters[t] = 0;
+            rep->refines[t] = 0;
+            rep->rel_residual[t] = 0.0;
+        }
+        if (t == 0) {
+            rep->flags = 0u;
+            rep->n_orphan = 0;
+            rep->n_invalid = 0;
+            rep->reserved = 0;
+        }
+    }
+}
+
+constexpr int kSyncWords = 2 * kGroups * 32 + 2 * 32;
+
+size_t al(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
+
+template <typename T, class TC, bool BATCH, bool STREAM>
+const void* pcg_kernel(int F) {
+    switch (F) {
+        case 1: return (const void*)k_pcg<T, TC, 1, BATCH, STREAM>;
+        case 2: return (const void*)k_pcg<T, TC, 2, BATCH, STREAM>;
+        case 3: return (const void*)k_pcg<T, TC, 3, BATCH, STREAM>;
+    }
+    return nullptr;
+}
+template <typename T>
+const void* pcg_pick(bool small, bool batch, bool stream, int F) {
+    if constexpr (sizeof(T) == 8) {
+        return small && !batch && !stream ? pcg_kernel<T, TileS, false, false>(F) : nullptr;
+    } else {
+        if (small && batch)
+            return stream ? pcg_kernel<T, TileS, true, true>(F) : pcg_kernel<T, TileS, true, false>(F);
+        if (small) return stream ? nullptr : pcg_kernel<T, TileS, false, false>(F);
+        if (batch)
+            return stream ? pcg_kernel<T, TileL, true, true>(F) : pcg_kernel<T, TileL, true, false>(F);
+        return stream ? pcg_kernel<T, TileL, false, true>(F) : pcg_kernel<T, TileL, false, false>(F);
+    }
+}
+
+// streamed state per tile, bytes
+template <typename T, class C>
+size_t stream_bytes(int F, int ntiles) {
+    const size_t n = (size_t)ntiles, own = (size_t)C::TX * C::TY;
+    return al(n * 6 * F * own * sizeof(T)) + al(n * 5 * F * C::NRP * sizeof(T)) +
+           al(n * own * sizeof(T)) + al(n * 3 * C::EN * sizeof(T));
+}
+
+}  // namespace
+
+// Meshes of at most kPolyTiles small tiles (512 x 512) take the 32 x 32 tile, one per
+// compute unit; larger ones the 64 x 64 tile, whose ring is a smaller share of it.
+bool pcg_small(const Mesh& m) {
+    return (int64_t)((m.nx + TileS::TX - 1) / TileS::TX) * ((m.ny + TileS::TY - 1) / TileS::TY) <=
+           kPolyTiles;
+}
+int pcg_tiles(const Mesh& m, bool small, int* per_row) {
+    const int tx = small ? TileS::TX : TileL::TX, ty = small ? TileS::TY : TileL::TY;
+    const int px = (m.nx + tx - 1) / tx;
+    if (per_row) *per_row = px;
+    return px * ((m.ny + ty - 1) / ty);
+}
+
+void pcg_interval(const Mesh& m, double pc[3]) {
+    const double ppc = (double)m.np / (double)m.nn;
+    const double lo = ppc >= 6.0 ? 0.4 : (ppc >= 3.5 ? 0.28 : 0.18);
+    const double hi = ppc >= 6.0 ? 2.1 : (ppc >= 3.5 ? 2.3 : 2.5);
+    const double de = 0.5 * (hi - lo), s = (hi + lo) / (hi - lo);
+    const double g = 1.0 / (4.0 * s * s * s - 3.0 * s);
+    pc[0] = g * (12.0 * s * s - 3.0) / de;
+    pc[1] = -12.0 * g * s / (de * de);
+    pc[2] = 4.0 * g / (de * de * de);
+}
+
+namespace {
+
+// workgroups of this kernel the device holds at once, at most two per compute unit
+int resident_groups(const void* fn, int nt, int device) {
+    int cus = 0, per = 0;
+    if (!fn ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, nt, 0) != hipSuccess || per < 1)
+        return 0;
+    return (per > 2 ? 2 : per) * cus;
+}
+
+template <typename T>
+int grid_of(bool small, bool batch, int F, int ntiles, int device) {
+    const int nt = small ? TileS::NT : TileL::NT;
+    const int held = resident_groups(pcg_pick<T>(small, batch, false, F), nt, device);
+    if (ntiles <= held) return ntiles;
+    return resident_groups(pcg_pick<T>(small, batch, true, F), nt, device);
+}
+
+}  // namespace
+
+int pcg_grid(int tsize, bool small, bool batch, int F, int ntiles, int device) {
+    if (F < 1 || F > kResidentMaxFields || ntiles < 1) return 0;
+    const int g = tsize == 8 ? grid_of<double>(small, batch, F, ntiles, device)
+                             : grid_of<float>(small, batch, F, ntiles, device);
+    return g < ntiles ? g : ntiles;
+}
+
+size_t pcg_workspace_bytes(int tsize, bool small, int F, int nprob, int ntiles, size_t nodes, int grid) {
+    size_t s = al(kSyncWords * sizeof(unsigned)) + al((size_t)2 * 3 * F * ntiles * sizeof(double)) +
+               al((size_t)2 * 3 * F * nprob * sizeof(double)) + al((size_t)F * nodes * sizeof(double)) +
+               3 * al((size_t)F * nodes * tsize) +
+               al((size_t)ntiles * F * (small ? TileS::NRP : TileL::NRP) * sizeof(double));
+    if (ntiles > grid) {
+        if (tsize == 8) s += stream_bytes<double, TileS>(F, ntiles);
+        else s += small ? stream_bytes<float, TileS>(F, ntiles) : stream_bytes<float, TileL>(F, ntiles);
+    }
+    return s;
+}
+
+template <typename T>
+hipError_t launch_pcg(const PolySolve<T>& ps, int start, const p2m_solve_opts& opts, hipStream_t stream) {
+    const bool batch = ps.inst != nullptr;
+    const void* fn = pcg_pick<T>(ps.small, batch, ps.ntiles > ps.grid, ps.F);
+    if (!fn || ps.grid < 1 || ps.nprob < 1 || (batch && ps.nprob * ps.F > kBatchMaxPairs))
+        return hipErrorInvalidValue;
+    const int F = ps.F;
+    char* p = (char*)ps.ws;
+    auto take = [&](size_t bytes) {
+        char* q = p;
+        p += al(bytes);
+        return q;
+    };
+    PArgs<T> a;
+    memset(&a, 0, sizeof(a));
+    a.one = ps.one;
+    a.inst = ps.inst;
+    a.rmap = ps.rmap;
+    a.order = ps.order;
+    a.nprob = ps.nprob;
+    a.ntiles = ps.ntiles;
+    a.coef = ps.coef;
+    a.b = ps.b;
+    a.w = ps.w;
+    a.start = start;
+    a.opts = opts;
+    unsigned* words = (unsigned*)take(kSyncWords * sizeof(unsigned));
+    a.sy.ctr = words;
+    a.sy.root = words + kGroups * 32;
+    a.sy.rel = words + kGroups * 32 + 32;
+    a.sy.abort = words + 2 * kGroups * 32 + 32;
+    a.sy.part = (double*)take((size_t)2 * 3 * F * ps.ntiles * sizeof(double));
+    a.sy.tot = (double*)take((size_t)2 * 3 * F * ps.nprob * sizeof(double));
+    a.sy.spin = ps.spin;
+    a.x64 = (double*)take((size_t)F * ps.nodes * sizeof(double));
+    a.pubR = (T*)take((size_t)F * ps.nodes * sizeof(T));
+    a.pubW[0] = (T*)take((size_t)F * ps.nodes * sizeof(T));
+    a.pubW[1] = (T*)take((size_t)F * ps.nodes * sizeof(T));
+    a.xring = (double*)take((size_t)ps.ntiles * F * (ps.small ? TileS::NRP : TileL::NRP) * sizeof(double));
+    if (ps.ntiles > ps.grid) {
+        const size_t n = (size_t)ps.ntiles;
+        const size_t own = ps.small ? TileS::TX * TileS::TY : TileL::TX * TileL::TY;
+        const size_t ring = ps.small ? TileS::NRP : TileL::NRP, en = ps.small ? TileS::EN : TileL::EN;
+        a.own = (T*)take(n * 6 * F * own * sizeof(T));
+        a.ring = (T*)take(n * 5 * F * ring * sizeof(T));
+        a.sqd = (T*)take(n * own * sizeof(T));
+        a.cimg = (T*)take(n * 3 * en * sizeof(T));
+    }
+    hipLaunchKernelGGL(k_pcg_clear, dim3(1), dim3(256), 0, stream, words, kSyncWords, ps.clear_rep);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    // An ordinary launch: the stream has finished every earlier kernel and the grid is
+    // at most what the device holds at once (pcg_grid), so all its workgroups are
+    // resident; the barrier is the kernel's own and every wait in it is bounded.
+    void* args[] = {&a};
+    return hipLaunchKernel(fn, dim3(ps.grid), dim3(ps.small ? TileS::NT : TileL::NT), args, 0, stream);
+}
+template hipError_t launch_pcg<float>(const PolySolve<float>&, int, const p2m_solve_opts&, hipStream_t);
+template hipError_t launch_pcg<double>(const PolySolve<double>&, int, const p2m_solve_opts&, hipStream_t);
+
+}  // namespace p2m

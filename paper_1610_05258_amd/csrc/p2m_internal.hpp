@@ -241,13 +241,6 @@ hipError_t launch_cg_resident(const Mesh& m, int F, float* coef, float* b, const
                               float* x, int start, void* ws, const p2m_solve_opts& opts,
                               p2m_report* rep, bool clear_rep, long spin, hipStream_t stream);
 
-// the register-resident solve with the degree-2 Chebyshev polynomial preconditioner
-// (k_cgrc.hip): same workspace as the Jacobi one (cgr_workspace_bytes)
-bool cgrc_supported(const Mesh& m, int F, int device);
-hipError_t launch_cg_resident_cheb(const Mesh& m, int F, float* coef, float* b, const float* w,
-                                   float* x, int start, void* ws, const p2m_solve_opts& opts,
-                                   p2m_report* rep, bool clear_rep, long spin, hipStream_t stream);
-
 // ---------------------------------------------------------------------------
 // batches (k_bin.hip, k_assemble.hip, k_cgb.hip)
 // ---------------------------------------------------------------------------
@@ -299,6 +292,43 @@ int cgt_grid(const Mesh& m, int F, int groups, int device);   // 0: not availabl
 hipError_t launch_cg_tiles(const Mesh& m, int F, float* coef, float* b, const float* w, float* x,
                            int start, void* ws, const p2m_solve_opts& opts, p2m_report* rep,
                            int groups, int device, long spin, hipStream_t stream);
+
+// Polynomial-preconditioned solve of 2D problems (k_pcg.hip): F <= 3; FP32 any mesh,
+// FP64 meshes whose 32 x 32 tiles are all resident at once.
+constexpr int kPolyTiles = 256;
+constexpr int kPolyMaxNodes = 1 << 27;   // byte offsets into one node array stay below 2^32
+// one instance: its nodes at F*no (4*no, no) of the node arrays, its tiles from pt
+struct PolyInst {
+    Mesh m;
+    void* out;             // [F][nn] start (USER) on entry, result on exit
+    p2m_report* rep;
+    int32_t no, pt, ptx, npt;   // first node, first tile, tiles per row, tiles
+    double pc[3];          // the preconditioner's polynomial (pcg_interval)
+};
+bool pcg_small(const Mesh& m);
+int pcg_tiles(const Mesh& m, bool small, int* per_row);
+// coefficients of the polynomial for this problem's particles per node
+void pcg_interval(const Mesh& m, double pc[3]);
+int pcg_grid(int tsize, bool small, bool batch, int F, int ntiles, int device);   // 0: not available
+size_t pcg_workspace_bytes(int tsize, bool small, int F, int nprob, int ntiles, size_t nodes, int grid);
+template <typename T>
+struct PolySolve {
+    PolyInst one{};                    // a single problem, or
+    const PolyInst* inst = nullptr;    // the instances of a batch with their tile maps
+    const int32_t* rmap = nullptr;     // tile -> instance
+    const int32_t* order = nullptr;    // dealing order of the tiles
+    int nprob = 1, F = 1, ntiles = 0, grid = 0;
+    bool small = true;                 // 32 x 32 tiles (pcg_small)
+    size_t nodes = 0;
+    T* coef = nullptr;
+    T* b = nullptr;
+    const T* w = nullptr;
+    void* ws = nullptr;                // pcg_workspace_bytes
+    p2m_report* clear_rep = nullptr;   // zeroed first (the report the kernel writes), or null
+    long spin = kSolveSpinDefault;     // bound of a grid-barrier wait (< 0: every wait ends at once)
+};
+template <typename T>
+hipError_t launch_pcg(const PolySolve<T>& ps, int start, const p2m_solve_opts& opts, hipStream_t stream);
 
 // learned warm start (k_learn.hip); X rows are BF16 [.][160]
 hipError_t launch_learn_features(const Mesh& m, Particles<float> P, const float* values, int F,
