@@ -335,9 +335,10 @@ bool poly_solve_for(const Context* c, const Mesh& m, int F, const Layout& L, Pol
     ps.F = F;
     ps.ntiles = I.npt;
     ps.nodes = (size_t)m.nn;
+    ps.cols = pcg_column_elems(m, I.ptx);
     ps.grid = pcg_grid((int)sizeof(T), ps.small, false, F, I.npt, c->device);
     if (ps.grid < 1 || (sizeof(T) == 8 && ps.grid < ps.ntiles)) return false;
-    return pcg_workspace_bytes((int)sizeof(T), ps.small, F, 1, ps.ntiles, ps.nodes, ps.grid) <=
+    return pcg_workspace_bytes((int)sizeof(T), ps.small, F, 1, ps.ntiles, ps.nodes, ps.cols, ps.grid) <=
            poly_area(L, sizeof(T)).bytes;
 }
 
@@ -446,6 +447,7 @@ struct BatchPlan {
         std::vector<PolyInst> inst;
         std::vector<int32_t> rmap, order;
         int grid = 0;
+        size_t cols = 0;                              // column-buffer elements per field
         size_t inst_o = 0, rmap_o = 0, order_o = 0;   // offsets in the uploaded head
     } poly[2];
     bool jacobi = false;                 // the diagonally preconditioned solve was asked for
@@ -565,6 +567,9 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
             I.pt = (int32_t)Q.rmap.size();
             I.npt = pcg_tiles(m, cls == 0, &I.ptx);
             pcg_interval(m, I.pc);
+            I.co = (int32_t)Q.cols;
+            Q.cols += pcg_column_elems(m, I.ptx);
+            if (Q.cols * F >= ((size_t)1 << 31)) return P2M_ERR_UNSUPPORTED;
             at[k] = (int)Q.inst.size();
             Q.rmap.insert(Q.rmap.end(), I.npt, at[k]);
             Q.inst.push_back(I);
@@ -599,7 +604,7 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
         Q.rmap_o = take(sizeof(int32_t) * Q.rmap.size());
         Q.order_o = take(sizeof(int32_t) * Q.order.size());
         const size_t n = pcg_workspace_bytes(4, cls == 0, F, (int)Q.inst.size(), (int)Q.rmap.size(),
-                                             (size_t)nn, Q.grid);
+                                             (size_t)nn, Q.cols, Q.grid);
         if (n > poly_b) poly_b = n;
     }
     P.head = off;
@@ -663,6 +668,7 @@ hipError_t enqueue_batch(const BatchPlan& P, char* ws, p2m_report* reps, const p
             ps.grid = Q.grid;
             ps.small = &Q == &P.poly[0];
             ps.nodes = (size_t)P.nn;
+            ps.cols = Q.cols;
             ps.coef = coef;
             ps.b = b;
             ps.w = w;

@@ -31,10 +31,14 @@
 //
 // Bound: the latency of one iteration (three LDS stencil products, a block sum, the
 // grid barrier), not traffic, while one tile per workgroup fits the chip; the traffic of
-// the streamed state beyond.  Solve kernel alone, before (diagonal preconditioner, or
-// the FP64 streaming solve) and now: 256 x 256 at 4 per cell, F = 1, 220 -> 80 us;
-// 1024 x 1024 at 8 per cell, F = 3, 346 -> 271 us; 2048 x 2048 3215 -> 1966 us; 512 x 512
-// FP64 at 8 per cell, F = 1, 1178 -> 105 us.
+// the streamed state beyond.  Whole mass assignment and interpolation, before (diagonal
+// preconditioner, or the FP64 streaming solve) and now: 256 x 256 at 4 per cell, F = 1,
+// 263 -> 119 us; 1024 x 1024 at 8 per cell, F = 3, 597 -> 419 us; 2048 x 2048
+// 4.09 -> 2.5 ms; 512 x 512 FP64 at 8 per cell, F = 1, 1312 -> 199 us.  What the large
+// tile's 24 us iteration (F = 3) answered to: x kept as the start formula until a field
+// needs a second correction (no FP64 x traffic in the usual two residual phases), border
+// columns published transposed in one 16-byte store a lane and read 64 rows a wave
+// (node-major columns cost 3 us of it), and no register spilled inside the loop.
 #include <string.h>
 
 #include "cg_common.hpp"
@@ -70,13 +74,15 @@ struct PArgs {
     T* b;                  // [F][nn] blocks at F*no (orphan entries set to 0 here)
     const T* w;            // [nn] blocks at no
     double* x64;           // [F][nn] blocks at F*no, owner-only
-    T* pubR;               // [F][nn] blocks at F*no, published scaled residual of the strips
+    T* pubR;               // [F][nn] blocks at F*no, published scaled residual of the row strips
     T* pubW[2];            // the same of w, by iteration parity
+    T* colR;               // [F][6 ptx][ny] blocks at F*co, the column strips, a column's rows
+    T* colW[2];            // adjacent (a wave reads and a lane writes whole runs)
     double* xring;         // [tile][F][NRP] ring copies of x, owner-only
     // streamed state (workgroups that own several tiles), by tile
     T* own;                // [tile][6][F][TX*TY]: p, d, s, r, w, u
     T* ring;               // [tile][5][F][NRP]: p, d, s, r, u
-    T* sqd;                // [tile][TX*TY] square roots of the diagonal
+    T* rsd;                // [tile][TX*TY] inverse square roots of the diagonal
     T* cimg;               // [tile][3][EN] scaled stencil
     RSync sy;              // part: [2][3F][ntiles]; tot: [2][nprob][3F]
     int start;
@@ -90,7 +96,7 @@ __device__ __forceinline__ double fma_t(double a, double b, double c) { return _
 __device__ __forceinline__ double dot_t(double acc, float a, float b) { return dot_acc(acc, a, b); }
 __device__ __forceinline__ double dot_t(double acc, double a, double b) { return __fma_rn(a, b, acc); }
 
-// 1/sqrt and sqrt of a diagonal entry; 1 for an orphan row (identity) and for a
+// 1/sqrt of a diagonal entry; 1 for an orphan row (identity) and for a
 // diagonal too small to invert (the row then decouples: its products with the
 // neighbours are below its rounding)
 __device__ __forceinline__ float rs_of(float d, bool orphan) {
@@ -99,12 +105,8 @@ __device__ __forceinline__ float rs_of(float d, bool orphan) {
 __device__ __forceinline__ double rs_of(double d, bool orphan) {
     return orphan || !(d >= 2.2250738585072014e-308) ? 1.0 : __ddiv_rn(1.0, __dsqrt_rn(d));
 }
-__device__ __forceinline__ float sq_of(float d, bool orphan) {
-    return orphan || !(d >= 1.17549435e-38f) ? 1.0f : __fsqrt_rn(d);
-}
-__device__ __forceinline__ double sq_of(double d, bool orphan) {
-    return orphan || !(d >= 2.2250738585072014e-308) ? 1.0 : __dsqrt_rn(d);
-}
+__device__ __forceinline__ float div_t(float a, float b) { return __fdiv_rn(a, b); }
+__device__ __forceinline__ double div_t(double a, double b) { return __ddiv_rn(a, b); }
 
 // Accesses at a 32-bit byte offset from a uniform base: one address register each
 // (meshes are at most kPolyMaxNodes)
@@ -119,7 +121,8 @@ __device__ __forceinline__ T* ato(T* p, uint32_t i) {
 
 // The value, opaque to the optimiser: addresses formed from it are formed where they are
 // used.  Hoisted out of the solve's loops they take more registers than its state does.
-__device__ __forceinline__ int fresh(int v) {
+template <typename V>
+__device__ __forceinline__ V fresh(V v) {
     asm volatile("" : "+v"(v));
     return v;
 }
@@ -147,18 +150,25 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
     constexpr size_t kTwo = ((size_t)(3 + 2 * F) * EN + NTN) * sizeof(T) + (BATCH ? 23000 : 1500);
     constexpr bool PP = kTwo <= (NT == 512 ? 80000u : 160000u);
     constexpr int UB = (PP ? 2 : 1) * F * EN;
-    static_assert((size_t)UB * sizeof(T) >= (size_t)EN * sizeof(double), "the x plane fits");
+    // three fields resident on the large tile: their state does not fit 128 registers (15 of
+    // them spilled and reloaded per iteration cost 5 us of 24), so two fields' d live in LDS
+    // and the inverse square roots, needed in the residual phases only, are formed again
+    constexpr int DL = !STREAM && !BATCH && NT == 1024 && F == 3 ? 2 : 0;
     constexpr int MAXP = BATCH ? kBatchMaxPairs : F, MAXK = BATCH ? kBatchMaxInstances : 1;
 
     __shared__ __align__(16) T cf[3 * EN];    // scaled E, N, NE of the tile and its ring
     __shared__ __align__(16) T ub[UB];        // exchange planes; x (FP64) in the residual phase
-    __shared__ T sqd[NTN];                    // square roots of the own nodes' diagonal, by thread
-    __shared__ double red[NW * NV];
+    __shared__ T rsl[DL ? 1 : NTN];           // inverse square roots of the own diagonal, by thread
+    __shared__ T dl[DL ? DL * NTN : 1];
+    __shared__ double red[NW * 4 * NV];
     __shared__ double vals[BATCH ? 3 * kBatchMaxPairs : NV];
     __shared__ double s_bb[MAXP], s_gam[MAXP], s_alpha[MAXP], s_relres[MAXP], s_target[MAXP];
     __shared__ T s_af[MAXP], s_bf[MAXP];
     __shared__ int s_iters[MAXP], s_refines[MAXP];
     __shared__ unsigned char s_done[MAXP], s_inner[MAXP], s_zero[MAXP];
+    // x is held in x64 / xring (else it is the start, formed from b and w where needed);
+    // the last inner solve went for the goal, so its residual is expected to be the last
+    __shared__ unsigned char s_held[MAXP], s_last[MAXP];
     __shared__ uint32_t s_flags[MAXK];
     __shared__ int s_ok;
 
@@ -169,9 +179,11 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
     constexpr bool keep = !STREAM;            // one tile per workgroup: its state stays here
 
     // ---- the current tile ----------------------------------------------------
-    int k = 0, tile = 0, i0 = 0, j0 = 0, nx = 0, ny = 0, nn = 0, no = 0, txa = 0, tya = 0;
+    int k = 0, tile = 0, i0 = 0, j0 = 0, nx = 0, ny = 0, nn = 0, no = 0, co = 0, cl = 0, txa = 0, tya = 0;
     int o_g0 = 0, o_rg = 0, o_rq = 0, rdep = 0;   // first own node; ring slot: node, LDS index, depth (0: none)
-    uint32_t am = 0, sm = 0;                  // own nodes inside the mesh; on the published strip
+    int o_rc = 0;                             // column-buffer element of a column ring slot, else -1
+    int o_cc = 0;                             // column-buffer element of the first own node, else -1
+    uint32_t am = 0, sm = 0;                  // own nodes inside the mesh; on the published row strips
     T c0 = 0, c1 = 0, c2 = 0;
     T* out = nullptr;
     auto inst_of = [&](int kk) -> const PolyInst& {
@@ -192,6 +204,8 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
         ny = I.m.ny;
         nn = I.m.nn;
         no = I.no;
+        co = I.co;
+        cl = 2 * PH * I.ptx * ny;
         out = (T*)I.out;
         c0 = (T)I.pc[0];
         c1 = (T)I.pc[1];
@@ -205,8 +219,12 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
             const int r = row0 + o;
             if (!(col < txa && r < tya)) continue;
             am |= 1u << o;
-            if (col < PH || col >= txa - PH || r < PH || r >= tya - PH) sm |= 1u << o;
+            if (r < PH || r >= tya - PH) sm |= 1u << o;
         }
+        // the published columns of a tile column: PH from the left, PH from the right
+        const int tc = i0 / TC::TX;
+        const int cs = col < PH ? col : (col >= txa - PH ? PH + col - (txa - PH) : -1);
+        o_cc = col < txa && cs >= 0 ? (2 * PH * tc + cs) * ny + j0 + row0 : -1;
         // ring slots: PH rows below, PH above (corners included), PH columns left, right
         const int rw = txa + 2 * PH;
         int h = tid, lc = 0, lr = 0;
@@ -221,8 +239,9 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
             h -= 2 * PH * rw;
             const bool right = h >= PH * tya;
             if (right) h -= PH * tya;
-            lr = h / PH;
-            lc = h - lr * PH + (right ? txa : -PH);
+            const int cc = h >= 2 * tya ? 2 : (h >= tya ? 1 : 0);
+            lr = h - cc * tya;
+            lc = cc + (right ? txa : -PH);
         }
         const int dx = lc < 0 ? -lc : (lc >= txa ? lc - txa + 1 : 0);
         const int dy = lr < 0 ? -lr : (lr >= tya ? lr - tya + 1 : 0);
@@ -231,6 +250,11 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
         if (gc < 0) gc += nx;
         if (gr < 0) gr += ny;
         o_rg = on ? gc + nx * gr : 0;
+        o_rc = -1;
+        if (on && lr >= 0 && lr < tya) {   // a column slot: where its owner publishes it
+            const int ot = gc / TC::TX, oc = gc - ot * TC::TX, ow = min(TC::TX, nx - ot * TC::TX);
+            o_rc = (2 * PH * ot + (oc < PH ? oc : PH + oc - (ow - PH))) * ny + gr;
+        }
         o_rq = on ? (lr + PH) * EX + lc + PH : 0;
     };
     auto inner_mask = [&]() {
@@ -244,6 +268,19 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
     // ---- state of the current tile -------------------------------------------
     T vp[F][OWN], vd[F][OWN], vs[F][OWN], vr[F][OWN], vw[F][OWN];
     T np_[F], nd[F], ns[F], nr[F];            // ring copies of p, d, s, r
+    // d is touched once an iteration: the first DL fields' in LDS
+    auto d_get = [&](int f) {
+        if (f < DL) {
+#pragma unroll
+            for (int o = 0; o < OWN; ++o) vd[f][o] = dl[(f * OWN + o) * NT + tid];
+        }
+    };
+    auto d_put = [&](int f) {
+        if (f < DL) {
+#pragma unroll
+            for (int o = 0; o < OWN; ++o) dl[(f * OWN + o) * NT + tid] = vd[f][o];
+        }
+    };
     struct Vec { T v[OWN]; };
     auto own_at = [&](int v, int f) {
         return ato(a.own + (((size_t)tile * 6 + v) * F + f) * NTN, tid * OWN);
@@ -269,35 +306,47 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
         Q* dst = reinterpret_cast<Q*>(cf);
         for (int i = tid; i < n; i += NT) dst[i] = src[i];
     };
+    // the start at an own node from its b and w (a user's start is held from the set-up on)
+    auto own_start = [&](T bk, T wk) -> double {
+        if (a.start == P2M_START_ZERO || !(wk > (T)0)) return 0.0;
+        return (double)div_t(bk, wk);
+    };
     auto start_value = [&](int f, int kk) -> double {
         if (a.start == P2M_START_ZERO) return 0.0;
-        const T wk = a.w[(size_t)no + kk];
+        const T wk = ldo(a.w + no, kk);
         if (!(wk > (T)0)) return 0.0;
-        const size_t o = (size_t)f * nn + kk;
-        return a.start == P2M_START_FLIP ? (double)a.b[(size_t)F * no + o] / (double)wk
-                                         : (double)out[o];
+        return a.start == P2M_START_FLIP
+                   ? (double)div_t(ldo(a.b + (size_t)F * no + (size_t)f * nn, kk), wk)
+                   : (double)ldo(out + (size_t)f * nn, kk);
     };
 
     unsigned epoch = 0;   // reductions done
     unsigned tep = 0;     // barrier passes done
     // block sums of the n values a thread holds (its sums over its nodes of the current
     // tile), in a fixed order, stored as the tile's partials of the next reduction
+    static_assert(NW <= 16 && NV <= 16 && 16 * NV <= NT, "block sum layout");
     auto store_sums = [&](const double (&v)[NV], int n) {
+        double mine = 0.0;
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
             if (j >= n) break;
             const double r = row_sum16(v[j]);
-            const double s =
-                (readlane_d(r, 0) + readlane_d(r, 16)) + (readlane_d(r, 32) + readlane_d(r, 48));
-            if (lane == 0) red[wave * NV + j] = s;
+            if ((lane & 15) == j) mine = r;
         }
+        if ((lane & 15) < n) red[(wave * 4 + (lane >> 4)) * NV + (lane & 15)] = mine;
         __syncthreads();
-        if (tid < n) {
-            double s = 0.0;
-#pragma unroll
-            for (int wv = 0; wv < NW; ++wv) s += red[wv * NV + tid];
-            // value-major: the lanes that sum one value read consecutive words
-            st_c(&a.sy.part[((size_t)((epoch + 1) & 1) * NV + tid) * a.ntiles + tile], s);
+        // value jv by one 16-lane row, lane l the four rows of wave l, then the row sum
+        if (tid < ((16 * n + 63) & ~63)) {
+            const int jv = tid >> 4, wv = tid & 15;
+            double t = 0.0;
+            if (jv < n && wv < NW) {
+                const double* q = red + wv * 4 * NV + jv;
+                t = (q[0] + q[NV]) + (q[2 * NV] + q[3 * NV]);
+            }
+            t = row_sum16(t);
+            // value-major: the lanes that sum one value over the tiles read consecutive words
+            if (jv < n && wv == 0)
+                st_c(&a.sy.part[((size_t)((epoch + 1) & 1) * NV + jv) * a.ntiles + tile], t);
         }
         if (!keep) __syncthreads();
     };
@@ -340,9 +389,10 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
     // One reduction: every tile's partials are stored, then each workgroup sums them
     // itself (a single problem), or the workgroup assigned to an instance sums that
     // instance's and publishes the totals (a batch).  vals[kk * nv + j] on return.
-    auto reduce = [&](int nv) -> bool {
+    auto reduce = [&](int nv, auto after) -> bool {
         ++epoch;
         if (!barrier()) return false;
+        after();
         if constexpr (BATCH) {
             double* tot = a.sy.tot + (size_t)(epoch & 1) * a.nprob * NV;
             for (int kk = g; kk < a.nprob; kk += G) {
@@ -363,6 +413,7 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
 
     for (int p = tid; p < a.nprob * F; p += NT) {
         s_iters[p] = 0; s_refines[p] = 0; s_done[p] = 0; s_inner[p] = 0; s_zero[p] = 0;
+        s_held[p] = a.start == P2M_START_USER; s_last[p] = 0;
         s_relres[p] = 0.0; s_bb[p] = 0.0;
     }
     for (int kk = tid; kk < a.nprob; kk += NT) s_flags[kk] = 0u;
@@ -373,6 +424,7 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
         const int g0 = o_g0, q0 = o_q0, rg = o_rg, rq = o_rq;
         T* C = a.coef + (size_t)4 * no;
         const T* w = a.w + no;
+        const bool user = a.start == P2M_START_USER;
         T dg[OWN], wg[OWN], e1[OWN], e2[OWN], e3[OWN], bg[F][OWN];
 #pragma unroll
         for (int o = 0; o < OWN; ++o) {
@@ -384,14 +436,13 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
             e3[o] = ldo(C + (size_t)3 * nn, kk);
 #pragma unroll
             for (int f = 0; f < F; ++f)
-                bg[f][o] = a.start == P2M_START_USER ? ldo(out + (size_t)f * nn, kk)
-                                                     : ldo(a.b + (size_t)F * no + (size_t)f * nn, kk);
+                bg[f][o] = user ? ldo(out + (size_t)f * nn, kk) : (T)0;
         }
         const T rd = ldo(C, rg), rw = ldo(w, rg), r1 = ldo(C + nn, rg), r2 = ldo(C + (size_t)2 * nn, rg),
                 r3 = ldo(C + (size_t)3 * nn, rg);
 #pragma unroll
         for (int f = 0; f < F; ++f)
-            if (rdep == 1) a.xring[((size_t)tile * F + f) * NRP + tid] = start_value(f, rg);
+            if (user && rdep == 1) a.xring[((size_t)tile * F + f) * NRP + tid] = start_value(f, rg);
         // the inverse square roots of the diagonal, in ub
         T rso[OWN];
         const T rsr = rs_of(rd, !(rw > (T)0));
@@ -399,7 +450,7 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
         for (int o = 0; o < OWN; ++o) {
             const bool orphan = !(wg[o] > (T)0);
             rso[o] = rs_of(dg[o], orphan);
-            sqd[o * NT + tid] = sq_of(dg[o], orphan);
+            if (!DL) rsl[o * NT + tid] = rso[o];
             if (am & (1u << o)) ub[q0 + o * EX] = rso[o];
         }
         if (rdep) ub[rq] = rsr;
@@ -429,18 +480,8 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
 #pragma unroll
             for (int f = 0; f < F; ++f) {
                 const size_t q = (size_t)F * no + (size_t)f * nn + kk;
-                double x0;
-                if (orphan) {
-                    a.b[q] = (T)0;
-                    x0 = 0.0;
-                } else if (a.start == P2M_START_FLIP) {
-                    x0 = (double)bg[f][o] / (double)wg[o];
-                } else if (a.start == P2M_START_ZERO) {
-                    x0 = 0.0;
-                } else {
-                    x0 = (double)bg[f][o];
-                }
-                a.x64[q] = x0;
+                if (orphan) a.b[q] = (T)0;
+                if (user) a.x64[q] = orphan ? 0.0 : (double)bg[f][o];
             }
             p2m_report* rep = inst_of(k).rep;
             if (orphan && rep) {
@@ -456,8 +497,8 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
             for (int q = tid; q < 3 * EN * (int)sizeof(T) / 16; q += NT) dst[q] = s4[q];
             Vec t;
 #pragma unroll
-            for (int o = 0; o < OWN; ++o) t.v[o] = sqd[o * NT + tid];
-            *reinterpret_cast<Vec*>(a.sqd + (size_t)tile * NTN + (size_t)tid * OWN) = t;
+            for (int o = 0; o < OWN; ++o) t.v[o] = rso[o];
+            *reinterpret_cast<Vec*>(a.rsd + (size_t)tile * NTN + (size_t)tid * OWN) = t;
             __syncthreads();
         }
     }
@@ -545,13 +586,30 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
     };
 
     // the ring's published values
-    auto ring_pub = [&](T* src, uint32_t im, T (&x)[F]) {
-        const int rg = fresh(o_rg);
+    auto ring_pub = [&](T* src, T* csrc, T (&x)[F]) {
+        const int rg = fresh(o_rg), rc = fresh(o_rc);
 #pragma unroll
         for (int f = 0; f < F; ++f) {
             x[f] = (T)0;
-            if (rdep && (im & (1u << f))) x[f] = ld_c(ato(src + (size_t)F * no + (size_t)f * nn, rg));
+            if (rc >= 0) x[f] = ld_c(ato(csrc + (size_t)F * co + (size_t)f * cl, rc));
+            else if (rdep) x[f] = ld_c(ato(src + (size_t)F * no + (size_t)f * nn, rg));
         }
+    };
+    // a thread's values of one field on the column strips: its rows are one run
+    auto col_pub = [&](T* dst, int f, const T (&x)[OWN]) {
+        const int cc = fresh(o_cc);
+        if (cc < 0) return;
+        T* const q = ato(dst + (size_t)F * co + (size_t)f * cl, cc);
+        if (OWN * sizeof(T) == 16 && am == (1u << OWN) - 1) {   // one 16-byte store
+            float v[4];
+            __builtin_memcpy(v, &x[0], 16);
+            st4f<kCoherent>(mkrs(dst + (size_t)F * co + (size_t)f * cl, (size_t)cl * sizeof(T)),
+                            cc * (int)sizeof(T), 0, v);
+            return;
+        }
+#pragma unroll
+        for (int o = 0; o < OWN; ++o)
+            if (am & (1u << o)) st_c(q + o, x[o]);
     };
     // p = u + beta p, d += alpha p, s = w + beta s, r -= alpha s, at the own nodes and the ring
     auto update = [&](uint32_t im, const T (&uo)[F][OWN], const T (&un)[F], const T (&wn)[F]) {
@@ -559,6 +617,7 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
         for (int f = 0; f < F; ++f) {
             if (!(im & (1u << f))) continue;
             const T al = s_af[k * F + f], be = s_bf[k * F + f];
+            d_get(f);
 #pragma unroll
             for (int o = 0; o < OWN; ++o) {
                 vp[f][o] = fma_t(be, vp[f][o], uo[f][o]);
@@ -566,6 +625,7 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                 vs[f][o] = fma_t(be, vs[f][o], vw[f][o]);
                 vr[f][o] = fma_t(-al, vs[f][o], vr[f][o]);
             }
+            d_put(f);
             np_[f] = fma_t(be, np_[f], un[f]);
             nd[f] = fma_t(al, np_[f], nd[f]);
             ns[f] = fma_t(be, ns[f], wn[f]);
@@ -584,73 +644,51 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
             for (int f = 0; f < F; ++f)
                 if (!s_done[k * F + f]) todo |= 1u << f;
             if (!todo) continue;
-            const T* C = a.coef + (size_t)4 * no;
-            const int g0 = fresh(o_g0), q0 = fresh(o_q0), rg = fresh(o_rg), rq = fresh(o_rq);
-            T c7[OWN][7];
-            double xo[F][OWN];
-            T bo[F][OWN];
-            const int dw = i0 + col == 0 ? nx - 1 : -1;
-#pragma unroll
-            for (int o = 0; o < OWN; ++o) {
-                const bool on = am & (1u << o);
-                const int kk = on ? g0 + o * nx : 0;
-                const int kw = on ? kk + dw : 0;
-                const int ds = j0 + row0 + o == 0 ? nn - nx : -nx;
-                const int ks = on ? kk + ds : 0, kd = on ? kw + ds : 0;
-                c7[o][0] = ldo(C, kk);
-                c7[o][1] = ldo(C + nn, kk);
-                c7[o][2] = ldo(C + nn, kw);
-                c7[o][3] = ldo(C + (size_t)2 * nn, kk);
-                c7[o][4] = ldo(C + (size_t)2 * nn, ks);
-                c7[o][5] = ldo(C + (size_t)3 * nn, kk);
-                c7[o][6] = ldo(C + (size_t)3 * nn, kd);
-#pragma unroll
-                for (int f = 0; f < F; ++f) {
-                    const size_t q = (size_t)F * no + (size_t)f * nn;
-                    xo[f][o] = ldo(a.x64 + q, kk);
-                    bo[f][o] = ldo(a.b + q, kk);
-                }
-            }
-            T rsr = (T)1;
-            double xn[F];
-#pragma unroll
-            for (int f = 0; f < F; ++f)
-                xn[f] = rdep == 1 ? a.xring[((size_t)tile * F + f) * NRP + tid] : 0.0;
-            if (outer > 0 && rdep == 1) rsr = rs_of(C[rg], !(a.w[(size_t)no + rg] > (T)0));
-            if (!keep) {
-#pragma unroll
-                for (int f = 0; f < F; ++f) {
-                    if (outer > 0) {
-                        ld_own(1, f, vd[f]);
-                        if (rdep == 1) nd[f] = *ring_at(1, f);
-                    }
-                }
-            }
-            T rso[OWN];
-#pragma unroll
-            for (int o = 0; o < OWN; ++o) rso[o] = rs_of(c7[o][0], false);
-            if (outer > 0) {
-#pragma unroll
-                for (int f = 0; f < F; ++f) {
-                    if (!(todo & (1u << f))) continue;
-#pragma unroll
-                    for (int o = 0; o < OWN; ++o) {
-                        xo[f][o] += (double)mul_t(vd[f][o], rso[o]);
-                        if (!(am & (1u << o))) continue;
-                        const size_t q = (size_t)f * nn;
-                        *ato(a.x64 + (size_t)F * no + q, g0 + o * nx) = xo[f][o];
-                        *ato(out + q, g0 + o * nx) = (T)xo[f][o];
-                    }
-                    if (rdep == 1) {
-                        xn[f] += (double)mul_t(nd[f], rsr);
-                        a.xring[((size_t)tile * F + f) * NRP + tid] = xn[f];
-                    }
-                }
-            }
-            double pr[NV];
+            double pr[NV];   // ||r||^2, ||b||^2 (first pass), ||D^-1/2 r||^2
 #pragma unroll
             for (int q = 0; q < NV; ++q) pr[q] = 0.0;
-            double* X = reinterpret_cast<double*>(ub);
+            double* const X = reinterpret_cast<double*>(ub);
+            T c7[OWN][7], bo[F][OWN], wo[OWN], rb[F], rw = (T)1, rd = (T)1;
+            {
+                const int g0 = fresh(o_g0), rg = fresh(o_rg);
+                const T* C = a.coef + (size_t)4 * no;
+                const int dw = i0 + col == 0 ? nx - 1 : -1;
+#pragma unroll
+                for (int o = 0; o < OWN; ++o) {
+                    const bool on = am & (1u << o);
+                    const int kk = on ? g0 + o * nx : 0;
+                    const int kw = on ? kk + dw : 0;
+                    const int ds = j0 + row0 + o == 0 ? nn - nx : -nx;
+                    const int ks = on ? kk + ds : 0, kd = on ? kw + ds : 0;
+                    c7[o][0] = ldo(C, kk);
+                    c7[o][1] = ldo(C + nn, kk);
+                    c7[o][2] = ldo(C + nn, kw);
+                    c7[o][3] = ldo(C + (size_t)2 * nn, kk);
+                    c7[o][4] = ldo(C + (size_t)2 * nn, ks);
+                    c7[o][5] = ldo(C + (size_t)3 * nn, kk);
+                    c7[o][6] = ldo(C + (size_t)3 * nn, kd);
+                    wo[o] = ldo(a.w + no, kk);
+#pragma unroll
+                    for (int f = 0; f < F; ++f) bo[f][o] = ldo(a.b + (size_t)F * no + (size_t)f * nn, kk);
+                }
+                if (rdep == 1) {
+                    rw = ldo(a.w + no, rg);
+                    rd = ldo(C, rg);
+                }
+#pragma unroll
+                for (int f = 0; f < F; ++f)
+                    rb[f] = rdep == 1 ? ldo(a.b + (size_t)F * no + (size_t)f * nn, rg) : (T)0;
+                if (STREAM) {
+                    const Vec t = *reinterpret_cast<const Vec*>(a.rsd + (size_t)tile * NTN +
+                                                                (size_t)tid * OWN);
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) rsl[o * NT + tid] = t.v[o];
+                }
+            }
+            const T rsr = rs_of(rd, !(rw > (T)0));
+            T rso[OWN];
+#pragma unroll
+            for (int o = 0; o < OWN; ++o) rso[o] = DL ? rs_of(c7[o][0], false) : rsl[o * NT + tid];
 #pragma unroll
             for (int f = 0; f < F; ++f) {
                 if (!(todo & (1u << f))) {
@@ -658,15 +696,50 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                     for (int o = 0; o < OWN; ++o) vr[f][o] = (T)0;
                     continue;
                 }
+                const int p = k * F + f;
+                const bool hf = s_held[p] != 0, st = outer > 0 && !s_last[p];
+                const int g0 = fresh(o_g0), q0 = fresh(o_q0), rq = fresh(o_rq);
+                const size_t qf = (size_t)F * no + (size_t)f * nn;
+                double* const xr = a.xring + ((size_t)tile * F + f) * NRP + tid;
+                double xo[OWN], xn = 0.0;
+                if (hf) {
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o)
+                        xo[o] = ldo(a.x64 + qf, (am & (1u << o)) ? g0 + o * nx : 0);
+                    if (rdep == 1) xn = *xr;
+                } else {
+                    xn = rdep == 1 ? own_start(rb[f], rw) : 0.0;
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) xo[o] = own_start(bo[f][o], wo[o]);
+                }
+                if (outer > 0) {
+                    if (STREAM) {
+                        ld_own(1, f, vd[f]);
+                        if (rdep == 1) nd[f] = *ring_at(1, f);
+                    }
+                            d_get(f);
+                    xn += (double)mul_t(nd[f], rsr);
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) xo[o] += (double)mul_t(vd[f][o], rso[o]);
+                }
 #pragma unroll
                 for (int o = 0; o < OWN; ++o)
-                    if (am & (1u << o)) X[q0 + o * EX] = xo[f][o];
-                if (rdep == 1) X[rq] = xn[f];
+                    if (am & (1u << o)) X[q0 + o * EX] = xo[o];
+                if (rdep == 1) X[rq] = xn;
                 __syncthreads();
+                if (outer > 0) {
+                    if (st && rdep == 1) *xr = xn;
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) {
+                        if (!(am & (1u << o))) continue;
+                        if (st) *ato(a.x64 + qf, g0 + o * nx) = xo[o];
+                        *ato(out + (size_t)f * nn, g0 + o * nx) = (T)xo[o];
+                    }
+                }
 #pragma unroll
                 for (int o = 0; o < OWN; ++o) {
                     const int q = q0 + o * EX;
-                    const double mx = stencil_x(c7[o], xo[f][o], X[q + 1], X[q - 1], X[q + EX],
+                    const double mx = stencil_x(c7[o], xo[o], X[q + 1], X[q - 1], X[q + EX],
                                                 X[q - EX], X[q + EX + 1], X[q - EX - 1]);
                     const bool on = am & (1u << o);
                     const double bk = on ? (double)bo[f][o] : 0.0;
@@ -674,23 +747,28 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                     pr[f] = sq_acc(pr[f], r64);
                     if (outer == 0) pr[F + f] = sq_acc(pr[F + f], bk);
                     vr[f][o] = mul_t((T)r64, rso[o]);
-                    if (sm & (1u << o))
-                        st_c(ato(a.pubR + (size_t)F * no + (size_t)f * nn, g0 + o * nx), vr[f][o]);
+                    const T rk = fresh(vr[f][o]);
+                    pr[2 * F + f] = dot_t(pr[2 * F + f], rk, rk);
+                    if (sm & (1u << o)) st_c(ato(a.pubR + qf, g0 + o * nx), vr[f][o]);
                 }
-                if (!keep) st_own(3, f, vr[f]);
+                col_pub(a.colR, f, vr[f]);
+                if (STREAM) st_own(3, f, vr[f]);
                 __syncthreads();
             }
-            store_sums(pr, 2 * F);
+            store_sums(pr, NV);
         }
-        alive = reduce(2 * F);
+        T wn[F];   // the ring's published values, loaded beside the partials
+        alive = reduce(NV, [&] {
+            if (keep) ring_pub(a.pubR, a.colR, wn);
+        });
         if (!alive) break;
         int more = 0;
         for (int p = tid; p < a.nprob * F; p += NT) {   // one thread per (instance, field)
             const int kk = BATCH ? p / F : 0, f = p - kk * F;
             if (s_done[p]) continue;
             s_refines[p] += 1;
-            const double rr = vals[kk * 2 * F + f];
-            if (outer == 0) s_bb[p] = vals[kk * 2 * F + F + f];
+            const double rr = vals[kk * NV + f];
+            if (outer == 0) s_bb[p] = vals[kk * NV + F + f];
             const double bb = s_bb[p];
             const double relres = bb == 0.0 ? 0.0 : sqrt(rr / bb);
             s_relres[p] = relres;
@@ -702,26 +780,69 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                 s_done[p] = 1;
                 if (!(relres <= a.opts.tol)) atomicOr(&s_flags[kk], (uint32_t)P2M_FLAG_NOT_CONVERGED);
             } else {
-                // a goal within a tenth of the inner reduction is gone for at once:
+                // a goal within a thirtieth of the inner reduction is gone for at once:
                 // a residual phase costs more than the last iteration it would save
                 const double goal = 0.25 * a.opts.tol * a.opts.tol * bb;
                 const double rel = a.opts.inner_rtol * a.opts.inner_rtol * rr;
-                s_target[p] = goal >= 0.01 * rel ? goal : rel;
+                const bool direct = goal * 900.0 >= rel;
+                // the inner solve measures its residual in the scaled norm
+                s_target[p] = (direct ? goal : rel) * (vals[kk * NV + 2 * F + f] / rr);
+                // x + d was not stored if this residual was expected to be the last
+                s_held[p] |= outer > 0 ? (s_last[p] ? 2 : 1) : 0;
+                s_last[p] = direct;
                 s_inner[p] = 1;
-                more = 1;
+                more |= s_held[p] & 2 ? 3 : 1;
             }
         }
-        if (!__syncthreads_or(more)) break;
+        more = __syncthreads_or(more);
+        if (!more) break;
+        // x += d where the residual phase left it out and the solve goes on after all
+        if (more & 2) {
+            for (int i = g; i < a.ntiles; i += G) {
+                if (!keep) set_tile(i);
+                const int g0 = fresh(o_g0), rg = fresh(o_rg);
+                const T* C = a.coef + (size_t)4 * no;
+                const T* w = a.w + no;
+                const T rsr = rdep == 1 ? rs_of(ldo(C, rg), !(ldo(w, rg) > (T)0)) : (T)1;
+#pragma unroll
+                for (int f = 0; f < F; ++f) {
+                    const int p = k * F + f;
+                    if (!s_inner[p] || !(s_held[p] & 2)) continue;
+                    const bool hf = s_held[p] & 1;
+                    d_get(f);
+                    const size_t q = (size_t)F * no + (size_t)f * nn;
+                    if (!keep) {
+                        ld_own(1, f, vd[f]);
+                        if (rdep == 1) nd[f] = *ring_at(1, f);
+                    }
+#pragma unroll
+                    for (int o = 0; o < OWN; ++o) {
+                        if (!(am & (1u << o))) continue;
+                        const int kk = g0 + o * nx;
+                        const double x = hf ? ldo(a.x64 + q, kk) : own_start(ldo(a.b + q, kk), ldo(w, kk));
+                        *ato(a.x64 + q, kk) = x + (double)mul_t(vd[f][o], rs_of(ldo(C, kk), !(ldo(w, kk) > (T)0)));
+                    }
+                            if (rdep == 1) {
+                        double* const xr = a.xring + ((size_t)tile * F + f) * NRP + tid;
+                        *xr = (hf ? *xr : start_value(f, rg)) + (double)mul_t(nd[f], rsr);
+                    }
+                }
+            }
+            __syncthreads();
+            for (int p = tid; p < a.nprob * F; p += NT)
+                if (s_held[p] & 2) s_held[p] = 1;
+            __syncthreads();
+        }
 
         // ---- inner iterations; the first only forms u, w and their products ------
         if (keep) {
-            const uint32_t im = inner_mask();
-            ring_pub(a.pubR, im, nr);
 #pragma unroll
             for (int f = 0; f < F; ++f) {
+                nr[f] = wn[f];
                 np_[f] = nd[f] = ns[f] = (T)0;
-#pragma unroll
+    #pragma unroll
                 for (int o = 0; o < OWN; ++o) vp[f][o] = vd[f][o] = vs[f][o] = (T)0;
+                d_put(f);
             }
         }
         for (int it = 0;; ++it) {
@@ -730,16 +851,10 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                 const uint32_t im = inner_mask();
                 if (!im) continue;
                 const int g0 = fresh(o_g0);
-                if (!keep) {
-                    load_img();
-                    const Vec t = *reinterpret_cast<const Vec*>(a.sqd + (size_t)tile * NTN +
-                                                                (size_t)tid * OWN);
-#pragma unroll
-                    for (int o = 0; o < OWN; ++o) sqd[o * NT + tid] = t.v[o];
-                }
+                if (!keep) load_img();
                 if (STREAM) {
-                    T uo[F][OWN], un[F], wn[F];
-                    ring_pub(it == 0 ? a.pubR : a.pubW[ex ^ 1], im, wn);
+                    T uo[F][OWN], un[F];
+                    ring_pub(it == 0 ? a.pubR : a.pubW[ex ^ 1], it == 0 ? a.colR : a.colW[ex ^ 1], wn);
 #pragma unroll
                     for (int f = 0; f < F; ++f) {
                         np_[f] = nd[f] = ns[f] = un[f] = (T)0;
@@ -830,17 +945,21 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                         if (sm & (1u << o))
                             st_c(ato(a.pubW[ex] + (size_t)F * no + (size_t)f * nn, g0 + o * nx), vw[f][o]);
                         const T uk = on ? bA[f * EN + q0 + o * EX] : (T)0;
-                        const T rk = mul_t(vr[f][o], sqd[o * NT + tid]);
-                        pd[f] = dot_t(pd[f], vr[f][o], uk);
+                        // opaque: its conversion to FP64 is made here, not carried along with r
+                        const T rk = fresh(vr[f][o]);
+                        pd[f] = dot_t(pd[f], rk, uk);
                         pd[F + f] = dot_t(pd[F + f], vw[f][o], uk);
                         pd[2 * F + f] = dot_t(pd[2 * F + f], rk, rk);
                     }
+                    col_pub(a.colW[ex], f, vw[f]);
                     if (!keep) st_own(4, f, vw[f]);
                 }
                 store_sums(pd, NV);
             }
             ex ^= 1;
-            alive = reduce(NV);
+            alive = reduce(NV, [&] {
+                if (keep) ring_pub(a.pubW[ex ^ 1], a.colW[ex ^ 1], wn);
+            });
             if (!alive) break;
             more = 0;
             for (int p = tid; p < a.nprob * F; p += NT) {
@@ -878,8 +997,7 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
             if (keep) {
                 const uint32_t im = inner_mask();
                 const int q0 = fresh(o_q0), rq = fresh(o_rq);
-                T uo[F][OWN], un[F], wn[F];
-                ring_pub(a.pubW[ex ^ 1], im, wn);
+                T uo[F][OWN], un[F];
 #pragma unroll
                 for (int f = 0; f < F; ++f) {
 #pragma unroll
@@ -906,8 +1024,11 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
 #pragma unroll
             for (int o = 0; o < OWN; ++o) {
                 if (!(am & (1u << o))) continue;
-                const size_t q = (size_t)f * nn + o_g0 + o * nx;
-                out[q] = s_zero[p] ? (T)0 : (T)a.x64[(size_t)F * no + q];
+                const int kk = fresh(o_g0) + o * nx;
+                const size_t q = (size_t)F * no + (size_t)f * nn;
+                const double x = s_held[p] ? ldo(a.x64 + q, kk)
+                                           : own_start(ldo(a.b + q, kk), ldo(a.w + no, kk));
+                *ato(out + (size_t)f * nn, kk) = s_zero[p] ? (T)0 : (T)x;
             }
         }
     }
@@ -1034,10 +1155,13 @@ int pcg_grid(int tsize, bool small, bool batch, int F, int ntiles, int device) {
     return g < ntiles ? g : ntiles;
 }
 
-size_t pcg_workspace_bytes(int tsize, bool small, int F, int nprob, int ntiles, size_t nodes, int grid) {
+size_t pcg_column_elems(const Mesh& m, int per_row) { return (size_t)2 * PH * per_row * m.ny; }
+
+size_t pcg_workspace_bytes(int tsize, bool small, int F, int nprob, int ntiles, size_t nodes,
+                           size_t cols, int grid) {
     size_t s = al(kSyncWords * sizeof(unsigned)) + al((size_t)2 * 3 * F * ntiles * sizeof(double)) +
                al((size_t)2 * 3 * F * nprob * sizeof(double)) + al((size_t)F * nodes * sizeof(double)) +
-               3 * al((size_t)F * nodes * tsize) +
+               3 * al((size_t)F * nodes * tsize) + 3 * al((size_t)F * cols * tsize) +
                al((size_t)ntiles * F * (small ? TileS::NRP : TileL::NRP) * sizeof(double));
     if (ntiles > grid) {
         if (tsize == 8) s += stream_bytes<double, TileS>(F, ntiles);
@@ -1084,6 +1208,9 @@ hipError_t launch_pcg(const PolySolve<T>& ps, int start, const p2m_solve_opts& o
     a.pubR = (T*)take((size_t)F * ps.nodes * sizeof(T));
     a.pubW[0] = (T*)take((size_t)F * ps.nodes * sizeof(T));
     a.pubW[1] = (T*)take((size_t)F * ps.nodes * sizeof(T));
+    a.colR = (T*)take((size_t)F * ps.cols * sizeof(T));
+    a.colW[0] = (T*)take((size_t)F * ps.cols * sizeof(T));
+    a.colW[1] = (T*)take((size_t)F * ps.cols * sizeof(T));
     a.xring = (double*)take((size_t)ps.ntiles * F * (ps.small ? TileS::NRP : TileL::NRP) * sizeof(double));
     if (ps.ntiles > ps.grid) {
         const size_t n = (size_t)ps.ntiles;
@@ -1091,7 +1218,7 @@ hipError_t launch_pcg(const PolySolve<T>& ps, int start, const p2m_solve_opts& o
         const size_t ring = ps.small ? TileS::NRP : TileL::NRP, en = ps.small ? TileS::EN : TileL::EN;
         a.own = (T*)take(n * 6 * F * own * sizeof(T));
         a.ring = (T*)take(n * 5 * F * ring * sizeof(T));
-        a.sqd = (T*)take(n * own * sizeof(T));
+        a.rsd = (T*)take(n * own * sizeof(T));
         a.cimg = (T*)take(n * 3 * en * sizeof(T));
     }
     hipLaunchKernelGGL(k_pcg_clear, dim3(1), dim3(256), 0, stream, words, kSyncWords, ps.clear_rep);
