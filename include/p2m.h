@@ -353,8 +353,10 @@ p2m_status p2m_x1d_volumes(void* ctx, const p2m_problem* prob, void* vol_out, p2
  * The mesh mass system is solved directly by a 2D FFT in FP64 when both sides are
  * at most 1024 or powers of two up to 2048 (it is circulant; the report then shows
  * 0 iterations),
- * otherwise, like the particle mass system, by the FP64 streaming CG to opts->tol
- * (NULL: 1e-14).  Kinds are those of p2m_x1d_kind; the quadrature is always the
+ * otherwise by the FP64 streaming CG to opts->tol (NULL: 1e-14).  The particle mass
+ * system is solved to opts->tol by the Chebyshev iteration on its known spectrum
+ * [1/2, 2] (F <= 3; the report's iterations are its steps) and, where that is not
+ * enough or does not apply, by the streaming CG.  Kinds are those of p2m_x1d_kind; the quadrature is always the
  * Appendix-B rule.
  * Each call synchronises `stream` once, after binning.  Particles that cannot be
  * located are left out (P2M) and get NaN (M2P). rep (device) is required.

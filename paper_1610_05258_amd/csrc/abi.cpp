@@ -1043,6 +1043,16 @@ p2m_status x2d_run_m2p(const Context* c, const Prepared& pp, const X2DLayout& X,
         cw.ell_col = ecol;
         cw.ell_w = P2M_X2D_MAXDEG;
         const p2m_solve_opts o = x1d_opts(opts, N);
+        // the Chebyshev iteration on the CG's vectors (its partials and counters on the
+        // second x64 half), then the CG, which returns at once where that sufficed
+        int* ok = nullptr;
+        char* spare = w8 + X.x64 + align_up((size_t)F * N * sizeof(double));
+        const size_t parts = align_up((size_t)2 * F * ((N + 255) / 256) * sizeof(double));
+        if (parts + pmass_sync_bytes() <= (size_t)F * N * sizeof(double) - kAlign && F * N > 4096)
+            P2M_TRY(launch_pmass(N, F, coef, ecol, cvec, A.vol, (double*)cw.p0, (double*)cw.p1,
+                                 (double*)cw.q, (double*)spare, spare + parts, o.tol, o.maxit,
+                                 pp.solve_spin, xs, rep, &ok, pp.stream));
+        cw.skip = ok;
         P2M_TRY(launch_cg<double>(mp, F, coef, cvec, A.vol, xs, P2M_START_FLIP, cw, o, rep,
                                   pp.stream));
     }

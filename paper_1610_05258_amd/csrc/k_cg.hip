@@ -95,6 +95,7 @@ struct CgArgs {
     long spin;         // polls before a grid-barrier wait gives up (< 0: at once)
     const int32_t* ecol;  // columns of the sparse-row form ([ew][nn]), else unused
     int ew;               // slots per row of that form
+    const int* skip;   // nothing to do if *skip is not 0 (null: always solve)
     p2m_solve_opts opts;
     p2m_report* rep;
 };
@@ -238,6 +239,7 @@ __device__ __forceinline__ double recip(double d) { return 1.0 / d; }
 
 template <typename T, int DIM, int F>
 __global__ __launch_bounds__(kCgBlock) void k_cg(CgArgs<T> a) {
+    if (a.skip && *a.skip) return;
     const Mesh& m = a.m;
     const int nn = m.nn;
     const int nblocks = gridDim.x;
@@ -628,6 +630,7 @@ hipError_t launch_cg(const Mesh& m, int F, T* coef, T* b, const T* w, T* x, int 
     a.spin = ws.spin;
     a.ecol = ws.ell_col;
     a.ew = ws.ell_w;
+    a.skip = ws.skip;
     a.opts = opts;
     a.rep = rep;
     void* args[] = {&a};

@@ -20,7 +20,8 @@
 //   k_x2d_mpart    the consistent particle mass matrix in the sparse-row form of
 //                  the streaming CG (diagonal, then the off-diagonal slots)
 //   k_x2d_mmesh    the consistent mesh mass stencil (D, E, N, NE)
-// The mass systems are solved by the streaming CG (k_cg.hip).
+// The particle mass system is solved by k_pmass.hip, the mesh one by FFT (k_ns.hip) or the
+// streaming CG (k_cg.hip).
 #include "p2m_internal.hpp"
 
 namespace p2m {
@@ -605,10 +606,9 @@ __global__ void k_x2d_mpart(Geo g, const double* __restrict__ xs, const double* 
         }
     }
     coef[k] = diag / 6.0;
-    for (int i = d; i < kCap; ++i) {
-        coef[N + (size_t)i * N + k] = 0.0;
-        ecol[(size_t)i * N + k] = -1;
-    }
+    // a column of -1 ends the row (the solves read no slot behind it); clearing all 32
+    // slots wrote 400 MB a million particles
+    if (d < kCap) ecol[(size_t)d * N + k] = -1;
 }
 
 // consistent mesh mass stencil (Sec. 2.4 on the "/" split): D = hx hy / 2 and

@@ -218,6 +218,7 @@ struct CgWorkspace {
     long spin = kSolveSpinDefault;   // bound of a grid-barrier wait (< 0: every wait ends at once)
     const int32_t* ell_col = nullptr;  // sparse-row matrix (Mesh::dim == 3): columns [ell_w][nn]
     int ell_w = 0;
+    const int* skip = nullptr;         // device word: the solve returns at once if it is not 0
 };
 size_t cg_partials_bytes(int blocks);
 // One persistent kernel with its own grid barrier: orphan regularisation of
@@ -229,6 +230,16 @@ hipError_t launch_cg(const Mesh& m, int F, T* coef, T* b, const T* w, T* x, int 
                      hipStream_t stream);
 template <typename T>
 int cg_max_blocks(int device);
+
+// particle mass system of the paper-exact 2D M2P by the Chebyshev iteration (k_pmass.hip),
+// F <= 3: x0, x1, d [F][N], part [2 F][(N + 255) / 256], sync pmass_sync_bytes().  *ok
+// receives the device word that is 1 once out holds the solution (null: not attempted);
+// the CG is enqueued behind it with that word as its skip
+size_t pmass_sync_bytes();
+hipError_t launch_pmass(int N, int F, const double* coef, const int32_t* ecol, const double* c,
+                        const double* vol, double* x0, double* x1, double* d, double* part, void* sync,
+                        double tol, int maxit, long spin, double* out, p2m_report* rep, int** ok,
+                        hipStream_t stream);
 
 // register-resident solve for 2D FP32 problems whose tiles fit one workgroup per
 // tile on the device (k_cgr.hip)
