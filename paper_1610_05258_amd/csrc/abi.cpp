@@ -818,7 +818,7 @@ p2m_solve_opts x1d_opts(const p2m_solve_opts* o, int n) {
 // ---------------------------------------------------------------------------
 struct X2DLayout {
     size_t key, counts, scan, cell_start, perm;          // binning (as in Layout)
-    size_t xs, ys, cell, As, deg, nbr, nsh, vol, volc, H, b, bw, coef, ecol, w, x, fft;
+    size_t xs, ys, cell, As, deg, lst, nleft, vol, volc, H, b, bw, coef, ecol, w, x, fft;
     size_t r, p0, p1, q, x64, dinv, part, report, total;
     int blocks;
 };
@@ -846,8 +846,8 @@ X2DLayout make_x2d_layout(const Context* c, const Mesh& m, int F) {
     L.cell = take(np * i4);
     L.As = take((size_t)F * np * d8);
     L.deg = take(np * i4);
-    L.nbr = take(np * cap * i4);
-    L.nsh = take(np * cap * i4);
+    L.lst = take(2 * np * cap * i4);
+    L.nleft = take(i4);
     L.vol = take(np * d8);
     L.volc = take(np * d8);
     L.H = take((size_t)F * 4 * n * d8);
@@ -926,8 +926,9 @@ p2m_status x2d_begin(void* ctx, const p2m_problem* prob, int F, const void* valu
     A.cell = (int32_t*)(w8 + X.cell);
     A.As = (double*)(w8 + X.As);
     A.deg = (int32_t*)(w8 + X.deg);
-    A.nbr = (int32_t*)(w8 + X.nbr);
-    A.nsh = (int32_t*)(w8 + X.nsh);
+    A.lst = (int32_t*)(w8 + X.lst);
+    A.nleft = (int32_t*)(w8 + X.nleft);
+    A.left = (int32_t*)(w8 + X.volc);   // the volumes in caller order are formed later
     A.vol = (double*)(w8 + X.vol);
     A.rep = pp.rep;
     P2M_TRY(x2d_triangulate(A, pp.stream));
@@ -1024,13 +1025,13 @@ p2m_status x2d_run_m2p(const Context* c, const Prepared& pp, const X2DLayout& X,
     char* w8 = pp.ws;
     double* cvec = (double*)(w8 + X.b);
     double* xs = (double*)(w8 + X.x);
-    P2M_TRY(x2d_rhs_part(A, nodal, cvec, pp.stream));
+    double* const coef = (double*)(w8 + X.coef);
+    int32_t* const ecol = (int32_t*)(w8 + X.ecol);
+    const bool mass = kind != P2M_X1D_LUMPED;
+    P2M_TRY(x2d_rhs_part(A, nodal, cvec, mass ? coef : nullptr, mass ? ecol : nullptr, pp.stream));
     if (kind == P2M_X1D_LUMPED) {
         P2M_TRY(x1d_div(N, F, cvec, A.vol, 0.0, xs, pp.stream));
     } else if (N > 0) {
-        double* coef = (double*)(w8 + X.coef);
-        int32_t* ecol = (int32_t*)(w8 + X.ecol);
-        P2M_TRY(x2d_mass_part(A, coef, ecol, pp.stream));
         Mesh mp;
         memset(&mp, 0, sizeof(mp));
         mp.dim = 3;

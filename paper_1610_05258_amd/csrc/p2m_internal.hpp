@@ -189,8 +189,10 @@ struct X2dArgs {
     int32_t* cell;         // [N]
     double* As;            // [F][N] values in binned order
     int32_t* deg;          // [N]
-    int32_t* nbr;          // [N][P2M_X2D_MAXDEG] neighbour slots, counter-clockwise
-    int32_t* nsh;          // [N][P2M_X2D_MAXDEG] packed image shifts
+    int32_t* lst;          // [N][2 P2M_X2D_MAXDEG] neighbour slots, counter-clockwise, and their
+                           // packed image shifts, in alternating groups of four
+    int32_t* nleft;        // particles left to the triangulation's general kernel, and
+    int32_t* left;         // [N] which
     double* vol;           // [N] int psi_mu
     p2m_report* rep;
 };
@@ -202,8 +204,9 @@ hipError_t x2d_export(const X2dArgs& a, int32_t* deg_out, int32_t* nbr_out, int3
 hipError_t x2d_locate(const X2dArgs& a, bool half, double* out, hipStream_t stream);
 hipError_t x2d_rhs_mesh(const X2dArgs& a, const double* H, double* b, hipStream_t stream);
 hipError_t x2d_mass_mesh(const X2dArgs& a, double* coef, double* w, hipStream_t stream);
-hipError_t x2d_rhs_part(const X2dArgs& a, const double* nodal, double* c, hipStream_t stream);
-hipError_t x2d_mass_part(const X2dArgs& a, double* coef, int32_t* ecol, hipStream_t stream);
+// with coef and ecol (not null) also the particle mass matrix in sparse-row form
+hipError_t x2d_rhs_part(const X2dArgs& a, const double* nodal, double* c, double* coef, int32_t* ecol,
+                        hipStream_t stream);
 
 // mass solve
 struct CgWorkspace {
