@@ -1368,11 +1368,9 @@ p2m_status p2m_ns_step(void* ctx, const p2m_problem* prob, int32_t assign, doubl
     //    O(n) CG iterations, so the pressure solve's cap is at least 64 per mesh side.
     const double sv = dt * nu / (h * h);
     if (c->fft && fft_supported(m)) {
-        P2M_TRY(launch_report_clear(&reps[1], pp.stream));
-        P2M_TRY(launch_report_clear(&reps[2], pp.stream));
-        P2M_TRY(launch_ns_fft_solve(m, 2, sv, 0, ubar, ustar, w + N.fft, pp.stream));
-        P2M_TRY(launch_ns_div(m, -(h / 6.0) / dt, 0, ustar, rhs, pp.stream));
-        P2M_TRY(launch_ns_fft_solve(m, 1, 0.0, 1, rhs, pr, w + N.fft, pp.stream));
+        P2M_TRY(launch_report_clear_n(&reps[1], 2, pp.stream));
+        P2M_TRY(launch_ns_viscous(m, sv, ubar, ustar, w + N.fft, pp.stream));
+        P2M_TRY(launch_ns_pressure(m, -(h / 6.0) / dt, ustar, pr, w + N.fft, pp.stream));
     } else {
         P2M_TRY(launch_ns_coef(m, (float)sv, cv, wv, cpr, wpr, pp.stream));
         Prepared pv = pp;
@@ -1383,7 +1381,7 @@ p2m_status p2m_ns_step(void* ctx, const p2m_problem* prob, int32_t assign, doubl
         s = run_solve<float>(c, pv, 2, ubar, wv, cv, P2M_START_FLIP, ov, ustar,
                              choose(c, m, P2M_F32, 2));
         if (s != P2M_OK) return s;
-        P2M_TRY(launch_ns_div(m, -(h / 6.0) / dt, 1, ustar, rhs, pp.stream));
+        P2M_TRY(launch_ns_div(m, -(h / 6.0) / dt, ustar, rhs, pp.stream));
         Prepared pq = pp;
         pq.rep = &reps[2];
         pq.clear_rep = true;

@@ -368,26 +368,28 @@ hipError_t launch_learned_start(const Mesh& m, Particles<float> P, const float* 
                                 void* ws, p2m_report* rep, hipStream_t stream);
 
 // particle fluid solver (k_ns.hip): stencil arrays of the viscous system I + s K and of
-// the pressure system K (node 0 held), the pressure right-hand side -(1/dt) D U*, the
-// projection U* - dt M_L^-1 G p, and the mid-point advection of the particles
+// the pressure system K (node 0 held), the pressure right-hand side -(1/dt) D U* (0 at
+// the held node), the projection U* - dt M_L^-1 G p, and the mid-point advection of the
+// particles
 hipError_t launch_ns_coef(const Mesh& m, float s, float* cv, float* wv, float* cp, float* wp,
                           hipStream_t stream);
-hipError_t launch_ns_div(const Mesh& m, double scale, int pin, const float* U, float* rhs,
-                         hipStream_t stream);
-// direct solve of nb right-hand sides of the viscous (I + s K, pressure = 0) or the
-// pressure system (K, zero-mean solution) by 2D FFT; power-of-two sides <= 2048
-// the same 2D FFT solve for nb right-hand sides of type R (mode: kFftViscous
-// (I + s K), kFftPressure (K, zero mean), kFftMass (the consistent P1 mass matrix
-// of the "/" split with s = hx hy)); workspace fft_workspace_bytes(m, nb)
-// Sides: powers of two up to 2048, other lengths up to 1024 (fft_supported).
+hipError_t launch_ns_div(const Mesh& m, double scale, const float* U, float* rhs, hipStream_t stream);
+// Direct solve of nb right-hand sides by 2D FFT (mode: kFftViscous (I + s K),
+// kFftPressure (K, zero mean), kFftMass (the consistent P1 mass matrix of the "/" split
+// with s = hx hy)); workspace fft_workspace_bytes(m, nb).  Sides: powers of two up to
+// 2048, other lengths up to 1024 (fft_supported).
 enum { kFftViscous = 0, kFftPressure = 1, kFftMass = 2 };
 bool fft_supported(const Mesh& m);
 size_t fft_workspace_bytes(const Mesh& m, int nb);
 template <typename R>
 hipError_t launch_fft_solve(const Mesh& m, int nb, double s, int mode, const R* rhs, R* x,
                             void* ws, hipStream_t stream);
-hipError_t launch_ns_fft_solve(const Mesh& m, int nb, double s, int pressure, const float* rhs,
-                               float* x, void* ws, hipStream_t stream);   // workspace for nb <= 2
+// the two solves of a fluid step: (I + s K) x = rhs for both components, and the
+// pressure with its right-hand side scale * div_sum(U) formed where it is read
+hipError_t launch_ns_viscous(const Mesh& m, double s, const float* rhs, float* x, void* ws,
+                             hipStream_t stream);
+hipError_t launch_ns_pressure(const Mesh& m, double scale, const float* U, float* p, void* ws,
+                              hipStream_t stream);
 hipError_t launch_ns_correct(const Mesh& m, double factor, const float* Us, const float* p,
                              float* Un, hipStream_t stream);
 hipError_t launch_ns_advect(const Mesh& m, double lx, double ly, double dt, const float* x,
