@@ -96,6 +96,7 @@ struct CgArgs {
     const int32_t* ecol;  // columns of the sparse-row form ([ew][nn]), else unused
     int ew;               // slots per row of that form
     const int* skip;   // nothing to do if *skip is not 0 (null: always solve)
+    int direct;        // 1D: start from direct_1d's solution
     p2m_solve_opts opts;
     p2m_report* rep;
 };
@@ -237,6 +238,123 @@ __device__ __forceinline__ void grid_total(const double* __restrict__ part, int 
 __device__ __forceinline__ float recip(float d) { return __frcp_rn(d); }
 __device__ __forceinline__ double recip(double d) { return 1.0 / d; }
 
+// Start vector of a 1D solve: the periodic tridiagonal system by parallel cyclic
+// reduction in FP64.  Step s = 1, 2, 4, ... takes the neighbours at distance s out of
+// every row; the couplings that remain, relative to the diagonals, are the squares of
+// those before, so for the consistent mass matrices (off-diagonal sums of at most half
+// the diagonal) nothing is left after 6 steps, whatever the number of nodes, and for
+// assembled ones of a few particles a cell after 7 to 9.  The periodic system is its own
+// unrolled line, so a row's result needs the rows within 255 only: a workgroup reduces
+// its 256 rows with 256 more on either side (8 steps), or, when 256 rows are the whole
+// period, the period itself.  The conjugate gradients that follow check the true
+// residual, as for any start, and end there; they still have the whole work where a
+// pivot of this workgroup's rows falls below 1e-6 of the diagonal (a near-singular
+// matrix, whose null space is theirs to keep out) or is not finite: those rows keep the
+// start formula.
+// Bound: the chain of 6 to 9 steps, each two workgroup barriers and a division.  64 nodes
+// FP64, the whole solve: 7.6 us; by conjugate gradients from the start formula
+// 62 us (two barriers and two reductions an iteration, 20 to 30 of them).
+constexpr int kPcrHalo = kCgBlock;
+constexpr int kPcrRows = kCgBlock + 2 * kPcrHalo;
+
+template <typename T, int F>
+__device__ void direct_1d(const CgArgs<T>& a) {
+    constexpr int R = kPcrRows / kCgBlock;
+    __shared__ double sh[(2 + F) * kPcrRows];
+    double* s_rb = sh;                // 1 / reduced diagonal
+    double* s_a = sh + kPcrRows;      // reduced coupling to the row at distance + s
+    double* s_f = sh + 2 * kPcrRows;  // [F] reduced right-hand sides
+    const int nn = a.m.nn, tid = threadIdx.x;
+    const bool cyc = nn <= kCgBlock;
+    const int W = cyc ? nn : kPcrRows;
+    for (int chunk = blockIdx.x; chunk * kCgBlock < nn; chunk += gridDim.x) {
+        double b[R], c[R], f[R][F], d0 = 1.0;
+        const int own = cyc ? 0 : 1;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int w = tid + r * kCgBlock;
+            b[r] = 1.0;
+            c[r] = 0.0;
+#pragma unroll
+            for (int q = 0; q < F; ++q) f[r][q] = 0.0;
+            if (w >= W) continue;
+            long g = (long)chunk * kCgBlock + w - (cyc ? 0 : kPcrHalo);
+            while (g < 0) g += nn;
+            while (g >= nn) g -= nn;
+            if (a.w[g] > (T)0) {
+                b[r] = (double)a.coef[g];
+                c[r] = (double)a.coef[(size_t)nn + g];
+#pragma unroll
+                for (int q = 0; q < F; ++q) f[r][q] = (double)a.b[(size_t)q * nn + g];
+            }
+            if (r == own) d0 = b[r];
+        }
+        int d = cyc ? 1 % nn : 1;
+        for (int step = 0; step < (cyc ? 12 : 8); ++step) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int w = tid + r * kCgBlock;
+                if (w >= W) continue;
+                s_rb[w] = 1.0 / b[r];
+                s_a[w] = c[r];
+#pragma unroll
+                for (int q = 0; q < F; ++q) s_f[q * kPcrRows + w] = f[r][q];
+            }
+            __syncthreads();
+            int left = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int w = tid + r * kCgBlock;
+                if (w >= W) continue;
+                int p = w + d, m = w - d;
+                if (cyc) {
+                    if (p >= nn) p -= nn;
+                    if (m < 0) m += nn;
+                }
+                double cp = 0.0, b_new = b[r];
+                if (m >= 0) {
+                    const double am = s_a[m], al = am * s_rb[m];
+                    b_new -= al * am;
+#pragma unroll
+                    for (int q = 0; q < F; ++q) f[r][q] -= al * s_f[q * kPcrRows + m];
+                }
+                if (p < W) {
+                    const double ga = c[r] * s_rb[p];
+                    b_new -= ga * c[r];
+                    cp = -ga * s_a[p];
+#pragma unroll
+                    for (int q = 0; q < F; ++q) f[r][q] -= ga * s_f[q * kPcrRows + p];
+                    // what is left couples rows whose pivots are near b_new and 1 / s_rb[p]
+                    left |= cp * cp * s_rb[p] > 0x1p-108 * b_new;
+                }
+                b[r] = b_new;
+                c[r] = cp;
+            }
+            if (!__syncthreads_or(left)) break;
+            d *= 2;
+            if (cyc) d %= nn;
+        }
+        double bo = b[0], xo[F];
+#pragma unroll
+        for (int q = 0; q < F; ++q) xo[q] = f[0][q];
+        if (!cyc) {
+            bo = b[1];
+#pragma unroll
+            for (int q = 0; q < F; ++q) xo[q] = f[1][q];
+        }
+        const int k = chunk * kCgBlock + tid;
+        bool bad = k < nn && !(bo > 1e-6 * d0);
+#pragma unroll
+        for (int q = 0; q < F; ++q) {
+            xo[q] /= bo;
+            bad = bad || (k < nn && !isfinite(xo[q]));
+        }
+        if (__syncthreads_or(bad ? 1 : 0) || k >= nn) continue;
+#pragma unroll
+        for (int q = 0; q < F; ++q) a.x64[(size_t)q * nn + k] = xo[q];
+    }
+}
+
 template <typename T, int DIM, int F>
 __global__ __launch_bounds__(kCgBlock) void k_cg(CgArgs<T> a) {
     if (a.skip && *a.skip) return;
@@ -338,6 +456,9 @@ __global__ __launch_bounds__(kCgBlock) void k_cg(CgArgs<T> a) {
             atomicAdd(&a.rep->n_orphan, 1);
             atomicOr(&a.rep->flags, (uint32_t)P2M_FLAG_ORPHAN);
         }
+    }
+    if constexpr (DIM == 1) {
+        if (a.direct) direct_1d<T, F>(a);
     }
     bool alive = gsync();
 
@@ -631,6 +752,7 @@ hipError_t launch_cg(const Mesh& m, int F, T* coef, T* b, const T* w, T* x, int 
     a.ecol = ws.ell_col;
     a.ew = ws.ell_w;
     a.skip = ws.skip;
+    a.direct = ws.direct && m.dim == 1 && start == P2M_START_FLIP;
     a.opts = opts;
     a.rep = rep;
     void* args[] = {&a};

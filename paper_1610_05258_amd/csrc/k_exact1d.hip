@@ -26,7 +26,7 @@
 //                  particles (g_{k-1} + g_k)/3, g_k/6 (cyclic tridiagonal)
 //   k_x1d_div / k_x1d_scatter
 //                  lumped divisions and the result in caller order
-// The mass solves themselves run in the streaming CG kernel (k_cg.hip) on these
+// The mass solves themselves run in the streaming kernel (k_cg.hip, by cyclic reduction) on these
 // stencils.
 #include "p2m_internal.hpp"
 

@@ -222,6 +222,7 @@ struct CgWorkspace {
     const int32_t* ell_col = nullptr;  // sparse-row matrix (Mesh::dim == 3): columns [ell_w][nn]
     int ell_w = 0;
     const int* skip = nullptr;         // device word: the solve returns at once if it is not 0
+    bool direct = false;               // 1D from the start formula: by cyclic reduction first
 };
 size_t cg_partials_bytes(int blocks);
 // One persistent kernel with its own grid barrier: orphan regularisation of
