@@ -260,6 +260,11 @@ p2m_status prepare(void* ctx, const p2m_problem* prob, int F, void* ws, size_t w
 template <typename T>
 p2m_status run_bin(const Prepared& pp, const p2m_problem* prob, int32_t* perm, int32_t* cs) {
     const Mesh& m = pp.m;
+    if (bin_small_fits(m)) {
+        P2M_TRY(launch_bin_small<T>(m, particles_of<T>(prob), cs, perm, pp.rep, pp.clear_rep, pp.stream));
+        pp.clear_rep = false;
+        return P2M_OK;
+    }
     int32_t* key = (int32_t*)(pp.ws + pp.L.key);
     int32_t* counts = (int32_t*)(pp.ws + pp.L.counts);
     int32_t* rank = key + m.np;
@@ -1218,12 +1223,11 @@ p2m_status p2m_interpolate(void* ctx, const p2m_problem* prob, const void* nodal
     DeviceGuard g(((Context*)ctx)->device);
     if (!g.ok) return P2M_ERR_HIP;
     hipStream_t strm = (hipStream_t)stream;
-    P2M_TRY(launch_report_clear(rep, strm));
     if (prob->dtype == P2M_F64)
         return st(launch_gather<double>(m, particles_of<double>(prob), (const double*)nodal, nfields,
-                                        (double*)values_out, rep, strm, ws, ws ? ws_bytes : 0));
+                                        (double*)values_out, rep, strm, ws, ws ? ws_bytes : 0, true));
     return st(launch_gather<float>(m, particles_of<float>(prob), (const float*)nodal, nfields,
-                                   (float*)values_out, rep, strm, ws, ws ? ws_bytes : 0));
+                                   (float*)values_out, rep, strm, ws, ws ? ws_bytes : 0, true));
 }
 
 p2m_status p2m_mass_assign(void* ctx, const p2m_problem* prob, const void* values, int32_t nfields,
@@ -1507,9 +1511,9 @@ p2m_status p2m_x1d_interpolate(void* ctx, const p2m_problem* prob, int32_t kind,
             if (s != P2M_OK) return s;
         }
         if (pp.m.dim != 1 || prob->dtype != P2M_F64) return P2M_ERR_UNSUPPORTED;
-        P2M_TRY(launch_report_clear(rep, (hipStream_t)stream));
         P2M_TRY(launch_gather<double>(pp.m, particles_of<double>(prob), (const double*)nodal,
-                                      nfields, (double*)values_out, rep, (hipStream_t)stream));
+                                      nfields, (double*)values_out, rep, (hipStream_t)stream, nullptr,
+                                      0, true));
         return P2M_OK;
     }
     Prepared pp;
@@ -1645,9 +1649,9 @@ p2m_status p2m_x2d_interpolate(void* ctx, const p2m_problem* prob, int32_t kind,
         Mesh m;
         s = x2d_check(ctx, prob, nfields, m);
         if (s != P2M_OK) return s;
-        P2M_TRY(launch_report_clear(rep, (hipStream_t)stream));
         P2M_TRY(launch_gather<double>(m, particles_of<double>(prob), (const double*)nodal,
-                                      nfields, (double*)values_out, rep, (hipStream_t)stream));
+                                      nfields, (double*)values_out, rep, (hipStream_t)stream, nullptr,
+                                      0, true));
         return P2M_OK;
     }
     Prepared pp;

@@ -10,7 +10,8 @@
 //   segment_sort : every cell sorts its slots by original index, which makes the
 //                  permutation exactly the stable (cell, original index) order
 //
-// The result does not depend on the order in which the atomics were served.
+// The result does not depend on the order in which the atomics were served.  A small
+// problem is binned by one kernel of one workgroup (k_bin_small).
 //
 // Every wait is bounded.  If the scan's look-back gives up on a predecessor, it
 // raises P2M_FLAG_BIN_TIMEOUT and an abort word; place then leaves every cell
@@ -24,38 +25,12 @@ namespace {
 
 constexpr int kBlock = kBinBlock;
 
-__global__ void k_report_clear(p2m_report* rep) {
-    int t = threadIdx.x;
-    if (t < 8) {
-        rep->iters[t] = 0;
-        rep->refines[t] = 0;
-        rep->rel_residual[t] = 0.0;
-    }
-    if (t == 0) {
-        rep->flags = 0u;
-        rep->n_orphan = 0;
-        rep->n_invalid = 0;
-        rep->reserved = 0;
-    }
-}
+__global__ void k_report_clear(p2m_report* rep) { report_clear(rep, 0u, 0); }
 
 // Fill of n ints; with rep, block 0 also zeroes that report (one launch for both).
 __global__ void k_fill_i32(int32_t* __restrict__ p, int32_t value, size_t n,
                            p2m_report* __restrict__ rep) {
-    if (rep && blockIdx.x == 0) {
-        const int t = threadIdx.x;
-        if (t < 8) {
-            rep->iters[t] = 0;
-            rep->refines[t] = 0;
-            rep->rel_residual[t] = 0.0;
-        }
-        if (t == 0) {
-            rep->flags = 0u;
-            rep->n_orphan = 0;
-            rep->n_invalid = 0;
-            rep->reserved = 0;
-        }
-    }
+    if (rep && blockIdx.x == 0) report_clear(rep, 0u, 0);
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     size_t stride = (size_t)gridDim.x * blockDim.x;
     for (; i < n; i += stride) p[i] = value;
@@ -456,7 +431,7 @@ __device__ __forceinline__ bool rank_sort_small(int32_t* __restrict__ seg, int n
     return n <= 8 ? sort_small<8>(seg, n) : sort_small<kSortReg>(seg, n);
 }
 
-// One segment of n entries sorted ascending by all kBlock threads of the
+// One segment of n entries sorted ascending by all BLOCK threads of the
 // workgroup (every thread calls it; seg is LDS or global memory private to the
 // workgroup).  Bitonic sort in the form whose comparators all put the smaller
 // value at the lower index: each merge of two sorted halves of a block of k
@@ -466,6 +441,7 @@ __device__ __forceinline__ bool rank_sort_small(int32_t* __restrict__ seg, int n
 // entries in place, so it is skipped and the padding is never stored.  The
 // values are distinct particle numbers.  Returns (to every thread) whether any
 // entry moved.
+template <int BLOCK = kBlock>
 __device__ __forceinline__ bool block_sort_segment(int32_t* seg, int n, int* moved_flag) {
     int P = 1;
     while (P < n) P <<= 1;
@@ -474,7 +450,7 @@ __device__ __forceinline__ bool block_sort_segment(int32_t* seg, int n, int* mov
     int moved = 0;
     for (int k = 2; k <= P; k <<= 1) {
         const int half = k >> 1;
-        for (int q = threadIdx.x; q < P / 2; q += kBlock) {
+        for (int q = threadIdx.x; q < P / 2; q += BLOCK) {
             const int blk = q / half, off = q - blk * half;
             const int i = blk * k + off, j = blk * k + k - 1 - off;
             if (j < n) {
@@ -488,7 +464,7 @@ __device__ __forceinline__ bool block_sort_segment(int32_t* seg, int n, int* mov
         }
         __syncthreads();
         for (int d = k >> 2; d >= 1; d >>= 1) {
-            for (int q = threadIdx.x; q < P / 2; q += kBlock) {
+            for (int q = threadIdx.x; q < P / 2; q += BLOCK) {
                 const int blk = q / d;
                 const int i = blk * 2 * d + (q - blk * d), j = i + d;
                 if (j < n) {
@@ -570,6 +546,119 @@ __global__ __launch_bounds__(kBlock) void k_segment_sort(int ncells,
     for (int t = lo + (int)threadIdx.x; t < hi; t += kBlock) perm[t] = st[t - lo];
 }
 
+// The whole binning by one workgroup, for at most kSmallMax cells and
+// kSmallMax particles: counts, ranks and the permutation stay in LDS, so the five kernels' waits
+// for memory and their launches become one.  With clear it writes the report whole,
+// otherwise it adds to it.  The result is that of the other kernels, the stable (cell,
+// original index) order.
+// Bound: the launch and the dependent passes' latency.  256 particles in 64 cells: 4.3 us,
+// against five launches of 14 us together and their gaps (the 64-node step went from 43 to
+// 27 us); 8100 particles in 8100 cells: 18 us (the 90 x 90 paper-exact pass from 340 to
+// 327 us).  The line lies at one scan tile, 8192: the time grows with the particles and
+// meets that of the five launches (30 us) soon after.
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallItems = 8;
+constexpr int kSmallMax = kSmallBlock * kSmallItems;   // one scan tile
+
+template <typename T>
+__global__ __launch_bounds__(kSmallBlock) void k_bin_small(Mesh m, Particles<T> P,
+                                                           int32_t* __restrict__ cell_start,
+                                                           int32_t* __restrict__ perm,
+                                                           p2m_report* __restrict__ rep, int clear) {
+    __shared__ int32_t s_cs[kSmallMax + 1], s_perm[kSmallMax];
+    __shared__ int s_wave[kSmallBlock / 64], s_big[kSmallBlock];
+    __shared__ int s_nbig, s_flag, s_inv;
+    __shared__ uint32_t s_flags;
+    const int tid = threadIdx.x, nc = m.nn;
+    T px[kSmallItems], py[kSmallItems];
+#pragma unroll
+    for (int u = 0; u < kSmallItems; ++u) {
+        const int i = tid + u * kSmallBlock;
+        px[u] = py[u] = (T)0;
+        if (i < m.np) {
+            px[u] = P.x[i];
+            if (m.dim == 2) py[u] = P.y[i];
+        }
+    }
+    for (int c = tid; c < nc; c += kSmallBlock) s_cs[c] = 0;
+    if (tid == 0) {
+        s_inv = 0;
+        s_flags = 0u;
+    }
+    __syncthreads();
+    int key[kSmallItems], rank[kSmallItems];
+#pragma unroll
+    for (int u = 0; u < kSmallItems; ++u) {
+        const int i = tid + u * kSmallBlock;
+        key[u] = -1;
+        rank[u] = 0;
+        if (i >= m.np) continue;
+        bool fin_x = true, fin_y = true;
+        int cx = 0, cy = 0;
+        double xi, eta;
+        bool ok = locate_axis((double)px[u], m.nx, m.inv_hx, cx, xi, fin_x);
+        if (m.dim == 2) ok = locate_axis((double)py[u], m.ny, m.inv_hy, cy, eta, fin_y) && ok;
+        if (ok) {
+            key[u] = cx + m.nx * cy;
+            rank[u] = atomicAdd(&s_cs[key[u]], 1);
+        } else {
+            atomicOr(&s_flags, fin_x && fin_y ? (uint32_t)P2M_FLAG_RANGE : (uint32_t)P2M_FLAG_NONFINITE);
+            atomicAdd(&s_inv, 1);
+        }
+    }
+    __syncthreads();
+    // exclusive scan of the counts in place, each thread a run of adjacent cells
+    const int per = (nc + kSmallBlock - 1) / kSmallBlock;
+    const int c0 = tid * per, c1 = min(c0 + per, nc);
+    int sum = 0;
+    for (int c = c0; c < c1; ++c) sum += s_cs[c];
+    const int inc = wave_inclusive_scan(sum);
+    if ((tid & 63) == 63) s_wave[tid >> 6] = inc;
+    __syncthreads();
+    int ex = inc - sum;
+    for (int w = 0; w < (tid >> 6); ++w) ex += s_wave[w];
+    for (int c = c0; c < c1; ++c) {
+        const int n = s_cs[c];
+        s_cs[c] = ex;
+        ex += n;
+    }
+    if (tid == kSmallBlock - 1) s_cs[nc] = ex;
+    __syncthreads();
+    const int valid = s_cs[nc];
+#pragma unroll
+    for (int u = 0; u < kSmallItems; ++u)
+        if (key[u] >= 0) s_perm[s_cs[key[u]] + rank[u]] = tid + u * kSmallBlock;
+    for (int c = tid; c <= nc; c += kSmallBlock) cell_start[c] = s_cs[c];
+    __syncthreads();
+    // the cells' slots by particle number: small cells by a thread each, the others one
+    // after the other by the workgroup
+    for (int b = 0; b < nc; b += kSmallBlock) {
+        if (tid == 0) s_nbig = 0;
+        __syncthreads();
+        const int c = b + tid;
+        if (c < nc) {
+            const int s = s_cs[c], n = s_cs[c + 1] - s;
+            if (n > kSortReg) s_big[atomicAdd(&s_nbig, 1)] = c;
+            else if (n > 1) rank_sort_small(s_perm + s, n);
+        }
+        __syncthreads();
+        const int nb = s_nbig;
+        for (int k = 0; k < nb; ++k) {
+            const int cc = s_big[k];
+            block_sort_segment<kSmallBlock>(s_perm + s_cs[cc], s_cs[cc + 1] - s_cs[cc], &s_flag);
+        }
+        __syncthreads();
+    }
+    for (int i = tid; i < m.np; i += kSmallBlock) perm[i] = i < valid ? s_perm[i] : -1;
+    if (!rep) return;
+    if (clear) {
+        report_clear(rep, s_flags, s_inv);
+    } else if (tid == 0 && s_inv > 0) {
+        atomicOr(&rep->flags, s_flags);
+        atomicAdd(&rep->n_invalid, s_inv);
+    }
+}
+
 inline int grid_for(size_t n, int block) { return (int)((n + block - 1) / block); }
 
 }  // namespace
@@ -589,6 +678,20 @@ hipError_t launch_fill_i32(int32_t* p, int32_t value, size_t n, hipStream_t stre
     hipLaunchKernelGGL(k_fill_i32, dim3(grid), dim3(kBlock), 0, stream, p, value, n, rep);
     return hipGetLastError();
 }
+
+bool bin_small_fits(const Mesh& m) { return m.nn <= kSmallMax && m.np <= kSmallMax && m.np > 0; }
+
+template <typename T>
+hipError_t launch_bin_small(const Mesh& m, Particles<T> P, int32_t* cell_start, int32_t* perm,
+                            p2m_report* rep, bool clear, hipStream_t stream) {
+    hipLaunchKernelGGL(k_bin_small<T>, dim3(1), dim3(kSmallBlock), 0, stream, m, P, cell_start, perm,
+                       rep, clear ? 1 : 0);
+    return hipGetLastError();
+}
+template hipError_t launch_bin_small<float>(const Mesh&, Particles<float>, int32_t*, int32_t*,
+                                            p2m_report*, bool, hipStream_t);
+template hipError_t launch_bin_small<double>(const Mesh&, Particles<double>, int32_t*, int32_t*,
+                                             p2m_report*, bool, hipStream_t);
 
 template <typename T>
 hipError_t launch_locate_count(const Mesh& m, Particles<T> P, int32_t* key, int32_t* rank,

@@ -21,6 +21,13 @@ __device__ __forceinline__ void flag_invalid(p2m_report* rep, bool finite) {
     if (rep) atomicOr(&rep->flags, finite ? (uint32_t)P2M_FLAG_RANGE : (uint32_t)P2M_FLAG_NONFINITE);
 }
 
+// The report's zeroing by a kernel of one workgroup, before any of its threads flags.
+__device__ __forceinline__ void clear_first(p2m_report* rep) {
+    report_clear(rep, 0u, 0);
+    __threadfence();
+    __syncthreads();
+}
+
 // Cell corners and P1 weights of particle i's triangle (the "/" split); ok is
 // false for a particle that cannot be located (flagged, NaN output).
 template <typename T>
@@ -66,7 +73,8 @@ constexpr int kGatherItems = 4;
 
 template <typename T>
 __global__ void k_gather2d(Mesh m, Particles<T> P, const T* __restrict__ nodal, int F,
-                           T* __restrict__ out, p2m_report* __restrict__ rep) {
+                           T* __restrict__ out, p2m_report* __restrict__ rep, int clear) {
+    if (clear) clear_first(rep);
     const int base = blockIdx.x * blockDim.x * kGatherItems + threadIdx.x;
     T px[kGatherItems], py[kGatherItems];
 #pragma unroll
@@ -144,7 +152,9 @@ __global__ void k_gather2d_nm(Mesh m, Particles<T> P, const T* __restrict__ nm,
 
 // nm[k * F + f] = nodal[f * nn + k]
 template <typename T>
-__global__ void k_node_major(const T* __restrict__ nodal, int F, int nn, T* __restrict__ nm) {
+__global__ void k_node_major(const T* __restrict__ nodal, int F, int nn, T* __restrict__ nm,
+                             p2m_report* __restrict__ clear_rep) {
+    if (clear_rep && blockIdx.x == 0) report_clear(clear_rep, 0u, 0);
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= nn) return;
     for (int f = 0; f < F; ++f) nm[(size_t)k * F + f] = nodal[(size_t)f * nn + k];
@@ -152,7 +162,8 @@ __global__ void k_node_major(const T* __restrict__ nodal, int F, int nn, T* __re
 
 template <typename T>
 __global__ void k_gather1d(Mesh m, Particles<T> P, const T* __restrict__ nodal, int F,
-                           T* __restrict__ out, p2m_report* __restrict__ rep) {
+                           T* __restrict__ out, p2m_report* __restrict__ rep, int clear) {
+    if (clear) clear_first(rep);
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= m.np) return;
     int cx;
@@ -292,16 +303,25 @@ __global__ void k_delta1d(Mesh m, Particles<T> P, const T* __restrict__ values, 
 
 template <typename T>
 hipError_t launch_gather(const Mesh& m, Particles<T> P, const T* nodal, int F, T* out,
-                         p2m_report* rep, hipStream_t stream, void* ws, size_t ws_bytes) {
-    if (m.np == 0) return hipSuccess;
+                         p2m_report* rep, hipStream_t stream, void* ws, size_t ws_bytes,
+                         bool clear) {
+    clear = clear && rep;
+    if (m.np == 0) return clear ? launch_report_clear(rep, stream) : hipSuccess;
     const int block = 256;
+    // The report is zeroed by the node-major copy's launch, or by the gather itself where
+    // it is one workgroup: a launch of its own costs 4 us where nothing hides it.
+    auto before = [&](int grid) -> hipError_t {
+        const bool own = clear && grid > 1;
+        clear = clear && !own;
+        return own ? launch_report_clear(rep, stream) : hipSuccess;
+    };
     if (m.dim == 2) {
         const int grid = (int)(((size_t)m.np + (size_t)block * kGatherItems - 1) /
                                ((size_t)block * kGatherItems));
         if (ws && F >= 2 && F <= 4 && ws_bytes >= (size_t)F * m.nn * sizeof(T)) {
             T* nm = (T*)ws;
             hipLaunchKernelGGL(k_node_major<T>, dim3((m.nn + block - 1) / block), dim3(block), 0,
-                               stream, nodal, F, m.nn, nm);
+                               stream, nodal, F, m.nn, nm, clear ? rep : nullptr);
             switch (F) {
                 case 2:
                     hipLaunchKernelGGL((k_gather2d_nm<T, 2>), dim3(grid), dim3(block), 0, stream, m,
@@ -317,17 +337,23 @@ hipError_t launch_gather(const Mesh& m, Particles<T> P, const T* nodal, int F, T
             }
             return hipGetLastError();
         }
-        hipLaunchKernelGGL(k_gather2d<T>, dim3(grid), dim3(block), 0, stream, m, P, nodal, F, out, rep);
+        hipError_t e = before(grid);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_gather2d<T>, dim3(grid), dim3(block), 0, stream, m, P, nodal, F, out, rep,
+                           clear ? 1 : 0);
     } else {
         const int grid = (m.np + block - 1) / block;
-        hipLaunchKernelGGL(k_gather1d<T>, dim3(grid), dim3(block), 0, stream, m, P, nodal, F, out, rep);
+        hipError_t e = before(grid);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_gather1d<T>, dim3(grid), dim3(block), 0, stream, m, P, nodal, F, out, rep,
+                           clear ? 1 : 0);
     }
     return hipGetLastError();
 }
 template hipError_t launch_gather<float>(const Mesh&, Particles<float>, const float*, int, float*,
-                                         p2m_report*, hipStream_t, void*, size_t);
+                                         p2m_report*, hipStream_t, void*, size_t, bool);
 template hipError_t launch_gather<double>(const Mesh&, Particles<double>, const double*, int,
-                                          double*, p2m_report*, hipStream_t, void*, size_t);
+                                          double*, p2m_report*, hipStream_t, void*, size_t, bool);
 
 template <typename T>
 hipError_t launch_delta1d(const Mesh& m, Particles<T> P, const T* values, int F,

@@ -70,6 +70,22 @@ __device__ __forceinline__ bool locate_axis(double x, int n, double inv, int& c,
     return valid;
 }
 
+// A report written by the first threads of a workgroup (every thread calls it).
+__device__ __forceinline__ void report_clear(p2m_report* rep, uint32_t flags, int n_invalid) {
+    const int t = threadIdx.x;
+    if (t < 8) {
+        rep->iters[t] = 0;
+        rep->refines[t] = 0;
+        rep->rel_residual[t] = 0.0;
+    }
+    if (t == 0) {
+        rep->flags = flags;
+        rep->n_orphan = 0;
+        rep->n_invalid = n_invalid;
+        rep->reserved = 0;
+    }
+}
+
 // P1 weights of the four corners of a cell for a particle at offsets (xi, eta)
 // on the "/"-split square: xi >= eta is the lower triangle (n00, n10, n11) with
 // barycentrics (1-xi, xi-eta, eta); otherwise the upper triangle (n00, n11, n01)
@@ -111,6 +127,11 @@ hipError_t launch_locate_count(const Mesh& m, Particles<T> P, int32_t* key, int3
 // scan_ws that the place kernels read
 constexpr long kScanSpinDefault = 1L << 26;
 constexpr long kSolveSpinDefault = 1L << 22;   // polls of a solve's grid-barrier wait
+// the whole binning in one launch, for problems that bin_small_fits
+bool bin_small_fits(const Mesh& m);
+template <typename T>
+hipError_t launch_bin_small(const Mesh& m, Particles<T> P, int32_t* cell_start, int32_t* perm,
+                            p2m_report* rep, bool clear, hipStream_t stream);
 size_t scan_workspace_bytes(int n);
 hipError_t launch_exclusive_scan(const int32_t* counts, int32_t* out, int n, void* scan_ws,
                                  long spin_max, p2m_report* reps, int nrep, hipStream_t stream);
@@ -135,11 +156,11 @@ hipError_t launch_finalize(const Mesh& m, int F, const T* b, const T* w, int pic
                            p2m_report* rep, hipStream_t stream);
 
 // M2P gather in caller order.  ws (optional, >= F * nn elements): 2D gathers of
-// 2-4 fields read a node-major copy built there
+// 2-4 fields read a node-major copy built there.  clear: the report is zeroed first
 template <typename T>
 hipError_t launch_gather(const Mesh& m, Particles<T> P, const T* nodal, int F, T* out,
                          p2m_report* rep, hipStream_t stream, void* ws = nullptr,
-                         size_t ws_bytes = 0);
+                         size_t ws_bytes = 0, bool clear = false);
 
 // 1D delta P2M from the binned particles
 template <typename T>
