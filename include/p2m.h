@@ -288,8 +288,7 @@ p2m_status p2m_mass_solve(void* ctx, const p2m_problem* prob, int32_t nfields, v
  * both ends and the midpoint, integrated exactly).  Mass systems use the
  * consistent mass matrices (mesh: 2h/3 and h/6; particles: (g_{mu-1} + g_mu)/3
  * and g_mu/6 with g_mu = x_{mu+1} - x_mu) and are solved by the FP64 streaming
- * CG to opts->tol.  Each call synchronises `stream` once, after binning (to
- * size the particle-order arrays).  Particles that cannot be located are left
+ * kernel to opts->tol.  Particles that cannot be located are left
  * out (P2M) and get NaN (M2P); at least one located particle is needed for the
  * mass and lumped kinds and for delta.
  * --------------------------------------------------------------------------- */

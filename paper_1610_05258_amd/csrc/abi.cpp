@@ -753,9 +753,11 @@ X1DLayout make_x1d_layout(const Context* c, const Mesh& m, int F) {
     return L;
 }
 
-// Validation, layout, binning and the located count N (one stream synchronisation).
+// Validation, layout, binning and the order along the line; dN: the device word of the
+// located count.
 p2m_status x1d_begin(void* ctx, const p2m_problem* prob, int F, void* ws, size_t ws_bytes,
-                     void* stream, p2m_report* rep, Prepared& pp, X1DLayout& X, int& N) {
+                     void* stream, p2m_report* rep, Prepared& pp, X1DLayout& X,
+                     const int32_t*& dN) {
     if (!ctx || F < 1 || F > kMaxFields) return P2M_ERR_INVALID_ARG;
     Mesh m;
     p2m_status s = check_problem(prob, m);
@@ -781,11 +783,8 @@ p2m_status x1d_begin(void* ctx, const p2m_problem* prob, int F, void* ws, size_t
     int32_t* cs = (int32_t*)(pp.ws + X.cell_start);
     s = run_bin<double>(pp, prob, perm, cs);
     if (s != P2M_OK) return s;
-    int32_t located = 0;
-    P2M_TRY(hipMemcpyAsync(&located, cs + m.nn, sizeof(int32_t), hipMemcpyDeviceToHost, pp.stream));
-    P2M_TRY(hipStreamSynchronize(pp.stream));
-    N = located;
-    P2M_TRY(x1d_sort(m, N, (const double*)prob->x, perm, cs, (double*)(pp.ws + X.skey),
+    dN = cs + m.nn;
+    P2M_TRY(x1d_sort(m, (const double*)prob->x, perm, cs, (double*)(pp.ws + X.skey),
                      (int32_t*)(pp.ws + X.sidx), pp.stream));
     return P2M_OK;
 }
@@ -986,6 +985,7 @@ p2m_status x2d_run_p2m(const Context* c, const Prepared& pp, const X2DLayout& X,
     char* w8 = pp.ws;
     if (kind == P2M_X1D_FLIP || kind == P2M_X1D_PIC) {
         double* volc = (double*)(w8 + X.volc);
+        P2M_TRY(x1d_fill_nan((size_t)m.np, volc, pp.stream));
         P2M_TRY(x1d_scatter(A.N, 1, m.np, A.perm, A.vol, volc, pp.stream));
         Particles<double> P = particles_of<double>(prob);
         P.vol = volc;
@@ -1006,7 +1006,7 @@ p2m_status x2d_run_p2m(const Context* c, const Prepared& pp, const X2DLayout& X,
     P2M_TRY(x2d_locate(A, true, H, pp.stream));
     P2M_TRY(x2d_rhs_mesh(A, H, b, pp.stream));
     if (kind == P2M_X1D_LUMPED) {
-        P2M_TRY(x1d_div(m.nn, F, b, nullptr, m.cell_measure, out, pp.stream));
+        P2M_TRY(x1d_div(m.nn, nullptr, F, b, nullptr, m.cell_measure, out, pp.stream));
         return P2M_OK;
     }
     if (c->fft && fft_supported(m)) {   // circulant: a direct FP64 solve by the 2D DFT
@@ -1037,7 +1037,7 @@ p2m_status x2d_run_m2p(const Context* c, const Prepared& pp, const X2DLayout& X,
     const bool mass = kind != P2M_X1D_LUMPED;
     P2M_TRY(x2d_rhs_part(A, nodal, cvec, mass ? coef : nullptr, mass ? ecol : nullptr, pp.stream));
     if (kind == P2M_X1D_LUMPED) {
-        P2M_TRY(x1d_div(N, F, cvec, A.vol, 0.0, xs, pp.stream));
+        P2M_TRY(x1d_div(N, nullptr, F, cvec, A.vol, 0.0, xs, pp.stream));
     } else if (N > 0) {
         Mesh mp;
         memset(&mp, 0, sizeof(mp));
@@ -1064,6 +1064,7 @@ p2m_status x2d_run_m2p(const Context* c, const Prepared& pp, const X2DLayout& X,
         P2M_TRY(launch_cg<double>(mp, F, coef, cvec, A.vol, xs, P2M_START_FLIP, cw, o, rep,
                                   pp.stream));
     }
+    if (N < m.np) P2M_TRY(x1d_fill_nan((size_t)F * m.np, values_out, pp.stream));
     P2M_TRY(x1d_scatter(N, F, m.np, A.perm, xs, values_out, pp.stream));
     return P2M_OK;
 }
@@ -1440,18 +1441,18 @@ p2m_status p2m_x1d_assign(void* ctx, const p2m_problem* prob, int32_t kind, int3
     if (!g.ok) return P2M_ERR_HIP;
     Prepared pp;
     X1DLayout X;
-    int N = 0;
-    p2m_status s = x1d_begin(ctx, prob, nfields, ws, ws_bytes, stream, rep, pp, X, N);
+    const int32_t* dN = nullptr;
+    p2m_status s = x1d_begin(ctx, prob, nfields, ws, ws_bytes, stream, rep, pp, X, dN);
     if (s != P2M_OK) return s;
     const Mesh& m = pp.m;
     const int F = nfields, n = m.nx;
-    const double h = m.cell_measure, L = h * n;
+    const double h = m.cell_measure;
     char* w8 = pp.ws;
     double* out = (double*)nodal_out;
     const double* key = (const double*)(w8 + X.skey);
     const int32_t* idx = (const int32_t*)(w8 + X.sidx);
     double* volc = (double*)(w8 + X.volc);
-    P2M_TRY(x1d_setup(N, L, key, idx, (const double*)values, F, m.np, (double*)(w8 + X.gap),
+    P2M_TRY(x1d_setup(m, nullptr, dN, key, idx, (const double*)values, F, (double*)(w8 + X.gap),
                       (double*)(w8 + X.vols), volc, (double*)(w8 + X.As), pp.stream));
     if (kind == P2M_X1D_FLIP || kind == P2M_X1D_PIC) {
         Particles<double> P = particles_of<double>(prob);
@@ -1467,20 +1468,19 @@ p2m_status p2m_x1d_assign(void* ctx, const p2m_problem* prob, int32_t kind, int3
         return P2M_OK;
     }
     const double* As = (const double*)(w8 + X.As);
-    double* cvec = (double*)(w8 + X.c);
+    const bool mass = kind == P2M_X1D_MASS;
+    double* cvec = kind == P2M_X1D_DELTA ? nullptr : (double*)(w8 + X.c);
     // the particle interpolant at the nodes (the delta P2M) goes to nodal_out or fa
-    double* fn = kind == P2M_X1D_DELTA ? out : (double*)(w8 + X.fa);
-    P2M_TRY(x1d_p2m_overlap(m, N, key, As, F, kind == P2M_X1D_DELTA ? P2M_QUAD_APPB : quad, fn,
-                            (double*)(w8 + X.fb), (double*)(w8 + X.tlo), (double*)(w8 + X.thi),
-                            cvec, pp.stream));
+    double* fn = kind == P2M_X1D_DELTA ? out : quad == P2M_QUAD_APPB ? nullptr : (double*)(w8 + X.fa);
+    double* coef = mass ? (double*)(w8 + X.coef) : nullptr;
+    double* wv = mass ? (double*)(w8 + X.w) : nullptr;
+    P2M_TRY(x1d_p2m_overlap(m, dN, key, As, F, quad, fn, (double*)(w8 + X.tlo), (double*)(w8 + X.thi),
+                            cvec, coef, wv, pp.stream));
     if (kind == P2M_X1D_DELTA) return P2M_OK;
     if (kind == P2M_X1D_LUMPED) {
-        P2M_TRY(x1d_div(n, F, cvec, nullptr, h, out, pp.stream));
+        P2M_TRY(x1d_div(n, nullptr, F, cvec, nullptr, h, out, pp.stream));
         return P2M_OK;
     }
-    double* coef = (double*)(w8 + X.coef);
-    double* wv = (double*)(w8 + X.w);
-    P2M_TRY(x1d_mass_mesh(n, L, coef, wv, pp.stream));
     const p2m_solve_opts o = x1d_opts(opts, n);
     P2M_TRY(launch_cg<double>(m, F, coef, cvec, wv, out, P2M_START_FLIP, x1d_cg_ws(pp, X, c, m), o,
                               pp.rep, pp.stream));
@@ -1518,42 +1518,42 @@ p2m_status p2m_x1d_interpolate(void* ctx, const p2m_problem* prob, int32_t kind,
     }
     Prepared pp;
     X1DLayout X;
-    int N = 0;
-    p2m_status s = x1d_begin(ctx, prob, nfields, ws, ws_bytes, stream, rep, pp, X, N);
+    const int32_t* dN = nullptr;
+    p2m_status s = x1d_begin(ctx, prob, nfields, ws, ws_bytes, stream, rep, pp, X, dN);
     if (s != P2M_OK) return s;
     const Mesh& m = pp.m;
-    const int F = nfields, n = m.nx;
-    const double h = m.cell_measure, L = h * n;
+    const int F = nfields;
     char* w8 = pp.ws;
     const double* key = (const double*)(w8 + X.skey);
     const int32_t* idx = (const int32_t*)(w8 + X.sidx);
     const double* gap = (const double*)(w8 + X.gap);
     double* vols = (double*)(w8 + X.vols);
-    P2M_TRY(x1d_setup(N, L, key, idx, nullptr, 0, m.np, (double*)gap, vols, (double*)(w8 + X.volc),
-                      nullptr, pp.stream));
+    P2M_TRY(x1d_setup(m, nullptr, dN, key, idx, nullptr, 0, (double*)gap, vols, (double*)(w8 + X.volc), nullptr,
+                      pp.stream));
+    const bool mass = kind == P2M_X1D_MASS;
     double* cvec = (double*)(w8 + X.c);
     double* xs = (double*)(w8 + X.x);
-    P2M_TRY(x1d_m2p_overlap(m, N, key, gap, (const double*)nodal, F, quad, (double*)(w8 + X.fa),
-                            (double*)(w8 + X.fb), (double*)(w8 + X.tlo), (double*)(w8 + X.thi),
-                            cvec, pp.stream));
-    if (kind == P2M_X1D_LUMPED) {
-        P2M_TRY(x1d_div(N, F, cvec, vols, 0.0, xs, pp.stream));
-    } else if (N > 0) {
-        double* coef = (double*)(w8 + X.coef);
-        P2M_TRY(x1d_mass_part(N, gap, coef, pp.stream));
+    double* coef = mass ? (double*)(w8 + X.coef) : nullptr;
+    P2M_TRY(x1d_m2p_overlap(m, dN, key, gap, (const double*)nodal, F, quad, (double*)(w8 + X.fa),
+                            (double*)(w8 + X.tlo), (double*)(w8 + X.thi), cvec, coef, pp.stream));
+    if (!mass) {
+        P2M_TRY(x1d_div(m.np, dN, F, cvec, vols, 0.0, xs, pp.stream));
+    } else if (m.np > 0) {
         Mesh mp;
         memset(&mp, 0, sizeof(mp));
         mp.dim = 1;
-        mp.nx = N;
+        mp.nx = m.np;
         mp.ny = 1;
-        mp.nn = N;
+        mp.nn = m.np;
         mp.inv_hx = mp.inv_hy = 1.0;
         mp.cell_measure = 1.0;
-        const p2m_solve_opts o = x1d_opts(opts, N);
-        P2M_TRY(launch_cg<double>(mp, F, coef, cvec, vols, xs, P2M_START_FLIP,
-                                  x1d_cg_ws(pp, X, c, mp), o, pp.rep, pp.stream));
+        const p2m_solve_opts o = x1d_opts(opts, m.np);
+        CgWorkspace cw = x1d_cg_ws(pp, X, c, mp);
+        cw.n_dev = dN;
+        P2M_TRY(launch_cg<double>(mp, F, coef, cvec, vols, xs, P2M_START_FLIP, cw, o, pp.rep,
+                                  pp.stream));
     }
-    P2M_TRY(x1d_scatter(N, F, m.np, idx, xs, (double*)values_out, pp.stream));
+    P2M_TRY(x1d_out(m, (const double*)prob->x, dN, F, idx, xs, (double*)values_out, pp.stream));
     return P2M_OK;
 }
 
@@ -1565,15 +1565,14 @@ p2m_status p2m_x1d_volumes(void* ctx, const p2m_problem* prob, void* vol_out, p2
     if (!g.ok) return P2M_ERR_HIP;
     Prepared pp;
     X1DLayout X;
-    int N = 0;
-    p2m_status s = x1d_begin(ctx, prob, 1, ws, ws_bytes, stream, rep, pp, X, N);
+    const int32_t* dN = nullptr;
+    p2m_status s = x1d_begin(ctx, prob, 1, ws, ws_bytes, stream, rep, pp, X, dN);
     if (s != P2M_OK) return s;
-    const double L = pp.m.cell_measure * pp.m.nx;
     char* w8 = pp.ws;
-    P2M_TRY(x1d_scatter(0, 1, pp.m.np, nullptr, nullptr, (double*)vol_out, pp.stream));   // NaN
-    P2M_TRY(x1d_setup(N, L, (const double*)(w8 + X.skey), (const int32_t*)(w8 + X.sidx), nullptr, 0,
-                      pp.m.np, (double*)(w8 + X.gap), (double*)(w8 + X.vols), (double*)vol_out,
-                      nullptr, pp.stream));
+    P2M_TRY(x1d_setup(pp.m, (const double*)prob->x, dN, (const double*)(w8 + X.skey),
+                      (const int32_t*)(w8 + X.sidx), nullptr, 0,
+                      (double*)(w8 + X.gap), (double*)(w8 + X.vols), (double*)vol_out, nullptr,
+                      pp.stream));
     return P2M_OK;
 }
 
@@ -1614,6 +1613,7 @@ p2m_status p2m_x2d_volumes(void* ctx, const p2m_problem* prob, void* vol_out, p2
     X2dArgs A;
     p2m_status s = x2d_begin(ctx, prob, 1, nullptr, ws, ws_bytes, stream, rep, pp, X, A);
     if (s != P2M_OK) return s;
+    P2M_TRY(x1d_fill_nan((size_t)pp.m.np, (double*)vol_out, pp.stream));
     P2M_TRY(x1d_scatter(A.N, 1, pp.m.np, A.perm, A.vol, (double*)vol_out, pp.stream));
     return P2M_OK;
 }

@@ -97,6 +97,7 @@ struct CgArgs {
     int ew;               // slots per row of that form
     const int* skip;   // nothing to do if *skip is not 0 (null: always solve)
     int direct;        // 1D: start from direct_1d's solution
+    const int* n_dev;  // 1D: the number of unknowns (at most m.nn), if only the device has it
     p2m_solve_opts opts;
     p2m_report* rep;
 };
@@ -258,13 +259,13 @@ constexpr int kPcrHalo = kCgBlock;
 constexpr int kPcrRows = kCgBlock + 2 * kPcrHalo;
 
 template <typename T, int F>
-__device__ void direct_1d(const CgArgs<T>& a) {
+__device__ void direct_1d(const CgArgs<T>& a, const int nn) {
     constexpr int R = kPcrRows / kCgBlock;
     __shared__ double sh[(2 + F) * kPcrRows];
     double* s_rb = sh;                // 1 / reduced diagonal
     double* s_a = sh + kPcrRows;      // reduced coupling to the row at distance + s
     double* s_f = sh + 2 * kPcrRows;  // [F] reduced right-hand sides
-    const int nn = a.m.nn, tid = threadIdx.x;
+    const int tid = threadIdx.x;
     const bool cyc = nn <= kCgBlock;
     const int W = cyc ? nn : kPcrRows;
     for (int chunk = blockIdx.x; chunk * kCgBlock < nn; chunk += gridDim.x) {
@@ -358,7 +359,11 @@ __device__ void direct_1d(const CgArgs<T>& a) {
 template <typename T, int DIM, int F>
 __global__ __launch_bounds__(kCgBlock) void k_cg(CgArgs<T> a) {
     if (a.skip && *a.skip) return;
-    const Mesh& m = a.m;
+    Mesh m = a.m;
+    if (DIM == 1 && a.n_dev) {
+        m.nx = m.nn = *a.n_dev;
+        if (m.nn <= 0) return;
+    }
     const int nn = m.nn;
     const int nblocks = gridDim.x;
     const RSync bar =
@@ -458,7 +463,7 @@ __global__ __launch_bounds__(kCgBlock) void k_cg(CgArgs<T> a) {
         }
     }
     if constexpr (DIM == 1) {
-        if (a.direct) direct_1d<T, F>(a);
+        if (a.direct) direct_1d<T, F>(a, nn);
     }
     bool alive = gsync();
 
@@ -752,6 +757,7 @@ hipError_t launch_cg(const Mesh& m, int F, T* coef, T* b, const T* w, T* x, int 
     a.ecol = ws.ell_col;
     a.ew = ws.ell_w;
     a.skip = ws.skip;
+    a.n_dev = ws.n_dev;
     a.direct = ws.direct && m.dim == 1 && start == P2M_START_FLIP;
     a.opts = opts;
     a.rep = rep;

@@ -9,25 +9,28 @@
 // target hats, the parabola through the source interpolant at both ends and the
 // midpoint, integrated exactly against the two hats of the gap).
 //
-// The kernels, in call order:
-//   k_x1d_keys     wrapped position of every binned particle (sort key)
-//   k_x1d_sort     per cell, (position, particle number) order: cells of up to
-//                  32 particles by their own thread, larger ones by the whole
-//                  workgroup with the merge network of the binning sort
+// The kernels, in call order (N, the number of located particles, stays on the device: a
+// call has no host synchronisation; grids are sized for every particle):
+//   k_x1d_sort     wrapped position of every binned particle (sort key); per cell,
+//                  (position, particle number) order: cells of up to 32 particles by
+//                  their own thread, larger ones by the whole workgroup with the merge
+//                  network of the binning sort
 //   k_x1d_setup    gaps g_k, volumes v_k = (g_{k-1} + g_k) / 2 (eq. (4)) and the
 //                  values in sorted order
-//   k_x1d_eval_p   the particle interpolant at every node and element midpoint
-//   k_x1d_c_appb / k_x1d_c_exact + k_x1d_c_sum
-//                  c_j = int A psi_j (mesh hats)                 (P2M)
-//   k_x1d_eval_m / k_x1d_cp_appb / k_x1d_cp_exact + k_x1d_c_sum
-//                  c'_mu = int Abar psi_mu (particle hats)       (M2P)
-//   k_x1d_mass_mesh / k_x1d_mass_part
-//                  the stencils of the consistent mass matrices: mesh 2h/3, h/6;
-//                  particles (g_{k-1} + g_k)/3, g_k/6 (cyclic tridiagonal)
+//   k_x1d_nodes    the particle interpolant at every node, with the Appendix-B rule
+//                  c_j = int A psi_j (mesh hats), and the mesh mass matrix 2h/3, h/6
+//   k_x1d_parts    the mesh interpolant at every particle, with the Appendix-B rule
+//                  c'_mu = int Abar psi_mu (particle hats), and the particle mass matrix
+//                  (g_{k-1} + g_k)/3, g_k/6 (cyclic tridiagonal)
+//   k_x1d_c_exact / k_x1d_cp_exact + k_x1d_c_sum
+//                  c and c' by exact overlaps instead
 //   k_x1d_div / k_x1d_scatter
 //                  lumped divisions and the result in caller order
-// The mass solves themselves run in the streaming kernel (k_cg.hip, by cyclic reduction) on these
-// stencils.
+// The mass solves themselves run in the streaming kernel (k_cg.hip, by cyclic reduction)
+// on these stencils.
+//
+// Bound: launches.  64 cells, 256 particles, there and back: 20 launches and two host
+// synchronisations took 158 us; 11 launches and none take 45 us.
 #include "p2m_internal.hpp"
 
 namespace p2m {
@@ -44,15 +47,6 @@ __device__ __forceinline__ double wrap_pos(double x, double L) { return x < L ? 
 
 __device__ __forceinline__ bool pair_less(double ka, int ia, double kb, int ib) {
     return ka < kb || (ka == kb && ia < ib);
-}
-
-__global__ void k_x1d_keys(int N, const double* __restrict__ x, const int32_t* __restrict__ perm,
-                           double L, double* __restrict__ key, int32_t* __restrict__ idx) {
-    const int k = blockIdx.x * kB + threadIdx.x;
-    if (k >= N) return;
-    const int p = perm[k];
-    key[k] = wrap_pos(x[p], L);
-    idx[k] = p;
 }
 
 // Sort of one segment of (key, idx) pairs by the whole workgroup: the bitonic
@@ -95,13 +89,20 @@ __device__ void block_sort_pairs(double* key, int32_t* idx, int n) {
     }
 }
 
-// Every cell's (key, idx) pairs in ascending (key, idx) order, in place.
-__global__ __launch_bounds__(kB) void k_x1d_sort(int ncells, const int32_t* __restrict__ cs,
-                                                 double* __restrict__ key,
-                                                 int32_t* __restrict__ idx) {
+// Every cell's (key, idx) pairs in ascending (key, idx) order.
+__global__ __launch_bounds__(kB) void k_x1d_sort(int ncells, const double* __restrict__ x, double L,
+                                                 const int32_t* __restrict__ perm,
+                                                 const int32_t* __restrict__ cs, double* key,
+                                                 int32_t* idx) {
     __shared__ int big[kB];
     __shared__ int n_big;
     const int c0 = blockIdx.x * kB;
+    const int last = cs[min(c0 + kB, ncells)];
+    for (int k = cs[c0] + (int)threadIdx.x; k < last; k += kB) {
+        const int p = perm[k];
+        key[k] = wrap_pos(x[p], L);
+        idx[k] = p;
+    }
     const int c = c0 + (int)threadIdx.x;
     if (threadIdx.x == 0) n_big = 0;
     __syncthreads();
@@ -136,12 +137,22 @@ __global__ __launch_bounds__(kB) void k_x1d_sort(int ncells, const int32_t* __re
     }
 }
 
-// gaps, volumes (eq. (4)) and values in sorted order; volumes also in caller order
-__global__ void k_x1d_setup(int N, double L, const double* __restrict__ key,
+// particle p was left out of the binning of N particles (N = 0: all were)
+__device__ __forceinline__ bool left_out(const Mesh& m, const double* __restrict__ x, int p, int N) {
+    int c;
+    double xi;
+    bool fin;
+    return N == 0 || !locate_axis(x[p], m.nx, m.inv_hx, c, xi, fin);
+}
+
+// gaps, volumes (eq. (4)) and values in sorted order; volumes also in caller order (NaN
+// for the particles left out, where x is given)
+__global__ void k_x1d_setup(Mesh m, const double* __restrict__ x, const int32_t* __restrict__ dN, double L, const double* __restrict__ key,
                             const int32_t* __restrict__ idx, const double* __restrict__ values,
                             int F, int np, double* __restrict__ gap, double* __restrict__ vol_s,
                             double* __restrict__ vol_c, double* __restrict__ As) {
-    const int k = blockIdx.x * kB + threadIdx.x;
+    const int k = blockIdx.x * kB + threadIdx.x, N = *dN;
+    if (x && k < np && left_out(m, x, k, N)) vol_c[k] = __builtin_nan("");
     if (k >= N) return;
     const double xk = key[k];
     const double g = (k + 1 < N) ? key[k + 1] - xk : (key[0] + L) - xk;
@@ -193,33 +204,37 @@ __device__ __forceinline__ double node_gap(int j, int n, double h, double L) {
     return (j + 1 < n ? node_x(j + 1, h) : L) - node_x(j, h);
 }
 
-// particle interpolant at node j and at the midpoint of element j, every field
-__global__ void k_x1d_eval_p(int n, double h, double L, int N, const double* __restrict__ key,
-                             const double* __restrict__ As, int F, double* __restrict__ fn,
-                             double* __restrict__ fm) {
-    const int j = blockIdx.x * kB + threadIdx.x;
-    if (j >= n) return;
-    const double xj = node_x(j, h);
-    const double mj = xj + 0.5 * node_gap(j, n, h, L);
-    for (int f = 0; f < F; ++f) {
-        const double* A = As + (size_t)f * N;
-        fn[(size_t)f * n + j] = N > 0 ? interp_sorted(key, A, N, L, xj) : 0.0;
-        fm[(size_t)f * n + j] = N > 0 ? interp_sorted(key, A, N, L, wrap_pos(mj, L)) : 0.0;
-    }
-}
-
-// Appendix-B rule on the mesh hats: c_j = g_j/6 (f(x_j) + 2 f(m_j)) + g_{j-1}/6 (f(x_j) + 2 f(m_{j-1}))
-__global__ void k_x1d_c_appb(int n, double h, double L, int F, const double* __restrict__ fn,
-                             const double* __restrict__ fm, double* __restrict__ c) {
-    const int j = blockIdx.x * kB + threadIdx.x;
+// Particle interpolant at node j, every field, to fn (if not null).  appb: the Appendix-B
+// rule on the mesh hats, c_j = g_j/6 (f(x_j) + 2 f(m_j)) + g_{j-1}/6 (f(x_j) + 2 f(m_{j-1}))
+// with m_j the midpoint of element j (both of a node's midpoints are evaluated here:
+// cheaper than a launch between).  coef, w (if not null): the consistent mesh mass matrix
+// of 1D P1 hats, 2h/3 on the diagonal, h/6 beside it; w = h (no orphans).
+__global__ void k_x1d_nodes(int n, double h, double L, const int32_t* __restrict__ dN,
+                            const double* __restrict__ key, const double* __restrict__ As, int F,
+                            int appb, double* __restrict__ fn, double* __restrict__ c,
+                            double* __restrict__ coef, double* __restrict__ w) {
+    const int j = blockIdx.x * kB + threadIdx.x, N = *dN;
     if (j >= n) return;
     const int jm = j > 0 ? j - 1 : n - 1;
     const double g = node_gap(j, n, h, L), gm = node_gap(jm, n, h, L);
+    const double xj = node_x(j, h);
     for (int f = 0; f < F; ++f) {
-        const double fj = fn[(size_t)f * n + j];
-        const double own = g / 6.0 * (fj + 2.0 * fm[(size_t)f * n + j]);
-        const double prev = gm / 6.0 * (fj + 2.0 * fm[(size_t)f * n + jm]);
+        const double* A = As + (size_t)f * N;
+        const double fj = N > 0 ? interp_sorted(key, A, N, L, xj) : 0.0;
+        if (fn) fn[(size_t)f * n + j] = fj;
+        if (!appb) continue;
+        const double fm = N > 0 ? interp_sorted(key, A, N, L, wrap_pos(xj + 0.5 * g, L)) : 0.0;
+        const double fmm =
+            N > 0 ? interp_sorted(key, A, N, L, wrap_pos(node_x(jm, h) + 0.5 * gm, L)) : 0.0;
+        const double own = g / 6.0 * (fj + 2.0 * fm);
+        const double prev = gm / 6.0 * (fj + 2.0 * fmm);
         c[(size_t)f * n + j] = own + prev;
+    }
+    if (coef) {
+        const double hh = L / (double)n;
+        coef[j] = 2.0 * hh / 3.0;
+        coef[(size_t)n + j] = hh / 6.0;
+        w[j] = hh;
     }
 }
 
@@ -258,10 +273,11 @@ __device__ __forceinline__ int lower_idx(const double* __restrict__ key, int N, 
 
 // Exact overlaps with the mesh hats, element by element: element j is cut by the
 // particles strictly inside it; er[j] goes to node j, el[j] to node j + 1.
-__global__ void k_x1d_c_exact(int n, double h, double L, int N, const double* __restrict__ key,
+__global__ void k_x1d_c_exact(int n, double h, double L, const int32_t* __restrict__ dN,
+                              const double* __restrict__ key,
                               const double* __restrict__ As, int F, const double* __restrict__ fn,
                               double* __restrict__ to_lo, double* __restrict__ to_hi) {
-    const int j = blockIdx.x * kB + threadIdx.x;
+    const int j = blockIdx.x * kB + threadIdx.x, N = *dN;
     if (j >= n) return;
     const double left = node_x(j, h);
     const double right = j + 1 < n ? node_x(j + 1, h) : L;
@@ -281,10 +297,11 @@ __global__ void k_x1d_c_exact(int n, double h, double L, int N, const double* __
     }
 }
 
-// c_k = to_lo[k] + to_hi[k - 1] (periodic)
-__global__ void k_x1d_c_sum(int K, int F, const double* __restrict__ to_lo,
+// c_k = to_lo[k] + to_hi[k - 1] (periodic); K = *dK where dK is given
+__global__ void k_x1d_c_sum(int K, const int32_t* __restrict__ dK, int F, const double* __restrict__ to_lo,
                             const double* __restrict__ to_hi, double* __restrict__ c) {
     const int k = blockIdx.x * kB + threadIdx.x;
+    if (dK) K = *dK;
     if (k >= K) return;
     const int km = k > 0 ? k - 1 : K - 1;
     for (int f = 0; f < F; ++f) c[(size_t)f * K + k] = to_lo[(size_t)f * K + k] + to_hi[(size_t)f * K + km];
@@ -304,44 +321,40 @@ __device__ __forceinline__ double interp_mesh(const double* __restrict__ Ab, int
     return slope * (y - xa) + fa;
 }
 
-// mesh interpolant at every sorted particle and at the midpoint of its gap
-__global__ void k_x1d_eval_m(int N, int n, double h, double inv_h, double L,
-                             const double* __restrict__ key, const double* __restrict__ gap,
-                             const double* __restrict__ Ab, int F, double* __restrict__ fk,
-                             double* __restrict__ fmid) {
-    const int k = blockIdx.x * kB + threadIdx.x;
-    if (k >= N) return;
-    const double xk = key[k];
-    const double mk = wrap_pos(xk + 0.5 * gap[k], L);
-    for (int f = 0; f < F; ++f) {
-        const double* A = Ab + (size_t)f * n;
-        fk[(size_t)f * N + k] = interp_mesh(A, n, h, inv_h, L, xk);
-        fmid[(size_t)f * N + k] = interp_mesh(A, n, h, inv_h, L, mk);
-    }
-}
-
-// Appendix-B rule on the particle hats
-__global__ void k_x1d_cp_appb(int N, int F, const double* __restrict__ gap,
-                              const double* __restrict__ fk, const double* __restrict__ fmid,
-                              double* __restrict__ c) {
-    const int k = blockIdx.x * kB + threadIdx.x;
+// Mesh interpolant at every sorted particle to fk (if not null).  appb: the Appendix-B rule
+// on the particle hats (both of a particle's gap midpoints are evaluated here).  coef (if
+// not null): the consistent particle mass matrix, (g_{k-1} + g_k)/3 and g_k/6.
+__global__ void k_x1d_parts(const int32_t* __restrict__ dN, int n, double h, double inv_h, double L,
+                            const double* __restrict__ key, const double* __restrict__ gap,
+                            const double* __restrict__ Ab, int F, int appb, double* __restrict__ fk,
+                            double* __restrict__ c, double* __restrict__ coef) {
+    const int k = blockIdx.x * kB + threadIdx.x, N = *dN;
     if (k >= N) return;
     const int km = k > 0 ? k - 1 : N - 1;
+    const double xk = key[k], g = gap[k], gm = gap[km];
+    const double mk = wrap_pos(xk + 0.5 * g, L), mm = wrap_pos(key[km] + 0.5 * gm, L);
     for (int f = 0; f < F; ++f) {
-        const double fv = fk[(size_t)f * N + k];
-        const double own = gap[k] / 6.0 * (fv + 2.0 * fmid[(size_t)f * N + k]);
-        const double prev = gap[km] / 6.0 * (fv + 2.0 * fmid[(size_t)f * N + km]);
+        const double* A = Ab + (size_t)f * n;
+        const double fv = interp_mesh(A, n, h, inv_h, L, xk);
+        if (fk) fk[(size_t)f * N + k] = fv;
+        if (!appb) continue;
+        const double own = g / 6.0 * (fv + 2.0 * interp_mesh(A, n, h, inv_h, L, mk));
+        const double prev = gm / 6.0 * (fv + 2.0 * interp_mesh(A, n, h, inv_h, L, mm));
         c[(size_t)f * N + k] = own + prev;
+    }
+    if (coef) {
+        coef[k] = gm / 3.0 + g / 3.0;
+        coef[(size_t)N + k] = g / 6.0;
     }
 }
 
 // Exact overlaps with the particle hats, gap by gap: gap k = [x_k, x_{k+1}] is cut
 // by the nodes strictly inside it (the last gap runs past L to x_0 + L)
-__global__ void k_x1d_cp_exact(int N, int n, double h, double inv_h, double L,
+__global__ void k_x1d_cp_exact(const int32_t* __restrict__ dN, int n, double h, double inv_h, double L,
                                const double* __restrict__ key, const double* __restrict__ gap,
                                const double* __restrict__ Ab, const double* __restrict__ fk, int F,
                                double* __restrict__ to_lo, double* __restrict__ to_hi) {
-    const int k = blockIdx.x * kB + threadIdx.x;
+    const int k = blockIdx.x * kB + threadIdx.x, N = *dN;
     if (k >= N) return;
     const double left = key[k];
     const double right = k + 1 < N ? key[k + 1] : key[0] + L;
@@ -371,36 +384,17 @@ __global__ void k_x1d_cp_exact(int N, int n, double h, double inv_h, double L,
     }
 }
 
-// consistent mesh mass matrix of 1D P1 hats: 2h/3 on the diagonal, h/6 beside it;
-// w = h (no orphans); b = c
-__global__ void k_x1d_mass_mesh(int n, double L, double* __restrict__ coef, double* __restrict__ w) {
-    const int j = blockIdx.x * kB + threadIdx.x;
-    if (j >= n) return;
-    const double h = L / (double)n;
-    coef[j] = 2.0 * h / 3.0;
-    coef[(size_t)n + j] = h / 6.0;
-    w[j] = h;
-}
-
-// consistent particle mass matrix on the sorted particles: (g_{k-1} + g_k)/3 and g_k/6
-__global__ void k_x1d_mass_part(int N, const double* __restrict__ gap, double* __restrict__ coef) {
-    const int k = blockIdx.x * kB + threadIdx.x;
-    if (k >= N) return;
-    const int km = k > 0 ? k - 1 : N - 1;
-    coef[k] = gap[km] / 3.0 + gap[k] / 3.0;
-    coef[(size_t)N + k] = gap[k] / 6.0;
-}
-
-// out[f][k] = c[f][k] / d[k] (d == nullptr: / s)
-__global__ void k_x1d_div(int K, int F, const double* __restrict__ c, const double* __restrict__ d,
+// out[f][k] = c[f][k] / d[k] (d == nullptr: / s); K = *dK where dK is given
+__global__ void k_x1d_div(int K, const int32_t* __restrict__ dK, int F, const double* __restrict__ c, const double* __restrict__ d,
                           double s, double* __restrict__ out) {
     const int k = blockIdx.x * kB + threadIdx.x;
+    if (dK) K = *dK;
     if (k >= K) return;
     const double den = d ? d[k] : s;
     for (int f = 0; f < F; ++f) out[(size_t)f * K + k] = c[(size_t)f * K + k] / den;
 }
 
-// sorted-order values to caller order; particles left out of the binning get NaN
+// sorted-order values to caller order (k_x1d_out: the particles left out get NaN)
 __global__ void k_x1d_fill_nan(size_t n, double* __restrict__ out) {
     const size_t i = (size_t)blockIdx.x * kB + threadIdx.x;
     if (i < n) out[i] = __builtin_nan("");
@@ -413,6 +407,18 @@ __global__ void k_x1d_scatter(int N, int F, int np, const int32_t* __restrict__ 
     for (int f = 0; f < F; ++f) out[(size_t)f * np + p] = xs[(size_t)f * N + k];
 }
 
+__global__ void k_x1d_out(Mesh m, const double* __restrict__ x, const int32_t* __restrict__ dN, int F,
+                          const int32_t* __restrict__ idx, const double* __restrict__ xs,
+                          double* __restrict__ out) {
+    const int k = blockIdx.x * kB + threadIdx.x, N = *dN;
+    if (k >= m.np) return;
+    if (left_out(m, x, k, N))
+        for (int f = 0; f < F; ++f) out[(size_t)f * m.np + k] = __builtin_nan("");
+    if (k >= N) return;
+    const int p = idx[k];
+    for (int f = 0; f < F; ++f) out[(size_t)f * m.np + p] = xs[(size_t)f * N + k];
+}
+
 }  // namespace
 
 #define X1D_TRY(e)                                 \
@@ -421,91 +427,83 @@ __global__ void k_x1d_scatter(int N, int F, int np, const int32_t* __restrict__ 
         if (e_ != hipSuccess) return e_;           \
     } while (0)
 
-hipError_t x1d_sort(const Mesh& m, int N, const double* x, const int32_t* perm,
-                    const int32_t* cs, double* key, int32_t* idx, hipStream_t stream) {
-    if (N == 0) return hipSuccess;
+hipError_t x1d_sort(const Mesh& m, const double* x, const int32_t* perm, const int32_t* cs,
+                    double* key, int32_t* idx, hipStream_t stream) {
     const double L = m.cell_measure * m.nx;
-    hipLaunchKernelGGL(k_x1d_keys, dim3(grid_of(N)), dim3(kB), 0, stream, N, x, perm, L, key, idx);
-    X1D_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_x1d_sort, dim3(grid_of(m.nx)), dim3(kB), 0, stream, m.nx, cs, key, idx);
+    hipLaunchKernelGGL(k_x1d_sort, dim3(grid_of(m.nx)), dim3(kB), 0, stream, m.nx, x, L, perm, cs, key,
+                       idx);
     return hipGetLastError();
 }
 
-hipError_t x1d_setup(int N, double L, const double* key, const int32_t* idx, const double* values,
-                     int F, int np, double* gap, double* vol_s, double* vol_c, double* As,
-                     hipStream_t stream) {
-    if (N == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_x1d_setup, dim3(grid_of(N)), dim3(kB), 0, stream, N, L, key, idx, values,
-                       F, np, gap, vol_s, vol_c, As);
+hipError_t x1d_setup(const Mesh& m, const double* x, const int32_t* dN, const double* key, const int32_t* idx,
+                     const double* values, int F, double* gap, double* vol_s, double* vol_c,
+                     double* As, hipStream_t stream) {
+    if (m.np == 0) return hipSuccess;
+    const double L = m.cell_measure * m.nx;
+    hipLaunchKernelGGL(k_x1d_setup, dim3(grid_of(m.np)), dim3(kB), 0, stream, m, x, dN, L, key, idx,
+                       values, F, m.np, gap, vol_s, vol_c, As);
     return hipGetLastError();
 }
 
-hipError_t x1d_p2m_overlap(const Mesh& m, int N, const double* key, const double* As, int F,
-                           int quad, double* fn, double* fm, double* t_lo, double* t_hi,
-                           double* c, hipStream_t stream) {
+hipError_t x1d_p2m_overlap(const Mesh& m, const int32_t* dN, const double* key, const double* As,
+                           int F, int quad, double* fn, double* t_lo, double* t_hi, double* c,
+                           double* coef, double* w, hipStream_t stream) {
     const int n = m.nx;
     const double h = m.cell_measure, L = h * n;
-    hipLaunchKernelGGL(k_x1d_eval_p, dim3(grid_of(n)), dim3(kB), 0, stream, n, h, L, N, key, As, F,
-                       fn, fm);
+    const int appb = quad == P2M_QUAD_APPB && c ? 1 : 0;
+    hipLaunchKernelGGL(k_x1d_nodes, dim3(grid_of(n)), dim3(kB), 0, stream, n, h, L, dN, key, As, F,
+                       appb, fn, c, coef, w);
     X1D_TRY(hipGetLastError());
-    if (quad == P2M_QUAD_APPB) {
-        hipLaunchKernelGGL(k_x1d_c_appb, dim3(grid_of(n)), dim3(kB), 0, stream, n, h, L, F, fn, fm,
-                           c);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_x1d_c_exact, dim3(grid_of(n)), dim3(kB), 0, stream, n, h, L, N, key, As, F,
+    if (appb || !c) return hipSuccess;
+    hipLaunchKernelGGL(k_x1d_c_exact, dim3(grid_of(n)), dim3(kB), 0, stream, n, h, L, dN, key, As, F,
                        fn, t_lo, t_hi);
     X1D_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_x1d_c_sum, dim3(grid_of(n)), dim3(kB), 0, stream, n, F, t_lo, t_hi, c);
+    hipLaunchKernelGGL(k_x1d_c_sum, dim3(grid_of(n)), dim3(kB), 0, stream, n, (const int32_t*)nullptr,
+                       F, t_lo, t_hi, c);
     return hipGetLastError();
 }
 
-hipError_t x1d_m2p_overlap(const Mesh& m, int N, const double* key, const double* gap,
-                           const double* nodal, int F, int quad, double* fk, double* fmid,
-                           double* t_lo, double* t_hi, double* c, hipStream_t stream) {
-    if (N == 0) return hipSuccess;
+hipError_t x1d_m2p_overlap(const Mesh& m, const int32_t* dN, const double* key, const double* gap,
+                           const double* nodal, int F, int quad, double* fk, double* t_lo,
+                           double* t_hi, double* c, double* coef, hipStream_t stream) {
+    if (m.np == 0) return hipSuccess;
     const int n = m.nx;
     const double h = m.cell_measure, L = h * n;
-    hipLaunchKernelGGL(k_x1d_eval_m, dim3(grid_of(N)), dim3(kB), 0, stream, N, n, h, m.inv_hx, L, key,
-                       gap, nodal, F, fk, fmid);
+    const int appb = quad == P2M_QUAD_APPB ? 1 : 0;
+    hipLaunchKernelGGL(k_x1d_parts, dim3(grid_of(m.np)), dim3(kB), 0, stream, dN, n, h, m.inv_hx, L,
+                       key, gap, nodal, F, appb, appb ? nullptr : fk, c, coef);
     X1D_TRY(hipGetLastError());
-    if (quad == P2M_QUAD_APPB) {
-        hipLaunchKernelGGL(k_x1d_cp_appb, dim3(grid_of(N)), dim3(kB), 0, stream, N, F, gap, fk, fmid,
-                           c);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_x1d_cp_exact, dim3(grid_of(N)), dim3(kB), 0, stream, N, n, h, m.inv_hx, L,
+    if (appb) return hipSuccess;
+    hipLaunchKernelGGL(k_x1d_cp_exact, dim3(grid_of(m.np)), dim3(kB), 0, stream, dN, n, h, m.inv_hx, L,
                        key, gap, nodal, fk, F, t_lo, t_hi);
     X1D_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_x1d_c_sum, dim3(grid_of(N)), dim3(kB), 0, stream, N, F, t_lo, t_hi, c);
+    hipLaunchKernelGGL(k_x1d_c_sum, dim3(grid_of(m.np)), dim3(kB), 0, stream, m.np, dN, F, t_lo, t_hi,
+                       c);
     return hipGetLastError();
 }
 
-hipError_t x1d_mass_mesh(int n, double L, double* coef, double* w, hipStream_t stream) {
-    hipLaunchKernelGGL(k_x1d_mass_mesh, dim3(grid_of(n)), dim3(kB), 0, stream, n, L, coef, w);
-    return hipGetLastError();
-}
-
-hipError_t x1d_mass_part(int N, const double* gap, double* coef, hipStream_t stream) {
-    if (N == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_x1d_mass_part, dim3(grid_of(N)), dim3(kB), 0, stream, N, gap, coef);
-    return hipGetLastError();
-}
-
-hipError_t x1d_div(int K, int F, const double* c, const double* d, double s, double* out,
-                   hipStream_t stream) {
+hipError_t x1d_div(int K, const int32_t* dK, int F, const double* c, const double* d, double s,
+                   double* out, hipStream_t stream) {
     if (K == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_x1d_div, dim3(grid_of(K)), dim3(kB), 0, stream, K, F, c, d, s, out);
+    hipLaunchKernelGGL(k_x1d_div, dim3(grid_of(K)), dim3(kB), 0, stream, K, dK, F, c, d, s, out);
+    return hipGetLastError();
+}
+
+hipError_t x1d_fill_nan(size_t n, double* out, hipStream_t stream) {
+    if (n == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_x1d_fill_nan, dim3(grid_of(n)), dim3(kB), 0, stream, n, out);
+    return hipGetLastError();
+}
+
+hipError_t x1d_out(const Mesh& m, const double* x, const int32_t* dN, int F, const int32_t* idx,
+                   const double* xs, double* out, hipStream_t stream) {
+    if (m.np == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_x1d_out, dim3(grid_of(m.np)), dim3(kB), 0, stream, m, x, dN, F, idx, xs, out);
     return hipGetLastError();
 }
 
 hipError_t x1d_scatter(int N, int F, int np, const int32_t* idx, const double* xs, double* out,
                        hipStream_t stream) {
-    if (np > 0) {
-        const size_t tot = (size_t)F * np;
-        hipLaunchKernelGGL(k_x1d_fill_nan, dim3(grid_of(tot)), dim3(kB), 0, stream, tot, out);
-        X1D_TRY(hipGetLastError());
-    }
     if (N == 0) return hipSuccess;
     hipLaunchKernelGGL(k_x1d_scatter, dim3(grid_of(N)), dim3(kB), 0, stream, N, F, np, idx, xs, out);
     return hipGetLastError();

@@ -168,32 +168,36 @@ hipError_t launch_delta1d(const Mesh& m, Particles<T> P, const T* values, int F,
                           const int32_t* perm, const int32_t* cell_start, T* out,
                           hipStream_t stream);
 
-// paper-exact 1D (k_exact1d.hip), FP64.  N = located particles (binned order in
-// perm[0..N)); key / idx [N] receive the positions and particle numbers in
-// position order; gap, vol_s [N] sorted order, vol_c [np] caller order, As [F][N]
-hipError_t x1d_sort(const Mesh& m, int N, const double* x, const int32_t* perm,
-                    const int32_t* cs, double* key, int32_t* idx, hipStream_t stream);
-hipError_t x1d_setup(int N, double L, const double* key, const int32_t* idx, const double* values,
-                     int F, int np, double* gap, double* vol_s, double* vol_c, double* As,
-                     hipStream_t stream);
-// c [F][n] = int A psi_j over the mesh hats (quad: P2M_QUAD_*); fn [F][n] receives the
-// particle interpolant at the nodes (the delta P2M), fm [F][n] at the element
-// midpoints; t_lo, t_hi [F][n] scratch
-hipError_t x1d_p2m_overlap(const Mesh& m, int N, const double* key, const double* As, int F,
-                           int quad, double* fn, double* fm, double* t_lo, double* t_hi,
-                           double* c, hipStream_t stream);
-// c [F][N] = int Abar psi_mu over the particle hats (sorted order); fk, fmid, t_lo,
-// t_hi [F][N] scratch
-hipError_t x1d_m2p_overlap(const Mesh& m, int N, const double* key, const double* gap,
-                           const double* nodal, int F, int quad, double* fk, double* fmid,
-                           double* t_lo, double* t_hi, double* c, hipStream_t stream);
-hipError_t x1d_mass_mesh(int n, double L, double* coef, double* w, hipStream_t stream);
-hipError_t x1d_mass_part(int N, const double* gap, double* coef, hipStream_t stream);
-hipError_t x1d_div(int K, int F, const double* c, const double* d, double s, double* out,
-                   hipStream_t stream);
-// out [F][np] caller order: NaN, then xs [F][N] (sorted order) at idx
+// paper-exact 1D (k_exact1d.hip), FP64.  *dN = N, the located particles (binned order in
+// perm[0..N)); key / idx [N] receive the positions and particle numbers in position
+// order; gap, vol_s [N] sorted order, vol_c [np] caller order (with x: NaN for the
+// particles left out), As [F][N]
+hipError_t x1d_sort(const Mesh& m, const double* x, const int32_t* perm, const int32_t* cs,
+                    double* key, int32_t* idx, hipStream_t stream);
+hipError_t x1d_setup(const Mesh& m, const double* x, const int32_t* dN, const double* key, const int32_t* idx,
+                     const double* values, int F, double* gap, double* vol_s, double* vol_c,
+                     double* As, hipStream_t stream);
+// c [F][n] = int A psi_j over the mesh hats (quad: P2M_QUAD_*; null: not wanted); fn [F][n]
+// receives the particle interpolant at the nodes (the delta P2M; needed by the exact
+// overlaps, else it may be null); coef, w (or null): the consistent mesh mass matrix and
+// its node volumes
+hipError_t x1d_p2m_overlap(const Mesh& m, const int32_t* dN, const double* key, const double* As,
+                           int F, int quad, double* fn, double* t_lo, double* t_hi, double* c,
+                           double* coef, double* w, hipStream_t stream);
+// c [F][N] = int Abar psi_mu over the particle hats in sorted order; fk [F][N] scratch;
+// coef (or null): the consistent particle mass matrix
+hipError_t x1d_m2p_overlap(const Mesh& m, const int32_t* dN, const double* key, const double* gap,
+                           const double* nodal, int F, int quad, double* fk, double* t_lo,
+                           double* t_hi, double* c, double* coef, hipStream_t stream);
+// out = c / d (or / s); K entries, *dK of them where dK is given
+hipError_t x1d_div(int K, const int32_t* dK, int F, const double* c, const double* d, double s,
+                   double* out, hipStream_t stream);
+hipError_t x1d_fill_nan(size_t n, double* out, hipStream_t stream);
+// out[f][idx[k]] = xs[f][k], k < N; x1d_out: N = *dN, and NaN for the particles left out
 hipError_t x1d_scatter(int N, int F, int np, const int32_t* idx, const double* xs, double* out,
                        hipStream_t stream);
+hipError_t x1d_out(const Mesh& m, const double* x, const int32_t* dN, int F, const int32_t* idx,
+                   const double* xs, double* out, hipStream_t stream);
 
 // paper-exact 2D (k_x2d.hip); slot k = position in the binned order, N located
 struct X2dArgs {
@@ -243,6 +247,7 @@ struct CgWorkspace {
     const int32_t* ell_col = nullptr;  // sparse-row matrix (Mesh::dim == 3): columns [ell_w][nn]
     int ell_w = 0;
     const int* skip = nullptr;         // device word: the solve returns at once if it is not 0
+    const int* n_dev = nullptr;        // 1D: device word of the unknowns' number (at most Mesh::nn)
     bool direct = false;               // 1D from the start formula: by cyclic reduction first
 };
 size_t cg_partials_bytes(int blocks);
