@@ -55,24 +55,69 @@ struct LWeights {
     float b4;
 };
 
-__device__ void load_weights(const float* __restrict__ th, const LWeights& w, __bf16* W2T,
-                             __bf16* W3T) {
-    for (int i = threadIdx.x; i < kLH * kLIn; i += blockDim.x)
-        w.W1[(i / kLIn) * XS + i % kLIn] = (__bf16)th[oW1 + i];
-    for (int i = threadIdx.x; i < kLH * kLH; i += blockDim.x) {
-        const int o = i / kLH, n = i % kLH;
-        const __bf16 a = (__bf16)th[oW2 + i], c = (__bf16)th[oW3 + i];
-        w.W2[o * HS + n] = a;
-        w.W3[o * HS + n] = c;
-        if (W2T) W2T[n * HS + o] = a;
-        if (W3T) W3T[n * HS + o] = c;
+// The weights' loads, all in flight at once (16 bytes each, from an aligned vector), and
+// their conversion into LDS; a workgroup of BLOCK
+// threads.
+
+template <int BLOCK>
+struct WRegs {
+    f32x4 a[kLH * kLIn / (4 * BLOCK)], b[kLH * kLH / (4 * BLOCK)], c[kLH * kLH / (4 * BLOCK)];
+};
+
+__device__ __forceinline__ f32x4 ld4f(const float* p, bool aligned) {
+    if (aligned) return *(const f32x4*)p;
+    return f32x4{p[0], p[1], p[2], p[3]};
+}
+
+template <int BLOCK>
+__device__ __forceinline__ void load_weights_issue(const float* __restrict__ th, WRegs<BLOCK>& g) {
+    const bool al = ((uintptr_t)th & 15) == 0;
+    const int t4 = 4 * threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < kLH * kLIn / (4 * BLOCK); ++u) g.a[u] = ld4f(th + oW1 + t4 + 4 * BLOCK * u, al);
+#pragma unroll
+    for (int u = 0; u < kLH * kLH / (4 * BLOCK); ++u) {
+        g.b[u] = ld4f(th + oW2 + t4 + 4 * BLOCK * u, al);
+        g.c[u] = ld4f(th + oW3 + t4 + 4 * BLOCK * u, al);
     }
-    for (int i = threadIdx.x; i < kLH; i += blockDim.x) {
+}
+
+template <int BLOCK>
+__device__ __forceinline__ void load_weights_store(const float* __restrict__ th, const WRegs<BLOCK>& g,
+                                                   const LWeights& w, __bf16* W2T, __bf16* W3T) {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    auto cvt = [](f32x4 v) { return bf16x4{(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]}; };
+    const int t4 = 4 * threadIdx.x;
+#pragma unroll
+    for (int u = 0; u < kLH * kLIn / (4 * BLOCK); ++u) {
+        const int i = t4 + 4 * BLOCK * u;
+        *(bf16x4*)(w.W1 + (i / kLIn) * XS + i % kLIn) = cvt(g.a[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kLH * kLH / (4 * BLOCK); ++u) {
+        const int i = t4 + 4 * BLOCK * u, o = i / kLH, n = i % kLH;
+        const bf16x4 a = cvt(g.b[u]), c = cvt(g.c[u]);
+        *(bf16x4*)(w.W2 + o * HS + n) = a;
+        *(bf16x4*)(w.W3 + o * HS + n) = c;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (W2T) W2T[(n + e) * HS + o] = a[e];
+            if (W3T) W3T[(n + e) * HS + o] = c[e];
+        }
+    }
+    for (int i = threadIdx.x; i < kLH; i += BLOCK) {
         w.b1[i] = th[ob1 + i];
         w.b2[i] = th[ob2 + i];
         w.b3[i] = th[ob3 + i];
         w.W4[i] = th[oW4 + i];
     }
+}
+
+template <int BLOCK>
+__device__ __forceinline__ void load_weights(const float* __restrict__ th, const LWeights& w) {
+    WRegs<BLOCK> g;
+    load_weights_issue(th, g);
+    load_weights_store(th, g, w, nullptr, nullptr);
 }
 
 // Synchronisation of the forward pass: the whole workgroup, or (kWave) only the
@@ -93,13 +138,18 @@ __device__ __forceinline__ void fwd_sync() {
 // One hidden layer for the wave's 16 rows: out[row][n] = bf16(relu(in . W[n] + b[n])),
 // K = 32 * KS.  Lane holds rows 4q .. 4q+3 of columns 16t + r.  Every product is
 // formed before the barrier and written after it, so out may be the input.
-template <int KS, bool kWave = false>
+// With NT < 4 the wave takes column tiles t0 .. t0 + NT - 1 only.
+template <int KS, bool kWave = false, int NT = 4>
 __device__ __forceinline__ void dense_relu_bf16(const __bf16* in, int in_stride, const __bf16* W,
-                                                int w_stride, const float* b, __bf16* out) {
+                                                int w_stride, const float* b, __bf16* out,
+                                                int t0 = 0) {
     const int l = threadIdx.x & 63, r = l & 15, q = l >> 4;
-    f32x4 acc[4];
+    W += 16 * t0 * w_stride;
+    b += 16 * t0;
+    out += 16 * t0;
+    f32x4 acc[NT];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < NT; ++t) {
         acc[t] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < KS; ++s)
@@ -108,7 +158,7 @@ __device__ __forceinline__ void dense_relu_bf16(const __bf16* in, int in_stride,
     }
     fwd_sync<kWave>();
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < NT; ++t) {
         const float bb = b[16 * t + r];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -120,13 +170,13 @@ __device__ __forceinline__ void dense_relu_bf16(const __bf16* in, int in_stride,
 // this wave (they may be the same buffer).  Returns h3 (FP32, [t][i] = row 4q+i,
 // column 16t+r) and y for rows 4q .. 4q+3 (every lane of a 16-lane group holds
 // its group's four y).
-template <bool kWave = false>
+template <bool kWave = false, int NT = 4>
 __device__ __forceinline__ void forward16(const __bf16* x, const LWeights& w, __bf16* h1,
-                                          __bf16* h2, float (&h3)[4][4], float (&y)[4]) {
+                                          __bf16* h2, float (&h3)[4][4], float (&y)[4], int t0 = 0) {
     const int l = threadIdx.x & 63, r = l & 15, q = l >> 4;
-    dense_relu_bf16<kLIn / 32, kWave>(x, XS, w.W1, XS, w.b1, h1);
+    dense_relu_bf16<kLIn / 32, kWave, NT>(x, XS, w.W1, XS, w.b1, h1, t0);
     fwd_sync<kWave>();
-    dense_relu_bf16<kLH / 32, kWave>(h1, HS, w.W2, HS, w.b2, h2);
+    dense_relu_bf16<kLH / 32, kWave, NT>(h1, HS, w.W2, HS, w.b2, h2, t0);
     fwd_sync<kWave>();
     float yp[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -325,7 +375,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_learn_forward(const float* __re
     __shared__ float b1[kLH], b2[kLH], b3[kLH], W4[kLH];
     __shared__ __align__(16) __bf16 xt[kWaves][16 * XS], h1[kWaves][16 * HS], h2[kWaves][16 * HS];
     LWeights w{W1, W2, W3, b1, b2, b3, W4, th[ob4]};
-    load_weights(th, w, nullptr, nullptr);
+    load_weights<64 * kWaves>(th, w);
     const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, r = l & 15, q = l >> 4;
     const int row0 = (blockIdx.x * kWaves + wave) * 16;
     for (int c = q * 40; c < q * 40 + 40; c += 8) {
@@ -356,7 +406,7 @@ __global__ __launch_bounds__(64 * kWaves) void k_learned_start(GatherIn g, int F
     __shared__ float sbase[kWaves][16], sscale[kWaves][16];
     __shared__ int suse[kWaves][16];
     LWeights w{W1, W2, W3, b1, b2, b3, W4, th[ob4]};
-    load_weights(th, w, nullptr, nullptr);
+    load_weights<64 * kWaves>(th, w);
     __syncthreads();
     // from here on a wave touches only its own tiles (and the read-only weights):
     // wave-level synchronisation, so the waves of a workgroup run independently
@@ -409,7 +459,14 @@ __global__ __launch_bounds__(64 * kWaves) void k_learned_start(GatherIn g, int F
 // workgroup's gradient (sum over its rows of the per-row gradient of
 // (1/B) sum (y - t)^2) goes to gpart[blockIdx.x][kNParam] and its squared error
 // sum to lpart[blockIdx.x].  Rows beyond the batch count as absent.
-__global__ __launch_bounds__(256) void k_learn_grad(const float* __restrict__ th,
+// Eight waves: wave = 16 rows (wave % 4) and half of the column tiles (wave / 4); the last
+// layer, whose row sums must keep their order, is computed by both halves.
+// Bound: a chain of about 20 dependent steps (loads, LDS, products, barriers) of one
+// workgroup on its own compute unit.  4096 rows: 15.3 us; 28 us with every load waited
+// for where it was used, 17.5 us with the loads ahead and four waves.
+constexpr int kLBlock = 512;
+
+__global__ __launch_bounds__(kLBlock) void k_learn_grad(const float* __restrict__ th,
                                                    const __bf16* __restrict__ X,
                                                    const float* __restrict__ target,
                                                    const int32_t* __restrict__ rows, int batch,
@@ -426,38 +483,59 @@ __global__ __launch_bounds__(256) void k_learn_grad(const float* __restrict__ th
     __shared__ float red[4][kWaves][kLH];   // db1, db2, db3 / dW4 partials per wave
     __shared__ float lsum[kWaves];
     LWeights w{W1, W2, W3, b1, b2, b3, W4, th[ob4]};
-    load_weights(th, w, W2T, W3T);
     const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, r = l & 15, q = l >> 4;
-    const int b0 = blockIdx.x * 64;
-    // rows of the batch: row-major and transposed copies of the inputs
-    for (int c = threadIdx.x; c < 64 * (kLIn / 8); c += 256) {
-        const int rr = c / (kLIn / 8), cc = (c % (kLIn / 8)) * 8;
-        bf16x8 v = {};
-        if (b0 + rr < batch) v = ld8(X + (size_t)rows[b0 + rr] * kLIn + cc);
-        *(bf16x8*)(Xs + rr * XS + cc) = v;
+    const int b0 = blockIdx.x * 64, rw = 16 * (wave & 3), half = wave >> 2, t0 = 2 * half;
+    // every load before the first use: row numbers, weights, then the rows' inputs and targets
+    constexpr int kXVecs = 64 * (kLIn / 8), kXIt = (kXVecs + kLBlock - 1) / kLBlock;
+    int rx[kXIt], rt[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) XT[(cc + e) * HS + rr] = v[e];
+    for (int u = 0; u < kXIt; ++u) {
+        const int c = threadIdx.x + u * kLBlock, rr = c / (kLIn / 8);
+        rx[u] = c < kXVecs && b0 + rr < batch ? rows[b0 + rr] : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rt[i] = b0 + rw + 4 * q + i < batch ? rows[b0 + rw + 4 * q + i] : -1;
+    WRegs<kLBlock> wr;
+    load_weights_issue<kLBlock>(th, wr);
+    bf16x8 xv[kXIt];
+#pragma unroll
+    for (int u = 0; u < kXIt; ++u) {
+        const int cc = ((threadIdx.x + u * kLBlock) % (kLIn / 8)) * 8;
+        xv[u] = bf16x8{};
+        if (rx[u] >= 0) xv[u] = ld8(X + (size_t)rx[u] * kLIn + cc);
+    }
+    float tgt[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) tgt[i] = rt[i] >= 0 ? target[rt[i]] : 0.f;
+    load_weights_store<kLBlock>(th, wr, w, W2T, W3T);
+    // rows of the batch: row-major and transposed copies of the inputs
+#pragma unroll
+    for (int u = 0; u < kXIt; ++u) {
+        const int c = threadIdx.x + u * kLBlock, rr = c / (kLIn / 8), cc = (c % (kLIn / 8)) * 8;
+        if (c >= kXVecs) break;
+        *(bf16x8*)(Xs + rr * XS + cc) = xv[u];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) XT[(cc + e) * HS + rr] = xv[u][e];
     }
     __syncthreads();
     // forward: this wave's 16 rows; H1 rows land in Pb, H2 rows in Qb
-    const int rw = 16 * wave;
     float h3[4][4], y[4];
-    forward16(Xs + rw * XS, w, Pb + rw * HS, Qb + rw * HS, h3, y);
+    forward16<false, 2>(Xs + rw * XS, w, Pb + rw * HS, Qb + rw * HS, h3, y, t0);
     // transposed activations for the weight gradients
-    for (int c = l; c < 16 * kLH; c += 64) {
+    for (int c = 64 * half + l; c < 16 * kLH; c += 128) {
         const int rr = c / kLH, n = c % kLH;
         H1T[n * HS + rw + rr] = Pb[(rw + rr) * HS + n];
         H2T[n * HS + rw + rr] = Qb[(rw + rr) * HS + n];
     }
     // dy = 2 (y - t) / B per row; squared error
     float le = 0.f;
-    if (r == 0) {
+    if (r == 0 && half == 0) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int rr = rw + 4 * q + i;
             float dy = 0.f;
             if (b0 + rr < batch) {
-                const float e = y[i] - target[rows[b0 + rr]];
+                const float e = y[i] - tgt[i];
                 dy = 2.f * e / (float)batch;
                 le = fmaf(e, e, le);
             }
@@ -466,39 +544,40 @@ __global__ __launch_bounds__(256) void k_learn_grad(const float* __restrict__ th
     }
     le += __shfl_xor(le, 16, 64);
     le += __shfl_xor(le, 32, 64);
-    if (l == 0) lsum[wave] = le;
+    if (l == 0 && half == 0) lsum[wave] = le;
     __syncthreads();
     // ---- layer 3: dz3 = dy W4 [z3 > 0]; dW4 = sum dy h3 -----------------------
-    float dz3[4][4];
+    float dz3[2][4];
     {
-        float pb[4], pw[4];
+        float pb[2], pw[2];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int t = 0; t < 2; ++t) {
+            const int n = 16 * (t0 + t) + r;
             pb[t] = 0.f;
             pw[t] = 0.f;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float dy = dys[rw + 4 * q + i];
-                dz3[t][i] = h3[t][i] > 0.f ? dy * W4[16 * t + r] : 0.f;
+                const float dy = dys[rw + 4 * q + i], h = half ? h3[t + 2][i] : h3[t][i];
+                dz3[t][i] = h > 0.f ? dy * W4[n] : 0.f;
                 pb[t] += dz3[t][i];
-                pw[t] = fmaf(dy, h3[t][i], pw[t]);
+                pw[t] = fmaf(dy, h, pw[t]);
             }
             pb[t] += __shfl_xor(pb[t], 16, 64);
             pb[t] += __shfl_xor(pb[t], 32, 64);
             pw[t] += __shfl_xor(pw[t], 16, 64);
             pw[t] += __shfl_xor(pw[t], 32, 64);
             if (q == 0) {
-                red[2][wave][16 * t + r] = pb[t];
-                red[3][wave][16 * t + r] = pw[t];
+                red[2][wave & 3][n] = pb[t];
+                red[3][wave & 3][n] = pw[t];
             }
         }
     }
     __syncthreads();   // H1, H2 rows (Pb, Qb) are no longer read
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int rr = rw + 4 * q + i, n = 16 * t + r;
+            const int rr = rw + 4 * q + i, n = 16 * (t0 + t) + r;
             const __bf16 v = (__bf16)dz3[t][i];
             Qb[rr * HS + n] = v;     // dZ3 [row][out]
             Pb[n * HS + rr] = v;     // dZ3T [out][row]
@@ -507,7 +586,7 @@ __global__ __launch_bounds__(256) void k_learn_grad(const float* __restrict__ th
     float* G = gpart + (size_t)blockIdx.x * kNParam;
     // dW3 [out][in] = dZ3T . H2 (K = 64 rows); wave = out tile
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = t0; t < t0 + 2; ++t) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < 2; ++s)
@@ -517,9 +596,9 @@ __global__ __launch_bounds__(256) void k_learn_grad(const float* __restrict__ th
         for (int i = 0; i < 4; ++i) G[oW3 + (rw + 4 * q + i) * kLH + 16 * t + r] = acc[i];
     }
     // dz2 = (dZ3 . W3) [z2 > 0] for this wave's rows
-    float dz2[4][4];
+    float dz2[2][4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = t0; t < t0 + 2; ++t) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < 2; ++s)
@@ -529,19 +608,19 @@ __global__ __launch_bounds__(256) void k_learn_grad(const float* __restrict__ th
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int rr = rw + 4 * q + i, n = 16 * t + r;
-            dz2[t][i] = (float)H2T[n * HS + rr] > 0.f ? acc[i] : 0.f;
-            pb += dz2[t][i];
+            dz2[t - t0][i] = (float)H2T[n * HS + rr] > 0.f ? acc[i] : 0.f;
+            pb += dz2[t - t0][i];
         }
         pb += __shfl_xor(pb, 16, 64);
         pb += __shfl_xor(pb, 32, 64);
-        if (q == 0) red[1][wave][16 * t + r] = pb;
+        if (q == 0) red[1][wave & 3][16 * t + r] = pb;
     }
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int rr = rw + 4 * q + i, n = 16 * t + r;
+            const int rr = rw + 4 * q + i, n = 16 * (t0 + t) + r;
             const __bf16 v = (__bf16)dz2[t][i];
             Qb[rr * HS + n] = v;
             Pb[n * HS + rr] = v;
@@ -549,7 +628,7 @@ __global__ __launch_bounds__(256) void k_learn_grad(const float* __restrict__ th
     __syncthreads();
     // dW2 = dZ2T . H1
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = t0; t < t0 + 2; ++t) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < 2; ++s)
@@ -559,9 +638,9 @@ __global__ __launch_bounds__(256) void k_learn_grad(const float* __restrict__ th
         for (int i = 0; i < 4; ++i) G[oW2 + (rw + 4 * q + i) * kLH + 16 * t + r] = acc[i];
     }
     // dz1 = (dZ2 . W2) [z1 > 0]
-    float dz1[4][4];
+    float dz1[2][4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = t0; t < t0 + 2; ++t) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < 2; ++s)
@@ -571,21 +650,22 @@ __global__ __launch_bounds__(256) void k_learn_grad(const float* __restrict__ th
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int rr = rw + 4 * q + i, n = 16 * t + r;
-            dz1[t][i] = (float)H1T[n * HS + rr] > 0.f ? acc[i] : 0.f;
-            pb += dz1[t][i];
+            dz1[t - t0][i] = (float)H1T[n * HS + rr] > 0.f ? acc[i] : 0.f;
+            pb += dz1[t - t0][i];
         }
         pb += __shfl_xor(pb, 16, 64);
         pb += __shfl_xor(pb, 32, 64);
-        if (q == 0) red[0][wave][16 * t + r] = pb;
+        if (q == 0) red[0][wave & 3][16 * t + r] = pb;
     }
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) Pb[(16 * t + r) * HS + rw + 4 * q + i] = (__bf16)dz1[t][i];
+        for (int i = 0; i < 4; ++i) Pb[(16 * (t0 + t) + r) * HS + rw + 4 * q + i] = (__bf16)dz1[t][i];
     __syncthreads();
     // dW1 [out][160] = dZ1T . X
-    for (int t = 0; t < kLIn / 16; ++t) {
+#pragma unroll
+    for (int t = half * (kLIn / 32); t < (half + 1) * (kLIn / 32); ++t) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int s = 0; s < 2; ++s)
@@ -595,7 +675,7 @@ __global__ __launch_bounds__(256) void k_learn_grad(const float* __restrict__ th
         for (int i = 0; i < 4; ++i) G[oW1 + (rw + 4 * q + i) * kLIn + 16 * t + r] = acc[i];
     }
     // biases, W4, b4 and the loss: the waves' partials in a fixed order
-    for (int n = threadIdx.x; n < kLH; n += 256) {
+    for (int n = threadIdx.x; n < kLH; n += kLBlock) {
         float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
         for (int wv = 0; wv < kWaves; ++wv) {
             s0 += red[0][wv][n];
@@ -619,7 +699,12 @@ __global__ __launch_bounds__(256) void k_learn_grad(const float* __restrict__ th
 
 // Training step, part 2: sum of the workgroup gradients in workgroup order, the
 // optional gradient output and the Adam update (FP32 master parameters).
-__global__ void k_learn_adam(float* __restrict__ th, float* __restrict__ am,
+// Bound: the partial gradients' latency (4.8 MB at 4096 rows): 32 loads of a thread in
+// flight and one wave a workgroup, 4.2 us; one load at a time on 73 workgroups took 18.
+constexpr int kAdamBlock = 64;
+constexpr int kAdamLoads = 32;   // loads in flight per thread
+
+__global__ __launch_bounds__(kAdamBlock) void k_learn_adam(float* __restrict__ th, float* __restrict__ am,
                              float* __restrict__ av, const float* __restrict__ gpart, int nwg,
                              const float* __restrict__ lpart, int batch, float lr, float bc1,
                              float bc2, int apply, float* __restrict__ grad_out,
@@ -627,7 +712,15 @@ __global__ void k_learn_adam(float* __restrict__ th, float* __restrict__ am,
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p < kNParam) {
         float g = 0.f;
-        for (int k = 0; k < nwg; ++k) g += gpart[(size_t)k * kNParam + p];
+        int k = 0;
+        for (; k + kAdamLoads <= nwg; k += kAdamLoads) {
+            float v[kAdamLoads];
+#pragma unroll
+            for (int u = 0; u < kAdamLoads; ++u) v[u] = gpart[(size_t)(k + u) * kNParam + p];
+#pragma unroll
+            for (int u = 0; u < kAdamLoads; ++u) g += v[u];
+        }
+        for (; k < nwg; ++k) g += gpart[(size_t)k * kNParam + p];
         if (grad_out) grad_out[p] = g;
         if (apply) {
             const float m = 0.9f * am[p] + 0.1f * g;
@@ -639,6 +732,7 @@ __global__ void k_learn_adam(float* __restrict__ th, float* __restrict__ am,
     }
     if (p == 0 && loss_out) {
         float s = 0.f;
+#pragma unroll 16
         for (int k = 0; k < nwg; ++k) s += lpart[k];
         loss_out[0] = s / (float)batch;
     }
@@ -792,12 +886,12 @@ hipError_t launch_learn_train(float* params, float* am, float* av, int step, flo
     const int nwg = (batch + 63) / 64;
     float* gpart = (float*)ws;
     float* lpart = (float*)((char*)ws + ((size_t)nwg * kNParam * sizeof(float) + 255) / 256 * 256);
-    hipLaunchKernelGGL(k_learn_grad, dim3(nwg), dim3(256), 0, stream, params, (const __bf16*)X,
+    hipLaunchKernelGGL(k_learn_grad, dim3(nwg), dim3(kLBlock), 0, stream, params, (const __bf16*)X,
                        target, rows, batch, gpart, lpart);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const float bc1 = 1.f - powf(0.9f, (float)step), bc2 = 1.f - powf(0.999f, (float)step);
-    hipLaunchKernelGGL(k_learn_adam, dim3((kNParam + 255) / 256), dim3(256), 0, stream, params, am,
+    hipLaunchKernelGGL(k_learn_adam, dim3((kNParam + kAdamBlock - 1) / kAdamBlock), dim3(kAdamBlock), 0, stream, params, am,
                        av, gpart, nwg, lpart, batch, lr, bc1, bc2, apply, grad_out, loss_out);
     return hipGetLastError();
 }
