@@ -753,11 +753,11 @@ X1DLayout make_x1d_layout(const Context* c, const Mesh& m, int F) {
     return L;
 }
 
-// Validation, layout, binning and the order along the line; dN: the device word of the
-// located count.
+// Validation and layout; then, with order, binning and the order along the line.  dN: the
+// device word of the located count.
 p2m_status x1d_begin(void* ctx, const p2m_problem* prob, int F, void* ws, size_t ws_bytes,
                      void* stream, p2m_report* rep, Prepared& pp, X1DLayout& X,
-                     const int32_t*& dN) {
+                     const int32_t*& dN, bool order) {
     if (!ctx || F < 1 || F > kMaxFields) return P2M_ERR_INVALID_ARG;
     Mesh m;
     p2m_status s = check_problem(prob, m);
@@ -781,12 +781,31 @@ p2m_status x1d_begin(void* ctx, const p2m_problem* prob, int F, void* ws, size_t
     pp.clear_rep = true;
     int32_t* perm = (int32_t*)(pp.ws + X.perm);
     int32_t* cs = (int32_t*)(pp.ws + X.cell_start);
+    dN = cs + m.nn;
+    if (!order && x1d_small_fits(m)) return P2M_OK;
     s = run_bin<double>(pp, prob, perm, cs);
     if (s != P2M_OK) return s;
-    dN = cs + m.nn;
     P2M_TRY(x1d_sort(m, (const double*)prob->x, perm, cs, (double*)(pp.ws + X.skey),
                      (int32_t*)(pp.ws + X.sidx), pp.stream));
     return P2M_OK;
+}
+
+// The arguments of x1d_small but for its evaluation.
+X1dSmall x1d_small_args(const Prepared& pp, const X1DLayout& X, const p2m_problem* prob, int F,
+                        const void* values) {
+    X1dSmall a;
+    memset(&a, 0, sizeof(a));
+    a.x = (const double*)prob->x;
+    a.values = (const double*)values;
+    a.F = F;
+    a.dN = (int32_t*)(pp.ws + X.cell_start) + pp.m.nn;
+    a.key = (double*)(pp.ws + X.skey);
+    a.idx = (int32_t*)(pp.ws + X.sidx);
+    a.gap = (double*)(pp.ws + X.gap);
+    a.vol_s = (double*)(pp.ws + X.vols);
+    a.vol_c = (double*)(pp.ws + X.volc);
+    a.As = (double*)(pp.ws + X.As);
+    return a;
 }
 
 CgWorkspace x1d_cg_ws(const Prepared& pp, const X1DLayout& X, const Context* c, const Mesh& ms) {
@@ -1442,7 +1461,8 @@ p2m_status p2m_x1d_assign(void* ctx, const p2m_problem* prob, int32_t kind, int3
     Prepared pp;
     X1DLayout X;
     const int32_t* dN = nullptr;
-    p2m_status s = x1d_begin(ctx, prob, nfields, ws, ws_bytes, stream, rep, pp, X, dN);
+    const bool order = kind == P2M_X1D_FLIP || kind == P2M_X1D_PIC;   // perm is used itself
+    p2m_status s = x1d_begin(ctx, prob, nfields, ws, ws_bytes, stream, rep, pp, X, dN, order);
     if (s != P2M_OK) return s;
     const Mesh& m = pp.m;
     const int F = nfields, n = m.nx;
@@ -1452,8 +1472,10 @@ p2m_status p2m_x1d_assign(void* ctx, const p2m_problem* prob, int32_t kind, int3
     const double* key = (const double*)(w8 + X.skey);
     const int32_t* idx = (const int32_t*)(w8 + X.sidx);
     double* volc = (double*)(w8 + X.volc);
-    P2M_TRY(x1d_setup(m, nullptr, dN, key, idx, (const double*)values, F, (double*)(w8 + X.gap),
-                      (double*)(w8 + X.vols), volc, (double*)(w8 + X.As), pp.stream));
+    const bool small = !order && x1d_small_fits(m);
+    if (!small)
+        P2M_TRY(x1d_setup(m, nullptr, dN, key, idx, (const double*)values, F, (double*)(w8 + X.gap),
+                          (double*)(w8 + X.vols), volc, (double*)(w8 + X.As), pp.stream));
     if (kind == P2M_X1D_FLIP || kind == P2M_X1D_PIC) {
         Particles<double> P = particles_of<double>(prob);
         P.vol = volc;
@@ -1474,8 +1496,18 @@ p2m_status p2m_x1d_assign(void* ctx, const p2m_problem* prob, int32_t kind, int3
     double* fn = kind == P2M_X1D_DELTA ? out : quad == P2M_QUAD_APPB ? nullptr : (double*)(w8 + X.fa);
     double* coef = mass ? (double*)(w8 + X.coef) : nullptr;
     double* wv = mass ? (double*)(w8 + X.w) : nullptr;
+    if (small) {
+        X1dSmall a = x1d_small_args(pp, X, prob, F, values);
+        a.eval = X1dSmall::kNodes;
+        a.appb = quad == P2M_QUAD_APPB && cvec ? 1 : 0;
+        a.f = fn;
+        a.c = cvec;
+        a.coef = coef;
+        a.w = wv;
+        P2M_TRY(x1d_small(m, a, pp.rep, pp.stream));
+    }
     P2M_TRY(x1d_p2m_overlap(m, dN, key, As, F, quad, fn, (double*)(w8 + X.tlo), (double*)(w8 + X.thi),
-                            cvec, coef, wv, pp.stream));
+                            cvec, coef, wv, small, pp.stream));
     if (kind == P2M_X1D_DELTA) return P2M_OK;
     if (kind == P2M_X1D_LUMPED) {
         P2M_TRY(x1d_div(n, nullptr, F, cvec, nullptr, h, out, pp.stream));
@@ -1519,7 +1551,7 @@ p2m_status p2m_x1d_interpolate(void* ctx, const p2m_problem* prob, int32_t kind,
     Prepared pp;
     X1DLayout X;
     const int32_t* dN = nullptr;
-    p2m_status s = x1d_begin(ctx, prob, nfields, ws, ws_bytes, stream, rep, pp, X, dN);
+    p2m_status s = x1d_begin(ctx, prob, nfields, ws, ws_bytes, stream, rep, pp, X, dN, false);
     if (s != P2M_OK) return s;
     const Mesh& m = pp.m;
     const int F = nfields;
@@ -1528,14 +1560,27 @@ p2m_status p2m_x1d_interpolate(void* ctx, const p2m_problem* prob, int32_t kind,
     const int32_t* idx = (const int32_t*)(w8 + X.sidx);
     const double* gap = (const double*)(w8 + X.gap);
     double* vols = (double*)(w8 + X.vols);
-    P2M_TRY(x1d_setup(m, nullptr, dN, key, idx, nullptr, 0, (double*)gap, vols, (double*)(w8 + X.volc), nullptr,
-                      pp.stream));
+    const bool small = x1d_small_fits(m);
+    if (!small)
+        P2M_TRY(x1d_setup(m, nullptr, dN, key, idx, nullptr, 0, (double*)gap, vols,
+                          (double*)(w8 + X.volc), nullptr, pp.stream));
     const bool mass = kind == P2M_X1D_MASS;
     double* cvec = (double*)(w8 + X.c);
     double* xs = (double*)(w8 + X.x);
     double* coef = mass ? (double*)(w8 + X.coef) : nullptr;
-    P2M_TRY(x1d_m2p_overlap(m, dN, key, gap, (const double*)nodal, F, quad, (double*)(w8 + X.fa),
-                            (double*)(w8 + X.tlo), (double*)(w8 + X.thi), cvec, coef, pp.stream));
+    double* fk = quad == P2M_QUAD_APPB ? nullptr : (double*)(w8 + X.fa);
+    if (small) {
+        X1dSmall a = x1d_small_args(pp, X, prob, F, nullptr);
+        a.eval = X1dSmall::kParts;
+        a.appb = quad == P2M_QUAD_APPB ? 1 : 0;
+        a.nodal = (const double*)nodal;
+        a.f = fk;
+        a.c = cvec;
+        a.coef = coef;
+        P2M_TRY(x1d_small(m, a, pp.rep, pp.stream));
+    }
+    P2M_TRY(x1d_m2p_overlap(m, dN, key, gap, (const double*)nodal, F, quad, fk, (double*)(w8 + X.tlo),
+                            (double*)(w8 + X.thi), cvec, coef, small, pp.stream));
     if (!mass) {
         P2M_TRY(x1d_div(m.np, dN, F, cvec, vols, 0.0, xs, pp.stream));
     } else if (m.np > 0) {
@@ -1566,9 +1611,16 @@ p2m_status p2m_x1d_volumes(void* ctx, const p2m_problem* prob, void* vol_out, p2
     Prepared pp;
     X1DLayout X;
     const int32_t* dN = nullptr;
-    p2m_status s = x1d_begin(ctx, prob, 1, ws, ws_bytes, stream, rep, pp, X, dN);
+    p2m_status s = x1d_begin(ctx, prob, 1, ws, ws_bytes, stream, rep, pp, X, dN, false);
     if (s != P2M_OK) return s;
     char* w8 = pp.ws;
+    if (x1d_small_fits(pp.m)) {
+        X1dSmall a = x1d_small_args(pp, X, prob, 1, nullptr);
+        a.vol_c = (double*)vol_out;
+        a.nan_volumes = 1;
+        P2M_TRY(x1d_small(pp.m, a, pp.rep, pp.stream));
+        return P2M_OK;
+    }
     P2M_TRY(x1d_setup(pp.m, (const double*)prob->x, dN, (const double*)(w8 + X.skey),
                       (const int32_t*)(w8 + X.sidx), nullptr, 0,
                       (double*)(w8 + X.gap), (double*)(w8 + X.vols), (double*)vol_out, nullptr,

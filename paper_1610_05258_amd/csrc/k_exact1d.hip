@@ -24,6 +24,8 @@
 //                  (g_{k-1} + g_k)/3, g_k/6 (cyclic tridiagonal)
 //   k_x1d_c_exact / k_x1d_cp_exact + k_x1d_c_sum
 //                  c and c' by exact overlaps instead
+//   (k_x1d_small does binning, k_x1d_sort, k_x1d_setup and k_x1d_nodes or k_x1d_parts of a
+//   small problem in one launch)
 //   k_x1d_div / k_x1d_scatter
 //                  lumped divisions and the result in caller order
 // The mass solves themselves run in the streaming kernel (k_cg.hip, by cyclic reduction)
@@ -53,12 +55,13 @@ __device__ __forceinline__ bool pair_less(double ka, int ia, double kb, int ib) 
 // network whose comparators all put the smaller pair at the lower index (each
 // merge first compares i with its mirror, then half-cleans), with comparators
 // beyond the segment skipped (virtual +infinity padding never moves).
+template <int BLOCK>
 __device__ void block_sort_pairs(double* key, int32_t* idx, int n) {
     int P = 1;
     while (P < n) P <<= 1;
     for (int k = 2; k <= P; k <<= 1) {
         const int half = k >> 1;
-        for (int q = threadIdx.x; q < P / 2; q += kB) {
+        for (int q = threadIdx.x; q < P / 2; q += BLOCK) {
             const int blk = q / half, off = q - blk * half;
             const int i = blk * k + off, j = blk * k + k - 1 - off;
             if (j < n && pair_less(key[j], idx[j], key[i], idx[i])) {
@@ -72,7 +75,7 @@ __device__ void block_sort_pairs(double* key, int32_t* idx, int n) {
         }
         __syncthreads();
         for (int d = k >> 2; d >= 1; d >>= 1) {
-            for (int q = threadIdx.x; q < P / 2; q += kB) {
+            for (int q = threadIdx.x; q < P / 2; q += BLOCK) {
                 const int blk = q / d;
                 const int i = blk * 2 * d + (q - blk * d), j = i + d;
                 if (j < n && pair_less(key[j], idx[j], key[i], idx[i])) {
@@ -86,6 +89,22 @@ __device__ void block_sort_pairs(double* key, int32_t* idx, int n) {
             }
             __syncthreads();
         }
+    }
+}
+
+// insertion sort of the n (at most kSortSmall) pairs from s on
+__device__ __forceinline__ void insertion_sort(double* key, int32_t* idx, int s, int n) {
+    for (int i = s + 1; i < s + n; ++i) {
+        const double kv = key[i];
+        const int iv = idx[i];
+        int j = i - 1;
+        while (j >= s && pair_less(kv, iv, key[j], idx[j])) {
+            key[j + 1] = key[j];
+            idx[j + 1] = idx[j];
+            --j;
+        }
+        key[j + 1] = kv;
+        idx[j + 1] = iv;
     }
 }
 
@@ -114,26 +133,14 @@ __global__ __launch_bounds__(kB) void k_x1d_sort(int ncells, const double* __res
     if (n > kSortSmall) {
         big[atomicAdd(&n_big, 1)] = c;   // any order: cells are independent
     } else if (n > 1) {
-        // insertion sort of at most kSortSmall pairs
-        for (int i = s + 1; i < s + n; ++i) {
-            const double kv = key[i];
-            const int iv = idx[i];
-            int j = i - 1;
-            while (j >= s && pair_less(kv, iv, key[j], idx[j])) {
-                key[j + 1] = key[j];
-                idx[j + 1] = idx[j];
-                --j;
-            }
-            key[j + 1] = kv;
-            idx[j + 1] = iv;
-        }
+        insertion_sort(key, idx, s, n);
     }
     __syncthreads();
     const int nb = n_big;
     for (int k = 0; k < nb; ++k) {
         const int cc = big[k];
         const int bs = cs[cc];
-        block_sort_pairs(key + bs, idx + bs, cs[cc + 1] - bs);
+        block_sort_pairs<kB>(key + bs, idx + bs, cs[cc + 1] - bs);
     }
 }
 
@@ -145,15 +152,9 @@ __device__ __forceinline__ bool left_out(const Mesh& m, const double* __restrict
     return N == 0 || !locate_axis(x[p], m.nx, m.inv_hx, c, xi, fin);
 }
 
-// gaps, volumes (eq. (4)) and values in sorted order; volumes also in caller order (NaN
-// for the particles left out, where x is given)
-__global__ void k_x1d_setup(Mesh m, const double* __restrict__ x, const int32_t* __restrict__ dN, double L, const double* __restrict__ key,
-                            const int32_t* __restrict__ idx, const double* __restrict__ values,
-                            int F, int np, double* __restrict__ gap, double* __restrict__ vol_s,
-                            double* __restrict__ vol_c, double* __restrict__ As) {
-    const int k = blockIdx.x * kB + threadIdx.x, N = *dN;
-    if (x && k < np && left_out(m, x, k, N)) vol_c[k] = __builtin_nan("");
-    if (k >= N) return;
+__device__ __forceinline__ void setup_at(int k, int N, double L, const double* key, const int32_t* idx,
+                                         const double* __restrict__ values, int F, int np, double* gap,
+                                         double* vol_s, double* vol_c, double* As) {
     const double xk = key[k];
     const double g = (k + 1 < N) ? key[k + 1] - xk : (key[0] + L) - xk;
     const double gm = (k > 0) ? xk - key[k - 1] : (key[0] + L) - key[N - 1];
@@ -165,9 +166,19 @@ __global__ void k_x1d_setup(Mesh m, const double* __restrict__ x, const int32_t*
     for (int f = 0; f < F; ++f) As[(size_t)f * N + k] = values[(size_t)f * np + p];
 }
 
+// gaps, volumes (eq. (4)) and values in sorted order; volumes also in caller order (NaN
+// for the particles left out, where x is given)
+__global__ void k_x1d_setup(Mesh m, const double* __restrict__ x, const int32_t* __restrict__ dN, double L, const double* __restrict__ key,
+                            const int32_t* __restrict__ idx, const double* __restrict__ values,
+                            int F, int np, double* __restrict__ gap, double* __restrict__ vol_s,
+                            double* __restrict__ vol_c, double* __restrict__ As) {
+    const int k = blockIdx.x * kB + threadIdx.x, N = *dN;
+    if (x && k < np && left_out(m, x, k, N)) vol_c[k] = __builtin_nan("");
+    if (k < N) setup_at(k, N, L, key, idx, values, F, np, gap, vol_s, vol_c, As);
+}
+
 // the periodic piecewise-linear interpolant through (key[k], A[k]) at y in [0, L)
-__device__ __forceinline__ double interp_sorted(const double* __restrict__ key,
-                                                const double* __restrict__ A, int N, double L,
+__device__ __forceinline__ double interp_sorted(const double* key, const double* A, int N, double L,
                                                 double y) {
     // a: the last knot with key <= y (none: the last knot, one period back)
     int lo = 0, hi = N;   // first index with key > y
@@ -209,12 +220,9 @@ __device__ __forceinline__ double node_gap(int j, int n, double h, double L) {
 // with m_j the midpoint of element j (both of a node's midpoints are evaluated here:
 // cheaper than a launch between).  coef, w (if not null): the consistent mesh mass matrix
 // of 1D P1 hats, 2h/3 on the diagonal, h/6 beside it; w = h (no orphans).
-__global__ void k_x1d_nodes(int n, double h, double L, const int32_t* __restrict__ dN,
-                            const double* __restrict__ key, const double* __restrict__ As, int F,
-                            int appb, double* __restrict__ fn, double* __restrict__ c,
-                            double* __restrict__ coef, double* __restrict__ w) {
-    const int j = blockIdx.x * kB + threadIdx.x, N = *dN;
-    if (j >= n) return;
+__device__ __forceinline__ void nodes_at(int j, int n, double h, double L, int N, const double* key,
+                                         const double* As, int F, int appb, double* fn, double* c,
+                                         double* coef, double* w) {
     const int jm = j > 0 ? j - 1 : n - 1;
     const double g = node_gap(j, n, h, L), gm = node_gap(jm, n, h, L);
     const double xj = node_x(j, h);
@@ -236,6 +244,14 @@ __global__ void k_x1d_nodes(int n, double h, double L, const int32_t* __restrict
         coef[(size_t)n + j] = hh / 6.0;
         w[j] = hh;
     }
+}
+
+__global__ void k_x1d_nodes(int n, double h, double L, const int32_t* __restrict__ dN,
+                            const double* __restrict__ key, const double* __restrict__ As, int F,
+                            int appb, double* __restrict__ fn, double* __restrict__ c,
+                            double* __restrict__ coef, double* __restrict__ w) {
+    const int j = blockIdx.x * kB + threadIdx.x;
+    if (j < n) nodes_at(j, n, h, L, *dN, key, As, F, appb, fn, c, coef, w);
 }
 
 // Simpson on one piece [a, b] with f linear on it (fm its mean) against the two
@@ -324,12 +340,9 @@ __device__ __forceinline__ double interp_mesh(const double* __restrict__ Ab, int
 // Mesh interpolant at every sorted particle to fk (if not null).  appb: the Appendix-B rule
 // on the particle hats (both of a particle's gap midpoints are evaluated here).  coef (if
 // not null): the consistent particle mass matrix, (g_{k-1} + g_k)/3 and g_k/6.
-__global__ void k_x1d_parts(const int32_t* __restrict__ dN, int n, double h, double inv_h, double L,
-                            const double* __restrict__ key, const double* __restrict__ gap,
-                            const double* __restrict__ Ab, int F, int appb, double* __restrict__ fk,
-                            double* __restrict__ c, double* __restrict__ coef) {
-    const int k = blockIdx.x * kB + threadIdx.x, N = *dN;
-    if (k >= N) return;
+__device__ __forceinline__ void parts_at(int k, int N, int n, double h, double inv_h, double L,
+                                         const double* key, const double* gap, const double* Ab, int F,
+                                         int appb, double* fk, double* c, double* coef) {
     const int km = k > 0 ? k - 1 : N - 1;
     const double xk = key[k], g = gap[k], gm = gap[km];
     const double mk = wrap_pos(xk + 0.5 * g, L), mm = wrap_pos(key[km] + 0.5 * gm, L);
@@ -346,6 +359,14 @@ __global__ void k_x1d_parts(const int32_t* __restrict__ dN, int n, double h, dou
         coef[k] = gm / 3.0 + g / 3.0;
         coef[(size_t)N + k] = g / 6.0;
     }
+}
+
+__global__ void k_x1d_parts(const int32_t* __restrict__ dN, int n, double h, double inv_h, double L,
+                            const double* __restrict__ key, const double* __restrict__ gap,
+                            const double* __restrict__ Ab, int F, int appb, double* __restrict__ fk,
+                            double* __restrict__ c, double* __restrict__ coef) {
+    const int k = blockIdx.x * kB + threadIdx.x, N = *dN;
+    if (k < N) parts_at(k, N, n, h, inv_h, L, key, gap, Ab, F, appb, fk, c, coef);
 }
 
 // Exact overlaps with the particle hats, gap by gap: gap k = [x_k, x_{k+1}] is cut
@@ -419,6 +440,124 @@ __global__ void k_x1d_out(Mesh m, const double* __restrict__ x, const int32_t* _
     for (int f = 0; f < F; ++f) out[(size_t)f * m.np + p] = xs[(size_t)f * N + k];
 }
 
+// Binning, order, setup and evaluation by one workgroup, for at most kSmallMax particles
+// and cells: what k_bin_small, k_x1d_sort, k_x1d_setup and k_x1d_nodes or k_x1d_parts do
+// (the particles' order by cell number is skipped: only the order along the line is
+// used), with the keys in LDS.  The report is written whole.
+// Bound: the launch and the dependent passes.  64 cells, 256 particles: 7.1 us instead of
+// four launches of 12 us and their gaps (there and back 45 -> 33 us).  2048 particles,
+// there and back: 67 us, by the general path 75; 4096: 86 and 83, so the line lies at 3072.
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallItems = 3;
+constexpr int kSmallMax = kSmallBlock * kSmallItems;
+
+__global__ __launch_bounds__(kSmallBlock) void k_x1d_small(Mesh m, X1dSmall a, p2m_report* __restrict__ rep) {
+    __shared__ double s_key[kSmallMax];
+    __shared__ int32_t s_idx[kSmallMax], s_cs[kSmallMax + 1];
+    __shared__ int s_wave[kSmallBlock / 64], s_big[kSmallBlock];
+    __shared__ int s_nbig, s_inv;
+    __shared__ uint32_t s_flags;
+    const int tid = threadIdx.x, nc = m.nx, np = m.np;
+    const double L = m.cell_measure * m.nx;
+    double px[kSmallItems];
+#pragma unroll
+    for (int u = 0; u < kSmallItems; ++u) {
+        const int i = tid + u * kSmallBlock;
+        px[u] = i < np ? a.x[i] : 0.0;
+    }
+    for (int c = tid; c < nc; c += kSmallBlock) s_cs[c] = 0;
+    if (tid == 0) {
+        s_inv = 0;
+        s_flags = 0u;
+    }
+    __syncthreads();
+    int cell[kSmallItems], rank[kSmallItems];
+#pragma unroll
+    for (int u = 0; u < kSmallItems; ++u) {
+        const int i = tid + u * kSmallBlock;
+        cell[u] = -1;
+        rank[u] = 0;
+        if (i >= np) continue;
+        int c;
+        double xi;
+        bool fin;
+        if (locate_axis(px[u], m.nx, m.inv_hx, c, xi, fin)) {
+            cell[u] = c;
+            rank[u] = atomicAdd(&s_cs[c], 1);
+        } else {
+            atomicOr(&s_flags, fin ? (uint32_t)P2M_FLAG_RANGE : (uint32_t)P2M_FLAG_NONFINITE);
+            atomicAdd(&s_inv, 1);
+        }
+    }
+    __syncthreads();
+    // exclusive scan of the counts in place, each thread a run of adjacent cells
+    const int per = (nc + kSmallBlock - 1) / kSmallBlock;
+    const int c0 = min(tid * per, nc), c1 = min(c0 + per, nc);
+    int sum = 0;
+    for (int c = c0; c < c1; ++c) sum += s_cs[c];
+    int inc = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int u = __shfl_up(inc, d, 64);
+        if ((tid & 63) >= d) inc += u;
+    }
+    if ((tid & 63) == 63) s_wave[tid >> 6] = inc;
+    __syncthreads();
+    int ex = inc - sum;
+    for (int w = 0; w < (tid >> 6); ++w) ex += s_wave[w];
+    for (int c = c0; c < c1; ++c) {
+        const int n = s_cs[c];
+        s_cs[c] = ex;
+        ex += n;
+    }
+    if (tid == kSmallBlock - 1) s_cs[nc] = ex;
+    __syncthreads();
+    const int N = s_cs[nc];
+#pragma unroll
+    for (int u = 0; u < kSmallItems; ++u) {
+        if (cell[u] < 0) continue;
+        const int k = s_cs[cell[u]] + rank[u];
+        s_key[k] = wrap_pos(px[u], L);
+        s_idx[k] = tid + u * kSmallBlock;
+    }
+    if (tid == 0) *a.dN = N;
+    __syncthreads();
+    for (int b = 0; b < nc; b += kSmallBlock) {
+        if (tid == 0) s_nbig = 0;
+        __syncthreads();
+        const int c = b + tid;
+        if (c < nc) {
+            const int s = s_cs[c], n = s_cs[c + 1] - s;
+            if (n > kSortSmall) s_big[atomicAdd(&s_nbig, 1)] = c;
+            else if (n > 1) insertion_sort(s_key, s_idx, s, n);
+        }
+        __syncthreads();
+        const int nb = s_nbig;
+        for (int q = 0; q < nb; ++q) {
+            const int cc = s_big[q], s = s_cs[cc];
+            block_sort_pairs<kSmallBlock>(s_key + s, s_idx + s, s_cs[cc + 1] - s);
+        }
+        __syncthreads();
+    }
+    for (int k = tid; k < np; k += kSmallBlock) {
+        if (a.nan_volumes && left_out(m, a.x, k, N)) a.vol_c[k] = __builtin_nan("");
+        if (k >= N) continue;
+        a.key[k] = s_key[k];
+        a.idx[k] = s_idx[k];
+        setup_at(k, N, L, s_key, s_idx, a.values, a.values ? a.F : 0, np, a.gap, a.vol_s, a.vol_c, a.As);
+    }
+    report_clear(rep, s_flags, s_inv);
+    __syncthreads();
+    if (a.eval == X1dSmall::kNodes) {
+        for (int j = tid; j < nc; j += kSmallBlock)
+            nodes_at(j, nc, m.cell_measure, L, N, s_key, a.As, a.F, a.appb, a.f, a.c, a.coef, a.w);
+    } else if (a.eval == X1dSmall::kParts) {
+        for (int k = tid; k < N; k += kSmallBlock)
+            parts_at(k, N, nc, m.cell_measure, m.inv_hx, L, s_key, a.gap, a.nodal, a.F, a.appb, a.f, a.c,
+                     a.coef);
+    }
+}
+
 }  // namespace
 
 #define X1D_TRY(e)                                 \
@@ -426,6 +565,13 @@ __global__ void k_x1d_out(Mesh m, const double* __restrict__ x, const int32_t* _
         hipError_t e_ = (e);                       \
         if (e_ != hipSuccess) return e_;           \
     } while (0)
+
+bool x1d_small_fits(const Mesh& m) { return m.np > 0 && m.np <= kSmallMax && m.nx <= kSmallMax; }
+
+hipError_t x1d_small(const Mesh& m, const X1dSmall& a, p2m_report* rep, hipStream_t stream) {
+    hipLaunchKernelGGL(k_x1d_small, dim3(1), dim3(kSmallBlock), 0, stream, m, a, rep);
+    return hipGetLastError();
+}
 
 hipError_t x1d_sort(const Mesh& m, const double* x, const int32_t* perm, const int32_t* cs,
                     double* key, int32_t* idx, hipStream_t stream) {
@@ -447,13 +593,15 @@ hipError_t x1d_setup(const Mesh& m, const double* x, const int32_t* dN, const do
 
 hipError_t x1d_p2m_overlap(const Mesh& m, const int32_t* dN, const double* key, const double* As,
                            int F, int quad, double* fn, double* t_lo, double* t_hi, double* c,
-                           double* coef, double* w, hipStream_t stream) {
+                           double* coef, double* w, bool evaluated, hipStream_t stream) {
     const int n = m.nx;
     const double h = m.cell_measure, L = h * n;
     const int appb = quad == P2M_QUAD_APPB && c ? 1 : 0;
-    hipLaunchKernelGGL(k_x1d_nodes, dim3(grid_of(n)), dim3(kB), 0, stream, n, h, L, dN, key, As, F,
-                       appb, fn, c, coef, w);
-    X1D_TRY(hipGetLastError());
+    if (!evaluated) {
+        hipLaunchKernelGGL(k_x1d_nodes, dim3(grid_of(n)), dim3(kB), 0, stream, n, h, L, dN, key, As, F,
+                           appb, fn, c, coef, w);
+        X1D_TRY(hipGetLastError());
+    }
     if (appb || !c) return hipSuccess;
     hipLaunchKernelGGL(k_x1d_c_exact, dim3(grid_of(n)), dim3(kB), 0, stream, n, h, L, dN, key, As, F,
                        fn, t_lo, t_hi);
@@ -465,14 +613,16 @@ hipError_t x1d_p2m_overlap(const Mesh& m, const int32_t* dN, const double* key, 
 
 hipError_t x1d_m2p_overlap(const Mesh& m, const int32_t* dN, const double* key, const double* gap,
                            const double* nodal, int F, int quad, double* fk, double* t_lo,
-                           double* t_hi, double* c, double* coef, hipStream_t stream) {
+                           double* t_hi, double* c, double* coef, bool evaluated, hipStream_t stream) {
     if (m.np == 0) return hipSuccess;
     const int n = m.nx;
     const double h = m.cell_measure, L = h * n;
     const int appb = quad == P2M_QUAD_APPB ? 1 : 0;
-    hipLaunchKernelGGL(k_x1d_parts, dim3(grid_of(m.np)), dim3(kB), 0, stream, dN, n, h, m.inv_hx, L,
-                       key, gap, nodal, F, appb, appb ? nullptr : fk, c, coef);
-    X1D_TRY(hipGetLastError());
+    if (!evaluated) {
+        hipLaunchKernelGGL(k_x1d_parts, dim3(grid_of(m.np)), dim3(kB), 0, stream, dN, n, h, m.inv_hx, L,
+                           key, gap, nodal, F, appb, fk, c, coef);
+        X1D_TRY(hipGetLastError());
+    }
     if (appb) return hipSuccess;
     hipLaunchKernelGGL(k_x1d_cp_exact, dim3(grid_of(m.np)), dim3(kB), 0, stream, dN, n, h, m.inv_hx, L,
                        key, gap, nodal, fk, F, t_lo, t_hi);

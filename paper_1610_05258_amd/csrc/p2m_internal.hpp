@@ -172,6 +172,24 @@ hipError_t launch_delta1d(const Mesh& m, Particles<T> P, const T* values, int F,
 // perm[0..N)); key / idx [N] receive the positions and particle numbers in position
 // order; gap, vol_s [N] sorted order, vol_c [np] caller order (with x: NaN for the
 // particles left out), As [F][N]
+// X1dSmall: all that in one launch (and the binning, the report and the evaluation that
+// the next functions start with), for problems that x1d_small_fits
+struct X1dSmall {
+    const double* x;
+    const double* values;   // [F][np] (P2M) or null
+    int F;
+    int32_t* dN;
+    double* key;
+    int32_t* idx;
+    double *gap, *vol_s, *vol_c, *As;
+    int nan_volumes;        // vol_c: NaN for the particles left out
+    enum { kNone = 0, kNodes, kParts };
+    int eval, appb;
+    const double* nodal;    // kParts
+    double *f, *c, *coef, *w;   // as in x1d_p2m_overlap / x1d_m2p_overlap
+};
+bool x1d_small_fits(const Mesh& m);
+hipError_t x1d_small(const Mesh& m, const X1dSmall& a, p2m_report* rep, hipStream_t stream);
 hipError_t x1d_sort(const Mesh& m, const double* x, const int32_t* perm, const int32_t* cs,
                     double* key, int32_t* idx, hipStream_t stream);
 hipError_t x1d_setup(const Mesh& m, const double* x, const int32_t* dN, const double* key, const int32_t* idx,
@@ -180,15 +198,16 @@ hipError_t x1d_setup(const Mesh& m, const double* x, const int32_t* dN, const do
 // c [F][n] = int A psi_j over the mesh hats (quad: P2M_QUAD_*; null: not wanted); fn [F][n]
 // receives the particle interpolant at the nodes (the delta P2M; needed by the exact
 // overlaps, else it may be null); coef, w (or null): the consistent mesh mass matrix and
-// its node volumes
+// its node volumes; evaluated: the launch before has done all but the exact overlaps
 hipError_t x1d_p2m_overlap(const Mesh& m, const int32_t* dN, const double* key, const double* As,
                            int F, int quad, double* fn, double* t_lo, double* t_hi, double* c,
-                           double* coef, double* w, hipStream_t stream);
+                           double* coef, double* w, bool evaluated, hipStream_t stream);
 // c [F][N] = int Abar psi_mu over the particle hats in sorted order; fk [F][N] scratch;
 // coef (or null): the consistent particle mass matrix
 hipError_t x1d_m2p_overlap(const Mesh& m, const int32_t* dN, const double* key, const double* gap,
                            const double* nodal, int F, int quad, double* fk, double* t_lo,
-                           double* t_hi, double* c, double* coef, hipStream_t stream);
+                           double* t_hi, double* c, double* coef, bool evaluated,
+                           hipStream_t stream);
 // out = c / d (or / s); K entries, *dK of them where dK is given
 hipError_t x1d_div(int K, const int32_t* dK, int F, const double* c, const double* d, double s,
                    double* out, hipStream_t stream);
