@@ -237,6 +237,10 @@ struct Prepared {
     // the report still has to be zeroed: the first launch of the call does it
     // together with its own clearing work (one launch fewer per call)
     mutable bool clear_rep = false;
+    // words that the binning's first launch zeroes besides its own (the solve's barrier
+    // words); set back to null when that is done
+    mutable unsigned* zero = nullptr;
+    mutable int nzero = 0;
 };
 
 p2m_status prepare(void* ctx, const p2m_problem* prob, int F, void* ws, size_t ws_bytes,
@@ -271,8 +275,10 @@ p2m_status run_bin(const Prepared& pp, const p2m_problem* prob, int32_t* perm, i
     void* scan_ws = pp.ws + pp.L.scan;
     const size_t clear = (pp.L.scan + scan_workspace_bytes(m.nn) - pp.L.counts) / sizeof(int32_t);
     // counts and the scan's words (and the report, when the call has not cleared it)
-    P2M_TRY(launch_fill_i32(counts, 0, clear, pp.stream, pp.clear_rep ? pp.rep : nullptr));
+    P2M_TRY(launch_fill_i32(counts, 0, clear, pp.stream, pp.clear_rep ? pp.rep : nullptr, pp.zero,
+                            pp.zero ? pp.nzero : 0));
     pp.clear_rep = false;
+    pp.zero = nullptr;
     P2M_TRY(launch_locate_count<T>(m, particles_of<T>(prob), key, rank, counts, pp.rep,
                                    pp.stream));
     P2M_TRY(launch_exclusive_scan(counts, cs, m.nn, scan_ws, pp.scan_spin, pp.rep, 1, pp.stream));
@@ -295,10 +301,8 @@ p2m_status run_assign(const Prepared& pp, const p2m_problem* prob, p2m_assign_ki
     }
     T* b = (T*)(pp.ws + pp.L.b);
     T* w = (T*)(pp.ws + pp.L.w);
-    P2M_TRY(launch_assemble<T>(pp.m, particles_of<T>(prob), (const T*)values, F, perm, cs, b, w,
-                               nullptr, pp.stream));
-    P2M_TRY(launch_finalize<T>(pp.m, F, b, w, kind == P2M_PIC ? 1 : 0, (T*)nodal_out, pp.rep,
-                               pp.stream));
+    P2M_TRY(launch_assemble_final<T>(pp.m, particles_of<T>(prob), (const T*)values, F, perm, cs, b, w,
+                                     kind == P2M_PIC ? 1 : 0, (T*)nodal_out, pp.rep, pp.stream));
     return P2M_OK;
 }
 
@@ -347,21 +351,27 @@ bool poly_solve_for(const Context* c, const Mesh& m, int F, const Layout& L, Pol
            poly_area(L, sizeof(T)).bytes;
 }
 
+bool takes_poly(const Choice& ch) {
+    return ch.solver == P2M_SOLVER_AUTO || ch.solver == P2M_SOLVER_RESIDENT_CHEB;
+}
+
 // Solve kernel: the choice's kernel where it applies.  AUTO and RESIDENT_CHEB take the
 // polynomial-preconditioned solve (2D, F <= 3), RESIDENT the register-resident one
 // with the diagonal preconditioner, RESIDENT beyond it and TILES the tile-streaming
 // one, and everything else the grid-synchronised streaming kernel (1D, F > 3, large
 // FP64 meshes).
+// known: the polynomial-preconditioned solve, where the caller has looked it up already.
 template <typename T>
 p2m_status run_solve(const Context* c, const Prepared& pp, int F, T* b, const T* w, T* coef,
-                     int start, const p2m_solve_opts& caller_opts, void* x, const Choice& ch) {
+                     int start, const p2m_solve_opts& caller_opts, void* x, const Choice& ch,
+                     const PolySolve<T>* known = nullptr) {
     p2m_solve_opts opts = caller_opts;
     if (ch.inner_rtol >= 0.0 && ch.inner_rtol < 1.0) opts.inner_rtol = ch.inner_rtol;
     const bool tiled = sizeof(T) == 4 && pp.m.dim == 2 && F <= kResidentMaxFields;
     const int kind = ch.solver;
     PolySolve<T> ps;
-    if ((kind == P2M_SOLVER_AUTO || kind == P2M_SOLVER_RESIDENT_CHEB) &&
-        poly_solve_for<T>(c, pp.m, F, pp.L, ps)) {
+    if (known) ps = *known;
+    if (known || (takes_poly(ch) && poly_solve_for<T>(c, pp.m, F, pp.L, ps))) {
         ps.one.out = x;
         ps.one.rep = pp.rep;
         ps.coef = coef;
@@ -369,6 +379,7 @@ p2m_status run_solve(const Context* c, const Prepared& pp, int F, T* b, const T*
         ps.w = w;
         ps.ws = pp.ws + poly_area(pp.L, sizeof(T)).off;
         ps.clear_rep = pp.clear_rep ? pp.rep : nullptr;
+        ps.cleared = pp.nzero > 0 && !pp.zero;
         ps.spin = pp.solve_spin;
         P2M_TRY(launch_pcg<T>(ps, start, opts, pp.stream));
         pp.clear_rep = false;
@@ -412,6 +423,12 @@ p2m_status run_mass(const Context* c, const Prepared& pp, const p2m_problem* pro
                     const Choice& ch) {
     int32_t* perm = (int32_t*)(pp.ws + pp.L.perm);
     int32_t* cs = (int32_t*)(pp.ws + pp.L.cell_start);
+    PolySolve<T> ps;
+    const bool poly = takes_poly(ch) && poly_solve_for<T>(c, pp.m, F, pp.L, ps);
+    if (poly) {
+        pp.zero = (unsigned*)(pp.ws + poly_area(pp.L, sizeof(T)).off);
+        pp.nzero = pcg_sync_words();
+    }
     p2m_status s = run_bin<T>(pp, prob, perm, cs);
     if (s != P2M_OK) return s;
     T* b = (T*)(pp.ws + pp.L.b);
@@ -433,7 +450,7 @@ p2m_status run_mass(const Context* c, const Prepared& pp, const p2m_problem* pro
                                   (T*)x, pp.stream));
         start = P2M_START_USER;
     }
-    return run_solve<T>(c, pp, F, b, w, coef, start, opts, x, ch);
+    return run_solve<T>(c, pp, F, b, w, coef, start, opts, x, ch, poly ? &ps : nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1010,10 +1027,8 @@ p2m_status x2d_run_p2m(const Context* c, const Prepared& pp, const X2DLayout& X,
         P.vol = volc;
         double* b = (double*)(w8 + X.b);
         double* bw = (double*)(w8 + X.bw);
-        P2M_TRY(launch_assemble<double>(m, P, (const double*)values, F, A.perm, A.cs, b, bw,
-                                        nullptr, pp.stream));
-        P2M_TRY(launch_finalize<double>(m, F, b, bw, kind == P2M_X1D_PIC ? 1 : 0, out, rep,
-                                        pp.stream));
+        P2M_TRY(launch_assemble_final<double>(m, P, (const double*)values, F, A.perm, A.cs, b, bw,
+                                              kind == P2M_X1D_PIC ? 1 : 0, out, rep, pp.stream));
         return P2M_OK;
     }
     if (kind == P2M_X1D_DELTA) {
@@ -1481,12 +1496,10 @@ p2m_status p2m_x1d_assign(void* ctx, const p2m_problem* prob, int32_t kind, int3
         P.vol = volc;
         double* b = (double*)(w8 + X.b);
         double* bw = (double*)(w8 + X.bw);
-        P2M_TRY(launch_assemble<double>(m, P, (const double*)values, F,
-                                        (const int32_t*)(w8 + X.perm),
-                                        (const int32_t*)(w8 + X.cell_start), b, bw, nullptr,
-                                        pp.stream));
-        P2M_TRY(launch_finalize<double>(m, F, b, bw, kind == P2M_X1D_PIC ? 1 : 0, out, pp.rep,
-                                        pp.stream));
+        P2M_TRY(launch_assemble_final<double>(m, P, (const double*)values, F,
+                                              (const int32_t*)(w8 + X.perm),
+                                              (const int32_t*)(w8 + X.cell_start), b, bw,
+                                              kind == P2M_X1D_PIC ? 1 : 0, out, pp.rep, pp.stream));
         return P2M_OK;
     }
     const double* As = (const double*)(w8 + X.As);

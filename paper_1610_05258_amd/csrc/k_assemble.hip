@@ -84,6 +84,32 @@ __device__ __forceinline__ void acc_particle(T (&acc)[NQ], T (&cmp)[NQ], T c00, 
     }
 }
 
+// FLIP or PIC in place of the sums: what finalize_node writes (out null: b and w).  The
+// node's sums are in registers then, so b and w need not go to memory and back (a launch
+// and 3 to 4 us on the 333 x 217 mesh).
+template <typename T>
+struct Final {
+    T* out;
+    int pic;
+    T measure;
+    p2m_report* rep;
+};
+
+// every active lane of the wave calls it
+__device__ __forceinline__ void flag_orphans(bool orphan, p2m_report* rep) {
+    if (!rep) return;
+    const uint64_t mask = __ballot(orphan);   // one atomic per wave that holds an orphan
+    if (mask && (int)(threadIdx.x & 63) == __ffsll((unsigned long long)mask) - 1) {
+        atomicAdd(&rep->n_orphan, (int)__popcll(mask));
+        atomicOr(&rep->flags, (uint32_t)P2M_FLAG_ORPHAN);
+    }
+}
+template <typename T>
+__device__ __forceinline__ T finalize_node(const Final<T>& fin, T bk, T wk) {
+    if (fin.pic) return bk / fin.measure;
+    return !(wk > (T)0) ? (T)0 : bk / wk;
+}
+
 // Staged 2D scatter.  A workgroup owns a TS x TS node tile and the (TS+1)^2 cells
 // around it.  The particles of those cells (their perm segments) are processed in
 // chunks of CH slots: first every thread loads particles slot-parallel (perm reads
@@ -99,7 +125,8 @@ __device__ __forceinline__ void assemble2d_tile(const Mesh& m, const Particles<T
                                                 const int32_t* __restrict__ perm, int po,
                                                 const int32_t* __restrict__ cell_start,
                                                 T* __restrict__ b, T* __restrict__ w,
-                                                T* __restrict__ coef, int tiles_x, int tile) {
+                                                T* __restrict__ coef, int tiles_x, int tile,
+                                                const Final<T>& fin) {
     constexpr int HS = TS + 1;
     constexpr int HC = HS * HS;
     constexpr int NT = (HC + 63) / 64 * 64;     // threads: one per cell
@@ -331,13 +358,17 @@ __device__ __forceinline__ void assemble2d_tile(const Mesh& m, const Particles<T
     const int cB = li + HS * (lj + 1);        // cell (i-1, j): node is its c10
     const int cC = li + HS * lj;              // cell (i-1, j-1): node is its c11
     const int cD = (li + 1) + HS * lj;        // cell (i, j-1): node is its c01
-    w[k] = ((part[Q_W00][cA] + part[Q_W10][cB]) + part[Q_W11][cC]) + part[Q_W01][cD];
+    const T wk = ((part[Q_W00][cA] + part[Q_W10][cB]) + part[Q_W11][cC]) + part[Q_W01][cD];
+    if (!fin.out) w[k] = wk;
 #pragma unroll
     for (int f = 0; f < F; ++f) {
-        b[(size_t)f * m.nn + k] = ((part[Q_B + 4 * f + 0][cA] + part[Q_B + 4 * f + 1][cB]) +
-                                   part[Q_B + 4 * f + 2][cC]) +
-                                  part[Q_B + 4 * f + 3][cD];
+        const T bk = ((part[Q_B + 4 * f + 0][cA] + part[Q_B + 4 * f + 1][cB]) +
+                      part[Q_B + 4 * f + 2][cC]) +
+                     part[Q_B + 4 * f + 3][cD];
+        if (fin.out) fin.out[(size_t)f * m.nn + k] = finalize_node(fin, bk, wk);
+        else b[(size_t)f * m.nn + k] = bk;
     }
+    if (fin.out) flag_orphans(!(wk > (T)0), fin.rep);
     if (coef) {
         coef[k] = ((part[Q_D00][cA] + part[Q_D10][cB]) + part[Q_D11][cC]) + part[Q_D01][cD];
         coef[(size_t)m.nn + k] = part[Q_EB][cA] + part[Q_ET][cD];       // M(k, k+x)
@@ -350,9 +381,9 @@ template <typename T, int F, int TS, int CH>
 __global__ __launch_bounds__(((TS + 1) * (TS + 1) + 63) / 64 * 64) void k_assemble2d(
     Mesh m, Particles<T> P, const T* __restrict__ values, const int32_t* __restrict__ perm,
     const int32_t* __restrict__ cell_start, T* __restrict__ b, T* __restrict__ w,
-    T* __restrict__ coef, int tiles_x) {
+    T* __restrict__ coef, int tiles_x, Final<T> fin) {
     assemble2d_tile<T, F, TS, CH>(m, P, values, perm, 0, cell_start, b, w, coef, tiles_x,
-                                  blockIdx.x);
+                                  blockIdx.x, fin);
 }
 
 // batch: tile t belongs to instance amap[t]; the instance's b, w and coef blocks
@@ -365,7 +396,7 @@ __global__ __launch_bounds__(((TS + 1) * (TS + 1) + 63) / 64 * 64) void k_assemb
     const BatchInst& I = inst[amap[blockIdx.x]];
     assemble2d_tile<float, F, TS, CH>(I.m, I.P, I.values, perm, I.po, cell_start + I.no,
                                       b + (size_t)F * I.no, w + I.no, coef + (size_t)4 * I.no,
-                                      I.atx, blockIdx.x - I.at);
+                                      I.atx, blockIdx.x - I.at, Final<float>{});
 }
 
 // 1D: a tile of TS nodes and the TS+1 cells touching it (one extra on the left).
@@ -377,7 +408,7 @@ __global__ __launch_bounds__(TS) void k_assemble1d(Mesh m, Particles<T> P,
                                                   const int32_t* __restrict__ perm,
                                                   const int32_t* __restrict__ cell_start,
                                                   T* __restrict__ b, T* __restrict__ w,
-                                                  T* __restrict__ coef) {
+                                                  T* __restrict__ coef, Final<T> fin) {
     constexpr int HC = TS + 1;
     constexpr int NQ = 5 + 2 * F;  // DL, DR, E, WL, WR, then bL, bR per field
     __shared__ T part[NQ][HC];
@@ -428,9 +459,15 @@ __global__ __launch_bounds__(TS) void k_assemble1d(Mesh m, Particles<T> P,
     if (gi >= m.nx) return;
     const int cA = threadIdx.x + 1;  // cell i: node is its left end
     const int cB = threadIdx.x;      // cell i-1: node is its right end
-    w[gi] = part[3][cA] + part[4][cB];
+    const T wk = part[3][cA] + part[4][cB];
+    if (!fin.out) w[gi] = wk;
 #pragma unroll
-    for (int f = 0; f < F; ++f) b[(size_t)f * m.nn + gi] = part[5 + 2 * f][cA] + part[6 + 2 * f][cB];
+    for (int f = 0; f < F; ++f) {
+        const T bk = part[5 + 2 * f][cA] + part[6 + 2 * f][cB];
+        if (fin.out) fin.out[(size_t)f * m.nn + gi] = finalize_node(fin, bk, wk);
+        else b[(size_t)f * m.nn + gi] = bk;
+    }
+    if (fin.out) flag_orphans(!(wk > (T)0), fin.rep);
     if (coef) {
         coef[gi] = part[0][cA] + part[1][cB];
         coef[(size_t)m.nn + gi] = part[2][cA];
@@ -439,29 +476,13 @@ __global__ __launch_bounds__(TS) void k_assemble1d(Mesh m, Particles<T> P,
 
 template <typename T>
 __global__ void k_finalize(int nn, int F, const T* __restrict__ b, const T* __restrict__ w,
-                           int pic, T measure, T* __restrict__ out,
-                           p2m_report* __restrict__ rep) {
-    int k = blockIdx.x * blockDim.x + threadIdx.x;
-    bool orphan = false;
-    if (k < nn) {
-        const T wk = w[k];
-        orphan = !(wk > (T)0);
-        for (int f = 0; f < F; ++f) {
-            const T bk = b[(size_t)f * nn + k];
-            T o;
-            if (pic) o = bk / measure;
-            else o = orphan ? (T)0 : bk / wk;
-            out[(size_t)f * nn + k] = o;
-        }
-    }
-    if (rep) {
-        // one atomic per wave that holds an orphan
-        uint64_t mask = __ballot(k < nn && orphan);
-        if (mask && (threadIdx.x & 63) == __ffsll((unsigned long long)mask) - 1) {
-            atomicAdd(&rep->n_orphan, (int)__popcll(mask));
-            atomicOr(&rep->flags, (uint32_t)P2M_FLAG_ORPHAN);
-        }
-    }
+                           Final<T> fin) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= nn) return;
+    const T wk = w[k];
+    for (int f = 0; f < F; ++f)
+        fin.out[(size_t)f * nn + k] = finalize_node(fin, b[(size_t)f * nn + k], wk);
+    flag_orphans(!(wk > (T)0), fin.rep);
 }
 
 // staged slots per chunk: the staging area stays within 32 KB
@@ -486,12 +507,13 @@ hipError_t assemble_batch_f(const BatchInst* inst, const int32_t* amap, int ntil
 
 template <typename T, int F, int TS>
 hipError_t assemble2d_ts(const Mesh& m, Particles<T> P, const T* values, const int32_t* perm,
-                         const int32_t* cs, T* b, T* w, T* coef, hipStream_t stream) {
+                         const int32_t* cs, T* b, T* w, T* coef, const Final<T>& fin,
+                         hipStream_t stream) {
     constexpr int CH = stage_chunk<T, F>();
     constexpr int NT = ((TS + 1) * (TS + 1) + 63) / 64 * 64;
     const int tx = (m.nx + TS - 1) / TS, ty = (m.ny + TS - 1) / TS;
     hipLaunchKernelGGL((k_assemble2d<T, F, TS, CH>), dim3(tx * ty), dim3(NT), 0, stream, m, P,
-                       values, perm, cs, b, w, coef, tx);
+                       values, perm, cs, b, w, coef, tx, fin);
     return hipGetLastError();
 }
 
@@ -499,12 +521,13 @@ hipError_t assemble2d_ts(const Mesh& m, Particles<T> P, const T* values, const i
 // 8 x 8), 8 = 8 x 8
 template <typename T, int F>
 hipError_t assemble_f(const Mesh& m, Particles<T> P, const T* values, const int32_t* perm,
-                      const int32_t* cs, T* b, T* w, T* coef, int tile, hipStream_t stream) {
+                      const int32_t* cs, T* b, T* w, T* coef, int tile, const Final<T>& fin,
+                      hipStream_t stream) {
     if (m.dim == 1) {
         constexpr int TS = 256;
         int grid = (m.nx + TS - 1) / TS;
         hipLaunchKernelGGL((k_assemble1d<T, F, TS>), dim3(grid), dim3(TS), 0, stream, m, P, values,
-                           perm, cs, b, w, coef);
+                           perm, cs, b, w, coef, fin);
         return hipGetLastError();
     }
     // tile 15x15 unless the per-cell parts of its 16x16 cells exceed 64 KB; chunk
@@ -512,8 +535,29 @@ hipError_t assemble_f(const Mesh& m, Particles<T> P, const T* values, const int3
     static_assert(Q_B == 13, "assemble_tile assumes 13 + 4F parts per cell");
     constexpr int TS = assemble_tile(F, (int)sizeof(T));
     if (tile == 8 && TS != 8)
-        return assemble2d_ts<T, F, 8>(m, P, values, perm, cs, b, w, coef, stream);
-    return assemble2d_ts<T, F, TS>(m, P, values, perm, cs, b, w, coef, stream);
+        return assemble2d_ts<T, F, 8>(m, P, values, perm, cs, b, w, coef, fin, stream);
+    return assemble2d_ts<T, F, TS>(m, P, values, perm, cs, b, w, coef, fin, stream);
+}
+
+}  // namespace
+
+namespace {
+
+template <typename T>
+hipError_t assemble_any(const Mesh& m, Particles<T> P, const T* values, int F, const int32_t* perm,
+                        const int32_t* cs, T* b, T* w, T* coef, int tile, const Final<T>& fin,
+                        hipStream_t stream) {
+    switch (F) {
+        case 1: return assemble_f<T, 1>(m, P, values, perm, cs, b, w, coef, tile, fin, stream);
+        case 2: return assemble_f<T, 2>(m, P, values, perm, cs, b, w, coef, tile, fin, stream);
+        case 3: return assemble_f<T, 3>(m, P, values, perm, cs, b, w, coef, tile, fin, stream);
+        case 4: return assemble_f<T, 4>(m, P, values, perm, cs, b, w, coef, tile, fin, stream);
+        case 5: return assemble_f<T, 5>(m, P, values, perm, cs, b, w, coef, tile, fin, stream);
+        case 6: return assemble_f<T, 6>(m, P, values, perm, cs, b, w, coef, tile, fin, stream);
+        case 7: return assemble_f<T, 7>(m, P, values, perm, cs, b, w, coef, tile, fin, stream);
+        case 8: return assemble_f<T, 8>(m, P, values, perm, cs, b, w, coef, tile, fin, stream);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace
@@ -522,17 +566,7 @@ template <typename T>
 hipError_t launch_assemble(const Mesh& m, Particles<T> P, const T* values, int F,
                            const int32_t* perm, const int32_t* cell_start, T* b, T* w, T* coef,
                            hipStream_t stream, int tile) {
-    switch (F) {
-        case 1: return assemble_f<T, 1>(m, P, values, perm, cell_start, b, w, coef, tile, stream);
-        case 2: return assemble_f<T, 2>(m, P, values, perm, cell_start, b, w, coef, tile, stream);
-        case 3: return assemble_f<T, 3>(m, P, values, perm, cell_start, b, w, coef, tile, stream);
-        case 4: return assemble_f<T, 4>(m, P, values, perm, cell_start, b, w, coef, tile, stream);
-        case 5: return assemble_f<T, 5>(m, P, values, perm, cell_start, b, w, coef, tile, stream);
-        case 6: return assemble_f<T, 6>(m, P, values, perm, cell_start, b, w, coef, tile, stream);
-        case 7: return assemble_f<T, 7>(m, P, values, perm, cell_start, b, w, coef, tile, stream);
-        case 8: return assemble_f<T, 8>(m, P, values, perm, cell_start, b, w, coef, tile, stream);
-        default: return hipErrorInvalidValue;
-    }
+    return assemble_any<T>(m, P, values, F, perm, cell_start, b, w, coef, tile, Final<T>{}, stream);
 }
 template hipError_t launch_assemble<float>(const Mesh&, Particles<float>, const float*, int,
                                            const int32_t*, const int32_t*, float*, float*, float*,
@@ -554,17 +588,30 @@ hipError_t launch_assemble_batch(int F, const BatchInst* inst, const int32_t* am
 }
 
 template <typename T>
-hipError_t launch_finalize(const Mesh& m, int F, const T* b, const T* w, int pic, T* out,
-                           p2m_report* rep, hipStream_t stream) {
+hipError_t launch_assemble_final(const Mesh& m, Particles<T> P, const T* values, int F,
+                                 const int32_t* perm, const int32_t* cell_start, T* b, T* w, int pic,
+                                 T* out, p2m_report* rep, hipStream_t stream) {
+    const Final<T> fin{out, pic, (T)m.cell_measure, rep};
+    // a result that lies over an input is written when every tile has read it
+    const char *lo = (const char*)out, *hi = (const char*)(out + (size_t)F * m.nn);
+    auto apart = [&](const T* p, size_t n) {
+        return !p || (const char*)(p + n) <= lo || (const char*)p >= hi;
+    };
+    if (apart(values, (size_t)F * m.np) && apart(P.x, m.np) && apart(P.y, m.np) && apart(P.vol, m.np))
+        return assemble_any<T>(m, P, values, F, perm, cell_start, b, w, (T*)nullptr, 0, fin, stream);
+    hipError_t e = assemble_any<T>(m, P, values, F, perm, cell_start, b, w, (T*)nullptr, 0, Final<T>{},
+                                   stream);
+    if (e != hipSuccess) return e;
     const int block = 256;
-    int grid = (m.nn + block - 1) / block;
-    hipLaunchKernelGGL(k_finalize<T>, dim3(grid), dim3(block), 0, stream, m.nn, F, b, w, pic,
-                       (T)m.cell_measure, out, rep);
+    hipLaunchKernelGGL(k_finalize<T>, dim3((m.nn + block - 1) / block), dim3(block), 0, stream, m.nn, F,
+                       b, w, fin);
     return hipGetLastError();
 }
-template hipError_t launch_finalize<float>(const Mesh&, int, const float*, const float*, int,
-                                           float*, p2m_report*, hipStream_t);
-template hipError_t launch_finalize<double>(const Mesh&, int, const double*, const double*, int,
-                                            double*, p2m_report*, hipStream_t);
+template hipError_t launch_assemble_final<float>(const Mesh&, Particles<float>, const float*, int,
+                                                 const int32_t*, const int32_t*, float*, float*, int,
+                                                 float*, p2m_report*, hipStream_t);
+template hipError_t launch_assemble_final<double>(const Mesh&, Particles<double>, const double*, int,
+                                                  const int32_t*, const int32_t*, double*, double*,
+                                                  int, double*, p2m_report*, hipStream_t);
 
 }  // namespace p2m

@@ -27,9 +27,12 @@ constexpr int kBlock = kBinBlock;
 
 __global__ void k_report_clear(p2m_report* rep) { report_clear(rep, 0u, 0); }
 
-// Fill of n ints; with rep, block 0 also zeroes that report (one launch for both).
+// Fill of n ints; with rep, block 0 also zeroes that report, and the nz words at z (one
+// launch for all).
 __global__ void k_fill_i32(int32_t* __restrict__ p, int32_t value, size_t n,
-                           p2m_report* __restrict__ rep) {
+                           p2m_report* __restrict__ rep, unsigned* __restrict__ z, int nz) {
+    if (blockIdx.x == 0)
+        for (int t = threadIdx.x; t < nz; t += blockDim.x) z[t] = 0u;
     if (rep && blockIdx.x == 0) report_clear(rep, 0u, 0);
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -670,12 +673,12 @@ hipError_t launch_report_clear(p2m_report* rep, hipStream_t stream) {
 }
 
 hipError_t launch_fill_i32(int32_t* p, int32_t value, size_t n, hipStream_t stream,
-                           p2m_report* rep) {
-    if (n == 0 && !rep) return hipSuccess;
+                           p2m_report* rep, unsigned* z, int nz) {
+    if (n == 0 && !rep && nz == 0) return hipSuccess;
     int grid = (int)((n + kBlock - 1) / kBlock);
     if (grid > 65536) grid = 65536;
     if (grid < 1) grid = 1;
-    hipLaunchKernelGGL(k_fill_i32, dim3(grid), dim3(kBlock), 0, stream, p, value, n, rep);
+    hipLaunchKernelGGL(k_fill_i32, dim3(grid), dim3(kBlock), 0, stream, p, value, n, rep, z, nz);
     return hipGetLastError();
 }
 
@@ -724,7 +727,7 @@ hipError_t launch_exclusive_scan(const int32_t* counts, int32_t* out, int n, voi
     unsigned* ctr = scan_ctr(scan_ws, n);
     if (nb == 0) {
         hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, stream, out, 0, (size_t)1,
-                           (p2m_report*)nullptr);
+                           (p2m_report*)nullptr, (unsigned*)nullptr, 0);
         return hipGetLastError();
     }
     if (!reps) nrep = 0;

@@ -1155,6 +1155,8 @@ int pcg_grid(int tsize, bool small, bool batch, int F, int ntiles, int device) {
     return g < ntiles ? g : ntiles;
 }
 
+int pcg_sync_words() { return kSyncWords; }
+
 size_t pcg_column_elems(const Mesh& m, int per_row) { return (size_t)2 * PH * per_row * m.ny; }
 
 size_t pcg_workspace_bytes(int tsize, bool small, int F, int nprob, int ntiles, size_t nodes,
@@ -1221,9 +1223,11 @@ hipError_t launch_pcg(const PolySolve<T>& ps, int start, const p2m_solve_opts& o
         a.rsd = (T*)take(n * own * sizeof(T));
         a.cimg = (T*)take(n * 3 * en * sizeof(T));
     }
-    hipLaunchKernelGGL(k_pcg_clear, dim3(1), dim3(256), 0, stream, words, kSyncWords, ps.clear_rep);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (!ps.cleared || ps.clear_rep) {
+        hipLaunchKernelGGL(k_pcg_clear, dim3(1), dim3(256), 0, stream, words, kSyncWords, ps.clear_rep);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     // An ordinary launch: the stream has finished every earlier kernel and the grid is
     // at most what the device holds at once (pcg_grid), so all its workgroups are
     // resident; the barrier is the kernel's own and every wait in it is bounded.

@@ -112,7 +112,7 @@ __device__ __forceinline__ void corner_weights(double xi, double eta, T& c00, T&
 hipError_t launch_report_clear(p2m_report* rep, hipStream_t stream);
 // fill n ints with value; with rep, the same launch zeroes that report
 hipError_t launch_fill_i32(int32_t* p, int32_t value, size_t n, hipStream_t stream,
-                           p2m_report* rep = nullptr);
+                           p2m_report* rep = nullptr, unsigned* z = nullptr, int nz = 0);
 
 // binning
 template <typename T>
@@ -150,10 +150,12 @@ hipError_t launch_assemble(const Mesh& m, Particles<T> P, const T* values, int F
                            const int32_t* perm, const int32_t* cell_start, T* b, T* w, T* coef,
                            hipStream_t stream, int tile = 0);
 
-// finalize: FLIP (divide by w, orphans 0) or PIC (divide by the mesh volume)
+// assembly and FLIP (divide by w, orphans 0) or PIC (divide by the mesh volume); b and w
+// are scratch
 template <typename T>
-hipError_t launch_finalize(const Mesh& m, int F, const T* b, const T* w, int pic, T* out,
-                           p2m_report* rep, hipStream_t stream);
+hipError_t launch_assemble_final(const Mesh& m, Particles<T> P, const T* values, int F,
+                                 const int32_t* perm, const int32_t* cell_start, T* b, T* w, int pic,
+                                 T* out, p2m_report* rep, hipStream_t stream);
 
 // M2P gather in caller order.  ws (optional, >= F * nn elements): 2D gathers of
 // 2-4 fields read a node-major copy built there.  clear: the report is zeroed first
@@ -389,8 +391,10 @@ struct PolySolve {
     const T* w = nullptr;
     void* ws = nullptr;                // pcg_workspace_bytes
     p2m_report* clear_rep = nullptr;   // zeroed first (the report the kernel writes), or null
+    bool cleared = false;              // the pcg_sync_words() words at ws are zero already
     long spin = kSolveSpinDefault;     // bound of a grid-barrier wait (< 0: every wait ends at once)
 };
+int pcg_sync_words();
 template <typename T>
 hipError_t launch_pcg(const PolySolve<T>& ps, int start, const p2m_solve_opts& opts, hipStream_t stream);
 
