@@ -340,15 +340,20 @@ bool poly_solve_for(const Context* c, const Mesh& m, int F, const Layout& L, Pol
     I.no = 0;
     I.pt = 0;
     I.npt = pcg_tiles(m, ps.small, &I.ptx);
-    pcg_interval(m, I.pc);
     ps.F = F;
     ps.ntiles = I.npt;
     ps.nodes = (size_t)m.nn;
-    ps.cols = pcg_column_elems(m, I.ptx);
-    ps.grid = pcg_grid((int)sizeof(T), ps.small, false, F, I.npt, c->device);
-    if (ps.grid < 1 || (sizeof(T) == 8 && ps.grid < ps.ntiles)) return false;
-    return pcg_workspace_bytes((int)sizeof(T), ps.small, F, 1, ps.ntiles, ps.nodes, ps.cols, ps.grid) <=
-           poly_area(L, sizeof(T)).bytes;
+    for (int depth = pcg_depth((int)sizeof(T), ps.small, F);; depth = 3) {
+        ps.depth = depth;
+        pcg_interval(m, depth, I.pc);
+        ps.cols = pcg_column_elems(m, depth, I.ptx);
+        ps.grid = pcg_grid((int)sizeof(T), ps.small, depth, false, F, I.npt, c->device);
+        if (ps.grid >= 1 && (sizeof(T) == 4 || ps.grid >= ps.ntiles) &&
+            pcg_workspace_bytes((int)sizeof(T), ps.small, depth, F, 1, ps.ntiles, ps.nodes, ps.cols,
+                                ps.grid) <= poly_area(L, sizeof(T)).bytes)
+            return true;
+        if (depth == 3) return false;
+    }
 }
 
 bool takes_poly(const Choice& ch) {
@@ -577,6 +582,7 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
     for (const BatchInst& I : P.inst) P.jacobi = P.jacobi || I.m.nn > kPolyMaxNodes;
     for (int cls = 0; cls < 2; ++cls) {
         BatchPlan::Poly& Q = P.poly[cls];
+        const int depth = pcg_depth(4, cls == 0, F);
         std::vector<int> at(nprob, -1);
         for (int k = 0; k < nprob; ++k) {
             const Mesh& m = P.inst[k].m;
@@ -589,9 +595,9 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
             I.no = P.inst[k].no;
             I.pt = (int32_t)Q.rmap.size();
             I.npt = pcg_tiles(m, cls == 0, &I.ptx);
-            pcg_interval(m, I.pc);
+            pcg_interval(m, depth, I.pc);
             I.co = (int32_t)Q.cols;
-            Q.cols += pcg_column_elems(m, I.ptx);
+            Q.cols += pcg_column_elems(m, depth, I.ptx);
             if (Q.cols * F >= ((size_t)1 << 31)) return P2M_ERR_UNSUPPORTED;
             at[k] = (int)Q.inst.size();
             Q.rmap.insert(Q.rmap.end(), I.npt, at[k]);
@@ -601,7 +607,7 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
             if (at[k] >= 0)
                 for (int t = 0; t < Q.inst[at[k]].npt; ++t) Q.order.push_back(Q.inst[at[k]].pt + t);
         if (!Q.rmap.empty()) {
-            Q.grid = pcg_grid(4, cls == 0, true, F, (int)Q.rmap.size(), c->device);
+            Q.grid = pcg_grid(4, cls == 0, depth, true, F, (int)Q.rmap.size(), c->device);
             if (Q.grid < 1) return P2M_ERR_UNSUPPORTED;
         }
     }
@@ -626,8 +632,9 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
         Q.inst_o = take(sizeof(PolyInst) * Q.inst.size());
         Q.rmap_o = take(sizeof(int32_t) * Q.rmap.size());
         Q.order_o = take(sizeof(int32_t) * Q.order.size());
-        const size_t n = pcg_workspace_bytes(4, cls == 0, F, (int)Q.inst.size(), (int)Q.rmap.size(),
-                                             (size_t)nn, Q.cols, Q.grid);
+        const bool small = cls == 0;
+        const size_t n = pcg_workspace_bytes(4, small, pcg_depth(4, small, F), F, (int)Q.inst.size(),
+                                             (int)Q.rmap.size(), (size_t)nn, Q.cols, Q.grid);
         if (n > poly_b) poly_b = n;
     }
     P.head = off;
@@ -690,6 +697,7 @@ hipError_t enqueue_batch(const BatchPlan& P, char* ws, p2m_report* reps, const p
             ps.ntiles = (int)Q.rmap.size();
             ps.grid = Q.grid;
             ps.small = &Q == &P.poly[0];
+            ps.depth = pcg_depth(4, ps.small, P.F);
             ps.nodes = (size_t)P.nn;
             ps.cols = Q.cols;
             ps.coef = coef;

@@ -7,16 +7,16 @@
 //
 //  * the inner system is scaled symmetrically, A = D^-1/2 M D^-1/2 (unit diagonal,
 //    so three stencil planes instead of four and no division), and preconditioned
-//    by the polynomial p(A) = c0 + c1 A + c2 A^2 that makes 1 - l p(l) the scaled
-//    Chebyshev polynomial T3 on [lo, hi].  T3 is odd: beyond hi, 1 - l p(l) is
+//    by the polynomial p(A) of degree 2 (or 4) that makes 1 - l p(l) the scaled
+//    Chebyshev polynomial T3 (T5) on [lo, hi].  Both are odd: beyond hi, 1 - l p(l) is
 //    negative, below lo it lies in (0, 1), so l p(l) > 0 for every l > 0 and the
 //    preconditioner is positive definite whatever the spectrum; [lo, hi] only
 //    decides how fast it is (pcg_interval);
 //  * Chronopoulos-Gear conjugate gradients: (r, u), (w, u) and (r, r) with u = p(A) r,
 //    w = A u are reduced together, so an iteration has one grid barrier, and needs a
-//    third of the iterations of the diagonal preconditioner (5-6 for 15 at 8
-//    particles per cell, 17 for 45 at 2);
-//  * the three stencil products of an iteration read r up to three nodes outside the
+//    third (T5: a fifth) of the iterations of the diagonal preconditioner (T3: 5-6 for
+//    15 at 8 particles per cell, 17 for 45 at 2);
+//  * the three (five) stencil products of an iteration read r as many nodes outside the
 //    tile.  A workgroup keeps its own copy of that ring's r and s (and, on the
 //    innermost ring, p, d and x), advanced by the same operations on the same values
 //    as their owners, so that per iteration only w crosses tiles: every tile publishes
@@ -29,12 +29,12 @@
 // depend on the tile only, never on how the tiles are dealt, so a problem gives the
 // same bits alone, in a batch, resident or streamed.
 //
-// Bound: the latency of one iteration (three LDS stencil products, a block sum, the
+// Bound: the latency of one iteration (its LDS stencil products, a block sum, the
 // grid barrier), not traffic, while one tile per workgroup fits the chip; the traffic of
 // the streamed state beyond.  Whole mass assignment and interpolation, before (diagonal
 // preconditioner, or the FP64 streaming solve) and now: 256 x 256 at 4 per cell, F = 1,
-// 263 -> 119 us; 1024 x 1024 at 8 per cell, F = 3, 597 -> 419 us; 2048 x 2048
-// 4.09 -> 2.5 ms; 512 x 512 FP64 at 8 per cell, F = 1, 1312 -> 199 us.  What the large
+// 263 -> 108 us; 1024 x 1024 at 8 per cell, F = 3, 597 -> 415 us; 2048 x 2048
+// 4.09 -> 2.47 ms; 512 x 512 FP64 at 8 per cell, F = 1, 1312 -> 189 us.  What the large
 // tile's 24 us iteration (F = 3) answered to: x kept as the start formula until a field
 // needs a second correction (no FP64 x traffic in the usual two residual phases), border
 // columns published transposed in one 16-byte store a lane and read 64 rows a wave
@@ -47,21 +47,21 @@ namespace p2m {
 
 namespace {
 
-constexpr int PH = 3;   // ring depth: one per stencil product of an iteration
-
 // Tile of TX x TY nodes on NT threads; a thread owns OWN consecutive rows of one
 // column (a column's stencil reads slide down the rows) and at most one ring slot.
-template <int TX_, int TY_, int NT_>
+template <int TX_, int TY_, int NT_, int PH_>
 struct PTile {
     static constexpr int TX = TX_, TY = TY_, NT = NT_;
+    static constexpr int PH = PH_;   // ring depth: one per stencil product of an iteration
     static constexpr int EX = TX + 2 * PH, EY = TY + 2 * PH, EN = EX * EY;
     static constexpr int OWN = TX * TY / NT;
     static constexpr int NRING = EN - TX * TY;
     static constexpr int NRP = (NRING + 63) / 64 * 64;
     static_assert(NT % TX == 0 && OWN * NT == TX * TY && NRING <= NT && EN % 4 == 0, "tile");
 };
-using TileS = PTile<32, 32, 512>;
-using TileL = PTile<64, 64, 1024>;
+using TileS = PTile<32, 32, 1024, 5>;
+using TileD = PTile<32, 32, 512, 3>;    // FP64 only (pcg_depth)
+using TileL = PTile<64, 64, 1024, 3>;
 
 template <typename T>
 struct PArgs {
@@ -76,7 +76,7 @@ struct PArgs {
     double* x64;           // [F][nn] blocks at F*no, owner-only
     T* pubR;               // [F][nn] blocks at F*no, published scaled residual of the row strips
     T* pubW[2];            // the same of w, by iteration parity
-    T* colR;               // [F][6 ptx][ny] blocks at F*co, the column strips, a column's rows
+    T* colR;               // [F][2 PH ptx][ny] blocks at F*co, the column strips, a column's rows
     T* colW[2];            // adjacent (a wave reads and a lane writes whole runs)
     double* xring;         // [tile][F][NRP] ring copies of x, owner-only
     // streamed state (workgroups that own several tiles), by tile
@@ -99,8 +99,13 @@ __device__ __forceinline__ double dot_t(double acc, double a, double b) { return
 // 1/sqrt of a diagonal entry; 1 for an orphan row (identity) and for a
 // diagonal too small to invert (the row then decouples: its products with the
 // neighbours are below its rounding)
+// (the instruction and one Newton step, written out: the compiler lowers an FP32 square
+// root with or without its refinement by context, and a ring copy has to equal its owner's
+// value bit for bit)
 __device__ __forceinline__ float rs_of(float d, bool orphan) {
-    return orphan || !(d >= 1.17549435e-38f) ? 1.0f : __fdiv_rn(1.0f, __fsqrt_rn(d));
+    if (orphan || !(d >= 1.17549435e-38f)) return 1.0f;
+    const float y = __builtin_amdgcn_rsqf(d);
+    return fmaf(0.5f * y, fmaf(-d * y, y, 1.0f), y);
 }
 __device__ __forceinline__ double rs_of(double d, bool orphan) {
     return orphan || !(d >= 2.2250738585072014e-308) ? 1.0 : __ddiv_rn(1.0, __dsqrt_rn(d));
@@ -143,6 +148,7 @@ __device__ __forceinline__ double stencil_x(const T (&c)[7], double x0, double x
 
 template <typename T, class TC, int F, bool BATCH, bool STREAM>
 __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
+    constexpr int PH = TC::PH;
     constexpr int NT = TC::NT, OWN = TC::OWN, EX = TC::EX, EN = TC::EN, NRP = TC::NRP;
     constexpr int NTN = TC::TX * TC::TY, NV = 3 * F, NW = NT / 64;
     // two exchange buffers per field where they fit (one workgroup barrier per stencil
@@ -184,7 +190,7 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
     int o_rc = 0;                             // column-buffer element of a column ring slot, else -1
     int o_cc = 0;                             // column-buffer element of the first own node, else -1
     uint32_t am = 0, sm = 0;                  // own nodes inside the mesh; on the published row strips
-    T c0 = 0, c1 = 0, c2 = 0;
+    T pc[PH];
     T* out = nullptr;
     auto inst_of = [&](int kk) -> const PolyInst& {
         if constexpr (BATCH) return a.inst[kk];
@@ -207,9 +213,8 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
         co = I.co;
         cl = 2 * PH * I.ptx * ny;
         out = (T*)I.out;
-        c0 = (T)I.pc[0];
-        c1 = (T)I.pc[1];
-        c2 = (T)I.pc[2];
+#pragma unroll
+        for (int j = 0; j < PH; ++j) pc[j] = (T)I.pc[j];
         txa = min(TC::TX, nx - i0);
         tya = min(TC::TY, ny - j0);
         o_g0 = (j0 + row0) * nx + i0 + col;
@@ -232,14 +237,18 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
         if (h < 2 * PH * rw) {
             const bool up = h >= PH * rw;
             if (up) h -= PH * rw;
-            const int rr = h >= 2 * rw ? 2 : (h >= rw ? 1 : 0);
+            int rr = 0;
+#pragma unroll
+            for (int q = 1; q < PH; ++q) rr += h >= q * rw;
             lr = up ? tya + rr : rr - PH;
             lc = h - rr * rw - PH;
         } else {
             h -= 2 * PH * rw;
             const bool right = h >= PH * tya;
             if (right) h -= PH * tya;
-            const int cc = h >= 2 * tya ? 2 : (h >= tya ? 1 : 0);
+            int cc = 0;
+#pragma unroll
+            for (int q = 1; q < PH; ++q) cc += h >= q * tya;
             lr = h - cc * tya;
             lc = cc + (right ? txa : -PH);
         }
@@ -516,7 +525,8 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
     auto apply = [&](const T* U, uint32_t im, bool rn, T (&qo)[F][OWN], T (&qn)[F]) {
         // two rows at a time: a window slides down each column, and the coefficients of
         // more rows at once would not fit beside the state
-        constexpr int R = 2;
+        constexpr int R = OWN < 2 ? 1 : 2;
+        static_assert(OWN % R == 0, "rows of a step");
 #pragma unroll
         for (int h = 0; h < OWN; h += R) {
             const int q0 = fresh(o_q0) + h * EX;
@@ -880,31 +890,29 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                     }
                     if (it > 0) update(im, uo, un, wn);
                 }
-                // u = c0 r + A (c1 r + c2 A r), w = A u
+                // u = p(A) r by Horner's rule (PH is odd: u ends in bA), w = A u
+                static_assert(PH % 2 == 1, "u in bA");
                 T qo[F][OWN], qn[F];
                 put(bA, im, vr, rdep != 0, nr);
                 __syncthreads();
-                apply(bA, im, rdep == 1 || rdep == 2, qo, qn);
 #pragma unroll
-                for (int f = 0; f < F; ++f) {
-                    if (!(im & (1u << f))) continue;
+                for (int j = 1; j < PH; ++j) {
+                    const bool rn = rdep >= 1 && rdep <= PH - j;
+                    apply(j & 1 ? bA : bB, im, rn, qo, qn);
+                    const T cj = pc[PH - 1 - j];
 #pragma unroll
-                    for (int o = 0; o < OWN; ++o) qo[f][o] = fma_t(c2, qo[f][o], mul_t(c1, vr[f][o]));
-                    qn[f] = fma_t(c2, qn[f], mul_t(c1, nr[f]));
+                    for (int f = 0; f < F; ++f) {
+                        if (!(im & (1u << f))) continue;
+#pragma unroll
+                        for (int o = 0; o < OWN; ++o)
+                            qo[f][o] = j == 1 ? fma_t(pc[PH - 1], qo[f][o], mul_t(cj, vr[f][o]))
+                                              : fma_t(cj, vr[f][o], qo[f][o]);
+                        qn[f] = j == 1 ? fma_t(pc[PH - 1], qn[f], mul_t(cj, nr[f])) : fma_t(cj, nr[f], qn[f]);
+                    }
+                    if (!PP) __syncthreads();
+                    put(j & 1 ? bB : bA, im, qo, rn, qn);
+                    if (j < PH - 1) __syncthreads();
                 }
-                if (!PP) __syncthreads();
-                put(bB, im, qo, rdep == 1 || rdep == 2, qn);
-                __syncthreads();
-                apply(bB, im, rdep == 1, qo, qn);
-#pragma unroll
-                for (int f = 0; f < F; ++f) {
-                    if (!(im & (1u << f))) continue;
-#pragma unroll
-                    for (int o = 0; o < OWN; ++o) qo[f][o] = fma_t(c0, vr[f][o], qo[f][o]);
-                    qn[f] = fma_t(c0, nr[f], qn[f]);
-                }
-                if (!PP) __syncthreads();
-                put(bA, im, qo, rdep == 1, qn);
                 if (!keep) {
 #pragma unroll
                     for (int f = 0; f < F; ++f) {
@@ -1079,10 +1087,13 @@ const void* pcg_kernel(int F) {
     return nullptr;
 }
 template <typename T>
-const void* pcg_pick(bool small, bool batch, bool stream, int F) {
+const void* pcg_pick(bool small, int depth, bool batch, bool stream, int F) {
     if constexpr (sizeof(T) == 8) {
-        return small && !batch && !stream ? pcg_kernel<T, TileS, false, false>(F) : nullptr;
+        if (!small || batch || stream) return nullptr;
+        if (depth == TileD::PH) return pcg_kernel<T, TileD, false, false>(F);
+        return F == 1 ? (const void*)k_pcg<T, TileS, 1, false, false> : nullptr;
     } else {
+        if (depth != (small ? TileS::PH : TileL::PH)) return nullptr;
         if (small && batch)
             return stream ? pcg_kernel<T, TileS, true, true>(F) : pcg_kernel<T, TileS, true, false>(F);
         if (small) return stream ? nullptr : pcg_kernel<T, TileS, false, false>(F);
@@ -1092,15 +1103,37 @@ const void* pcg_pick(bool small, bool batch, bool stream, int F) {
     }
 }
 
+// what the host needs to know of a tile
+struct TileInfo {
+    int nt, own, en, nrp;
+};
+template <class C>
+constexpr TileInfo tile_info() {
+    return TileInfo{C::NT, C::TX * C::TY, C::EN, C::NRP};
+}
+TileInfo tile_of(bool small, int depth) {
+    if (!small) return tile_info<TileL>();
+    return depth == TileS::PH ? tile_info<TileS>() : tile_info<TileD>();
+}
+
 // streamed state per tile, bytes
-template <typename T, class C>
-size_t stream_bytes(int F, int ntiles) {
-    const size_t n = (size_t)ntiles, own = (size_t)C::TX * C::TY;
-    return al(n * 6 * F * own * sizeof(T)) + al(n * 5 * F * C::NRP * sizeof(T)) +
-           al(n * own * sizeof(T)) + al(n * 3 * C::EN * sizeof(T));
+size_t stream_bytes(int tsize, const TileInfo& t, int F, int ntiles) {
+    const size_t n = (size_t)ntiles;
+    return al(n * 6 * F * t.own * tsize) + al(n * 5 * F * t.nrp * tsize) + al(n * t.own * tsize) +
+           al(n * 3 * t.en * tsize);
 }
 
 }  // namespace
+
+// Stencil products of an iteration (the preconditioner's degree + 1).  The small tile takes
+// five: at 4 particles per cell 4 iterations for 6 to the same residual, and the barrier,
+// the sums and the ring exchange cost as much as two products.  256 x 256, F = 1: the solve
+// 80 -> 65 us; 512 x 512 FP64, F = 1: 101 -> 85; two and three fields gain 0 to 2% of a
+// pass.  In FP64 two and three fields do not fit the 128 registers of 1024 threads (384 x
+// 384, F = 3: pass 224 us with three products on 512 threads, 255 with five); the ring of
+// five on the large tile is more slots than it has threads.  Where the wider ring does not
+// fit the workspace (FP64 strips a few nodes wide) the caller takes three.
+int pcg_depth(int tsize, bool small, int F) { return small && (tsize == 4 || F == 1) ? 5 : 3; }
 
 // Meshes of at most kPolyTiles small tiles (512 x 512) take the 32 x 32 tile, one per
 // compute unit; larger ones the 64 x 64 tile, whose ring is a smaller share of it.
@@ -1115,11 +1148,21 @@ int pcg_tiles(const Mesh& m, bool small, int* per_row) {
     return px * ((m.ny + ty - 1) / ty);
 }
 
-void pcg_interval(const Mesh& m, double pc[3]) {
+void pcg_interval(const Mesh& m, int depth, double pc[5]) {
     const double ppc = (double)m.np / (double)m.nn;
     const double lo = ppc >= 6.0 ? 0.4 : (ppc >= 3.5 ? 0.28 : 0.18);
     const double hi = ppc >= 6.0 ? 2.1 : (ppc >= 3.5 ? 2.3 : 2.5);
     const double de = 0.5 * (hi - lo), s = (hi + lo) / (hi - lo);
+    // 1 - l p(l) = T(s - l / de) / T(s), expanded at s
+    if (depth == 5) {
+        const double s2 = s * s, g = 1.0 / (s * (16.0 * s2 * s2 - 20.0 * s2 + 5.0));
+        pc[0] = g * (80.0 * s2 * s2 - 60.0 * s2 + 5.0) / de;
+        pc[1] = -g * s * (160.0 * s2 - 60.0) / (de * de);
+        pc[2] = g * (160.0 * s2 - 20.0) / (de * de * de);
+        pc[3] = -80.0 * g * s / (de * de * de * de);
+        pc[4] = 16.0 * g / (de * de * de * de * de);
+        return;
+    }
     const double g = 1.0 / (4.0 * s * s * s - 3.0 * s);
     pc[0] = g * (12.0 * s * s - 3.0) / de;
     pc[1] = -12.0 * g * s / (de * de);
@@ -1139,46 +1182,47 @@ int resident_groups(const void* fn, int nt, int device) {
 }
 
 template <typename T>
-int grid_of(bool small, bool batch, int F, int ntiles, int device) {
-    const int nt = small ? TileS::NT : TileL::NT;
-    const int held = resident_groups(pcg_pick<T>(small, batch, false, F), nt, device);
+int grid_of(bool small, int depth, bool batch, int F, int ntiles, int device) {
+    const int nt = tile_of(small, depth).nt;
+    const int held = resident_groups(pcg_pick<T>(small, depth, batch, false, F), nt, device);
     if (ntiles <= held) return ntiles;
-    return resident_groups(pcg_pick<T>(small, batch, true, F), nt, device);
+    return resident_groups(pcg_pick<T>(small, depth, batch, true, F), nt, device);
 }
 
 }  // namespace
 
-int pcg_grid(int tsize, bool small, bool batch, int F, int ntiles, int device) {
+int pcg_grid(int tsize, bool small, int depth, bool batch, int F, int ntiles, int device) {
     if (F < 1 || F > kResidentMaxFields || ntiles < 1) return 0;
-    const int g = tsize == 8 ? grid_of<double>(small, batch, F, ntiles, device)
-                             : grid_of<float>(small, batch, F, ntiles, device);
+    const int g = tsize == 8 ? grid_of<double>(small, depth, batch, F, ntiles, device)
+                             : grid_of<float>(small, depth, batch, F, ntiles, device);
     return g < ntiles ? g : ntiles;
 }
 
 int pcg_sync_words() { return kSyncWords; }
 
-size_t pcg_column_elems(const Mesh& m, int per_row) { return (size_t)2 * PH * per_row * m.ny; }
+size_t pcg_column_elems(const Mesh& m, int depth, int per_row) {
+    return (size_t)2 * depth * per_row * m.ny;
+}
 
-size_t pcg_workspace_bytes(int tsize, bool small, int F, int nprob, int ntiles, size_t nodes,
-                           size_t cols, int grid) {
+size_t pcg_workspace_bytes(int tsize, bool small, int depth, int F, int nprob, int ntiles,
+                           size_t nodes, size_t cols, int grid) {
+    const TileInfo t = tile_of(small, depth);
     size_t s = al(kSyncWords * sizeof(unsigned)) + al((size_t)2 * 3 * F * ntiles * sizeof(double)) +
                al((size_t)2 * 3 * F * nprob * sizeof(double)) + al((size_t)F * nodes * sizeof(double)) +
                3 * al((size_t)F * nodes * tsize) + 3 * al((size_t)F * cols * tsize) +
-               al((size_t)ntiles * F * (small ? TileS::NRP : TileL::NRP) * sizeof(double));
-    if (ntiles > grid) {
-        if (tsize == 8) s += stream_bytes<double, TileS>(F, ntiles);
-        else s += small ? stream_bytes<float, TileS>(F, ntiles) : stream_bytes<float, TileL>(F, ntiles);
-    }
+               al((size_t)ntiles * F * t.nrp * sizeof(double));
+    if (ntiles > grid) s += stream_bytes(tsize, t, F, ntiles);
     return s;
 }
 
 template <typename T>
 hipError_t launch_pcg(const PolySolve<T>& ps, int start, const p2m_solve_opts& opts, hipStream_t stream) {
     const bool batch = ps.inst != nullptr;
-    const void* fn = pcg_pick<T>(ps.small, batch, ps.ntiles > ps.grid, ps.F);
+    const void* fn = pcg_pick<T>(ps.small, ps.depth, batch, ps.ntiles > ps.grid, ps.F);
     if (!fn || ps.grid < 1 || ps.nprob < 1 || (batch && ps.nprob * ps.F > kBatchMaxPairs))
         return hipErrorInvalidValue;
     const int F = ps.F;
+    const TileInfo t = tile_of(ps.small, ps.depth);
     char* p = (char*)ps.ws;
     auto take = [&](size_t bytes) {
         char* q = p;
@@ -1213,15 +1257,13 @@ hipError_t launch_pcg(const PolySolve<T>& ps, int start, const p2m_solve_opts& o
     a.colR = (T*)take((size_t)F * ps.cols * sizeof(T));
     a.colW[0] = (T*)take((size_t)F * ps.cols * sizeof(T));
     a.colW[1] = (T*)take((size_t)F * ps.cols * sizeof(T));
-    a.xring = (double*)take((size_t)ps.ntiles * F * (ps.small ? TileS::NRP : TileL::NRP) * sizeof(double));
+    a.xring = (double*)take((size_t)ps.ntiles * F * t.nrp * sizeof(double));
     if (ps.ntiles > ps.grid) {
         const size_t n = (size_t)ps.ntiles;
-        const size_t own = ps.small ? TileS::TX * TileS::TY : TileL::TX * TileL::TY;
-        const size_t ring = ps.small ? TileS::NRP : TileL::NRP, en = ps.small ? TileS::EN : TileL::EN;
-        a.own = (T*)take(n * 6 * F * own * sizeof(T));
-        a.ring = (T*)take(n * 5 * F * ring * sizeof(T));
-        a.rsd = (T*)take(n * own * sizeof(T));
-        a.cimg = (T*)take(n * 3 * en * sizeof(T));
+        a.own = (T*)take(n * 6 * F * t.own * sizeof(T));
+        a.ring = (T*)take(n * 5 * F * t.nrp * sizeof(T));
+        a.rsd = (T*)take(n * t.own * sizeof(T));
+        a.cimg = (T*)take(n * 3 * t.en * sizeof(T));
     }
     if (!ps.cleared || ps.clear_rep) {
         hipLaunchKernelGGL(k_pcg_clear, dim3(1), dim3(256), 0, stream, words, kSyncWords, ps.clear_rep);
@@ -1232,7 +1274,7 @@ hipError_t launch_pcg(const PolySolve<T>& ps, int start, const p2m_solve_opts& o
     // at most what the device holds at once (pcg_grid), so all its workgroups are
     // resident; the barrier is the kernel's own and every wait in it is bounded.
     void* args[] = {&a};
-    return hipLaunchKernel(fn, dim3(ps.grid), dim3(ps.small ? TileS::NT : TileL::NT), args, 0, stream);
+    return hipLaunchKernel(fn, dim3(ps.grid), dim3(t.nt), args, 0, stream);
 }
 template hipError_t launch_pcg<float>(const PolySolve<float>&, int, const p2m_solve_opts&, hipStream_t);
 template hipError_t launch_pcg<double>(const PolySolve<double>&, int, const p2m_solve_opts&, hipStream_t);

@@ -366,17 +366,20 @@ struct PolyInst {
     p2m_report* rep;
     int32_t no, pt, ptx, npt;   // first node, first tile, tiles per row, tiles
     int32_t co, pad;       // first element of its block of the column buffers
-    double pc[3];          // the preconditioner's polynomial (pcg_interval)
+    double pc[5];          // the preconditioner's polynomial (pcg_interval)
 };
 bool pcg_small(const Mesh& m);
 int pcg_tiles(const Mesh& m, bool small, int* per_row);
-// coefficients of the polynomial for this problem's particles per node
-void pcg_interval(const Mesh& m, double pc[3]);
-int pcg_grid(int tsize, bool small, bool batch, int F, int ntiles, int device);   // 0: not available
+// stencil products of an iteration, by preference; the polynomial's coefficients for this
+// problem's particles per node
+int pcg_depth(int tsize, bool small, int F);
+void pcg_interval(const Mesh& m, int depth, double pc[5]);
+int pcg_grid(int tsize, bool small, int depth, bool batch, int F, int ntiles,
+             int device);   // 0: not available
 // elements per field of a problem's column buffer
-size_t pcg_column_elems(const Mesh& m, int per_row);
-size_t pcg_workspace_bytes(int tsize, bool small, int F, int nprob, int ntiles, size_t nodes,
-                           size_t cols, int grid);
+size_t pcg_column_elems(const Mesh& m, int depth, int per_row);
+size_t pcg_workspace_bytes(int tsize, bool small, int depth, int F, int nprob, int ntiles,
+                           size_t nodes, size_t cols, int grid);
 template <typename T>
 struct PolySolve {
     PolyInst one{};                    // a single problem, or
@@ -385,6 +388,7 @@ struct PolySolve {
     const int32_t* order = nullptr;    // dealing order of the tiles
     int nprob = 1, F = 1, ntiles = 0, grid = 0;
     bool small = true;                 // 32 x 32 tiles (pcg_small)
+    int depth = 5;                     // pcg_depth
     size_t nodes = 0, cols = 0;        // of all instances
     T* coef = nullptr;
     T* b = nullptr;
