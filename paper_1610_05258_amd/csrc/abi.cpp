@@ -384,7 +384,9 @@ p2m_status run_solve(const Context* c, const Prepared& pp, int F, T* b, const T*
         ps.w = w;
         ps.ws = pp.ws + poly_area(pp.L, sizeof(T)).off;
         ps.clear_rep = pp.clear_rep ? pp.rep : nullptr;
-        ps.cleared = pp.nzero > 0 && !pp.zero;
+        ps.cleared = pp.nzero > 0 && !pp.zero;   // good for one solve
+        pp.zero = nullptr;
+        pp.nzero = 0;
         ps.spin = pp.solve_spin;
         P2M_TRY(launch_pcg<T>(ps, start, opts, pp.stream));
         pp.clear_rep = false;
@@ -430,6 +432,8 @@ p2m_status run_mass(const Context* c, const Prepared& pp, const p2m_problem* pro
     int32_t* cs = (int32_t*)(pp.ws + pp.L.cell_start);
     PolySolve<T> ps;
     const bool poly = takes_poly(ch) && poly_solve_for<T>(c, pp.m, F, pp.L, ps);
+    pp.zero = nullptr;
+    pp.nzero = 0;
     if (poly) {
         pp.zero = (unsigned*)(pp.ws + poly_area(pp.L, sizeof(T)).off);
         pp.nzero = pcg_sync_words();
@@ -1421,6 +1425,12 @@ p2m_status p2m_ns_step(void* ctx, const p2m_problem* prob, int32_t assign, doubl
         P2M_TRY(launch_ns_viscous(m, sv, ubar, ustar, w + N.fft, pp.stream));
         P2M_TRY(launch_ns_pressure(m, -(h / 6.0) / dt, ustar, pr, w + N.fft, pp.stream));
     } else {
+        // the polynomial's interval is that of mass matrices; a Poisson system's condition
+        // (10^4 at 192 x 192) stalls its FP32 recurrence, so these keep the diagonal
+        auto diagonal = [](Choice ch) {
+            if (takes_poly(ch)) ch.solver = P2M_SOLVER_RESIDENT;
+            return ch;
+        };
         P2M_TRY(launch_ns_coef(m, (float)sv, cv, wv, cpr, wpr, pp.stream));
         Prepared pv = pp;
         pv.rep = &reps[1];
@@ -1428,7 +1438,7 @@ p2m_status p2m_ns_step(void* ctx, const p2m_problem* prob, int32_t assign, doubl
         p2m_solve_opts ov = *opts;
         ov.start = P2M_START_FLIP;
         s = run_solve<float>(c, pv, 2, ubar, wv, cv, P2M_START_FLIP, ov, ustar,
-                             choose(c, m, P2M_F32, 2));
+                             diagonal(choose(c, m, P2M_F32, 2)));
         if (s != P2M_OK) return s;
         P2M_TRY(launch_ns_div(m, -(h / 6.0) / dt, ustar, rhs, pp.stream));
         Prepared pq = pp;
@@ -1439,7 +1449,7 @@ p2m_status p2m_ns_step(void* ctx, const p2m_problem* prob, int32_t assign, doubl
         const int64_t cap = 64 * (int64_t)(m.nx > m.ny ? m.nx : m.ny);
         if (op.maxit < cap) op.maxit = (int32_t)(cap < INT32_MAX ? cap : INT32_MAX);
         s = run_solve<float>(c, pq, 1, rhs, wpr, cpr, P2M_START_FLIP, op, pr,
-                             choose(c, m, P2M_F32, 1));
+                             diagonal(choose(c, m, P2M_F32, 1)));
         if (s != P2M_OK) return s;
     }
     // 4. projection U^{n+1} = U* - dt M_L^-1 G p

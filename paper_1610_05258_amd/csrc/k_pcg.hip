@@ -63,6 +63,8 @@ using TileS = PTile<32, 32, 1024, 5>;
 using TileD = PTile<32, 32, 512, 3>;    // FP64 only (pcg_depth)
 using TileL = PTile<64, 64, 1024, 3>;
 
+constexpr int kStall = 40;
+
 template <typename T>
 struct PArgs {
     PolyInst one;          // the problem of a single solve
@@ -171,6 +173,9 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
     __shared__ double s_bb[MAXP], s_gam[MAXP], s_alpha[MAXP], s_relres[MAXP], s_target[MAXP];
     __shared__ T s_af[MAXP], s_bf[MAXP];
     __shared__ int s_iters[MAXP], s_refines[MAXP];
+    __shared__ float s_best[MAXP];          // smallest (r,r) of the inner solve, and the
+    __shared__ short s_since[MAXP];         // iterations since
+    __shared__ unsigned char s_diag[MAXP];  // the polynomial has stalled: p(A) = 1 from here on
     __shared__ unsigned char s_done[MAXP], s_inner[MAXP], s_zero[MAXP];
     // x is held in x64 / xring (else it is the start, formed from b and w where needed);
     // the last inner solve went for the goal, so its residual is expected to be the last
@@ -421,7 +426,7 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
     };
 
     for (int p = tid; p < a.nprob * F; p += NT) {
-        s_iters[p] = 0; s_refines[p] = 0; s_done[p] = 0; s_inner[p] = 0; s_zero[p] = 0;
+        s_iters[p] = 0; s_refines[p] = 0; s_done[p] = 0; s_inner[p] = 0; s_zero[p] = 0; s_diag[p] = 0;
         s_held[p] = a.start == P2M_START_USER; s_last[p] = 0;
         s_relres[p] = 0.0; s_bb[p] = 0.0;
     }
@@ -801,13 +806,15 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                 s_held[p] |= outer > 0 ? (s_last[p] ? 2 : 1) : 0;
                 s_last[p] = direct;
                 s_inner[p] = 1;
+                s_best[p] = 3.0e38f;
+                s_since[p] = 0;
                 more |= s_held[p] & 2 ? 3 : 1;
             }
         }
-        more = __syncthreads_or(more);
-        if (!more) break;
+        const int left_out = __syncthreads_or(more & 2);   // (its result is 0 or 1)
+        if (!__syncthreads_or(more)) break;
         // x += d where the residual phase left it out and the solve goes on after all
-        if (more & 2) {
+        if (left_out) {
             for (int i = g; i < a.ntiles; i += G) {
                 if (!keep) set_tile(i);
                 const int g0 = fresh(o_g0), rg = fresh(o_rg);
@@ -892,6 +899,11 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                 }
                 // u = p(A) r by Horner's rule (PH is odd: u ends in bA), w = A u
                 static_assert(PH % 2 == 1, "u in bA");
+                uint32_t dm = 0;   // fields whose polynomial is 1
+#pragma unroll
+                for (int f = 0; f < F; ++f)
+                    if (s_diag[k * F + f]) dm |= 1u << f;
+                dm = __builtin_amdgcn_readfirstlane(dm);
                 T qo[F][OWN], qn[F];
                 put(bA, im, vr, rdep != 0, nr);
                 __syncthreads();
@@ -899,15 +911,16 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                 for (int j = 1; j < PH; ++j) {
                     const bool rn = rdep >= 1 && rdep <= PH - j;
                     apply(j & 1 ? bA : bB, im, rn, qo, qn);
-                    const T cj = pc[PH - 1 - j];
 #pragma unroll
                     for (int f = 0; f < F; ++f) {
                         if (!(im & (1u << f))) continue;
+                        const bool one = dm & (1u << f);
+                        const T cj = one ? (T)(j == PH - 1) : pc[PH - 1 - j], ct = one ? (T)0 : pc[PH - 1];
 #pragma unroll
                         for (int o = 0; o < OWN; ++o)
-                            qo[f][o] = j == 1 ? fma_t(pc[PH - 1], qo[f][o], mul_t(cj, vr[f][o]))
+                            qo[f][o] = j == 1 ? fma_t(ct, qo[f][o], mul_t(cj, vr[f][o]))
                                               : fma_t(cj, vr[f][o], qo[f][o]);
-                        qn[f] = j == 1 ? fma_t(pc[PH - 1], qn[f], mul_t(cj, nr[f])) : fma_t(cj, nr[f], qn[f]);
+                        qn[f] = j == 1 ? fma_t(ct, qn[f], mul_t(cj, nr[f])) : fma_t(cj, nr[f], qn[f]);
                     }
                     if (!PP) __syncthreads();
                     put(j & 1 ? bB : bA, im, qo, rn, qn);
@@ -979,6 +992,21 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                 double beta = 0.0;
                 if (it > 0) {
                     s_iters[p] += 1;
+                    // An ill-conditioned system's recurrence can stall above its target and
+                    // then run away from the true residual.  When kStall iterations brought
+                    // nothing, or the residual has grown by 10, it starts again from the true
+                    // one, with the diagonal alone, whose rounding such systems bear.
+                    // (As a ratio to the target: (r,r) itself may leave FP32's range.)
+                    const float at = (float)(rho / s_target[p]);
+                    if (at < s_best[p]) {
+                        s_best[p] = at;
+                        s_since[p] = 0;
+                    } else if (!s_diag[p] && (++s_since[p] >= kStall ||
+                                              (s_since[p] >= 8 && at > 100.f * s_best[p]))) {
+                        s_diag[p] = 1;
+                        s_inner[p] = 0;
+                        continue;
+                    }
                     if (!(rho > s_target[p]) || s_iters[p] >= a.opts.maxit) {
                         s_inner[p] = 0;
                         continue;
