@@ -797,7 +797,9 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
             } else {
                 // a goal within a thirtieth of the inner reduction is gone for at once:
                 // a residual phase costs more than the last iteration it would save
-                const double goal = 0.25 * a.opts.tol * a.opts.tol * bb;
+                // (FP64: half of that again, as its answer's error is the residual's: a step of
+                // five products may pass the goal only just)
+                const double goal = (sizeof(T) == 8 ? 0.0625 : 0.25) * a.opts.tol * a.opts.tol * bb;
                 const double rel = a.opts.inner_rtol * a.opts.inner_rtol * rr;
                 const bool direct = goal * 900.0 >= rel;
                 // the inner solve measures its residual in the scaled norm
