@@ -348,9 +348,9 @@ bool poly_solve_for(const Context* c, const Mesh& m, int F, const Layout& L, Pol
         pcg_interval(m, depth, I.pc);
         ps.cols = pcg_column_elems(m, depth, I.ptx);
         ps.grid = pcg_grid((int)sizeof(T), ps.small, depth, false, F, I.npt, c->device);
-        if (ps.grid >= 1 && (sizeof(T) == 4 || ps.grid >= ps.ntiles) &&
+        if (ps.grid.groups >= 1 &&
             pcg_workspace_bytes((int)sizeof(T), ps.small, depth, F, 1, ps.ntiles, ps.nodes, ps.cols,
-                                ps.grid) <= poly_area(L, sizeof(T)).bytes)
+                                ps.grid.stream) <= poly_area(L, sizeof(T)).bytes)
             return true;
         if (depth == 3) return false;
     }
@@ -478,7 +478,7 @@ struct BatchPlan {
     struct Poly {
         std::vector<PolyInst> inst;
         std::vector<int32_t> rmap, order;
-        int grid = 0;
+        SolveGrid grid{0, false};
         size_t cols = 0;                              // column-buffer elements per field
         size_t inst_o = 0, rmap_o = 0, order_o = 0;   // offsets in the uploaded head
     } poly[2];
@@ -612,7 +612,7 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
                 for (int t = 0; t < Q.inst[at[k]].npt; ++t) Q.order.push_back(Q.inst[at[k]].pt + t);
         if (!Q.rmap.empty()) {
             Q.grid = pcg_grid(4, cls == 0, depth, true, F, (int)Q.rmap.size(), c->device);
-            if (Q.grid < 1) return P2M_ERR_UNSUPPORTED;
+            if (Q.grid.groups < 1) return P2M_ERR_UNSUPPORTED;
         }
     }
     P.grid = cgb_grid(F, P.nrt, c->device);
@@ -638,7 +638,7 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
         Q.order_o = take(sizeof(int32_t) * Q.order.size());
         const bool small = cls == 0;
         const size_t n = pcg_workspace_bytes(4, small, pcg_depth(4, small, F), F, (int)Q.inst.size(),
-                                             (int)Q.rmap.size(), (size_t)nn, Q.cols, Q.grid);
+                                             (int)Q.rmap.size(), (size_t)nn, Q.cols, Q.grid.stream);
         if (n > poly_b) poly_b = n;
     }
     P.head = off;

@@ -1212,20 +1212,19 @@ int resident_groups(const void* fn, int nt, int device) {
 }
 
 template <typename T>
-int grid_of(bool small, int depth, bool batch, int F, int ntiles, int device) {
+SolveGrid grid_of(bool small, int depth, bool batch, int F, int ntiles, int device) {
     const int nt = tile_of(small, depth).nt;
     const int held = resident_groups(pcg_pick<T>(small, depth, batch, false, F), nt, device);
-    if (ntiles <= held) return ntiles;
-    return resident_groups(pcg_pick<T>(small, depth, batch, true, F), nt, device);
+    if (ntiles <= held) return solve_grid(held, 0, ntiles);
+    return solve_grid(held, resident_groups(pcg_pick<T>(small, depth, batch, true, F), nt, device), ntiles);
 }
 
 }  // namespace
 
-int pcg_grid(int tsize, bool small, int depth, bool batch, int F, int ntiles, int device) {
-    if (F < 1 || F > kResidentMaxFields || ntiles < 1) return 0;
-    const int g = tsize == 8 ? grid_of<double>(small, depth, batch, F, ntiles, device)
-                             : grid_of<float>(small, depth, batch, F, ntiles, device);
-    return g < ntiles ? g : ntiles;
+SolveGrid pcg_grid(int tsize, bool small, int depth, bool batch, int F, int ntiles, int device) {
+    if (F < 1 || F > kResidentMaxFields) return {0, false};
+    return tsize == 8 ? grid_of<double>(small, depth, batch, F, ntiles, device)
+                      : grid_of<float>(small, depth, batch, F, ntiles, device);
 }
 
 int pcg_sync_words() { return kSyncWords; }
@@ -1235,21 +1234,21 @@ size_t pcg_column_elems(const Mesh& m, int depth, int per_row) {
 }
 
 size_t pcg_workspace_bytes(int tsize, bool small, int depth, int F, int nprob, int ntiles,
-                           size_t nodes, size_t cols, int grid) {
+                           size_t nodes, size_t cols, bool stream) {
     const TileInfo t = tile_of(small, depth);
     size_t s = al(kSyncWords * sizeof(unsigned)) + al((size_t)2 * 3 * F * ntiles * sizeof(double)) +
                al((size_t)2 * 3 * F * nprob * sizeof(double)) + al((size_t)F * nodes * sizeof(double)) +
                3 * al((size_t)F * nodes * tsize) + 3 * al((size_t)F * cols * tsize) +
                al((size_t)ntiles * F * t.nrp * sizeof(double));
-    if (ntiles > grid) s += stream_bytes(tsize, t, F, ntiles);
+    if (stream) s += stream_bytes(tsize, t, F, ntiles);
     return s;
 }
 
 template <typename T>
 hipError_t launch_pcg(const PolySolve<T>& ps, int start, const p2m_solve_opts& opts, hipStream_t stream) {
     const bool batch = ps.inst != nullptr;
-    const void* fn = pcg_pick<T>(ps.small, ps.depth, batch, ps.ntiles > ps.grid, ps.F);
-    if (!fn || ps.grid < 1 || ps.nprob < 1 || (batch && ps.nprob * ps.F > kBatchMaxPairs))
+    const void* fn = pcg_pick<T>(ps.small, ps.depth, batch, ps.grid.stream, ps.F);
+    if (!fn || ps.grid.groups < 1 || ps.nprob < 1 || (batch && ps.nprob * ps.F > kBatchMaxPairs))
         return hipErrorInvalidValue;
     const int F = ps.F;
     const TileInfo t = tile_of(ps.small, ps.depth);
@@ -1288,7 +1287,7 @@ hipError_t launch_pcg(const PolySolve<T>& ps, int start, const p2m_solve_opts& o
     a.colW[0] = (T*)take((size_t)F * ps.cols * sizeof(T));
     a.colW[1] = (T*)take((size_t)F * ps.cols * sizeof(T));
     a.xring = (double*)take((size_t)ps.ntiles * F * t.nrp * sizeof(double));
-    if (ps.ntiles > ps.grid) {
+    if (ps.grid.stream) {
         const size_t n = (size_t)ps.ntiles;
         a.own = (T*)take(n * 6 * F * t.own * sizeof(T));
         a.ring = (T*)take(n * 5 * F * t.nrp * sizeof(T));
@@ -1304,7 +1303,7 @@ hipError_t launch_pcg(const PolySolve<T>& ps, int start, const p2m_solve_opts& o
     // at most what the device holds at once (pcg_grid), so all its workgroups are
     // resident; the barrier is the kernel's own and every wait in it is bounded.
     void* args[] = {&a};
-    return hipLaunchKernel(fn, dim3(ps.grid), dim3(t.nt), args, 0, stream);
+    return hipLaunchKernel(fn, dim3(ps.grid.groups), dim3(t.nt), args, 0, stream);
 }
 template hipError_t launch_pcg<float>(const PolySolve<float>&, int, const p2m_solve_opts&, hipStream_t);
 template hipError_t launch_pcg<double>(const PolySolve<double>&, int, const p2m_solve_opts&, hipStream_t);

@@ -30,6 +30,21 @@ struct Mesh {
 p2m_status check_problem(const p2m_problem* p, Mesh& m);
 p2m_status check_opts(const p2m_solve_opts* opts);
 
+// Launch of a solve whose grid barriers need every workgroup resident: the kernel that
+// keeps one tile per workgroup, held of which fit the device at once, while that takes all
+// tiles; else the one that streams several, on as many of its workgroups as fit.  A grid
+// larger than its own kernel's count would wait for workgroups that cannot start, so the
+// kernel and its grid are chosen together.  groups 0: neither can run.
+struct SolveGrid {
+    int groups;
+    bool stream;
+};
+inline SolveGrid solve_grid(int held, int held_stream, int ntiles) {
+    if (ntiles < 1) return {0, false};
+    if (ntiles <= held) return {ntiles, false};
+    return {held_stream < ntiles ? (held_stream > 0 ? held_stream : 0) : ntiles, true};
+}
+
 // Plan file: a JSON object, one plan per line,
 //   "key": {"solver": S, "groups": G, "scatter_tile": T, "inner_rtol": R, "time_ms": M}
 // A line without a quote is skipped (the braces); a plan line with a key longer

@@ -374,19 +374,20 @@ int pcg_tiles(const Mesh& m, bool small, int* per_row);
 // problem's particles per node
 int pcg_depth(int tsize, bool small, int F);
 void pcg_interval(const Mesh& m, int depth, double pc[5]);
-int pcg_grid(int tsize, bool small, int depth, bool batch, int F, int ntiles,
-             int device);   // 0: not available
+// the kernel (resident or streamed) and its grid; groups 0: not available
+SolveGrid pcg_grid(int tsize, bool small, int depth, bool batch, int F, int ntiles, int device);
 // elements per field of a problem's column buffer
 size_t pcg_column_elems(const Mesh& m, int depth, int per_row);
 size_t pcg_workspace_bytes(int tsize, bool small, int depth, int F, int nprob, int ntiles,
-                           size_t nodes, size_t cols, int grid);
+                           size_t nodes, size_t cols, bool stream);
 template <typename T>
 struct PolySolve {
     PolyInst one{};                    // a single problem, or
     const PolyInst* inst = nullptr;    // the instances of a batch with their tile maps
     const int32_t* rmap = nullptr;     // tile -> instance
     const int32_t* order = nullptr;    // dealing order of the tiles
-    int nprob = 1, F = 1, ntiles = 0, grid = 0;
+    int nprob = 1, F = 1, ntiles = 0;
+    SolveGrid grid{0, false};          // pcg_grid
     bool small = true;                 // 32 x 32 tiles (pcg_small)
     int depth = 5;                     // pcg_depth
     size_t nodes = 0, cols = 0;        // of all instances
