@@ -141,7 +141,8 @@ p2m_status p2m_destroy(void* ctx);
 /* Mass-solve kernels.  Every one solves the same system to the same tolerance;
  * their rounding differs, except that RESIDENT and TILES give identical bits (the
  * same per-tile arithmetic and reduction order), and so do AUTO and RESIDENT_CHEB.
- *   P2M_SOLVER_AUTO       RESIDENT_CHEB where it applies, else the streaming kernel
+ *   P2M_SOLVER_AUTO       RESIDENT_CHEB where it applies, else RESIDENT (2D FP32,
+ *                         F <= 3), else the streaming kernel
  *                         (1D from the FLIP start: by cyclic reduction, and the
  *                         iteration only for what its residual leaves); a tuned plan of the problem's shape class (p2m_tune)
  *                         overrides this choice
@@ -156,7 +157,9 @@ p2m_status p2m_destroy(void* ctx);
  *                         of the diagonal one (D = diag M): the same system and
  *                         tolerance in a third of the iterations, one grid barrier
  *                         each (2D, F <= 3; FP32 meshes of any size up to 2^27 nodes,
- *                         resident or streamed; FP64 where every 32 x 32 node tile
+ *                         resident or streamed, but for strips of more than 256 of its
+ *                         64 x 64 node tiles that RESIDENT's tiles or its own workspace
+ *                         leave it out of; FP64 where every 32 x 32 node tile
  *                         fits the device at once); where it does not apply, as AUTO */
 enum { P2M_SOLVER_AUTO = 0, P2M_SOLVER_STREAMING = 1, P2M_SOLVER_RESIDENT = 2, P2M_SOLVER_TILES = 3,
        P2M_SOLVER_RESIDENT_CHEB = 4 };

@@ -330,7 +330,12 @@ PolyArea poly_area(const Layout& L, size_t tsize) {
 
 // The polynomial-preconditioned solve of this problem, if it applies: 2D, F <= 3, and
 // in FP64 only where every tile is resident (the streamed state has no FP64 form).
-// False: another kernel has to take it.
+// False: another kernel has to take it.  A batch asks for each of its instances, so that
+// single and batched calls take the same solve.
+// FP32 strips are left to the diagonal solve: the square tiles are mostly empty there.
+// Where its 128 x 32 tiles are resident and the 64 x 64 ones would be streamed (sides of up
+// to about 32), it is the faster one (16500 x 2, F = 1, 237 us; 20000 x 16, F = 2, 337 us
+// against 565 streamed); longer strips of a few nodes do not fit the tile solvers' workspace.
 template <typename T>
 bool poly_solve_for(const Context* c, const Mesh& m, int F, const Layout& L, PolySolve<T>& ps) {
     if (m.dim != 2 || F > kResidentMaxFields || m.nn > kPolyMaxNodes) return false;
@@ -348,6 +353,7 @@ bool poly_solve_for(const Context* c, const Mesh& m, int F, const Layout& L, Pol
         pcg_interval(m, depth, I.pc);
         ps.cols = pcg_column_elems(m, depth, I.ptx);
         ps.grid = pcg_grid((int)sizeof(T), ps.small, depth, false, F, I.npt, c->device);
+        if (sizeof(T) == 4 && ps.grid.stream && cgr_supported(m, F, c->device)) return false;
         if (ps.grid.groups >= 1 &&
             pcg_workspace_bytes((int)sizeof(T), ps.small, depth, F, 1, ps.ntiles, ps.nodes, ps.cols,
                                 ps.grid.stream) <= poly_area(L, sizeof(T)).bytes)
@@ -361,10 +367,10 @@ bool takes_poly(const Choice& ch) {
 }
 
 // Solve kernel: the choice's kernel where it applies.  AUTO and RESIDENT_CHEB take the
-// polynomial-preconditioned solve (2D, F <= 3), RESIDENT the register-resident one
-// with the diagonal preconditioner, RESIDENT beyond it and TILES the tile-streaming
-// one, and everything else the grid-synchronised streaming kernel (1D, F > 3, large
-// FP64 meshes).
+// polynomial-preconditioned solve (2D, F <= 3), what they leave of FP32 and RESIDENT the
+// register-resident one with the diagonal preconditioner, beyond its size and TILES the
+// tile-streaming one, and everything else the grid-synchronised streaming kernel (1D,
+// F > 3, large FP64 meshes).
 // known: the polynomial-preconditioned solve, where the caller has looked it up already.
 template <typename T>
 p2m_status run_solve(const Context* c, const Prepared& pp, int F, T* b, const T* w, T* coef,
@@ -392,7 +398,7 @@ p2m_status run_solve(const Context* c, const Prepared& pp, int F, T* b, const T*
         pp.clear_rep = false;
         return P2M_OK;
     }
-    if (tiled && kind == P2M_SOLVER_RESIDENT && cgr_supported(pp.m, F, c->device)) {
+    if (tiled && (kind == P2M_SOLVER_RESIDENT || takes_poly(ch)) && cgr_supported(pp.m, F, c->device)) {
         P2M_TRY(launch_cg_resident(pp.m, F, (float*)coef, (float*)b, (const float*)w, (float*)x,
                                    start, pp.ws + pp.L.resident, opts, pp.rep, pp.clear_rep,
                                    pp.solve_spin, pp.stream));
@@ -468,13 +474,20 @@ p2m_status run_mass(const Context* c, const Prepared& pp, const p2m_problem* pro
 struct BatchPlan {
     int nprob = 0, F = 0;
     int64_t np = 0, nn = 0;              // particles and nodes of the whole batch
-    int nlb = 0, nat = 0, nrt = 0;       // locate blocks, scatter tiles, solver tiles
-    int grid = 0;                        // workgroups of the batched solve
+    int nlb = 0, nat = 0;                // locate blocks, scatter tiles
     std::vector<BatchInst> inst;
-    std::vector<int32_t> lmap, amap, rmap, omap;
-    size_t inst_b = 0, lmap_b = 0, amap_b = 0, rmap_b = 0, omap_b = 0;   // upload sections
-    // the polynomial-preconditioned solve: the instances with small and with large
-    // tiles are two launches, each with its own tables
+    std::vector<int32_t> lmap, amap;
+    size_t inst_b = 0, lmap_b = 0, amap_b = 0;   // upload sections
+    // the diagonally preconditioned solve (k_cgb): every instance where that was asked for,
+    // else those whose own single call takes it (poly_solve_for)
+    struct Diag {
+        std::vector<BatchInst> inst;
+        std::vector<int32_t> rmap, order;
+        int grid = 0;
+        size_t inst_o = 0, rmap_o = 0, order_o = 0;   // offsets in the uploaded head
+    } diag;
+    // the polynomial-preconditioned solve: the other instances, those with small and those
+    // with large tiles in two launches, each with its own tables
     struct Poly {
         std::vector<PolyInst> inst;
         std::vector<int32_t> rmap, order;
@@ -528,7 +541,6 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
         I.lb = (int32_t)nlb;
         I.at = (int32_t)nat;
         I.atx = atx;
-        I.rt = (int32_t)nrt;
         I.rtx = rtx;
         I.nrt = rtx * rty;
         np += m.np;
@@ -544,17 +556,17 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
     P.nn = nn;
     P.nlb = (int)nlb;
     P.nat = (int)nat;
-    P.nrt = (int)nrt;
+    // the diagonal solve of the whole batch has to fit whichever solve runs: the option
+    // may change between the size query and the call
+    if (nrt >= ((int64_t)1 << 31) - 1 || cgb_grid(F, (int)nrt, c->device) < 1) return P2M_ERR_UNSUPPORTED;
     P.lmap.resize(P.nlb);
     P.amap.resize(P.nat);
-    P.rmap.resize(P.nrt);
     for (int k = 0; k < nprob; ++k) {
         const BatchInst& I = P.inst[k];
         const int lbk = (I.m.np + kBinBlock - 1) / kBinBlock;
         const int ts2 = (I.m.ny + ts - 1) / ts;
         for (int b = 0; b < lbk; ++b) P.lmap[I.lb + b] = k;
         for (int t = 0; t < I.atx * ts2; ++t) P.amap[I.at + t] = k;
-        for (int t = 0; t < I.nrt; ++t) P.rmap[I.rt + t] = k;
     }
     // Dealing order of the solver tiles (workgroup g owns the tiles at positions
     // g, g + grid, ...): instances with fewer particles per node first (they need
@@ -577,20 +589,37 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
                 ord[j] = ord[j - 1];
                 ord[j - 1] = t;
             }
-        P.omap.clear();
-        P.omap.reserve(P.nrt);
-        for (int k : ord)
-            for (int t = 0; t < P.inst[k].nrt; ++t) P.omap.push_back(P.inst[k].rt + t);
     }
     P.jacobi = c->solver_mode == P2M_SOLVER_RESIDENT || c->solver_mode == P2M_SOLVER_TILES;
-    for (const BatchInst& I : P.inst) P.jacobi = P.jacobi || I.m.nn > kPolyMaxNodes;
+    std::vector<char> poly(nprob, 0);   // which solve the instance's own call takes
+    for (int k = 0; k < nprob; ++k) {
+        const Mesh& m = P.inst[k].m;
+        PolySolve<float> ps;
+        poly[k] = poly_solve_for<float>(c, m, F, make_layout(m, F, 4, cg_blocks_for(c, m, P2M_F32)), ps);
+    }
+    {
+        BatchPlan::Diag& D = P.diag;
+        std::vector<int> at(nprob, -1);
+        for (int k = 0; k < nprob; ++k) {
+            if (poly[k] && !P.jacobi) continue;
+            BatchInst I = P.inst[k];
+            I.rt = (int32_t)D.rmap.size();
+            at[k] = (int)D.inst.size();
+            D.rmap.insert(D.rmap.end(), I.nrt, at[k]);
+            D.inst.push_back(I);
+        }
+        for (int k : ord)
+            if (at[k] >= 0)
+                for (int t = 0; t < P.inst[k].nrt; ++t) D.order.push_back(D.inst[at[k]].rt + t);
+        if (!D.rmap.empty()) D.grid = cgb_grid(F, (int)D.rmap.size(), c->device);
+    }
     for (int cls = 0; cls < 2; ++cls) {
         BatchPlan::Poly& Q = P.poly[cls];
         const int depth = pcg_depth(4, cls == 0, F);
         std::vector<int> at(nprob, -1);
         for (int k = 0; k < nprob; ++k) {
             const Mesh& m = P.inst[k].m;
-            if (pcg_small(m) != (cls == 0)) continue;
+            if (!poly[k] || pcg_small(m) != (cls == 0)) continue;
             PolyInst I;
             memset(&I, 0, sizeof(I));
             I.m = m;
@@ -600,9 +629,8 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
             I.pt = (int32_t)Q.rmap.size();
             I.npt = pcg_tiles(m, cls == 0, &I.ptx);
             pcg_interval(m, depth, I.pc);
-            I.co = (int32_t)Q.cols;
+            I.co = (int32_t)Q.cols;   // (cgb_grid bounds the batch's tiles, so its columns too)
             Q.cols += pcg_column_elems(m, depth, I.ptx);
-            if (Q.cols * F >= ((size_t)1 << 31)) return P2M_ERR_UNSUPPORTED;
             at[k] = (int)Q.inst.size();
             Q.rmap.insert(Q.rmap.end(), I.npt, at[k]);
             Q.inst.push_back(I);
@@ -615,8 +643,6 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
             if (Q.grid.groups < 1) return P2M_ERR_UNSUPPORTED;
         }
     }
-    P.grid = cgb_grid(F, P.nrt, c->device);
-    if (P.grid < 1) return P2M_ERR_UNSUPPORTED;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         size_t o = off;
@@ -626,9 +652,10 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
     P.inst_b = align_up(sizeof(BatchInst) * nprob);
     P.lmap_b = align_up(sizeof(int32_t) * P.nlb);
     P.amap_b = align_up(sizeof(int32_t) * P.nat);
-    P.rmap_b = align_up(sizeof(int32_t) * P.nrt);
-    P.omap_b = align_up(sizeof(int32_t) * P.nrt);
-    take(P.inst_b + P.lmap_b + P.amap_b + P.rmap_b + P.omap_b);
+    take(P.inst_b + P.lmap_b + P.amap_b);
+    P.diag.inst_o = take(sizeof(BatchInst) * nprob);
+    P.diag.rmap_o = take(sizeof(int32_t) * (size_t)nrt);
+    P.diag.order_o = take(sizeof(int32_t) * (size_t)nrt);
     size_t poly_b = 0;
     for (int cls = 0; cls < 2; ++cls) {
         BatchPlan::Poly& Q = P.poly[cls];
@@ -650,8 +677,8 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
     P.o_b = take(sizeof(float) * (size_t)F * nn);
     P.o_w = take(sizeof(float) * (size_t)nn);
     P.o_coef = take(sizeof(float) * (size_t)4 * nn);
-    const size_t cgb_b = cgb_workspace_bytes(F, nprob, P.nrt, (size_t)nn);
-    P.o_solve = take(cgb_b > poly_b ? cgb_b : poly_b);   // either solve, and both tile classes in turn
+    const size_t cgb_b = cgb_workspace_bytes(F, nprob, (int)nrt, (size_t)nn);
+    P.o_solve = take(cgb_b > poly_b ? cgb_b : poly_b);   // the solves take it in turn
     P.total = off;
     return P2M_OK;
 }
@@ -662,8 +689,6 @@ hipError_t enqueue_batch(const BatchPlan& P, char* ws, p2m_report* reps, const p
     const BatchInst* inst = (const BatchInst*)ws;
     const int32_t* lmap = (const int32_t*)(ws + P.inst_b);
     const int32_t* amap = (const int32_t*)(ws + P.inst_b + P.lmap_b);
-    const int32_t* rmap = (const int32_t*)(ws + P.inst_b + P.lmap_b + P.amap_b);
-    const int32_t* omap = (const int32_t*)(ws + P.inst_b + P.lmap_b + P.amap_b + P.rmap_b);
     int32_t* key = (int32_t*)(ws + P.o_key);
     int32_t* counts = (int32_t*)(ws + P.o_counts);
     int32_t* cs = (int32_t*)(ws + P.o_cs);
@@ -711,20 +736,20 @@ hipError_t enqueue_batch(const BatchPlan& P, char* ws, p2m_report* reps, const p
             ps.spin = solve_spin;
             if ((e = launch_pcg<float>(ps, opts.start, opts, stream)) != hipSuccess) return e;
         }
-        return hipSuccess;
     }
+    if (P.diag.rmap.empty()) return hipSuccess;
     BatchSolveBufs bb;
-    bb.inst = inst;
-    bb.nprob = P.nprob;
-    bb.rmap = rmap;
-    bb.order = omap;
-    bb.ntiles = P.nrt;
+    bb.inst = (const BatchInst*)(ws + P.diag.inst_o);
+    bb.nprob = (int)P.diag.inst.size();
+    bb.rmap = (const int32_t*)(ws + P.diag.rmap_o);
+    bb.order = (const int32_t*)(ws + P.diag.order_o);
+    bb.ntiles = (int)P.diag.rmap.size();
     bb.coef = coef;
     bb.b = b;
     bb.w = w;
     bb.ws = ws + P.o_solve;
     bb.spin = solve_spin;
-    return launch_cg_batch(P.F, bb, (size_t)P.nn, P.grid, opts.start, opts, stream);
+    return launch_cg_batch(P.F, bb, (size_t)P.nn, P.diag.grid, opts.start, opts, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -1872,9 +1897,9 @@ p2m_status p2m_mass_assign_batched(void* ctx, const p2m_problem* probs, int32_t 
         memcpy(u, P.inst.data(), sizeof(BatchInst) * P.nprob);
         memcpy(u + P.inst_b, P.lmap.data(), sizeof(int32_t) * P.nlb);
         memcpy(u + P.inst_b + P.lmap_b, P.amap.data(), sizeof(int32_t) * P.nat);
-        memcpy(u + P.inst_b + P.lmap_b + P.amap_b, P.rmap.data(), sizeof(int32_t) * P.nrt);
-        memcpy(u + P.inst_b + P.lmap_b + P.amap_b + P.rmap_b, P.omap.data(),
-               sizeof(int32_t) * P.nrt);
+        memcpy(u + P.diag.inst_o, P.diag.inst.data(), sizeof(BatchInst) * P.diag.inst.size());
+        memcpy(u + P.diag.rmap_o, P.diag.rmap.data(), sizeof(int32_t) * P.diag.rmap.size());
+        memcpy(u + P.diag.order_o, P.diag.order.data(), sizeof(int32_t) * P.diag.order.size());
         for (const BatchPlan::Poly& Q : P.poly) {
             if (Q.rmap.empty()) continue;
             memcpy(u + Q.inst_o, Q.inst.data(), sizeof(PolyInst) * Q.inst.size());

@@ -41,6 +41,8 @@
 // (node-major columns cost 3 us of it), and no register spilled inside the loop.
 #include <string.h>
 
+#include <atomic>
+
 #include "cg_common.hpp"
 
 namespace p2m {
@@ -1201,22 +1203,35 @@ void pcg_interval(const Mesh& m, int depth, double pc[5]) {
 
 namespace {
 
-// workgroups of this kernel the device holds at once, at most two per compute unit
-int resident_groups(const void* fn, int nt, int device) {
+// Workgroups of a kernel the device holds at once, at most two per compute unit.  Kept per
+// device and kernel after the first query (a batch asks once per instance).
+constexpr int kMaxDevices = 16;
+int resident_groups(const void* fn, int nt, int device, std::atomic<int>* known) {
+    if (!fn) return 0;
+    if (known) {
+        const int v = known->load(std::memory_order_relaxed);
+        if (v > 0) return v;
+    }
     int cus = 0, per = 0;
-    if (!fn ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
+    if (        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, nt, 0) != hipSuccess || per < 1)
         return 0;
-    return (per > 2 ? 2 : per) * cus;
+    const int v = (per > 2 ? 2 : per) * cus;
+    if (known) known->store(v, std::memory_order_relaxed);
+    return v;
 }
 
 template <typename T>
 SolveGrid grid_of(bool small, int depth, bool batch, int F, int ntiles, int device) {
+    static std::atomic<int> known[kMaxDevices][2][2][2][2][kResidentMaxFields + 1];
     const int nt = tile_of(small, depth).nt;
-    const int held = resident_groups(pcg_pick<T>(small, depth, batch, false, F), nt, device);
-    if (ntiles <= held) return solve_grid(held, 0, ntiles);
-    return solve_grid(held, resident_groups(pcg_pick<T>(small, depth, batch, true, F), nt, device), ntiles);
+    auto held = [&](bool stream) {
+        std::atomic<int>* k = device >= 0 && device < kMaxDevices
+                                  ? &known[device][small][depth == 5][batch][stream][F] : nullptr;
+        return resident_groups(pcg_pick<T>(small, depth, batch, stream, F), nt, device, k);
+    };
+    const int h = held(false);
+    return solve_grid(h, ntiles <= h ? 0 : held(true), ntiles);
 }
 
 }  // namespace
