@@ -158,9 +158,11 @@ p2m_status p2m_destroy(void* ctx);
  *                         tolerance in a third of the iterations, one grid barrier
  *                         each (2D, F <= 3; FP32 meshes of any size up to 2^27 nodes,
  *                         resident or streamed, but for strips of more than 256 of its
- *                         64 x 64 node tiles that RESIDENT's tiles or its own workspace
- *                         leave it out of; FP64 where every 32 x 32 node tile
- *                         fits the device at once); where it does not apply, as AUTO */
+ *                         64 x 64 node tiles where RESIDENT has every tile resident or
+ *                         this solve needs a quarter more workspace than TILES; FP64
+ *                         where every 32 x 32 node tile fits the device at once; in
+ *                         either type not where its workspace would lift the problem over
+ *                         P2M_SCRATCH_BYTES); where it does not apply, as AUTO */
 enum { P2M_SOLVER_AUTO = 0, P2M_SOLVER_STREAMING = 1, P2M_SOLVER_RESIDENT = 2, P2M_SOLVER_TILES = 3,
        P2M_SOLVER_RESIDENT_CHEB = 4 };
 

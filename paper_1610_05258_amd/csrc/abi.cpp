@@ -105,13 +105,14 @@ void* scratch_address(int device) {
     return g_scratch_dev[device];
 }
 
-// Workspace carve-up.  Offsets are fixed functions of (problem, F, cg blocks).
+// Workspace carve-up.  Offsets are fixed functions of (problem, F, cg blocks, more); more:
+// bytes behind the solvers' areas for the polynomial solve (make_layout).
 struct Layout {
     size_t key, counts, cell_start, perm, scan, b, w, coef, r, p0, p1, q, dinv, x64, partials,
         resident, tiles, learned, report, total;
 };
 
-Layout make_layout(const Mesh& m, int F, size_t tsize, int cg_blocks) {
+Layout lay_out(const Mesh& m, int F, size_t tsize, int cg_blocks, size_t more) {
     Layout L;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -140,19 +141,100 @@ Layout make_layout(const Mesh& m, int F, size_t tsize, int cg_blocks) {
                           ? cgr_workspace_bytes(m, F, cgr_tiles(m)) : 0);
     L.tiles = take((m.dim == 2 && F <= kResidentMaxFields && tsize == 4) ? cgt_workspace_bytes(m, F)
                                                                          : 0);
+    take(more);
     L.learned = take((m.dim == 2 && tsize == 4) ? learned_start_workspace_bytes(m, F) : 0);
     L.report = take(sizeof(p2m_report));
     L.total = off;
     return L;
 }
 
-inline size_t tsize_of(const p2m_problem* p) { return p->dtype == P2M_F64 ? 8 : 4; }
+// The polynomial-preconditioned solve of this problem, if it applies: 2D, F <= 3, and
+// in FP64 only where every tile is resident (the streamed state has no FP64 form).
+// False: another kernel has to take it.
+// FP32 meshes whose 64 x 64 tiles would be streamed while the diagonal solve's 128 x 32
+// tiles are resident (strips of up to about 32 rows) are left to that solve: the square
+// tiles are mostly empty there (20000 x 16, F = 2: 339 us against 564 streamed).
+template <typename T>
+bool poly_shape(const Context* c, const Mesh& m, int F, PolySolve<T>& ps) {
+    if (m.dim != 2 || F > kResidentMaxFields || m.nn > kPolyMaxNodes) return false;
+    ps.small = sizeof(T) == 8 || pcg_small(m);
+    PolyInst& I = ps.one;
+    I.m = m;
+    I.no = 0;
+    I.pt = 0;
+    I.npt = pcg_tiles(m, ps.small, &I.ptx);
+    ps.F = F;
+    ps.ntiles = I.npt;
+    ps.nodes = (size_t)m.nn;
+    const int first = pcg_depth((int)sizeof(T), ps.small, F);
+    ps.depth = first;
+    ps.grid = pcg_grid((int)sizeof(T), ps.small, first, false, F, I.npt, c->device);
+    if (sizeof(T) == 8 && first != 3 && ps.grid.groups < 1) {   // more tiles, on half the threads
+        ps.depth = 3;
+        ps.grid = pcg_grid((int)sizeof(T), ps.small, 3, false, F, I.npt, c->device);
+    }
+    if (ps.grid.groups < 1 || (sizeof(T) == 4 && ps.grid.stream && cgr_supported(m, F, c->device)))
+        return false;
+    pcg_interval(m, ps.depth, I.pc);
+    ps.cols = pcg_column_elems(m, ps.depth, I.ptx);
+    return true;
+}
+template <typename T>
+size_t poly_bytes(const PolySolve<T>& ps) {
+    return pcg_workspace_bytes((int)sizeof(T), ps.small, ps.depth, ps.F, 1, ps.ntiles, ps.nodes, ps.cols,
+                               ps.grid.stream);
+}
+
+// Workspace of the polynomial-preconditioned solve inside a problem's layout: FP32
+// problems use the areas of the two tile solvers, FP64 ones those of the streaming solve,
+// with what is added to either for it (adjacent).
+struct PolyArea {
+    size_t off, bytes;
+};
+PolyArea poly_area(const Layout& L, size_t tsize) {
+    const size_t at = tsize == 4 ? L.resident : L.r;
+    return PolyArea{at, L.learned - at};
+}
 
 int cg_blocks_for(const Context* c, const Mesh& m, int dtype) {
     int maxb = dtype == P2M_F64 ? c->cg_blocks_f64 : c->cg_blocks_f32;
     int need = (m.nn + 255) / 256;
     int b = need < maxb ? need : maxb;
     return b < 1 ? 1 : b;
+}
+
+// The layout of a problem.  The polynomial solve's state mostly fits the areas of the other
+// solves; where it does not (FP64 meshes of a few tiles or a few nodes across, FP32 strips
+// of up to 4 columns), it gets the rest, but for
+//  * FP32 strips that would need a quarter more than those areas and beyond (up to 3.3 times:
+//    two rows of 64 x 64 tiles), which take the diagonal solve;
+//  * problems that the added bytes would lift over the static scratch of
+//    p2m_mass_assign_noalloc: that entry point takes them as it did.
+Layout make_layout(const Context* c, const Mesh& m, int F, int dtype) {
+    const size_t tsize = dtype == P2M_F64 ? 8 : 4;
+    const int blocks = cg_blocks_for(c, m, dtype);
+    const Layout L = lay_out(m, F, tsize, blocks, 0);
+    if (m.dim != 2 || F > kResidentMaxFields) return L;
+    DeviceGuard g(c->device);   // the size queries do not make it current themselves
+    size_t need = 0;
+    if (tsize == 8) {
+        PolySolve<double> ps;
+        if (poly_shape<double>(c, m, F, ps)) need = poly_bytes(ps);
+    } else {
+        PolySolve<float> ps;
+        if (poly_shape<float>(c, m, F, ps)) need = poly_bytes(ps);
+    }
+    const size_t have = poly_area(L, tsize).bytes;
+    if (need <= have || (tsize == 4 && need > have + have / 4)) return L;
+    const Layout M = lay_out(m, F, tsize, blocks, need - have);
+    return L.total <= kScratchBytes && M.total > kScratchBytes ? L : M;
+}
+
+// poly_shape, where the layout holds its state.  A batch asks for each of its instances,
+// so that single and batched calls take the same solve.
+template <typename T>
+bool poly_solve_for(const Context* c, const Mesh& m, int F, const Layout& L, PolySolve<T>& ps) {
+    return poly_shape<T>(c, m, F, ps) && poly_bytes(ps) <= poly_area(L, sizeof(T)).bytes;
 }
 
 template <typename T>
@@ -250,7 +332,7 @@ p2m_status prepare(void* ctx, const p2m_problem* prob, int F, void* ws, size_t w
     p2m_status s = check_problem(prob, out.m);
     if (s != P2M_OK) return s;
     const Context* c = (const Context*)ctx;
-    out.L = make_layout(out.m, F, tsize_of(prob), cg_blocks_for(c, out.m, prob->dtype));
+    out.L = make_layout(c, out.m, F, prob->dtype);
     if (!ws || ws_bytes < out.L.total) return P2M_ERR_WORKSPACE;
     if (((uintptr_t)ws) % kAlign) return P2M_ERR_WORKSPACE;
     out.ws = (char*)ws;
@@ -316,50 +398,6 @@ p2m_status run_assemble(const Prepared& pp, const p2m_problem* prob, const void*
     P2M_TRY(launch_assemble<T>(pp.m, particles_of<T>(prob), (const T*)values, F, perm, cs, (T*)b,
                                (T*)w, (T*)coef, pp.stream, ch.tile));
     return P2M_OK;
-}
-
-// Workspace of the polynomial-preconditioned solve inside a problem's layout: FP32
-// problems use the areas of the two tile solvers (adjacent), FP64 ones those of the
-// streaming solve.
-struct PolyArea {
-    size_t off, bytes;
-};
-PolyArea poly_area(const Layout& L, size_t tsize) {
-    return tsize == 4 ? PolyArea{L.resident, L.learned - L.resident} : PolyArea{L.r, L.resident - L.r};
-}
-
-// The polynomial-preconditioned solve of this problem, if it applies: 2D, F <= 3, and
-// in FP64 only where every tile is resident (the streamed state has no FP64 form).
-// False: another kernel has to take it.  A batch asks for each of its instances, so that
-// single and batched calls take the same solve.
-// FP32 strips are left to the diagonal solve: the square tiles are mostly empty there.
-// Where its 128 x 32 tiles are resident and the 64 x 64 ones would be streamed (sides of up
-// to about 32), it is the faster one (16500 x 2, F = 1, 237 us; 20000 x 16, F = 2, 337 us
-// against 565 streamed); longer strips of a few nodes do not fit the tile solvers' workspace.
-template <typename T>
-bool poly_solve_for(const Context* c, const Mesh& m, int F, const Layout& L, PolySolve<T>& ps) {
-    if (m.dim != 2 || F > kResidentMaxFields || m.nn > kPolyMaxNodes) return false;
-    ps.small = sizeof(T) == 8 || pcg_small(m);
-    PolyInst& I = ps.one;
-    I.m = m;
-    I.no = 0;
-    I.pt = 0;
-    I.npt = pcg_tiles(m, ps.small, &I.ptx);
-    ps.F = F;
-    ps.ntiles = I.npt;
-    ps.nodes = (size_t)m.nn;
-    for (int depth = pcg_depth((int)sizeof(T), ps.small, F);; depth = 3) {
-        ps.depth = depth;
-        pcg_interval(m, depth, I.pc);
-        ps.cols = pcg_column_elems(m, depth, I.ptx);
-        ps.grid = pcg_grid((int)sizeof(T), ps.small, depth, false, F, I.npt, c->device);
-        if (sizeof(T) == 4 && ps.grid.stream && cgr_supported(m, F, c->device)) return false;
-        if (ps.grid.groups >= 1 &&
-            pcg_workspace_bytes((int)sizeof(T), ps.small, depth, F, 1, ps.ntiles, ps.nodes, ps.cols,
-                                ps.grid.stream) <= poly_area(L, sizeof(T)).bytes)
-            return true;
-        if (depth == 3) return false;
-    }
 }
 
 bool takes_poly(const Choice& ch) {
@@ -595,7 +633,7 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
     for (int k = 0; k < nprob; ++k) {
         const Mesh& m = P.inst[k].m;
         PolySolve<float> ps;
-        poly[k] = poly_solve_for<float>(c, m, F, make_layout(m, F, 4, cg_blocks_for(c, m, P2M_F32)), ps);
+        poly[k] = poly_solve_for<float>(c, m, F, make_layout(c, m, F, P2M_F32), ps);
     }
     {
         BatchPlan::Diag& D = P.diag;
@@ -1235,7 +1273,7 @@ p2m_status p2m_workspace_size(void* ctx, const p2m_problem* prob, int32_t nfield
     p2m_status s = check_problem(prob, m);
     if (s != P2M_OK) return s;
     const Context* c = (const Context*)ctx;
-    *bytes = make_layout(m, nfields, tsize_of(prob), cg_blocks_for(c, m, prob->dtype)).total;
+    *bytes = make_layout(c, m, nfields, prob->dtype).total;
     return P2M_OK;
 }
 
@@ -1389,7 +1427,7 @@ p2m_status p2m_ns_workspace_size(void* ctx, const p2m_problem* prob, size_t* byt
     p2m_status s = check_ns_problem(prob, m);
     if (s != P2M_OK) return s;
     const Context* c = (const Context*)ctx;
-    const Layout L = make_layout(m, 2, sizeof(float), cg_blocks_for(c, m, P2M_F32));
+    const Layout L = make_layout(c, m, 2, P2M_F32);
     *bytes = make_ns_layout(L.total, m).total;
     return P2M_OK;
 }

@@ -1163,8 +1163,8 @@ size_t stream_bytes(int tsize, const TileInfo& t, int F, int ntiles) {
 // 80 -> 65 us; 512 x 512 FP64, F = 1: 101 -> 85; two and three fields gain 0 to 2% of a
 // pass.  In FP64 two and three fields do not fit the 128 registers of 1024 threads (384 x
 // 384, F = 3: pass 224 us with three products on 512 threads, 255 with five); the ring of
-// five on the large tile is more slots than it has threads.  Where the wider ring does not
-// fit the workspace (FP64 strips a few nodes wide) the caller takes three.
+// five on the large tile is more slots than it has threads.  FP64 meshes of more tiles than
+// the device holds at 1024 threads each (256) take three, twice as many of which it holds.
 int pcg_depth(int tsize, bool small, int F) { return small && (tsize == 4 || F == 1) ? 5 : 3; }
 
 // Meshes of at most kPolyTiles small tiles (512 x 512) take the 32 x 32 tile, one per
