@@ -531,13 +531,13 @@ __device__ __forceinline__ int find_entry(const int32_t* __restrict__ lst, int d
 // lanes a particle, each its own neighbours (a lane alone waits for them one by one).
 __global__ void k_x2d_check(Geo g, const int32_t* __restrict__ deg, const int32_t* __restrict__ lst,
                             p2m_report* rep) {
-    const int t = blockIdx.x * kB + threadIdx.x;
-    const int k = t >> 2;
+    const size_t t = (size_t)blockIdx.x * kB + threadIdx.x;
+    const int k = (int)(t >> 2);
     if (k >= g.N) return;
     const int d = deg[k];   // 0: flagged by the star kernel
     const int32_t* lk = lst + (size_t)k * 2 * kCap;
     bool ok = true;
-    for (int i = t & 3; i < d && ok; i += 4) {
+    for (int i = (int)(t & 3); i < d && ok; i += 4) {
         const int a = lk[at_slot(i)], sa = lk[at_shift(i)];
         const int i1 = (i + 1 == d) ? 0 : i + 1;
         const int b = lk[at_slot(i1)], sb = lk[at_shift(i1)];
@@ -831,15 +831,17 @@ __global__ void k_x2d_mmesh(int nn, double cm, double* __restrict__ coef, double
 __global__ void k_x2d_export(Geo g, const int32_t* __restrict__ perm, const int32_t* __restrict__ deg,
                              const int32_t* __restrict__ lst, int32_t* __restrict__ deg_out,
                              int32_t* __restrict__ nbr_out, int32_t* __restrict__ sh_out) {
-    // a lane an entry: a particle's rows are written whole
-    const int t = blockIdx.x * kB + threadIdx.x;
-    const int k = t / kCap, i = t - k * kCap;
-    if (k >= g.N) return;
-    const int p = perm[k], d = deg[k];
-    if (i == 0) deg_out[p] = d;
-    const int32_t* lk = lst + (size_t)k * 2 * kCap;
-    nbr_out[(size_t)p * kCap + i] = i < d ? perm[lk[at_slot(i)]] : -1;
-    sh_out[(size_t)p * kCap + i] = i < d ? lk[at_shift(i)] : 0;
+    // a lane an entry: a particle's rows are written whole (entry numbers pass 2^31 from
+    // 67,108,864 particles on)
+    const size_t n = (size_t)g.N * kCap;
+    for (size_t t = (size_t)blockIdx.x * kB + threadIdx.x; t < n; t += (size_t)gridDim.x * kB) {
+        const int k = (int)(t / kCap), i = (int)(t % kCap);
+        const int p = perm[k], d = deg[k];
+        if (i == 0) deg_out[p] = d;
+        const int32_t* lk = lst + (size_t)k * 2 * kCap;
+        nbr_out[(size_t)p * kCap + i] = i < d ? perm[lk[at_slot(i)]] : -1;
+        sh_out[(size_t)p * kCap + i] = i < d ? lk[at_shift(i)] : 0;
+    }
 }
 
 __global__ void k_x2d_clear_export(int np, int32_t* __restrict__ deg_out,
@@ -922,8 +924,8 @@ hipError_t x2d_export(const X2dArgs& a, int32_t* deg_out, int32_t* nbr_out, int3
     }
     if (a.N == 0) return hipSuccess;
     const Geo g = geo_of(a.m, a.N, a.lx, a.ly);
-    if ((size_t)a.N * kCap > (size_t)INT32_MAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_x2d_export, dim3(grid_of((size_t)a.N * kCap)), dim3(kB), 0, stream, g, a.perm,
+    const int most = 1 << 24, need = grid_of((size_t)a.N * kCap);   // a launch has at most 2^32 threads
+    hipLaunchKernelGGL(k_x2d_export, dim3(need < most ? need : most), dim3(kB), 0, stream, g, a.perm,
                        a.deg, a.lst, deg_out, nbr_out, sh_out);
     return hipGetLastError();
 }
