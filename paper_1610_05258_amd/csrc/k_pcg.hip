@@ -908,11 +908,21 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                 for (int f = 0; f < F; ++f)
                     if (s_diag[k * F + f]) dm |= 1u << f;
                 dm = __builtin_amdgcn_readfirstlane(dm);
+                const bool poly = __builtin_amdgcn_readfirstlane(im & ~dm) != 0;
                 T qo[F][OWN], qn[F];
                 put(bA, im, vr, rdep != 0, nr);
                 __syncthreads();
+                if (!poly && !keep) {   // u = r, in bA already
+#pragma unroll
+                    for (int f = 0; f < F; ++f) {
+                        qn[f] = nr[f];
+#pragma unroll
+                        for (int o = 0; o < OWN; ++o) qo[f][o] = vr[f][o];
+                    }
+                }
 #pragma unroll
                 for (int j = 1; j < PH; ++j) {
+                    if (!poly) break;   // the products would only be multiplied by 0
                     const bool rn = rdep >= 1 && rdep <= PH - j;
                     apply(j & 1 ? bA : bB, im, rn, qo, qn);
 #pragma unroll
