@@ -558,7 +558,9 @@ __global__ __launch_bounds__(kBlock) void k_segment_sort(int ncells,
 // against five launches of 14 us together and their gaps (the 64-node step went from 43 to
 // 27 us); 8100 particles in 8100 cells: 18 us (the 90 x 90 paper-exact pass from 340 to
 // 327 us).  The line lies at one scan tile, 8192: the time grows with the particles and
-// meets that of the five launches (30 us) soon after.
+// meets that of the five launches (30 us) soon after.  Cells of 17 to 64 particles are
+// sorted by a wave each: by the whole workgroup one after the other, 8192 particles in
+// 20 x 32 cells took 365 us (five launches, 256 threads a workgroup: 190).
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallItems = 8;
 constexpr int kSmallMax = kSmallBlock * kSmallItems;   // one scan tile
@@ -569,8 +571,8 @@ __global__ __launch_bounds__(kSmallBlock) void k_bin_small(Mesh m, Particles<T> 
                                                            int32_t* __restrict__ perm,
                                                            p2m_report* __restrict__ rep, int clear) {
     __shared__ int32_t s_cs[kSmallMax + 1], s_perm[kSmallMax];
-    __shared__ int s_wave[kSmallBlock / 64], s_big[kSmallBlock];
-    __shared__ int s_nbig, s_flag, s_inv;
+    __shared__ int s_wave[kSmallBlock / 64], s_big[kSmallBlock];   // s_big: cells for the
+    __shared__ int s_nbig, s_nmid, s_flag, s_inv;   // workgroup from the front, for a wave from the back
     __shared__ uint32_t s_flags;
     const int tid = threadIdx.x, nc = m.nn;
     T px[kSmallItems], py[kSmallItems];
@@ -633,19 +635,30 @@ __global__ __launch_bounds__(kSmallBlock) void k_bin_small(Mesh m, Particles<T> 
         if (key[u] >= 0) s_perm[s_cs[key[u]] + rank[u]] = tid + u * kSmallBlock;
     for (int c = tid; c <= nc; c += kSmallBlock) cell_start[c] = s_cs[c];
     __syncthreads();
-    // the cells' slots by particle number: small cells by a thread each, the others one
-    // after the other by the workgroup
+    // the cells' slots by particle number: small cells by a thread each, cells of at most 64
+    // by a wave (a lane an entry, its place the number of smaller ones), the others one after
+    // the other by the workgroup
     for (int b = 0; b < nc; b += kSmallBlock) {
-        if (tid == 0) s_nbig = 0;
+        if (tid == 0) s_nbig = s_nmid = 0;
         __syncthreads();
         const int c = b + tid;
         if (c < nc) {
             const int s = s_cs[c], n = s_cs[c + 1] - s;
-            if (n > kSortReg) s_big[atomicAdd(&s_nbig, 1)] = c;
+            if (n > 64) s_big[atomicAdd(&s_nbig, 1)] = c;
+            else if (n > kSortReg) s_big[kSmallBlock - 1 - atomicAdd(&s_nmid, 1)] = c;
             else if (n > 1) rank_sort_small(s_perm + s, n);
         }
         __syncthreads();
-        const int nb = s_nbig;
+        const int nb = s_nbig, nm = s_nmid, lane = tid & 63;
+        for (int k = tid >> 6; k < nm; k += kSmallBlock / 64) {
+            const int cc = s_big[kSmallBlock - 1 - k], s = s_cs[cc], n = s_cs[cc + 1] - s;
+            const int v = lane < n ? s_perm[s + lane] : 0x7fffffff;
+            int at = 0;
+            for (int j = 0; j < n; ++j) at += s_perm[s + j] < v;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // all read before any writes
+            if (lane < n) s_perm[s + at] = v;
+        }
+        __syncthreads();
         for (int k = 0; k < nb; ++k) {
             const int cc = s_big[k];
             block_sort_segment<kSmallBlock>(s_perm + s_cs[cc], s_cs[cc + 1] - s_cs[cc], &s_flag);
