@@ -9,6 +9,8 @@
 //           interpolation between the two consecutive particles that bracket
 //           node i.  Positions are compared in the cell coordinate s = c + xi of
 //           the locate step and particles are ordered by (s, original index).
+#include <type_traits>
+
 #include "p2m_internal.hpp"
 
 namespace p2m {
@@ -110,12 +112,18 @@ __global__ void k_gather2d(Mesh m, Particles<T> P, const T* __restrict__ nodal, 
 }
 
 // The same from a node-major copy nm[k * F + f] of the nodal values: one load of
-// F consecutive values per corner instead of F loads.  VEC: a thread's particles are
+// F consecutive values per corner instead of F loads.  VEC (FP32): a thread's particles are
 // adjacent, its positions and results 16-byte accesses (np a multiple of kGatherItems,
-// arrays aligned to 16 bytes); they pass the caches by, which the nodal values need.
-// Bound: memory; 8.4 million particles, F = 3, 168 MB: 41 us (one particle an access,
-// through the caches: 54).
-template <typename T, int F, bool VEC>
+// arrays aligned to 16 bytes).  In FP64 that takes two accesses a quantity and lost: 4
+// million particles, F = 3, in cell order 59 us, one particle an access 47.  The results pass
+// the caches by, which the nodal values need; the positions do so (PAST) only where they and
+// the results exceed the caches: else whoever moved the particles has left them there
+// (4 million, F = 3, FP32: 27 us, bypassing loads 31; 8.4 million over 2048 x 2048 in FP64,
+// F = 2, 268 MB: 79 and 83; F = 3, 336 MB: 125 and 117).
+// Bound: memory.  Whole call, F = 3, FP32, 8.4 million particles over 1024 x 1024 nodes in
+// cell order, 168 MB: 48 -> 41 us; in random order the corners' cache misses, 293 -> 287.
+constexpr size_t kCacheBytes = (size_t)288 << 20;   // last-level cache and the eight L2s
+template <typename T, int F, bool VEC, bool PAST>
 __global__ void k_gather2d_nm(Mesh m, Particles<T> P, const T* __restrict__ nm,
                               T* __restrict__ out, p2m_report* __restrict__ rep) {
     constexpr int W = 16 / (int)sizeof(T);   // values of a 16-byte access
@@ -129,8 +137,9 @@ __global__ void k_gather2d_nm(Mesh m, Particles<T> P, const T* __restrict__ nm,
         for (int u = 0; u < kGatherItems; u += W) {
             vec x = {}, y = {};
             if (base < m.np) {
-                x = __builtin_nontemporal_load((const vec*)(P.x + base + u));
-                y = __builtin_nontemporal_load((const vec*)(P.y + base + u));
+                const vec *vx = (const vec*)(P.x + base + u), *vy = (const vec*)(P.y + base + u);
+                x = PAST ? __builtin_nontemporal_load(vx) : *vx;
+                y = PAST ? __builtin_nontemporal_load(vy) : *vy;
             }
 #pragma unroll
             for (int q = 0; q < W; ++q) {
@@ -143,8 +152,8 @@ __global__ void k_gather2d_nm(Mesh m, Particles<T> P, const T* __restrict__ nm,
         for (int u = 0; u < kGatherItems; ++u) {
             px[u] = py[u] = (T)0;
             if (at(u) < m.np) {
-                px[u] = __builtin_nontemporal_load(P.x + at(u));
-                py[u] = __builtin_nontemporal_load(P.y + at(u));
+                px[u] = PAST ? __builtin_nontemporal_load(P.x + at(u)) : P.x[at(u)];
+                py[u] = PAST ? __builtin_nontemporal_load(P.y + at(u)) : P.y[at(u)];
             }
         }
     }
@@ -357,15 +366,22 @@ hipError_t launch_gather(const Mesh& m, Particles<T> P, const T* nodal, int F, T
             T* nm = (T*)ws;
             hipLaunchKernelGGL(k_node_major<T>, dim3((m.nn + block - 1) / block), dim3(block), 0,
                                stream, nodal, F, m.nn, nm, clear ? rep : nullptr);
-            const bool vec = m.np % kGatherItems == 0 &&
+            constexpr bool kVec = sizeof(T) == 4;   // (no FP64 form)
+            const bool vec = kVec && m.np % kGatherItems == 0 &&
                              (((uintptr_t)P.x | (uintptr_t)P.y | (uintptr_t)out) & 15) == 0;
-            auto go = [&](auto with, auto without) {
-                hipLaunchKernelGGL(vec ? with : without, dim3(grid), dim3(block), 0, stream, m, P,
-                                   (const T*)nm, out, rep);
+            const bool past = (size_t)m.np * (2 + F) * sizeof(T) > kCacheBytes;
+            auto go = [&](auto vec_past, auto vec_kept, auto one_past, auto one_kept) {
+                hipLaunchKernelGGL(vec ? (past ? vec_past : vec_kept) : (past ? one_past : one_kept),
+                                   dim3(grid), dim3(block), 0, stream, m, P, (const T*)nm, out, rep);
             };
-            if (F == 2) go(k_gather2d_nm<T, 2, true>, k_gather2d_nm<T, 2, false>);
-            else if (F == 3) go(k_gather2d_nm<T, 3, true>, k_gather2d_nm<T, 3, false>);
-            else go(k_gather2d_nm<T, 4, true>, k_gather2d_nm<T, 4, false>);
+            auto of = [&](auto f) {
+                constexpr int N = decltype(f)::value;
+                go(k_gather2d_nm<T, N, kVec, true>, k_gather2d_nm<T, N, kVec, false>,
+                   k_gather2d_nm<T, N, false, true>, k_gather2d_nm<T, N, false, false>);
+            };
+            if (F == 2) of(std::integral_constant<int, 2>{});
+            else if (F == 3) of(std::integral_constant<int, 3>{});
+            else of(std::integral_constant<int, 4>{});
             return hipGetLastError();
         }
         hipError_t e = before(grid);
