@@ -221,8 +221,9 @@ Layout make_layout(const Context* c, const Mesh& m, int F, int dtype) {
         PolySolve<double> ps;
         if (poly_shape<double>(c, m, F, ps)) need = poly_bytes(ps);
     } else {
+        // (the resident state takes less than a third of the tile solvers' areas)
         PolySolve<float> ps;
-        if (poly_shape<float>(c, m, F, ps)) need = poly_bytes(ps);
+        if (poly_shape<float>(c, m, F, ps) && ps.grid.stream) need = poly_bytes(ps);
     }
     const size_t have = poly_area(L, tsize).bytes;
     if (need <= have || (tsize == 4 && need > have + have / 4)) return L;
@@ -632,8 +633,10 @@ p2m_status plan_batch(const Context* c, const p2m_problem* probs, int nprob, int
     std::vector<char> poly(nprob, 0);   // which solve the instance's own call takes
     for (int k = 0; k < nprob; ++k) {
         const Mesh& m = P.inst[k].m;
-        PolySolve<float> ps;
-        poly[k] = poly_solve_for<float>(c, m, F, make_layout(c, m, F, P2M_F32), ps);
+        PolySolve<float> ps;   // (poly_solve_for, without the layout where it need not be asked)
+        poly[k] = poly_shape<float>(c, m, F, ps) &&
+                  (!ps.grid.stream ||
+                   poly_bytes(ps) <= poly_area(make_layout(c, m, F, P2M_F32), sizeof(float)).bytes);
     }
     {
         BatchPlan::Diag& D = P.diag;

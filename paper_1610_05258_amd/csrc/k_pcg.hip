@@ -155,15 +155,21 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
     constexpr int PH = TC::PH;
     constexpr int NT = TC::NT, OWN = TC::OWN, EX = TC::EX, EN = TC::EN, NRP = TC::NRP;
     constexpr int NTN = TC::TX * TC::TY, NV = 3 * F, NW = NT / 64;
+    // (two and) three fields resident on the large tile: their state does not fit 128 registers
+    // (15 of them spilled and reloaded per iteration cost 5 us of 24), so two fields' d live in
+    // LDS and the inverse square roots, needed in the residual phases only, are formed again.
+    // Two fields give up the second exchange buffer for it: 700 x 700, whole pass 187 -> 183 us
+    constexpr int DL = !STREAM && !BATCH && NT == 1024 && (F == 3 || (F == 2 && OWN > 1)) ? 2 : 0;
     // two exchange buffers per field where they fit (one workgroup barrier per stencil
     // product), else one (two barriers)
-    constexpr size_t kTwo = ((size_t)(3 + 2 * F) * EN + NTN) * sizeof(T) + (BATCH ? 23000 : 1500);
+    constexpr size_t kTwo = ((size_t)(3 + 2 * F) * EN + (DL ? DL : 1) * NTN) * sizeof(T) + (BATCH ? 23000 : 1500);
     constexpr bool PP = kTwo <= (NT == 512 ? 80000u : 160000u);
     constexpr int UB = (PP ? 2 : 1) * F * EN;
-    // three fields resident on the large tile: their state does not fit 128 registers (15 of
-    // them spilled and reloaded per iteration cost 5 us of 24), so two fields' d live in LDS
-    // and the inverse square roots, needed in the residual phases only, are formed again
-    constexpr int DL = !STREAM && !BATCH && NT == 1024 && F == 3 ? 2 : 0;
+    // One product and no u in memory where the active fields are all on the diagonal.  Two
+    // fields streamed or in FP64 form every product: the branch costs them 1% of an ordinary
+    // pass, and their stalled systems are faster than by the diagonal kernels as it is (1400 x
+    // 1400, one particle per cell, 500 iterations: 26.1 ms by that one, 24.9)
+    constexpr bool kSkip = F != 2 || (!STREAM && sizeof(T) == 4);
     constexpr int MAXP = BATCH ? kBatchMaxPairs : F, MAXK = BATCH ? kBatchMaxInstances : 1;
 
     __shared__ __align__(16) T cf[3 * EN];    // scaled E, N, NE of the tile and its ring
@@ -866,6 +872,8 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                 d_put(f);
             }
         }
+        uint32_t dm = 0;    // fields whose polynomial is 1
+        bool poly = true;   // any active one's is not
         for (int it = 0;; ++it) {
             for (int i = g; i < a.ntiles; i += G) {
                 if (!keep) set_tile(i);
@@ -886,9 +894,15 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                         ld_own(3, f, vr[f]);
                         if (it == 0) continue;
                         ld_own(4, f, vw[f]);
-                        ld_own(5, f, uo[f]);
                         if (rdep) nr[f] = *ring_at(3, f);
-                        if (rdep == 1) un[f] = *ring_at(4, f);
+                        if (kSkip && s_diag[k * F + f]) {   // u = r
+#pragma unroll
+                            for (int o = 0; o < OWN; ++o) uo[f][o] = vr[f][o];
+                            un[f] = nr[f];
+                        } else {
+                            ld_own(5, f, uo[f]);
+                            if (rdep == 1) un[f] = *ring_at(4, f);
+                        }
                         if (it == 1) continue;   // p = d = s = 0 so far
                         ld_own(0, f, vp[f]);
                         ld_own(1, f, vd[f]);
@@ -903,26 +917,21 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                 }
                 // u = p(A) r by Horner's rule (PH is odd: u ends in bA), w = A u
                 static_assert(PH % 2 == 1, "u in bA");
-                uint32_t dm = 0;   // fields whose polynomial is 1
+                if (BATCH || STREAM || it == 0) {   // (a field stalls at the end of an inner solve)
+                    dm = 0;
 #pragma unroll
-                for (int f = 0; f < F; ++f)
-                    if (s_diag[k * F + f]) dm |= 1u << f;
-                dm = __builtin_amdgcn_readfirstlane(dm);
-                const bool poly = __builtin_amdgcn_readfirstlane(im & ~dm) != 0;
+                    for (int f = 0; f < F; ++f)
+                        if (s_diag[k * F + f]) dm |= 1u << f;
+                    dm = __builtin_amdgcn_readfirstlane(dm);
+                    if (F == 1) poly = dm == 0;
+                }
+                if (F > 1) poly = !kSkip || __builtin_amdgcn_readfirstlane(im & ~dm) != 0;
                 T qo[F][OWN], qn[F];
                 put(bA, im, vr, rdep != 0, nr);
                 __syncthreads();
-                if (!poly && !keep) {   // u = r, in bA already
-#pragma unroll
-                    for (int f = 0; f < F; ++f) {
-                        qn[f] = nr[f];
-#pragma unroll
-                        for (int o = 0; o < OWN; ++o) qo[f][o] = vr[f][o];
-                    }
-                }
 #pragma unroll
                 for (int j = 1; j < PH; ++j) {
-                    if (!poly) break;   // the products would only be multiplied by 0
+                    if (__builtin_expect(!poly, 0)) break;   // the products would only be multiplied by 0
                     const bool rn = rdep >= 1 && rdep <= PH - j;
                     apply(j & 1 ? bA : bB, im, rn, qo, qn);
 #pragma unroll
@@ -944,8 +953,10 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
 #pragma unroll
                     for (int f = 0; f < F; ++f) {
                         if (!(im & (1u << f))) continue;
-                        st_own(5, f, qo[f]);
-                        if (rdep == 1) *ring_at(4, f) = qn[f];
+                        if (!kSkip || !(dm & (1u << f))) {
+                            st_own(5, f, qo[f]);
+                            if (rdep == 1) *ring_at(4, f) = qn[f];
+                        }
                         if (it > 0) {
                             st_own(0, f, vp[f]);
                             st_own(1, f, vd[f]);
