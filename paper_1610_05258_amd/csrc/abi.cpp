@@ -1659,7 +1659,7 @@ p2m_status p2m_x1d_interpolate(void* ctx, const p2m_problem* prob, int32_t kind,
     double* vols = (double*)(w8 + X.vols);
     const bool small = x1d_small_fits(m);
     if (!small)
-        P2M_TRY(x1d_setup(m, nullptr, dN, key, idx, nullptr, 0, (double*)gap, vols,
+        P2M_TRY(x1d_setup(m, (const double*)prob->x, dN, key, idx, nullptr, 0, (double*)gap, vols,
                           (double*)(w8 + X.volc), nullptr, pp.stream));
     const bool mass = kind == P2M_X1D_MASS;
     double* cvec = (double*)(w8 + X.c);
@@ -1668,6 +1668,7 @@ p2m_status p2m_x1d_interpolate(void* ctx, const p2m_problem* prob, int32_t kind,
     double* fk = quad == P2M_QUAD_APPB ? nullptr : (double*)(w8 + X.fa);
     if (small) {
         X1dSmall a = x1d_small_args(pp, X, prob, F, nullptr);
+        a.nan_volumes = 1;
         a.eval = X1dSmall::kParts;
         a.appb = quad == P2M_QUAD_APPB ? 1 : 0;
         a.nodal = (const double*)nodal;
@@ -1695,7 +1696,7 @@ p2m_status p2m_x1d_interpolate(void* ctx, const p2m_problem* prob, int32_t kind,
         P2M_TRY(launch_cg<double>(mp, F, coef, cvec, vols, xs, P2M_START_FLIP, cw, o, pp.rep,
                                   pp.stream));
     }
-    P2M_TRY(x1d_out(m, (const double*)prob->x, dN, F, idx, xs, (double*)values_out, pp.stream));
+    P2M_TRY(x1d_out(m, (const double*)(w8 + X.volc), dN, F, idx, xs, (double*)values_out, pp.stream));
     return P2M_OK;
 }
 
@@ -1718,10 +1719,15 @@ p2m_status p2m_x1d_volumes(void* ctx, const p2m_problem* prob, void* vol_out, p2
         P2M_TRY(x1d_small(pp.m, a, pp.rep, pp.stream));
         return P2M_OK;
     }
-    P2M_TRY(x1d_setup(pp.m, (const double*)prob->x, dN, (const double*)(w8 + X.skey),
-                      (const int32_t*)(w8 + X.sidx), nullptr, 0,
-                      (double*)(w8 + X.gap), (double*)(w8 + X.vols), (double*)vol_out, nullptr,
-                      pp.stream));
+    // volumes that go over the positions are copied there when every thread has read its own
+    const double* x = (const double*)prob->x;
+    const bool over = (double*)vol_out < x + pp.m.np && x < (double*)vol_out + pp.m.np;
+    double* vol = over ? (double*)(w8 + X.volc) : (double*)vol_out;
+    P2M_TRY(x1d_setup(pp.m, x, dN, (const double*)(w8 + X.skey), (const int32_t*)(w8 + X.sidx), nullptr, 0,
+                      (double*)(w8 + X.gap), (double*)(w8 + X.vols), vol, nullptr, pp.stream));
+    if (over)
+        P2M_TRY(hipMemcpyAsync(vol_out, vol, (size_t)pp.m.np * sizeof(double), hipMemcpyDeviceToDevice,
+                               pp.stream));
     return P2M_OK;
 }
 

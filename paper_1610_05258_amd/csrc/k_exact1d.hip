@@ -144,7 +144,8 @@ __global__ __launch_bounds__(kB) void k_x1d_sort(int ncells, const double* __res
     }
 }
 
-// particle p was left out of the binning of N particles (N = 0: all were)
+// particle p was left out of the binning of N particles (N = 0: all were).  Asked before
+// anything is written to the caller: a result may lie over the positions.
 __device__ __forceinline__ bool left_out(const Mesh& m, const double* __restrict__ x, int p, int N) {
     int c;
     double xi;
@@ -415,7 +416,8 @@ __global__ void k_x1d_div(int K, const int32_t* __restrict__ dK, int F, const do
     for (int f = 0; f < F; ++f) out[(size_t)f * K + k] = c[(size_t)f * K + k] / den;
 }
 
-// sorted-order values to caller order (k_x1d_out: the particles left out get NaN)
+// sorted-order values to caller order (k_x1d_out: the particles left out, whose volume is
+// NaN, get NaN)
 __global__ void k_x1d_fill_nan(size_t n, double* __restrict__ out) {
     const size_t i = (size_t)blockIdx.x * kB + threadIdx.x;
     if (i < n) out[i] = __builtin_nan("");
@@ -428,12 +430,12 @@ __global__ void k_x1d_scatter(int N, int F, int np, const int32_t* __restrict__ 
     for (int f = 0; f < F; ++f) out[(size_t)f * np + p] = xs[(size_t)f * N + k];
 }
 
-__global__ void k_x1d_out(Mesh m, const double* __restrict__ x, const int32_t* __restrict__ dN, int F,
+__global__ void k_x1d_out(Mesh m, const double* __restrict__ vol_c, const int32_t* __restrict__ dN, int F,
                           const int32_t* __restrict__ idx, const double* __restrict__ xs,
                           double* __restrict__ out) {
     const int k = blockIdx.x * kB + threadIdx.x, N = *dN;
     if (k >= m.np) return;
-    if (left_out(m, x, k, N))
+    if (!(vol_c[k] == vol_c[k]))
         for (int f = 0; f < F; ++f) out[(size_t)f * m.np + k] = __builtin_nan("");
     if (k >= N) return;
     const int p = idx[k];
@@ -539,8 +541,10 @@ __global__ __launch_bounds__(kSmallBlock) void k_x1d_small(Mesh m, X1dSmall a, p
         }
         __syncthreads();
     }
-    for (int k = tid; k < np; k += kSmallBlock) {
-        if (a.nan_volumes && left_out(m, a.x, k, N)) a.vol_c[k] = __builtin_nan("");
+#pragma unroll
+    for (int u = 0; u < kSmallItems; ++u) {
+        const int k = tid + u * kSmallBlock;
+        if (a.nan_volumes && k < np && cell[u] < 0) a.vol_c[k] = __builtin_nan("");
         if (k >= N) continue;
         a.key[k] = s_key[k];
         a.idx[k] = s_idx[k];
@@ -645,10 +649,10 @@ hipError_t x1d_fill_nan(size_t n, double* out, hipStream_t stream) {
     return hipGetLastError();
 }
 
-hipError_t x1d_out(const Mesh& m, const double* x, const int32_t* dN, int F, const int32_t* idx,
+hipError_t x1d_out(const Mesh& m, const double* vol_c, const int32_t* dN, int F, const int32_t* idx,
                    const double* xs, double* out, hipStream_t stream) {
     if (m.np == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_x1d_out, dim3(grid_of(m.np)), dim3(kB), 0, stream, m, x, dN, F, idx, xs, out);
+    hipLaunchKernelGGL(k_x1d_out, dim3(grid_of(m.np)), dim3(kB), 0, stream, m, vol_c, dN, F, idx, xs, out);
     return hipGetLastError();
 }
 

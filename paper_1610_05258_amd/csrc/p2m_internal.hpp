@@ -215,9 +215,10 @@ hipError_t x1d_div(int K, const int32_t* dK, int F, const double* c, const doubl
                    double* out, hipStream_t stream);
 hipError_t x1d_fill_nan(size_t n, double* out, hipStream_t stream);
 // out[f][idx[k]] = xs[f][k], k < N; x1d_out: N = *dN, and NaN for the particles left out
+// (NaN in vol_c)
 hipError_t x1d_scatter(int N, int F, int np, const int32_t* idx, const double* xs, double* out,
                        hipStream_t stream);
-hipError_t x1d_out(const Mesh& m, const double* x, const int32_t* dN, int F, const int32_t* idx,
+hipError_t x1d_out(const Mesh& m, const double* vol_c, const int32_t* dN, int F, const int32_t* idx,
                    const double* xs, double* out, hipStream_t stream);
 
 // paper-exact 2D (k_x2d.hip); slot k = position in the binned order, N located
