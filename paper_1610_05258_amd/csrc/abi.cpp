@@ -464,7 +464,7 @@ p2m_status run_solve(const Context* c, const Prepared& pp, int F, T* b, const T*
     cw.dinv = pp.ws + pp.L.dinv;
     cw.blocks = cg_blocks_for(c, pp.m, sizeof(T) == 8 ? P2M_F64 : P2M_F32);
     cw.spin = pp.solve_spin;
-    cw.direct = kind == P2M_SOLVER_AUTO;
+    cw.direct = takes_poly(ch);   // 1D
     P2M_TRY(launch_cg<T>(pp.m, F, coef, b, w, (T*)x, start, cw, opts, pp.rep, pp.stream));
     return P2M_OK;
 }
