@@ -2087,6 +2087,8 @@ p2m_status p2m_tune(void* ctx, const p2m_problem* prob, const void* values, int3
             const int half = cgt_grid(pp.m, nfields, cap / 2, c->device);
             if (half > 0 && half < cap) add(P2M_SOLVER_TILES, half, tile);
         }
+        // (1D: AUTO is the streaming kernel with the cyclic reduction before it)
+        if (pp.m.dim == 1 && opts->start == P2M_START_FLIP) add(P2M_SOLVER_AUTO, 0, tile);
         add(P2M_SOLVER_STREAMING, 0, tile);
     }
     hipStream_t strm = (hipStream_t)stream;

@@ -1,5 +1,6 @@
 """The 1D solve by cyclic reduction where it has to run: from the FLIP start under AUTO and
-RESIDENT_CHEB (which is AUTO where it does not apply).  That it is the reduction that solves, and not the conjugate gradients
+RESIDENT_CHEB (which is AUTO where it does not apply), and after p2m_tune, whose plan must not
+be slower than no plan.  That it is the reduction that solves, and not the conjugate gradients
 behind it, shows in the iterations: none or one, at the edges of its forms too (the whole
 period in a workgroup, overlapping windows, several of them), against at least 8 without it.
 Orphans and both types with it."""
@@ -43,3 +44,22 @@ def test_iterations(n, ppc, empty, dt):
     assert ra.flags & ~B.FLAG_ORPHAN == 0 and (ra.iters <= 1).all()
     assert n < 17 or (rs.iters >= 8).all()
     assert torch.equal(a, c) and list(ra.iters) == list(rc.iters)
+
+
+def test_tuned():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1610_05258_amd import binding as B
+    x, A = _case(300, 8, 0, 4)
+    ctx = B.Context(0)
+    try:
+        before, r0 = solve(B, ctx, x, A, 300, "f8")
+        d = B.Particles(dim=1, nx=300, ny=1, lx=1.0, ly=1.0, x=torch.tensor(x, device="cuda"))
+        plan, out, rep = B.p2m_tune(ctx, d, torch.tensor(A, device="cuda"),
+                                    B.solve_opts(tol=1e-12, maxit=4000, max_refine=20, fp64=True))
+        after, r1 = solve(B, ctx, x, A, 300, "f8")
+        print(plan, flush=True)
+        assert plan.solver == B.SOLVER_AUTO and list(r0.iters) == list(r1.iters) and (r1.iters <= 1).all()
+        assert torch.equal(before, after)
+    finally:
+        ctx.close()
