@@ -798,7 +798,7 @@ hipError_t enqueue_batch(const BatchPlan& P, char* ws, p2m_report* reps, const p
 // ---------------------------------------------------------------------------
 struct X1DLayout {
     size_t key, counts, scan, cell_start, perm;          // binning (as in Layout)
-    size_t skey, sidx, gap, vols, volc, As, fa, fb, tlo, thi, c, coef, w, x, b, bw;
+    size_t skey, sidx, gap, vols, volc, As, fa, tlo, thi, c, coef, w, x, b, bw;
     size_t r, p0, p1, q, x64, dinv, part, report, total;
     int blocks;
 };
@@ -827,7 +827,6 @@ X1DLayout make_x1d_layout(const Context* c, const Mesh& m, int F) {
     L.volc = take(np * d8);
     L.As = take((size_t)F * np * d8);
     L.fa = take((size_t)F * K * d8);
-    L.fb = take((size_t)F * K * d8);
     L.tlo = take((size_t)F * K * d8);
     L.thi = take((size_t)F * K * d8);
     L.c = take((size_t)F * K * d8);
@@ -1168,7 +1167,7 @@ p2m_status x2d_run_m2p(const Context* c, const Prepared& pp, const X2DLayout& X,
         int* ok = nullptr;
         char* spare = w8 + X.x64 + align_up((size_t)F * N * sizeof(double));
         const size_t parts = align_up((size_t)2 * F * ((N + 255) / 256) * sizeof(double));
-        if (parts + pmass_sync_bytes() <= (size_t)F * N * sizeof(double) - kAlign && F * N > 4096)
+        if (parts + pmass_sync_bytes() <= (size_t)F * N * sizeof(double) - kAlign && (size_t)F * N > 4096)
             P2M_TRY(launch_pmass(N, F, coef, ecol, cvec, A.vol, (double*)cw.p0, (double*)cw.p1,
                                  (double*)cw.q, (double*)spare, spare + parts, o.tol, o.maxit,
                                  pp.solve_spin, xs, rep, &ok, pp.stream));
