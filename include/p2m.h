@@ -173,7 +173,7 @@ enum { P2M_SOLVER_AUTO = 0, P2M_SOLVER_STREAMING = 1, P2M_SOLVER_RESIDENT = 2, P
  *   P2M_OPT_SCAN_SPIN  bound on the polls of the binning scan's wait for a
  *                      preceding workgroup's prefix (0: the default, 2^26); a
  *                      negative value ends every such wait at once, which
- *                      raises P2M_FLAG_BIN_TIMEOUT on any mesh of more than 2048
+ *                      raises P2M_FLAG_BIN_TIMEOUT on any mesh of more than 8192
  *                      cells (for testing the timeout handling)
  *   P2M_OPT_SOLVE_SPIN bound on the polls of a mass solve's grid-barrier wait
  *                      (0: the default, 2^22); a negative value ends every such
@@ -425,16 +425,17 @@ p2m_status p2m_x2d_round_trip(void* ctx, const p2m_problem* prob, int32_t kind_p
  * Step 1's mass system is solved by the mass-matrix solver (FP32 CG, FP64
  * residuals and refinement) to opts->tol from opts->start, which must be
  * P2M_START_FLIP or P2M_START_ZERO.  The systems of steps 2 and 3 are circulant:
- * when nx and ny are powers of two (at most 2048) they are solved exactly by 2D FFT
- * in FP64 (zero-mean pressure instead of the held node; reports 1 and 2 then show
- * no iteration), otherwise by the same solver from b / diag, the pressure solve with
- * an iteration cap of at least 64 per mesh side.
+ * when both sides are at most 1024 or powers of two up to 2048 (P2M_OPT_FFT) they are
+ * solved exactly by 2D FFT in FP64 (zero-mean pressure instead of the held node;
+ * reports 1 and 2 then show no iteration), otherwise by the diagonally preconditioned
+ * mass-matrix solver from b / diag, the pressure solve with an iteration cap of at
+ * least 64 per mesh side.
  * --------------------------------------------------------------------------- */
 typedef enum { P2M_NS_FLIP = 0, P2M_NS_MASS = 1 } p2m_ns_assign;
 
 /* Workspace bytes of p2m_ns_step for this problem (the F = 2 assignment workspace
- * plus 20 floats per node, and 64 bytes per node of transform buffers when both
- * sides are powers of two). */
+ * plus 20 floats per node, and 64 bytes per node of transform buffers for sides that
+ * the FFT takes). */
 p2m_status p2m_ns_workspace_size(void* ctx, const p2m_problem* prob, size_t* bytes);
 /* One time step dt with kinematic viscosity nu (dt > 0, nu >= 0, finite).
  *   vel       [2][np] FP32, in: the particle velocities at prob->x, prob->y;
@@ -459,7 +460,8 @@ p2m_status p2m_ns_step(void* ctx, const p2m_problem* prob, int32_t assign, doubl
  * particles and volumes) with the same field count F, 1 <= F <= 3, nprob <= 128
  * and nprob * F <= 256.  Every instance is mass-assigned exactly as
  * p2m_mass_assign would do it alone under the same P2M_OPT_SOLVER (AUTO and
- * RESIDENT_CHEB: the polynomial-preconditioned solve; RESIDENT and TILES: the
+ * RESIDENT_CHEB: the polynomial-preconditioned solve, or the diagonally preconditioned
+ * one where the instance's own call takes that; RESIDENT and TILES: the
  * diagonally preconditioned one; STREAMING: as AUTO, equal to the single call under
  * AUTO): the same binning, the same scatter sums and the same solver arithmetic in
  * the same order, so each instance's nodal values and report equal the
@@ -467,7 +469,8 @@ p2m_status p2m_ns_step(void* ctx, const p2m_problem* prob, int32_t assign, doubl
  *
  * The whole batch is one HIP graph: clears, binning, scatter of all instances
  * and one persistent solve kernel over the solver tiles of all instances (two where
- * meshes above and below 512 x 512 nodes meet in a batch; tiles are shared out over
+ * meshes above and below 512 x 512 nodes meet in a batch, one more for strips that
+ * take the diagonal solve; tiles are shared out over
  * at most two workgroups per compute unit; the kernel's grid-wide barriers rely on all its workgroups being resident, which holds on a
  * device not shared with other work, and its waits are bounded: a timed-out wait
  * ends the solve with P2M_FLAG_BREAKDOWN | P2M_FLAG_NOT_CONVERGED).

@@ -33,8 +33,10 @@
 // grid barrier), not traffic, while one tile per workgroup fits the chip; the traffic of
 // the streamed state beyond.  Whole mass assignment and interpolation, before (diagonal
 // preconditioner, or the FP64 streaming solve) and now: 256 x 256 at 4 per cell, F = 1,
-// 263 -> 108 us; 1024 x 1024 at 8 per cell, F = 3, 597 -> 415 us; 2048 x 2048
-// 4.09 -> 2.47 ms; 512 x 512 FP64 at 8 per cell, F = 1, 1312 -> 189 us.  What the large
+// 263 -> 108 us; 1024 x 1024 at 8 per cell, F = 3, 597 -> 403 us; 2048 x 2048
+// 4.09 -> 2.39 ms; 512 x 512 FP64 at 8 per cell, F = 1, 1312 -> 193 us.  Two random particles
+// per cell (50 to 440 iterations): 600 x 600, F = 1, 1.92 -> 1.65 ms, F = 3, 6.41 -> 5.91;
+// 1400 x 1400, F = 3, 32.1 -> 29.4 ms.  What the large
 // tile's 24 us iteration (F = 3) answered to: x kept as the start formula until a field
 // needs a second correction (no FP64 x traffic in the usual two residual phases), border
 // columns published transposed in one 16-byte store a lane and read 64 rows a wave
@@ -740,7 +742,7 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                         ld_own(1, f, vd[f]);
                         if (rdep == 1) nd[f] = *ring_at(1, f);
                     }
-                            d_get(f);
+                    d_get(f);
                     xn += (double)mul_t(nd[f], rsr);
 #pragma unroll
                     for (int o = 0; o < OWN; ++o) xo[o] += (double)mul_t(vd[f][o], rso[o]);
@@ -849,7 +851,7 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                         const double x = hf ? ldo(a.x64 + q, kk) : own_start(ldo(a.b + q, kk), ldo(w, kk));
                         *ato(a.x64 + q, kk) = x + (double)mul_t(vd[f][o], rs_of(ldo(C, kk), !(ldo(w, kk) > (T)0)));
                     }
-                            if (rdep == 1) {
+                    if (rdep == 1) {
                         double* const xr = a.xring + ((size_t)tile * F + f) * NRP + tid;
                         *xr = (hf ? *xr : start_value(f, rg)) + (double)mul_t(nd[f], rsr);
                     }
@@ -867,7 +869,7 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
             for (int f = 0; f < F; ++f) {
                 nr[f] = wn[f];
                 np_[f] = nd[f] = ns[f] = (T)0;
-    #pragma unroll
+#pragma unroll
                 for (int o = 0; o < OWN; ++o) vp[f][o] = vd[f][o] = vs[f][o] = (T)0;
                 d_put(f);
             }
@@ -1189,7 +1191,11 @@ size_t stream_bytes(int tsize, const TileInfo& t, int F, int ntiles) {
 int pcg_depth(int tsize, bool small, int F) { return small && (tsize == 4 || F == 1) ? 5 : 3; }
 
 // Meshes of at most kPolyTiles small tiles (512 x 512) take the 32 x 32 tile, one per
-// compute unit; larger ones the 64 x 64 tile, whose ring is a smaller share of it.
+// compute unit; larger ones the 64 x 64 tile, whose ring is a smaller share of it.  Past the
+// line a quarter of the tiles hold four times the nodes and three products replace five, on
+// 81 of 256 compute units at first: whole pass at 6 per cell, F = 1 / 3, 512 x 512 99 / 167 us,
+// 520 x 520 125 / 265, 640 x 640 138 / 291, 960 x 960 (225 tiles) 189 / 350; by the diagonal
+// solve 218 / 396, 220 / 409, 225 / 427, 280 / 498.
 bool pcg_small(const Mesh& m) {
     return (int64_t)((m.nx + TileS::TX - 1) / TileS::TX) * ((m.ny + TileS::TY - 1) / TileS::TY) <=
            kPolyTiles;

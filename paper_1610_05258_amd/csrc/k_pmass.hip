@@ -16,6 +16,10 @@
 //  * few rows (kSmallRows): one persistent kernel, a row per thread with its entries in
 //    registers, x exchanged through device-coherent accesses and one counter-tree barrier
 //    a step: a launch per step would cost more than the step.  8,100 rows: 383 -> 120 us.
+//    Whole M2P by the one kernel and by the launches, F = 1: 8,100 rows 230 and 250 us, 32,761
+//    rows 260 and 288, 65,536 rows 300 and 323; F = 3: 287 and 318, 322 and 352, 394 and 399,
+//    90,000 rows 462 and 451.  The line at 32,768, below the crossing, keeps one workgroup on
+//    every second compute unit, so that the grid is resident beside other work.
 //
 // A solve that does not reach tol, or that meets a row without a volume or a value that
 // is not finite, leaves the word `ok` at 0; the streaming CG enqueued behind it then does

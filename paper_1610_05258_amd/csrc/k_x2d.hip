@@ -344,9 +344,12 @@ __global__ __launch_bounds__(kB) void k_x2d_star_left(Geo g, const double* __res
 // that is expected to hold 28 others (from the count of the 3 x 3 cells) are collected
 // into LDS first, and the wrap scans those instead of whole cells; it stands when every
 // circle's diameter is within that radius.  A particle whose list overflows or whose
-// star is not closed that way goes to the general kernel's list.  Bound: FP64 arithmetic
-// of the scans; 1,048,576 particles at 4 per cell: 100 candidates per scan, 2340 us, ->
-// 28 and a one-off filter of the 100.  Comparisons, rounding and ties as in the general
+// star is not closed that way goes to the general kernel's list.  1,048,576 particles at 4
+// per cell: 100 candidates per scan, 2340 us, -> 28 and a one-off filter of the 100, 717 us.
+// Bound: VALU issue, 4560 instructions a wave of 16 particles (cross products, key products
+// and the quad's exchanges, more than their FP64 operations alone); they take two thirds of
+// the SIMDs' cycles with 62% of the lanes on, at 2.4 waves a SIMD that wait 42% of the time
+// on loads (LDS 2%, its conflicts 2%).  Comparisons, rounding and ties as in the general
 // kernel, so the lists and volumes are the same.
 __device__ __forceinline__ double quad_move_d(double v, bool two) {
     return two ? dpp_quad<0x4E>(v) : dpp_quad<0xB1>(v);   // lanes two apart, or one
