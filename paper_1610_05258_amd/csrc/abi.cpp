@@ -1385,7 +1385,7 @@ p2m_status p2m_mass_assign_noalloc(void* ctx, const p2m_problem* prob, const voi
 // ---------------------------------------------------------------------------
 // The step's arrays after the F = 2 layout of the problem: Ubar, U*, U^{n+1} [2][nn],
 // the viscous and pressure stencils [4][nn] with their diagonals [nn], the pressure
-// right-hand side and the pressure [nn], and (power-of-two sides) the transform
+// right-hand side and the pressure [nn], and (sides the FFT takes) the transform
 // buffers of the direct solves.
 struct NsLayout {
     size_t ubar, ustar, unew, cv, wv, cp, wp, rhs, p, fft, total;

@@ -658,8 +658,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_bin_small(Mesh m, Particles<T> 
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // all read before any writes
             if (lane < n) s_perm[s + at] = v;
         }
-        __syncthreads();
-        for (int k = 0; k < nb; ++k) {
+        for (int k = 0; k < nb; ++k) {   // (other slots: nothing to wait for)
             const int cc = s_big[k];
             block_sort_segment<kSmallBlock>(s_perm + s_cs[cc], s_cs[cc + 1] - s_cs[cc], &s_flag);
         }

@@ -349,7 +349,7 @@ __global__ __launch_bounds__(kB) void k_x2d_star_left(Geo g, const double* __res
 // Bound: VALU issue, 4560 instructions a wave of 16 particles (cross products, key products
 // and the quad's exchanges, more than their FP64 operations alone); they take two thirds of
 // the SIMDs' cycles with 62% of the lanes on, at 2.4 waves a SIMD that wait 42% of the time
-// on loads (LDS 2%, its conflicts 2%).  Comparisons, rounding and ties as in the general
+// (LDS conflicts: 2%).  Comparisons, rounding and ties as in the general
 // kernel, so the lists and volumes are the same.
 __device__ __forceinline__ double quad_move_d(double v, bool two) {
     return two ? dpp_quad<0x4E>(v) : dpp_quad<0xB1>(v);   // lanes two apart, or one
