@@ -114,7 +114,9 @@ typedef struct {
     double tol;           /* relative FP64 residual target, > 0 (e.g. 1e-6) */
     double inner_rtol;    /* each inner CG solve reduces its residual by this factor (0: to tol) */
     int32_t maxit;        /* cap on CG iterations per field, summed over outer iterations */
-    int32_t max_refine;   /* cap on FP64 residual evaluations after the first (>= 0) */
+    int32_t max_refine;   /* cap on FP64 residual evaluations after the first (>= 0); from 1 on the
+                             polynomial-preconditioned solve may take one more after a stalled
+                             recurrence and one more after an inner solve that missed tol */
     int32_t start;        /* p2m_start */
     int32_t reserved;     /* must be 0 */
 } p2m_solve_opts;
