@@ -188,8 +188,8 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
     __shared__ unsigned char s_diag[MAXP];  // the polynomial has stalled: p(A) = 1 from here on
     __shared__ unsigned char s_done[MAXP], s_inner[MAXP], s_zero[MAXP];
     // corrections that are this solve's own doing and not on the caller's max_refine: bit 0 the
-    // one after a stalled recurrence, bit 1 one after an inner solve that did reach the goal in
-    // its scaled norm (or its FP32 recurrence) and missed it in the true residual
+    // one after a stalled recurrence, bit 1 one after an inner solve that went for the goal (and
+    // missed it: its norm is the scaled one, its recurrence perhaps FP32)
     __shared__ unsigned char s_more[MAXP];
     // x is held in x64 / xring (else it is the start, formed from b and w where needed);
     // the last inner solve went for the goal, so its residual is expected to be the last
@@ -797,9 +797,9 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
             const int kk = BATCH ? p / F : 0, f = p - kk * F;
             if (s_done[p]) continue;
             s_refines[p] += 1;
-            // (s_more's two bits; read here: in the comparison below it makes the 64 x 64 tile spill
-            // more, 2.40 -> 2.43 ms for one field of 2048^2 nodes)
-            const int counted = outer - ((s_more[p] + 1) >> 1);
+            // (read here: in the comparison below it makes the 64 x 64 tile spill more, 2.40 ->
+            // 2.43 ms at 2048^2 nodes)
+            const int own = s_more[p], counted = outer - ((own + 1) >> 1);   // less its two bits
             const double rr = vals[kk * NV + f];
             if (outer == 0) s_bb[p] = vals[kk * NV + F + f];
             const double bb = s_bb[p];
@@ -825,6 +825,7 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                 // x + d was not stored if this residual was expected to be the last
                 s_held[p] |= outer > 0 ? (s_last[p] ? 2 : 1) : 0;
                 s_last[p] = direct;
+                s_more[p] = own | (direct ? 2 : 0);
                 s_inner[p] = 1;
                 s_best[p] = 3.0e38f;
                 s_since[p] = 0;
@@ -1045,7 +1046,6 @@ __global__ __launch_bounds__(TC::NT) void k_pcg(PArgs<T> a) {
                     }
                     if (!(rho > s_target[p]) || s_iters[p] >= a.opts.maxit) {
                         s_inner[p] = 0;
-                        if (s_last[p]) s_more[p] |= 2;
                         continue;
                     }
                     beta = gam / s_gam[p];
