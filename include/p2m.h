@@ -144,10 +144,10 @@ p2m_status p2m_destroy(void* ctx);
  * their rounding differs, except that RESIDENT and TILES give identical bits (the
  * same per-tile arithmetic and reduction order), and so do AUTO and RESIDENT_CHEB.
  *   P2M_SOLVER_AUTO       RESIDENT_CHEB where it applies, else RESIDENT (2D FP32,
- *                         F <= 3), else the streaming kernel
- *                         (1D from the FLIP start: by cyclic reduction, and the
- *                         iteration only for what its residual leaves); a tuned plan of the problem's shape class (p2m_tune)
- *                         overrides this choice
+ *                         F <= 3), else the streaming kernel (1D from the FLIP
+ *                         start: by cyclic reduction, and the iteration only for what
+ *                         its residual leaves); a tuned plan of the problem's shape
+ *                         class (p2m_tune) overrides this choice
  *   P2M_SOLVER_STREAMING  grid-synchronised streaming kernel (any problem)
  *   P2M_SOLVER_RESIDENT   register-resident kernel with the diagonal preconditioner
  *                         (2D FP32, F <= 3, at most one 128 x 32 node tile per
