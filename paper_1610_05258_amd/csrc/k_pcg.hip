@@ -1250,7 +1250,7 @@ int resident_groups(const void* fn, int nt, int device, std::atomic<int>* known)
         if (v > 0) return v;
     }
     int cus = 0, per = 0;
-    if (        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, nt, 0) != hipSuccess || per < 1)
         return 0;
     const int v = (per > 2 ? 2 : per) * cus;
